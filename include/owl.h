@@ -114,14 +114,13 @@ typedef struct owl_verify_desc {
 
 /* What the library decided for a descriptor; informational (bench, tests). */
 typedef struct owl_plan {
-    int32_t split_tokens;    /* tokens of the logical sequence (prefix + drafts) per split */
-                             /* for a context of max_ctx_len.  With a library-chosen size   */
-                             /* the kernels follow the real lengths: one shorter sequence   */
-                             /* is cut into max_splits shorter splits, a ragged batch into  */
-                             /* the shortest splits that still fill whole rounds of one     */
-                             /* workgroup per compute unit (never below the planner's       */
-                             /* minimum, never above this value)                            */
-    int32_t max_splits;      /* most splits one sequence can be cut into (sizes the partials) */
+    int32_t split_tokens;    /* tokens of the logical sequence (prefix + drafts) per split of the */
+                             /* plan.  With a caller-chosen size the kernels cut exactly so; with  */
+                             /* a library-chosen one they share out the actual lengths evenly: as  */
+                             /* many workers per KV head (and row group) as run at a time, each    */
+                             /* with an equal run of 64-token stages of the sequences laid end to  */
+                             /* end                                                                */
+    int32_t max_splits;      /* splits of the plan in the longest sequence it admits        */
     int32_t rows_per_kv;     /* R = (Hq/Hkv) * N query rows packed against one KV stream   */
     int32_t row_tiles;       /* 16-row MFMA tiles covering R                               */
     int32_t row_groups;      /* workgroups sharing one KV split, each owning some tiles    */

@@ -59,10 +59,12 @@ owl_status check_desc(const owl_verify_desc *d)
 struct FullPlan {
     owl_plan pub;
     const Variant *variant;
-    size_t part_o_bytes, part_ml_bytes, plan_bytes;
+    size_t part_o_bytes, part_ml_bytes, info_offset;
     bool half_partials;       // normalised fp16 partials (16-bit inputs unless the caller asks for fp32 ones)
-    int32_t adapt, c_min, group_tiles;
-    int64_t item_slots;       // adapt == 2: (sequence, split) pairs the grid has room for
+    int32_t group_tiles;
+    bool dealt;               // the kernels cut the work by the actual lengths (deal_units)
+    int32_t min_units, round_workers, max_workers, seq_extra, n_slots;
+    Deal full;                // one sequence of the greatest length
     dim3 grid;                // of the split-KV pass
 };
 
@@ -137,32 +139,60 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     if (C > kMaxSplitTokens) C = kMaxSplitTokens;
     if (C < kSplitQuantum) C = kSplitQuantum;
     int64_t max_splits = (T + C - 1) / C;
-    // One sequence and a library-chosen split size: the kernels cut a context
-    // shorter than max_ctx_len into the same number of splits (never below the
-    // minimum used above), so the launch still fills the chip.
-    // A batch with a library-chosen size: the kernels shrink the split so that the real
-    // (ragged) lengths fill whole rounds of workgroups (batch_split_tokens).  Going from
-    // k-and-a-bit rounds to k + 1 full ones never needs less than half the planned size,
-    // so the grid and the partials are sized for splits of C / 2.
-    fp->adapt = d->split_tokens != 0 ? 0 : (d->batch == 1 ? 1 : 2);
-    fp->c_min = (int32_t)(cmin < C ? cmin : C);
-    fp->item_slots = (int64_t)d->batch * max_splits;
-    if (fp->adapt == 2) {
-        // The device never asks for more pairs than the planned size gives at full length,
-        // rounded up to whole rounds, plus one per sequence for rounding: that many slots,
-        // numbered densely, are launched; a single sequence may use up to twice its share.
-        const int64_t streams = (int64_t)d->n_kv_heads * rgs;
-        fp->item_slots = (int64_t)d->batch * max_splits + (device_cus() + streams - 1) / streams + d->batch;
-        int64_t c_floor = align_up((size_t)(C / 2), kSplitQuantum);
-        if (c_floor < fp->c_min) c_floor = fp->c_min;
-        max_splits = (T + c_floor - 1) / c_floor;
-        if (fp->item_slots > (int64_t)d->batch * max_splits) fp->item_slots = (int64_t)d->batch * max_splits;
+    // A library-chosen split size: what is launched is a set of workers that share out the actual
+    // lengths (deal_units), one workgroup per compute unit.  The worker count follows the same two rules as
+    // above: fill the compute units in one round, and keep the row groups of a stream on one XCD.
+    // A share is never below R tokens: there the fp16 partials it leaves are half the K/V it reads (a share of
+    // 4 R, which keeps them to an eighth, costs a 5K context with 240 rows 2 us of 20 and a 512-token fp32
+    // call 9 us of 20: short calls are bound by the chain of stages, not by bytes; R / 4 gains nothing more).
+    // Beyond its stages a sequence counts 8 units in a batch, where the worker that ends it begins the next
+    // one with a set-up and an empty ring (0 instead of 8: 284 against 259 us on four sequences of 3K-16K
+    // tokens with 240 rows in four layers; 4: 268, 10: 260), and 1-2 for the masked steps of a lone sequence.
+    const int64_t stages_at_most = (T + kSplitQuantum - 1) / kSplitQuantum;
+    fp->seq_extra = d->batch == 1 ? (RT > 4 ? 2 : 1) : 8;
+    const int64_t units_at_most = (int64_t)d->batch * (stages_at_most + fp->seq_extra);
+    fp->dealt = d->split_tokens == 0 && units_at_most < ((int64_t)1 << 30);
+    const int64_t head_groups = (int64_t)d->n_kv_heads * rgs;
+    int64_t per_round = 1;
+    for (int k = 1; k <= 4; ++k) {                  // more heads than compute units divide evenly into: up to four rounds
+        per_round = (int64_t)device_cus() * k / head_groups;
+        if (rgs > 1) {
+            const int64_t streams = (int64_t)(device_cus() / 8 / rgs) * 8 * k;
+            if (streams >= d->n_kv_heads) per_round = streams / d->n_kv_heads;
+        }
+        if (per_round >= 1 && 20 * per_round * head_groups >= 17 * (int64_t)device_cus() * k) break;
+        if (per_round > 4) break;
     }
+    if (per_round < 1) per_round = 1;
+    fp->round_workers = (int32_t)per_round;
+    fp->min_units = (R + kSplitQuantum - 1) / kSplitQuantum;
+    const int64_t rounds = 1 + (units_at_most - 1) / (per_round * kMaxPieceUnits);
+    int64_t workers = units_at_most / fp->min_units;
+    if (workers > per_round * rounds) workers = per_round * rounds;
+    if (workers < 1) workers = 1;
+    fp->max_workers = (int32_t)workers;
+    fp->full = Deal{(int32_t)workers, (int32_t)(units_at_most / workers), (int32_t)(units_at_most % workers)};
+    const int64_t n_slots = fp->dealt ? workers + d->batch - 1 : (int64_t)d->batch * max_splits;
+    fp->n_slots = (int32_t)n_slots;
 
-    const size_t slots = (size_t)d->batch * d->n_kv_heads * (size_t)max_splits * RT;
+    // Workspace: the partials that are written, and never less than equal splits of half the planned size
+    // would need for a batch (the planned size for one sequence): what a caller's buffer holds and what
+    // owl_verify_attn_noalloc admits does not depend on how the work is dealt out.
+    int64_t sized_splits = max_splits;
+    if (fp->dealt && d->batch > 1) {
+        int64_t c_floor = align_up((size_t)(C / 2), kSplitQuantum);
+        if (c_floor < cmin) c_floor = cmin < C ? cmin : C;
+        max_splits = sized_splits = (T + c_floor - 1) / c_floor;
+    }
     fp->half_partials = d->qkv_dtype != OWL_F32 && !(d->flags & OWL_FLAG_FP32_PARTIALS);
-    fp->part_o_bytes = align_up(slots * (size_t)d->head_dim * kRowTile * (fp->half_partials ? 2 : 4), 256);
-    fp->part_ml_bytes = align_up(slots * kPartMl * sizeof(float), 256);
+    const size_t o_bytes = (size_t)d->head_dim * kRowTile * (fp->half_partials ? 2 : 4), ml_bytes = kPartMl * sizeof(float);
+    const size_t slots = (size_t)d->n_kv_heads * (size_t)n_slots * RT;
+    const size_t sized = (size_t)d->batch * d->n_kv_heads * (size_t)sized_splits * RT;
+    fp->part_o_bytes = align_up(slots * o_bytes, 256);
+    fp->part_ml_bytes = align_up(slots * ml_bytes, 256);
+    size_t part_bytes = align_up(sized * o_bytes, 256) + align_up(sized * ml_bytes, 256);
+    if (part_bytes < fp->part_o_bytes + fp->part_ml_bytes) part_bytes = fp->part_o_bytes + fp->part_ml_bytes;
+    fp->info_offset = part_bytes;
     fp->variant = v;
     owl_plan &pl = fp->pub;
     pl.reserved_ = 0;
@@ -173,23 +203,17 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     pl.row_groups = rgs;
     pl.tiles_per_wave = tpw;
     pl.kernel_variant = variant_index(v);
-    // KV heads vary fastest (see the kernel's block-index comment); for a batch with a library-chosen
-    // split size (y, z) merely number its (sequence, split) pairs densely
-    // With row groups the kernel deals the workgroups out in units of eight (KV head, split, sequence)
-    // streams: the grid is padded so that their number is a multiple of 8 (the surplus exits at once).
-    int64_t grid_y = max_splits;
+    // KV heads vary fastest (see the kernel's block-index comment).
+    // With row groups the kernel deals the workgroups out in units of eight (KV head, share) streams: the
+    // grid is padded so that their number is a multiple of 8 (the surplus exits at once).
+    int64_t grid_y = fp->dealt ? workers : max_splits;
+    const int64_t grid_z = fp->dealt ? 1 : d->batch;
     if (rgs > 1)
-        while (((int64_t)d->n_kv_heads * grid_y * d->batch) % 8 != 0) ++grid_y;
-    fp->grid = dim3(d->n_kv_heads * rgs, (unsigned)grid_y, d->batch);
-    if (fp->adapt == 2) {
-        int64_t per_z = fp->item_slots < 32768 ? fp->item_slots : 32768;
-        if (rgs > 1) per_z = (per_z + 7) / 8 * 8;
-        fp->grid = dim3(d->n_kv_heads * rgs, (unsigned)per_z, (unsigned)((fp->item_slots + per_z - 1) / per_z));
-    }
+        while (((int64_t)d->n_kv_heads * grid_y * grid_z) % 8 != 0) ++grid_y;
+    fp->grid = dim3(d->n_kv_heads * rgs, (unsigned)grid_y, (unsigned)grid_z);
     if ((int64_t)fp->grid.x * fp->grid.y * fp->grid.z >= ((int64_t)1 << 31)) return OWL_ERR_UNSUPPORTED;   // the kernel numbers them in 32 bits
     pl.n_workgroups = (int32_t)((int64_t)fp->grid.x * fp->grid.y * fp->grid.z);
-    fp->plan_bytes = align_up(((size_t)d->batch + 3) * sizeof(int32_t), 256);     // the batch plan
-    pl.workspace_bytes = fp->part_o_bytes + fp->part_ml_bytes + fp->plan_bytes;
+    pl.workspace_bytes = fp->info_offset + align_up(((size_t)d->batch + 3) * sizeof(int32_t), 256);     // + write_batch_info's words
     return OWL_OK;
 }
 
@@ -328,7 +352,7 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     st = ensure_lds_attr(variant);
     if (st != OWL_OK) return st;
 
-    // workspace: partial O | partial (m, l, s) | batch plan
+    // workspace: partial O | partial (m, l, s) | ... | write_batch_info's words
     char *ws = static_cast<char *>(workspace);
     KParams p;
     memset(&p, 0, sizeof p);
@@ -338,7 +362,7 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     p.part_o = ws;
     p.half_partials = fp.half_partials ? 1 : 0;
     p.part_ml = reinterpret_cast<float *>(ws + fp.part_o_bytes);
-    p.dev_c = reinterpret_cast<int32_t *>(ws + fp.part_o_bytes + fp.part_ml_bytes);
+    p.batch_info = fp.dealt && desc->batch > 1 ? reinterpret_cast<int32_t *>(ws + fp.info_offset) : nullptr;
     p.out = out;
     p.out_dtype = desc->out_dtype;
     p.dev_status = dev_status;
@@ -346,8 +370,9 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     p.G = p.Hq / p.Hkv; p.R = fp.pub.rows_per_kv;
     p.max_pages = desc->max_pages_per_seq; p.max_ctx_len = desc->max_ctx_len;
     p.C = fp.pub.split_tokens; p.max_splits = fp.pub.max_splits;
-    p.adapt = fp.adapt; p.c_min = fp.c_min;
-    p.n_cu = device_cus();
+    p.dealt = fp.dealt ? 1 : 0; p.min_units = fp.min_units; p.round_workers = fp.round_workers;
+    p.max_workers = fp.max_workers; p.seq_extra = fp.seq_extra; p.n_slots = fp.n_slots;
+    p.full = fp.full;
     p.RT = fp.pub.row_tiles; p.row_groups = fp.pub.row_groups; p.group_tiles = fp.group_tiles;
     p.stride_page = desc->kv_stride_page; p.stride_head = desc->kv_stride_head;
     p.stride_token = desc->kv_stride_token; p.n_pool_pages = desc->n_pool_pages;
@@ -355,11 +380,8 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     p.timeline = variant->timeline ? hook.buffer : nullptr;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    p.item_slots = (int32_t)fp.item_slots;
-    const dim3 grid = fp.grid;
     if (phases & OWL_PHASE_SPLIT) {
-        if (p.adapt == 2 && launch_batch_plan(p, s) != hipSuccess) return OWL_ERR_HIP;
-        variant->launch(p, grid, s, ev_start, ev_stop);
+        variant->launch(p, fp.grid, s, ev_start, ev_stop);
         if (hipGetLastError() != hipSuccess) return OWL_ERR_HIP;
     }
     if (phases & OWL_PHASE_COMBINE)

@@ -16,10 +16,14 @@ namespace owl {
 // its largest magnitude, as fp16: uint4 [slot][u/2][lane] holds the lane's four
 // channels of tiles u and u + 1; the weight of split s is then 2^(m_s - M) l_s s_s.
 //
-// One workgroup per (sequence, KV head, 16-row tile, pair of channel tiles);
-// its WAVES wavefronts (4, or 8 when there are more than 32 splits; 16 gained nothing) take every
-// WAVES-th split, reduce their share against their own running maximum, and are
-// merged through LDS with the same formula.
+// Two ways to spread the work, chosen by the launch:
+//   few sequences  One workgroup per (sequence, KV head, 16-row tile, pair of channel tiles); its WAVES
+//                  wavefronts (4, or 8 when there are more than 32 partials; 16 gained nothing) take every
+//                  WAVES-th partial, reduce their share against their own running maximum, and are
+//                  merged through LDS with the same formula.
+//   batches        (BY_CHANNEL) a sequence has few partials but there are many rows: one workgroup per
+//                  (sequence, KV head, 16-row tile), a wavefront per pair of channel tiles, each merging
+//                  all partials by itself: a quarter of the workgroups, no LDS, no barrier.
 // ---------------------------------------------------------------------------
 typedef _Float16 c_f16x2 __attribute__((ext_vector_type(2)));
 
@@ -29,97 +33,129 @@ __device__ __forceinline__ float2 unpack_half2(uint32_t w)
     return make_float2((float)h[0], (float)h[1]);
 }
 
-template <int D, bool HALF, int WAVES>
+template <int D, bool HALF, int WAVES, bool BY_CHANNEL>
 __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
 {
-    constexpr int NT = D / 16, UPW = 2;              // channel tiles per workgroup
+    constexpr int NT = D / 16, UPW = 2;              // channel tiles per wavefront
     constexpr int NUG = NT / UPW;
-    const int tg = blockIdx.x / NUG, u0 = (blockIdx.x % NUG) * UPW;
+    static_assert(!BY_CHANNEL || WAVES == NUG, "one wavefront per pair of channel tiles");
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tg = BY_CHANNEL ? blockIdx.x : blockIdx.x / NUG;
+    const int u0 = (BY_CHANNEL ? w : (int)(blockIdx.x % NUG)) * UPW;
     const int g = blockIdx.y, b = blockIdx.z;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, qd = lane >> 4;
+    constexpr int kStride = BY_CHANNEL ? 1 : WAVES;  // this wavefront's partials: first, first + kStride, ...
+    const int first = BY_CHANNEL ? 0 : w;
 
-    const int L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, nullptr);
+    // The merge is a chain (each partial rescales the running sums), the loads are not: the
+    // partials of kInFlight splits are requested together, so that a wavefront pays the
+    // memory latency once per batch rather than once per split (up to 32 splits: once).
+    constexpr int kInFlight = 8;
+    float ms[kInFlight], ls[kInFlight], ss[kInFlight];
+    uint4 raw[kInFlight][HALF ? 1 : UPW];                    // fp16 or fp32 values as they are stored
+    auto load = [&](int s_first, int s0, int limit) {        // past the end: re-read the last one, not merged
+        const size_t slot0 = ((size_t)g * p.n_slots + s_first) * p.RT + tg;
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k) {
+            const size_t slot = slot0 + (size_t)min(s0 + kStride * k, limit - 1) * p.RT;
+            ms[k] = p.part_ml[slot * kPartMl + j];
+            ls[k] = p.part_ml[slot * kPartMl + 16 + j];
+            ss[k] = HALF ? p.part_ml[slot * kPartMl + 32 + j] : 1.f;
+            const uint4 *po = static_cast<const uint4 *>(p.part_o) + slot * (size_t)(NT / (HALF ? 2 : 1) * 64) + lane;
+            static_assert(UPW == 2, "one 16-byte piece per lane holds a pair of channel tiles");
+            if constexpr (HALF) raw[k][0] = po[(u0 / 2) * 64];
+            else
+#pragma unroll
+                for (int u = 0; u < UPW; ++u) raw[k][u] = po[(u0 + u) * 64];
+        }
+    };
+
+    // The partials of this row tile: `ns` slots from s_first on (wave-uniform).  Where they begin depends on
+    // the lengths only in a batch; otherwise the first ones are requested before the length is known.
+    const bool late = p.dealt && p.B > 1;
+    int s_first = p.dealt ? 0 : b * p.max_splits, limit = p.dealt ? p.max_workers : p.max_splits, ns = 0;
+    if (!late) load(s_first, first, limit);
     const int Nb = load_n_draft(p.n_draft_seq, b, p.N, nullptr);
-    int C = split_tokens_for(p, L + Nb);
-    if (p.adapt == 2) {                                           // what the split-KV pass derived for this batch;
-        C = *p.dev_c;                                             // forced into range should that pass not have run
-        C = min(max(C / kSplitQuantum, 1) * kSplitQuantum, p.C);
+    const int T_b = Nb == 0 ? 0 : load_ctx_len(p.ctx_lens, b, p.max_ctx_len, nullptr) + Nb;
+    if (T_b > 0) {                                            // a sequence without drafts wrote no partials
+        if (!p.dealt) {
+            ns = min((T_b + p.C - 1) / p.C, p.max_splits);
+        } else if (p.B == 1) {
+            const Deal deal = T_b == p.max_ctx_len + p.N ? p.full : deal_units(p, seq_units(p, T_b));
+            ns = deal_worker(deal, stages_of(T_b) - 1) + 1;
+        } else {
+            const BatchUnits u = batch_units(p);
+            const Deal deal = deal_units(p, u.total);
+            const int before = units_before(p, u, b), w0 = deal_worker(deal, before);
+            s_first = w0 + b;
+            limit = ns = deal_worker(deal, before + stages_of(T_b) - 1) - w0 + 1;
+            load(s_first, first, limit);
+        }
     }
-    int ns = Nb == 0 ? 0 : (L + Nb + C - 1) / C;                  // a sequence without drafts wrote no partials
-    ns = min(ns, p.max_splits);
-    const size_t slot0 = (((size_t)b * p.Hkv + g) * p.max_splits) * p.RT + tg;
 
     float mw = -INFINITY, lw = 0.f;
     float4 acc[UPW];
 #pragma unroll
     for (int u = 0; u < UPW; ++u) acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // The merge is a chain (each split rescales the running sums), the loads are not: the
-    // partials of kInFlight splits are requested together, so that a wavefront pays the
-    // memory latency once per batch rather than once per split (up to 32 splits: once).
-    constexpr int kInFlight = 8;
-    for (int s0 = w; s0 < ns; s0 += WAVES * kInFlight) {
-        float ms[kInFlight], ls[kInFlight], os[kInFlight];
-        float4 x[kInFlight][UPW];
+    for (int s0 = first; s0 < ns;) {
 #pragma unroll
         for (int k = 0; k < kInFlight; ++k) {
-            const int s = min(s0 + WAVES * k, ns - 1);       // past the end: re-read the last split, not merged
-            const size_t slot = slot0 + (size_t)s * p.RT;
-            ms[k] = p.part_ml[slot * kPartMl + j];
-            ls[k] = p.part_ml[slot * kPartMl + 16 + j];
-            if constexpr (HALF) {
-                static_assert(UPW == 2, "one 16-byte piece per lane holds a pair of channel tiles");
-                os[k] = ls[k] * p.part_ml[slot * kPartMl + 32 + j];   // the stored rows are O / (l s)
-                const uint4 h = static_cast<const uint4 *>(p.part_o)[slot * (size_t)(NT / 2 * 64) + (u0 / 2) * 64 + lane];
-                const float2 a0 = unpack_half2(h.x), a1 = unpack_half2(h.y), b0 = unpack_half2(h.z), b1 = unpack_half2(h.w);
-                x[k][0] = make_float4(a0.x, a0.y, a1.x, a1.y);
-                x[k][1] = make_float4(b0.x, b0.y, b1.x, b1.y);
-            } else {
-                const float4 *po = static_cast<const float4 *>(p.part_o) + slot * (size_t)(NT * 64) + lane;
-#pragma unroll
-                for (int u = 0; u < UPW; ++u) x[k][u] = po[(u0 + u) * 64];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kInFlight; ++k) {
-            if (s0 + WAVES * k < ns) {                       // uniform over the wavefront
+            if (s0 + kStride * k < ns) {                     // uniform over the wavefront
                 const float mn = fmaxf(mw, ms[k]);
                 const float a = __builtin_amdgcn_exp2f(mw - mn);     // 0 on the first round (mw = -inf)
                 const float c = __builtin_amdgcn_exp2f(ms[k] - mn);
                 mw = mn;
                 lw = lw * a + ls[k] * c;
-                const float co = HALF ? c * os[k] : c;       // weight of the stored O fragment
+                const float co = HALF ? c * (ls[k] * ss[k]) : c;     // the stored rows are O / (l s)
 #pragma unroll
                 for (int u = 0; u < UPW; ++u) {
-                    acc[u].x = acc[u].x * a + x[k][u].x * co; acc[u].y = acc[u].y * a + x[k][u].y * co;
-                    acc[u].z = acc[u].z * a + x[k][u].z * co; acc[u].w = acc[u].w * a + x[k][u].w * co;
+                    float4 x;
+                    if constexpr (HALF) {
+                        const float2 lo = unpack_half2(u ? raw[k][0].z : raw[k][0].x), hi = unpack_half2(u ? raw[k][0].w : raw[k][0].y);
+                        x = make_float4(lo.x, lo.y, hi.x, hi.y);
+                    } else {
+                        x = __builtin_bit_cast(float4, raw[k][u]);
+                    }
+                    acc[u].x = acc[u].x * a + x.x * co; acc[u].y = acc[u].y * a + x.y * co;
+                    acc[u].z = acc[u].z * a + x.z * co; acc[u].w = acc[u].w * a + x.w * co;
                 }
             }
         }
+        s0 += kStride * kInFlight;
+        if (s0 < ns) load(s_first, s0, limit);
     }
-    __shared__ float4 s_acc[WAVES][UPW][64];
-    __shared__ float s_m[WAVES][64], s_l[WAVES][64];
-#pragma unroll
-    for (int u = 0; u < UPW; ++u) s_acc[w][u][lane] = acc[u];
-    s_m[w][lane] = mw;
-    s_l[w][lane] = lw;
-    __syncthreads();
-    if (w != 0) return;
-    float M = s_m[0][lane];
-#pragma unroll
-    for (int k = 1; k < WAVES; ++k) M = fmaxf(M, s_m[k][lane]);
-    float lsum = 0.f;
+    const bool last_block = p.batch_info && blockIdx.x + blockIdx.y + blockIdx.z == 0;
+    float lsum = lw;
     float4 tot[UPW];
+    if constexpr (BY_CHANNEL) {
 #pragma unroll
-    for (int u = 0; u < UPW; ++u) tot[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int u = 0; u < UPW; ++u) tot[u] = acc[u];
+        if (last_block && w == 0) write_batch_info(p);
+    } else {
+        __shared__ float4 s_acc[WAVES][UPW][64];
+        __shared__ float s_m[WAVES][64], s_l[WAVES][64];
 #pragma unroll
-    for (int k = 0; k < WAVES; ++k) {
-        const float wk = s_m[k][lane] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[k][lane] - M);
-        lsum += wk * s_l[k][lane];
+        for (int u = 0; u < UPW; ++u) s_acc[w][u][lane] = acc[u];
+        s_m[w][lane] = mw;
+        s_l[w][lane] = lw;
+        __syncthreads();
+        if (last_block && w == 1) write_batch_info(p);
+        if (w != 0) return;
+        float M = s_m[0][lane];
 #pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            const float4 x = s_acc[k][u][lane];
-            tot[u].x += wk * x.x; tot[u].y += wk * x.y; tot[u].z += wk * x.z; tot[u].w += wk * x.w;
+        for (int k = 1; k < WAVES; ++k) M = fmaxf(M, s_m[k][lane]);
+        lsum = 0.f;
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) tot[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) {
+            const float wk = s_m[k][lane] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[k][lane] - M);
+            lsum += wk * s_l[k][lane];
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) {
+                const float4 y = s_acc[k][u][lane];
+                tot[u].x += wk * y.x; tot[u].y += wk * y.y; tot[u].z += wk * y.z; tot[u].w += wk * y.w;
+            }
         }
     }
     const int row = tg * kRowTile + j;
@@ -135,22 +171,33 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
                    p.out_dtype);
 }
 
-template <int WAVES>
-static void launch_combine_waves(const KParams &p, int D, bool half_partials, dim3 grid, hipStream_t s)
+template <int D, int WAVES, bool BY_CHANNEL>
+static void launch_combine_as(const KParams &p, bool half_partials, dim3 grid, hipStream_t s)
 {
     const dim3 block(64 * WAVES);
-    if (D == 128 && half_partials) hipLaunchKernelGGL((combine_kernel<128, true, WAVES>), grid, block, 0, s, p);
-    else if (D == 128) hipLaunchKernelGGL((combine_kernel<128, false, WAVES>), grid, block, 0, s, p);
-    else if (half_partials) hipLaunchKernelGGL((combine_kernel<64, true, WAVES>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((combine_kernel<64, false, WAVES>), grid, block, 0, s, p);
+    if (half_partials) hipLaunchKernelGGL((combine_kernel<D, true, WAVES, BY_CHANNEL>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((combine_kernel<D, false, WAVES, BY_CHANNEL>), grid, block, 0, s, p);
+}
+
+template <int D>
+static void launch_combine_d(const KParams &p, bool half_partials, hipStream_t s)
+{
+    // Partials per sequence on average, if all sequences are alike.
+    const int per_seq = p.dealt ? (p.max_workers + p.B - 1) / p.B : p.max_splits;
+    if (p.B > 1 && per_seq <= 8) {
+        launch_combine_as<D, D / 32, true>(p, half_partials, dim3(p.RT, p.Hkv, p.B), s);
+        return;
+    }
+    const dim3 grid(p.RT * (D / 32), p.Hkv, p.B);
+    // a wavefront merges its splits as a chain, 8 loads in flight: beyond 32 splits more wavefronts share them
+    if (per_seq > 32) launch_combine_as<D, 8, false>(p, half_partials, grid, s);
+    else launch_combine_as<D, 4, false>(p, half_partials, grid, s);
 }
 
 hipError_t launch_combine(const KParams &p, int D, bool half_partials, hipStream_t s)
 {
-    dim3 grid(p.RT * (D / 32), p.Hkv, p.B);
-    // a wavefront merges its splits as a chain, 8 loads in flight: beyond 32 splits more wavefronts share them
-    if (p.max_splits > 32) launch_combine_waves<8>(p, D, half_partials, grid, s);
-    else launch_combine_waves<4>(p, D, half_partials, grid, s);
+    if (D == 128) launch_combine_d<128>(p, half_partials, s);
+    else launch_combine_d<64>(p, half_partials, s);
     return hipGetLastError();
 }
 
@@ -223,44 +270,6 @@ hipError_t launch_gather(const owl_verify_desc &d, const void *cache, const int3
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Batch plan (batches with a library-chosen split size): one wavefront derives the
-// split size from the actual lengths (batch_split_tokens) and numbers the
-// (sequence, split) pairs densely; the split-KV pass and the combine read the
-// result instead of deriving it once per workgroup (which cost every workgroup of
-// the batched benchmark shape 4 us).
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) batch_plan_kernel(const KParams p)
-{
-    const int lane = threadIdx.x;
-    const int C = batch_split_tokens(p);
-    int32_t *prefix = p.dev_c + kPlanHeader;
-    int base = 0;
-    for (int b0 = 0; b0 < p.B; b0 += 64) {
-        const bool live = b0 + lane < p.B;
-        const int n = live ? (seq_tokens(p, b0 + lane) + C - 1) / C : 0;
-        int scan = n;                                 // inclusive scan over the lanes
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(scan, off);
-            if (lane >= off) scan += up;
-        }
-        if (live) prefix[b0 + lane] = base + scan - n;
-        base += __builtin_amdgcn_readlane(scan, 63);
-    }
-    if (lane == 0) {
-        prefix[p.B] = base;
-        p.dev_c[0] = C;
-        p.dev_c[1] = base;
-    }
-}
-
-hipError_t launch_batch_plan(const KParams &p, hipStream_t s)
-{
-    hipLaunchKernelGGL(batch_plan_kernel, dim3(1), dim3(64), 0, s, p);
-    return hipGetLastError();
-}
-
 // Makes the runtime resolve the combine kernels now, so that their first launch may happen
 // inside a stream capture.
 hipError_t load_aux_kernels()
@@ -268,14 +277,17 @@ hipError_t load_aux_kernels()
     hipFuncAttributes a;
     hipError_t e = hipSuccess;
     const void *fns[] = {
-        reinterpret_cast<const void *>(&combine_kernel<128, true, 4>), reinterpret_cast<const void *>(&combine_kernel<128, false, 4>),
-        reinterpret_cast<const void *>(&combine_kernel<64, true, 4>), reinterpret_cast<const void *>(&combine_kernel<64, false, 4>),
-        reinterpret_cast<const void *>(&combine_kernel<128, true, 8>), reinterpret_cast<const void *>(&combine_kernel<128, false, 8>),
-        reinterpret_cast<const void *>(&combine_kernel<64, true, 8>), reinterpret_cast<const void *>(&combine_kernel<64, false, 8>),
+        reinterpret_cast<const void *>(&combine_kernel<128, true, 4, false>), reinterpret_cast<const void *>(&combine_kernel<128, true, 8, false>),
+        reinterpret_cast<const void *>(&combine_kernel<128, true, 4, true>),
+        reinterpret_cast<const void *>(&combine_kernel<128, false, 4, false>), reinterpret_cast<const void *>(&combine_kernel<128, false, 8, false>),
+        reinterpret_cast<const void *>(&combine_kernel<128, false, 4, true>),
+        reinterpret_cast<const void *>(&combine_kernel<64, true, 4, false>), reinterpret_cast<const void *>(&combine_kernel<64, true, 8, false>),
+        reinterpret_cast<const void *>(&combine_kernel<64, true, 2, true>),
+        reinterpret_cast<const void *>(&combine_kernel<64, false, 4, false>), reinterpret_cast<const void *>(&combine_kernel<64, false, 8, false>),
+        reinterpret_cast<const void *>(&combine_kernel<64, false, 2, true>),
     };
     for (const void *f : fns)
         if (e == hipSuccess) e = hipFuncGetAttributes(&a, f);
-    if (e == hipSuccess) e = hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&batch_plan_kernel));
     return e;
 }
 

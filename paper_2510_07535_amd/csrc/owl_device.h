@@ -33,11 +33,17 @@ __device__ __forceinline__ void store_out4(void *out, int64_t e, float4 v, int o
     *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + e) = w;
 }
 
+// Reads through the scalar cache; for arrays no kernel of the launch writes, uniform index.
+__device__ __forceinline__ int load_uniform(const int32_t *a, int i)
+{
+    return ((const __attribute__((address_space(4))) int32_t *)reinterpret_cast<uintptr_t>(a))[i];
+}
+
 // Prefix length of sequence b, forced into [0, max_ctx_len].
 __device__ __forceinline__ int load_ctx_len(const int32_t *ctx_lens, int b, int max_ctx_len,
                                             uint32_t *st)
 {
-    int L = ctx_lens[b];
+    int L = load_uniform(ctx_lens, b);
     if (L < 0 || L > max_ctx_len) {
         flag_status(st, OWL_DEV_BAD_CTX_LEN);
         L = L < 0 ? 0 : max_ctx_len;
@@ -50,25 +56,12 @@ __device__ __forceinline__ int load_ctx_len(const int32_t *ctx_lens, int b, int 
 __device__ __forceinline__ int load_n_draft(const int32_t *n_draft_seq, int b, int N, uint32_t *st)
 {
     if (!n_draft_seq) return N;
-    int n = n_draft_seq[b];
+    int n = load_uniform(n_draft_seq, b);
     if (n < 0 || n > N) {
         flag_status(st, OWL_DEV_BAD_NDRAFT);
         n = n < 0 ? 0 : N;
     }
     return n;
-}
-
-// Tokens per split for a sequence of T cached rows.  The host plans for the
-// longest context it was told about; a lone, shorter sequence is cut into the
-// same number of (shorter) splits instead of leaving most of the chip idle.
-// Never above p.C, never below the planner's minimum, a multiple of the stage.
-__device__ __forceinline__ int split_tokens_for(const KParams &p, int T)
-{
-    if (p.adapt != 1) return p.C;
-    int C = (T + p.max_splits - 1) / p.max_splits;
-    C = (C + kSplitQuantum - 1) / kSplitQuantum * kSplitQuantum;
-    C = max(C, p.c_min);
-    return min(C, p.C);
 }
 
 // Cached rows of sequence b that the pass has to scan: 0 for a sequence without drafts.
@@ -81,112 +74,138 @@ __device__ __forceinline__ int seq_tokens(const KParams &p, int b)
     return n == 0 ? 0 : L + n;
 }
 
-// Sum / maximum over lanes [0, n) of a wavefront, as scalars (n uniform, <= 64).
-__device__ __forceinline__ int lanes_sum(int v, int n)
-{
-    int s = 0;
-    for (int l = 0; l < n; ++l) s += __builtin_amdgcn_readlane(v, l);
-    return s;
-}
-__device__ __forceinline__ int lanes_max(int v, int n)
-{
-    int m = 0;
-    for (int l = 0; l < n; ++l) m = max(m, __builtin_amdgcn_readlane(v, l));
-    return m;
-}
-
-// Split size for a batch (adapt == 2).  The host plans for B sequences of the
-// longest admissible length; a real batch is ragged, and with one workgroup per
-// compute unit at a time a launch of, say, 1.4 rounds leaves most of the chip
-// idle for its last round.  Every wavefront derives, from the actual lengths,
-// about the smallest split size (a multiple of the stage, within the planner's
-// bounds and the launched grid) whose workgroup count still fits the whole
-// number of rounds that the planned size needs: the rounds come out full and as
-// short as they can be.  All lanes of the calling wavefront, and every wavefront
-// of the launch, get the same value: it depends only on p and the two length
-// arrays, and the combine reads the value the split-KV pass stored.
+// ---------------------------------------------------------------------------
+// How the K/V of a launch is dealt out when the caller leaves the split size to
+// the library.  A KV head (and row group) has `workers` workgroups, all resident
+// at once, one per compute unit; the sequences' stages of 64 tokens are laid end
+// to end and every worker takes an equal run of them, crossing from one sequence
+// into the next where its share asks for it.  Each run is cut at the sequence
+// boundaries into pieces, one partial per piece.  So every compute unit gets the
+// same work whatever the lengths are, and pays for set-up and epilogue once or
+// twice instead of once per split.  (Equal splits in 4-5 rounds of workgroups, the
+// alternative, left 9 % of the compute units idle in the last round and 9 % of
+// the time in set-up and epilogues on 16 sequences of 8K-64K tokens.)
 //
-// The search runs across lanes: lane l prices one candidate size against all
-// sequences (their lengths travel as scalars), a ballot picks the first
-// candidate that fits, a second pass refines between it and its neighbour.
-// Workgroup counts of candidates are formed in float: a count that is off by
-// one moves the choice by a stage, never the validity of the result.
-__device__ __forceinline__ int batch_split_tokens(const KParams &p)
+// A sequence counts `seq_extra` units beyond its stages, at its end: what the masked
+// steps over its drafts and the set-up of the following piece cost.
+// ---------------------------------------------------------------------------
+// a / b for 0 <= a, 0 < b and quotients below 2^20: a multiplication and a correction instead of the
+// thirty dependent instructions of an integer division (four of them cost a workgroup half a microsecond).
+__device__ __forceinline__ int quotient(int a, int b)
 {
-    const int lane = threadIdx.x & 63;
-    const int streams = p.Hkv * p.row_groups;        // workgroups per split
-    // sequence lengths: sequence b < 64 sits in lane b; further ones are re-read (uniform loads)
-    const int t_lane = lane < p.B ? seq_tokens(p, lane) : 0;
-    const int n_lane = min(p.B, 64);
-    auto tokens_of = [&](int b) { return b < 64 ? __builtin_amdgcn_readlane(t_lane, b) : seq_tokens(p, b); };
-
-    int max_t = lanes_max(t_lane, n_lane);
-    for (int b = 64; b < p.B; ++b) max_t = max(max_t, seq_tokens(p, b));
-
-    const int hi = p.C / kSplitQuantum;
-    int lo = ((max_t + p.max_splits - 1) / p.max_splits + kSplitQuantum - 1) / kSplitQuantum;   // the grid has max_splits
-    lo = min(max(max(lo, p.c_min / kSplitQuantum), 1), hi);
-
-    // whole rounds the planned size needs (exact)
-    int at_hi = lanes_sum((t_lane + p.C - 1) / p.C, n_lane);
-    for (int b = 64; b < p.B; ++b) at_hi += (seq_tokens(p, b) + p.C - 1) / p.C;
-    const int rounds = (at_hi * streams + p.n_cu - 1) / p.n_cu;
-    const float budget = (float)(rounds * p.n_cu) / (float)streams + 0.5f;      // splits that fit
-
-    // first candidate q0 + lane * step (capped at hi) whose split count fits; -1 if none does
-    auto first_fit = [&](int q0, int step) {
-        const int q = min(q0 + lane * step, hi);
-        const float rc = 1.0f / (float)(q * kSplitQuantum);
-        float n = 0.f;
-        for (int b = 0; b < p.B; ++b) n += ceilf((float)tokens_of(b) * rc);
-        const unsigned long long ok = __ballot(n <= budget);
-        return ok ? (int)__ffsll((long long)ok) - 1 : -1;
-    };
-    if (hi == lo) return hi * kSplitQuantum;
-    const int step = (hi - lo + 62) / 63;            // lane 63 reaches hi; <= 5 for the largest split the planner allows
-    const int l1 = first_fit(lo, step);
-    if (l1 < 0) return hi * kSplitQuantum;
-    int q = lo + l1 * step;
-    if (l1 > 0 && step > 1) {                        // refine between the last misfit and the first fit
-        const int q1 = lo + (l1 - 1) * step + 1;
-        const int l2 = first_fit(q1, 1);
-        if (l2 >= 0) q = q1 + l2;
-    }
-    const int C = min(q, hi) * kSplitQuantum;
-    // the launched grid has room for what the bounds above allow; should the float counts ever
-    // have let more through, the planned size (which always fits) is used instead
-    int total = lanes_sum((t_lane + C - 1) / C, n_lane);
-    for (int b = 64; b < p.B; ++b) total += (seq_tokens(p, b) + C - 1) / C;
-    return total <= p.item_slots ? C : p.C;
+    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+    int r = a - q * b;
+    if (r < 0) --q, r += b;
+    if (r >= b) ++q;
+    return __builtin_amdgcn_readfirstlane(q);
 }
 
-// Layout of the batch plan that batch_plan_kernel leaves in the workspace (int32): [0] the split
-// size C derived from the lengths, [1] the number of (sequence, split) pairs, [2 + b] the pairs
-// of the sequences before b (b = 0 .. B).
-constexpr int kPlanHeader = 2;
+__device__ __forceinline__ Deal deal_units(const KParams &p, int units)
+{
+    // more than one round only where a share would outgrow the page list in LDS
+    int n = p.round_workers;
+    if (units > n * kMaxPieceUnits) n *= quotient(units + n * kMaxPieceUnits - 1, n * kMaxPieceUnits);
+    n = min(n, p.max_workers);
+    if (units < n * p.min_units) n = max(1, quotient(units, p.min_units));
+    const int q = quotient(units, n);
+    return Deal{n, q, units - q * n};
+}
+__device__ __forceinline__ int deal_begin(const Deal &d, int worker) { return worker * d.q + min(worker, d.r); }
+__device__ __forceinline__ int deal_worker(const Deal &d, int unit)
+{
+    const int cut = d.r * (d.q + 1);
+    return unit < cut ? quotient(unit, d.q + 1) : d.r + quotient(unit - cut, d.q);
+}
 
-// The (sequence, split) pair that work item `id` of a batch stands for when the items of all
-// sequences are numbered densely, sequence by sequence: workgroups that have something to do then
-// come first in launch order and the surplus of the grid (sized for the worst case) trails behind,
-// instead of being dispatched in between and holding up the ones behind them.  Reads the plan; one
-// round trip for up to 64 sequences.  Wave-uniform; false if id is beyond the last item.
-__device__ __forceinline__ bool batch_item(const KParams &p, int id, int *b_out, int *c_out)
+__device__ __forceinline__ int stages_of(int tokens) { return (tokens + kSplitQuantum - 1) / kSplitQuantum; }
+__device__ __forceinline__ int seq_units(const KParams &p, int tokens)
+{
+    return tokens == 0 ? 0 : stages_of(tokens) + p.seq_extra;
+}
+
+// Inclusive sum over the lanes of the wavefront.
+__device__ __forceinline__ int lane_scan(int v)
 {
     const int lane = threadIdx.x & 63;
-    const int32_t *prefix = p.dev_c + kPlanHeader;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(v, off);
+        if (lane >= off) v += up;
+    }
+    return v;
+}
+
+// The units of a batch: lane l of the calling wavefront keeps the running sum through sequence l;
+// sequences from 64 on are read again when they are asked for.
+struct BatchUnits {
+    int scan, total;
+};
+
+__device__ __forceinline__ int chunk_scan(const KParams &p, int b0)
+{
+    const int b = b0 + (threadIdx.x & 63);
+    return lane_scan(b < p.B ? seq_units(p, seq_tokens(p, b)) : 0);
+}
+
+__device__ __forceinline__ BatchUnits batch_units(const KParams &p)
+{
+    BatchUnits u;
+    u.scan = chunk_scan(p, 0);
+    u.total = __builtin_amdgcn_readlane(u.scan, 63);
+    for (int b0 = 64; b0 < p.B; b0 += 64) u.total += __builtin_amdgcn_readlane(chunk_scan(p, b0), 63);
+    return u;
+}
+
+// Sequence that unit x falls into (0 <= x < total) and the units before it.  Wave-uniform.
+__device__ __forceinline__ void find_unit(const KParams &p, const BatchUnits &u, int x, int *b_out, int *before_out)
+{
+    int base = 0, scan = u.scan;
+    for (int b0 = 0;;) {
+        const unsigned long long hit = __ballot(x < base + scan);
+        if (hit || b0 + 64 >= p.B) {
+            const int l = hit ? (int)__ffsll((long long)hit) - 1 : 63;
+            *b_out = min(b0 + l, p.B - 1);
+            *before_out = base + (l > 0 ? __builtin_amdgcn_readlane(scan, max(l - 1, 0)) : 0);
+            return;
+        }
+        base += __builtin_amdgcn_readlane(scan, 63);
+        b0 += 64;
+        scan = chunk_scan(p, b0);
+    }
+}
+
+// Units before sequence b.  Wave-uniform.
+__device__ __forceinline__ int units_before(const KParams &p, const BatchUnits &u, int b)
+{
+    int base = 0, scan = u.scan;
+    for (int b0 = 0; b >= b0 + 64;) {
+        base += __builtin_amdgcn_readlane(scan, 63);
+        b0 += 64;
+        scan = chunk_scan(p, b0);
+    }
+    const int l = b & 63;
+    return base + (l > 0 ? __builtin_amdgcn_readlane(scan, max(l - 1, 0)) : 0);
+}
+
+// The last words of a batch's workspace say what equal splits of the planned size would make of it
+// (int32): [0] that size C, [1] the number of (sequence, split) pairs, [2 + b] the pairs of the
+// sequences before b (b = 0 .. B).  For inspection; no kernel reads it.  One wavefront.
+__device__ __forceinline__ void write_batch_info(const KParams &p)
+{
+    const int lane = threadIdx.x & 63;
+    int base = 0;
     for (int b0 = 0; b0 < p.B; b0 += 64) {
         const bool live = b0 + lane < p.B;
-        const int lo = live ? prefix[b0 + lane] : 0x7fffffff;
-        const int up = live ? prefix[b0 + lane + 1] : 0x7fffffff;
-        const unsigned long long hit = __ballot(live && id >= lo && id < up);
-        if (hit) {
-            const int l = (int)__ffsll((long long)hit) - 1;
-            *b_out = b0 + l;
-            *c_out = id - __builtin_amdgcn_readlane(lo, l);
-            return true;
-        }
+        const int n = live ? (seq_tokens(p, b0 + lane) + p.C - 1) / p.C : 0;
+        const int scan = lane_scan(n);
+        if (live) p.batch_info[2 + b0 + lane] = base + scan - n;
+        base += __builtin_amdgcn_readlane(scan, 63);
     }
-    return false;
+    if (lane == 0) {
+        p.batch_info[2 + p.B] = base;
+        p.batch_info[0] = p.C;
+        p.batch_info[1] = base;
+    }
 }
 
 // Physical page of logical page lp of sequence b; an id outside the pool (or a

@@ -1,8 +1,10 @@
 // Split-KV pass of the verify-step attention for gfx950 (MI355X).
 //
-// One workgroup (8 wavefronts, two per SIMD) owns one (sequence, KV head, KV
-// split, row group).  It streams its split of the paged K/V cache through LDS
-// exactly once and holds, in MFMA accumulators, the un-normalised outputs of
+// One workgroup (8 wavefronts, two per SIMD) owns one (KV head, row group, share of
+// the K/V): a share is one split of one sequence, or an even run of the whole
+// batch's stages that may cross from one sequence into the next (deal_units), and is
+// worked through piece by piece, one piece per sequence.  A piece streams its part of
+// the paged K/V cache through LDS exactly once and holds, in MFMA accumulators, the un-normalised outputs of
 // ALL query rows that share this KV head: rows = (draft node i, query head
 // within the group), R = (Hq/Hkv) * N of them, cut into 16-row tiles that are
 // dealt out to the wavefronts.  That packing is what makes the cost of
@@ -158,15 +160,42 @@ struct Geo {
     static constexpr int QREGS = kF32 ? D / 4 : D / 32; // Q fragment slots per tile
     static constexpr int KSWZ = (PPR - 1) & 15;         // K rows: piece ^= key & KSWZ
     static constexpr int VSWM = PPR >= 16 ? 7 : PPR / 2 - 1;   // V rows: piece ^= (key & VSWM) << 1
-    static constexpr size_t LDS = (size_t)NS * 2 * STAGE + kMaxPagesPerSplit * 4 + 64 * 8 + 64 * 4;
+    static constexpr size_t LDS = (size_t)NS * 2 * STAGE + kMaxPiecePages * 4 + 64 * 8 + 64 * 4;
     static_assert(WR * WK == kWaves && (WK == 1 || WK == 2), "eight wavefronts per workgroup");
     static_assert(NS * LPS < 64, "loads in flight must fit vmcnt");
     static_assert((WK - 1) * WR * TPW * (4 * (NT + 1) + 1) * 256 <= NS * 2 * STAGE,
                   "cross-wave merge buffer must fit in the stage ring");
 };
 
-template <typename T, int D, int TPW, int WR, int WK, bool TL>
-__global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
+// One piece of work: the stages of sequence b between two token positions.
+struct Piece {
+    int b, L, Nb;                                    // sequence, its prefix length and number of drafts
+    int pos0, pos1;                                  // [pos0, pos1) of its L + Nb cached rows, pos0 a multiple of 64
+    size_t slot;                                     // where the partials of row tile 0 go
+};
+
+// Page-table entries requested for a window that begins at pos0, before the context length that
+// decides about the window was known (pos0 < 0: none).
+struct PageGuess {
+    int pos0;
+    int page[2];
+};
+
+__device__ __forceinline__ PageGuess guess_pages(const KParams &p, int b, int pos0)
+{
+    PageGuess gs;
+    gs.pos0 = pos0;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {                    // no branch: an entry past the window is simply not used
+        const int lp = pos0 / kPage + (int)threadIdx.x + r * kThreads;
+        gs.page[r] = p.page_table ? p.page_table[(int64_t)b * p.max_pages + min(lp, p.max_pages - 1)] : lp;
+    }
+    return gs;
+}
+
+template <typename T, int D, int TPW, int WR, int WK, typename Stamp>
+__device__ __forceinline__ void run_piece(const KParams &p, unsigned char *smem, int g, int rg, const Piece &pc,
+                                          const PageGuess &guess, Stamp &&stamp)
 {
     using GEO = Geo<T, D, TPW, WR, WK>;
     constexpr bool kF32 = GEO::kF32;
@@ -176,165 +205,76 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     constexpr int KSWZ = GEO::KSWZ, VSWM = GEO::VSWM, VREG = GEO::VREG;
     constexpr int KQ = kF32 ? 1 : QREGS;             // K/Q fragment slots of the 16-bit paths
 
-    extern __shared__ __align__(16) unsigned char smem[];
     int32_t *s_pages = reinterpret_cast<int32_t *>(smem + NS * 2 * STAGE);
-    uint64_t *s_anc = reinterpret_cast<uint64_t *>(s_pages + kMaxPagesPerSplit);
+    uint64_t *s_anc = reinterpret_cast<uint64_t *>(s_pages + kMaxPiecePages);
     int32_t *s_parent = reinterpret_cast<int32_t *>(s_anc + 64);
     const uint32_t lds0 =
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // What follows from the thread's number and the KV head is derived once per piece: kept across the
+    // pieces of a share (as the compiler would by itself) it does not fit the registers of the loops.
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    asm volatile("" : "+s"(g), "+s"(rg));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % WR, wk = wave / WR;
     const int j = lane & 15, qd = lane >> 4;
 
-    // Workgroups go to the chip's eight XCDs round-robin in launch order, whether or not
-    // they have work.  KV heads (all with the same amount of work) vary fastest, so that
-    // splits that do not exist for a short sequence do not leave whole XCDs idle.
-    // n numbers the workgroups in launch order; a "stream" is one (KV head, split, sequence).
-    // Row groups (workgroups that take different row tiles of the same stream, each reading its
-    // K/V) are laid out so that the groups of a stream follow each other on ONE XCD: stream u sits
-    // on XCD u mod 8, its groups in consecutive slots of that XCD, and all but the first find the
-    // split in that XCD's L2.  With a single row group this is the plain order (n = u).
-    // (the host keeps the workgroup count of a launch below 2^31)
-    uint32_t n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    int rg = 0;
-    if (p.row_groups > 1) {                          // the host pads the stream count to a multiple of 8
-        const uint32_t slot = n >> 3;
-        rg = (int)(slot % (uint32_t)p.row_groups);
-        n = ((slot / (uint32_t)p.row_groups) << 3) | (n & 7);
-    }
-    const int g = (int)(n % (uint32_t)p.Hkv);
-    const uint32_t item = n / (uint32_t)p.Hkv;       // (split, sequence), split fastest
-    int c = (int)(item % gridDim.y);
-    int b = (int)(item / gridDim.y);
-    if (p.adapt != 2 && b >= p.B) return;            // cannot happen with the grids the host launches
+    const int b = pc.b, L = pc.L, Nb = pc.Nb, pos0 = pc.pos0, pos1 = pc.pos1, Ttot = L + Nb;
+    const int nstages = (pos1 - pos0 + SK - 1) / SK;
+    const bool has_drafts = pos1 > L;               // uniform over the workgroup
 
-    // timeline of this workgroup (profiling instantiations only; the production kernels
-    // carry neither the pointer nor a branch)
-    long long *tl = nullptr;
-    if constexpr (TL) {
-        const long long flat = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
-        tl = p.timeline + 10 * flat;
-        if (tid == 0) {
-            tl[0] = wall_clock64();
-            tl[1] = tl[2] = tl[3] = tl[4] = tl[5] = tl[8] = tl[9] = 0;
-            // XCC_ID register (bits 3:0) above the shader-engine / CU id: one value per compute unit
-            tl[6] = ((long long)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15) << 16) | __smid();
-            tl[7] = flat;
-        }
-    }
-    auto stamp = [&](int k) {
-        if constexpr (TL) {
-            if (tid == 0) {
-                tl[k] = wall_clock64();
-                if (k == 2) tl[8] = clock64();        // shader cycles at both ends of the fast loop:
-                if (k == 3) tl[9] = clock64();        // their rate is the clock the chip really ran at
-            }
-        }
-    };
-
-    // ---- everything that does not depend on the context length is requested
-    // first, so that all of the kernel's set-up reads are in flight together:
-    // raw page-table entries of this split's window, the parent array, Q ----
-    int C = p.C;                                      // revised below once the context length is known
-    if (p.adapt == 2) {                               // a batch: the split size follows all its lengths
-        C = p.dev_c[0];                               // derived by the plan kernel that precedes this launch
-        C = min(max(C / kSplitQuantum, 1) * kSplitQuantum, p.C);
-        // (y, z) is only a number here: the items that exist are the first ones in launch order
-        if (item >= (uint32_t)p.item_slots || !batch_item(p, (int)item, &b, &c)) return;
-    }
-    int pos0 = c * C;
-    // drafted tokens of this sequence (a batch may mix tree sizes): rows of nodes >= Nb are
-    // idle, their K/V rows are not part of the sequence, and the combine writes zeros for them
-    const int Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status);
-    if (Nb == 0) return;
-    // The context length is requested before everything else: vector loads complete in
-    // order, so asked for after the query fragments it would only arrive behind them
-    // (2.4 us later with 15-20 row tiles), and the whole prologue hangs on it.
-    const int L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status);
-    int raw_page[kMaxPagesPerSplit / kThreads];
-    auto request_pages = [&]() {
-        const int win_pages = C / kPage;             // pages a full split spans (<= kMaxPagesPerSplit)
-#pragma unroll
-        for (int r = 0; r < kMaxPagesPerSplit / kThreads; ++r) {
-            const int idx = tid + r * kThreads, lp = pos0 / kPage + idx;
-            raw_page[r] = -1;
-            if (idx < win_pages) {
-                if (!p.page_table) raw_page[r] = lp;
-                else if (lp < p.max_pages) raw_page[r] = p.page_table[(int64_t)b * p.max_pages + lp];
-            }
-        }
-    };
-    request_pages();
-    if (tid < p.N) s_parent[tid] = p.parent[(int64_t)b * p.N + tid];
+    // ---- set-up: page list, parents and query rows are requested together, one memory round trip ----
+    const int npg = (pos1 - pos0 + kPage - 1) / kPage;
+    PageGuess pages = guess;
+    if (guess.pos0 != pos0) pages = guess_pages(p, b, pos0);
+    int parent = 0;
+    if (has_drafts) parent = p.parent[(int64_t)b * p.N + min(tid, p.N - 1)];
     // ---- this wave's query rows: tiles wr, wr + WR, ... of the row group ----
+    // Row `row` belongs to node row / G; the quotient is exact: rows stay below 2^12, where the error of
+    // the product is far below the half that is added.
+    const float inv_g = __builtin_amdgcn_rcpf((float)p.G);
+    auto node_of = [&](int row) -> int { return (int)(((float)row + 0.5f) * inv_g); };
+    const unsigned char *q_head = static_cast<const unsigned char *>(p.q) + ((int64_t)b * p.N * p.Hq + (int64_t)g * p.G) * D * ES;
+    auto row_offset = [&](int row) -> int64_t { return ((int64_t)node_of(row) * (p.Hq - p.G) + row) * ROWB; };
     uint4 qf[TPW][KQ];
     float qs[TPW][kF32 ? QREGS : 1];
     int irow[TPW];
     int my_nt = 0;
-    // Requested only after the first K/V stage (below): the query fragments of all workgroups of
-    // a KV head are the same few L2 lines, they take ~2 us to come in with 15-20 row tiles, and
-    // vector loads complete in order, so the first stage's DMA would queue up behind them.
-    auto load_queries = [&]() {
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         const int tg = rg * p.group_tiles + t * WR + wr;
         const bool tile_ok = t * WR + wr < p.group_tiles && tg < p.RT;
         my_nt += tile_ok ? 1 : 0;
-        const int row = tg * kRowTile + j;
-        const bool ok = tile_ok && row < p.R && row / p.G < Nb;
-        const int i = ok ? row / p.G : 0;
-        const int hh = ok ? row % p.G : 0;
-        irow[t] = ok ? i : -1;
-        const unsigned char *qp = static_cast<const unsigned char *>(p.q) +
-            ((((int64_t)b * p.N + i) * p.Hq + g * p.G + hh) * D) * ES;
+        const int row = tg * kRowTile + j, i = node_of(row);
+        irow[t] = tile_ok && row < p.R && i < Nb ? i : -1;
         if constexpr (kF32) {
+            const float *qp = reinterpret_cast<const float *>(q_head + row_offset(min(row, p.R - 1)));
 #pragma unroll
-            for (int kk = 0; kk < QREGS; ++kk)
-                qs[t][kk] = ok ? reinterpret_cast<const float *>(qp)[4 * kk + qd] : 0.f;
-        } else {
-#pragma unroll
-            for (int kk = 0; kk < QREGS; ++kk)
-                qf[t][kk] = ok ? *reinterpret_cast<const uint4 *>(qp + (32 * kk + 8 * qd) * ES)
-                               : make_uint4(0, 0, 0, 0);
-        }
-    }
-    my_nt = __builtin_amdgcn_readfirstlane(my_nt);
-    };
-
-    const int Ttot = L + Nb;
-    if (p.adapt == 1 && split_tokens_for(p, Ttot) != C) {   // uniform: a context shorter than planned for
-        C = split_tokens_for(p, Ttot);
-        pos0 = c * C;
-        request_pages();                            // the window moved: one more round trip
-    }
-    if (pos0 >= Ttot) return;                       // this split does not exist for b
-    const int pos1 = min(pos0 + C, Ttot);
-    const int nstages = (pos1 - pos0 + SK - 1) / SK;
-
-    // ---- page list of this split (validated now that its extent is known),
-    // and the tree mask if drafts are in reach ----
-    {
-        const int npg = (pos1 - pos0 + kPage - 1) / kPage;
-#pragma unroll
-        for (int r = 0; r < kMaxPagesPerSplit / kThreads; ++r) {
-            const int idx = tid + r * kThreads;
-            if (idx < npg) {
-                int pg = raw_page[r];
-                if (pg < 0 || pg >= p.n_pool_pages) {    // also: logical page beyond the table
-                    flag_status(p.dev_status, OWL_DEV_BAD_PAGE);
-                    pg = 0;
-                }
-                s_pages[idx] = pg;
+            for (int kk = 0; kk < QREGS; ++kk) {
+                const float x = qp[4 * kk + qd];
+                qs[t][kk] = irow[t] >= 0 ? x : 0.f;
             }
         }
     }
-    const bool has_drafts = pos1 > L;               // uniform over the workgroup
-    __syncthreads();
-    if (has_drafts) {
-        if (tid < Nb) s_anc[tid] = ancestor_set(s_parent, tid, nullptr, p.dev_status);
-        __syncthreads();
+
+    auto keep_page = [&](int idx, int pg) {
+        if (idx >= npg) return;
+        if (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages)) {
+            flag_status(p.dev_status, OWL_DEV_BAD_PAGE);
+            pg = 0;
+        }
+        s_pages[idx] = pg;
+    };
+#pragma unroll
+    for (int r = 0; r < 2; ++r) keep_page(tid + r * kThreads, pages.page[r]);
+    for (int first = 2 * kThreads; first < npg; first += 2 * kThreads) {       // more than 16K tokens in one piece
+        const PageGuess more = guess_pages(p, b, pos0 + first * kPage);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) keep_page(first + tid + r * kThreads, more.page[r]);
     }
+    if (has_drafts && tid < p.N) s_parent[tid] = parent;
+    __syncthreads();
     stamp(1);
 
     // ---- stage issue ----
@@ -398,6 +338,42 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         }
     };
     auto issue_stage = [&](int s) { issue_stage_pg(s, stage_page(s)); };
+
+    // The query rows travel like K pages: by DMA, 16 bytes a lane, rows contiguous, into the ring slots
+    // behind the stages that are requested with them (TPW slots, one tile of every wavefront each), from
+    // where each wavefront picks its own fragments.  (Loaded straight into registers they took 2 us for
+    // 20 row tiles, as 64-byte pieces of 16 rows per instruction, and the compiler, which does not see the
+    // ring's transfers in the wait counter, drained the whole ring before it used them.)
+    constexpr int kQSlot0 = NS - TPW;                // first ring slot the queries occupy
+    auto q_lds = [&](int t) -> uint32_t {            // offset of this wavefront's tile t in the ring
+        return (uint32_t)((kQSlot0 + t) * STAGE + (wave & 3) * (kPage * ROWB) + (wave >> 2) * VREG);
+    };
+    auto issue_queries = [&]() {
+        if constexpr (!kF32) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                const int row0 = (rg * p.group_tiles + t * WR + wr) * kRowTile;
+#pragma unroll
+                for (int it = 0; it < LPS; ++it) {
+                    const int slot = it * RPI + ld_row;
+                    dma16(q_head + row_offset(min(row0 + slot, p.R - 1)) + ((ld_piece ^ (slot & KSWZ)) << 4),
+                          __builtin_amdgcn_readfirstlane(lds0 + q_lds(t) + it * RPI * ROWB));
+                }
+            }
+        }
+    };
+    auto take_queries = [&]() {
+        if constexpr (!kF32) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                for (int kk = 0; kk < KQ; ++kk) {
+                    const uint4 x = *reinterpret_cast<const uint4 *>(smem + q_lds(t) + j * ROWB + (((4 * kk + qd) ^ (j & KSWZ)) << 4));
+                    qf[t][kk] = irow[t] >= 0 ? x : make_uint4(0, 0, 0, 0);
+                }
+        }
+    };
+    static_assert(kF32 || (TPW < NS && 4 * kPage * ROWB == STAGE), "the queries leave at least one ring slot to the first stage");
 
     f32x4 O[TPW][NT + 1];
     float m[TPW];
@@ -649,30 +625,31 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     };
 
     // ---- careful softmax of one row tile over one 32-key step: mask + exact online rescale ----
+    // Straight-line code, so that the chains of a wavefront's tiles overlap: the visible keys of a row
+    // come as one 32-bit word per step, and the rescale is done whether or not a reference moved
+    // (a factor of one changes nothing).
     auto softmax_step = [&](f32x4 &s0, f32x4 &s1, int t, int step_pos) {
         if (step_pos + 32 > L) {                     // reaches drafts or the ragged end (uniform)
-            uint64_t anc = ~(uint64_t)0;
-            if (has_drafts && irow[t] >= 0) anc = s_anc[irow[t]];
+            uint64_t anc = 0;                        // the drafts row t sees; a row without a node sees all of them
+            if (has_drafts) anc = irow[t] >= 0 ? s_anc[irow[t]] : ~(uint64_t)0 >> (64 - Nb);
+            const int ahead = L - step_pos;          // prefix keys in this step (< 32), or minus the drafts before it
+            const uint32_t word = ahead >= 0 ? ((1u << ahead) - 1u) | (uint32_t)(anc << ahead)
+                                             : (-ahead < 64 ? (uint32_t)(anc >> -ahead) : 0u);
+            const uint32_t va = word >> (4 * qd), vb = va >> 16;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int pa = step_pos + 4 * qd + r, pb = pa + 16;
-                const bool va = pa < L || (pa < Ttot && ((anc >> (pa - L)) & 1));
-                const bool vb = pb < L || (pb < Ttot && ((anc >> (pb - L)) & 1));
-                s0[r] = va ? s0[r] : -INFINITY;
-                s1[r] = vb ? s1[r] : -INFINITY;
+                s0[r] = (va >> r) & 1u ? s0[r] : -INFINITY;
+                s1[r] = (vb >> r) & 1u ? s1[r] : -INFINITY;
             }
         }
         float tm = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
                          fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
         tm = quad_column_max(tm);
-        const float sc = tm * p.c_log2;
-        if (__builtin_amdgcn_ballot_w64(sc > m[t]) != 0) {          // uniform over the wave
-            const float mn = fmaxf(m[t], sc);
-            const float alpha = fast_exp2(m[t] - mn);
-            m[t] = mn;
+        const float mn = fmaxf(m[t], tm * p.c_log2);
+        const float alpha = fast_exp2(m[t] - mn);
+        m[t] = mn;
 #pragma unroll
-            for (int u = 0; u <= NT; ++u) O[t][u] *= alpha;
-        }
+        for (int u = 0; u <= NT; ++u) O[t][u] *= alpha;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             s0[r] = fast_exp2(__builtin_fmaf(s0[r], p.c_log2, -m[t]));
@@ -682,6 +659,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
 
     // ---- careful step: any step, any type ----
     auto careful_step = [&](int buf, int ks, int step_pos) {
+        if (my_nt == 0) return;
         const unsigned char *Kb = smem + buf * STAGE + ks * 32 * ROWB;
         const unsigned char *Vb = Kb + VREG;
         if constexpr (kF32) {
@@ -706,7 +684,6 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
                 }
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) {
-                    if (t >= my_nt) continue;
                     f32x4 s0 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int kk = 0; kk < QREGS; ++kk)
@@ -729,9 +706,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
             load_k_frags(Kb, kf);
             uint4 pf[TPW];
 #pragma unroll
-            for (int t = 0; t < TPW; ++t) {
-                pf[t] = make_uint4(0, 0, 0, 0);
-                if (t >= my_nt) continue;
+            for (int t = 0; t < TPW; ++t) {          // (a tile the wavefront does not own has zero queries and is dropped)
                 f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kk = 0; kk < KQ; ++kk) {
@@ -944,9 +919,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     };
     static_assert(TPW <= 3, "run_fast dispatches on at most three tile counts");
 
-    // The set-up loads are drained here, so that vmcnt counts the K/V stages from now on; the
-    // query fragments, requested between stage 0 and stage 1, complete in order with them (a
-    // wait that leaves only younger stages outstanding covers stage 0 and the queries alike).
+    // The set-up loads are drained here, so that vmcnt counts the K/V stages from now on.
     wait_vmcnt<0>();
 
     // Pass 0: stages that lie wholly inside the prefix run the fast step with a
@@ -957,21 +930,26 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     // an fp16 P overflows 12 above it (and the redo is then the price).  fp32 is
     // the small correctness shape and has no fast loop.
     constexpr bool kHasFast = !kF32;
-    issue_stage(0);                                   // nstages >= 1: the split exists
-    load_queries();
+    if constexpr (!kF32) {
+        // stage 0 (a piece is not empty), the queries, and the stages whose slots the queries leave free
+        issue_stage(0);
+        issue_queries();
+        for (issued = 1; issued < kQSlot0 && issued < nstages; ++issued) issue_stage(issued);
+    }
+    if (has_drafts && tid < Nb) s_anc[tid] = ancestor_set(s_parent, tid, nullptr, p.dev_status);
+    if constexpr (!kF32) {
+        wait_stage(0);                                // the queries were requested before stage 1: they are in as well
+        take_queries();
+        __syncthreads();                              // everyone has; their slots are free
+    }
     for (int pass = 0; pass < 2; ++pass) {
-        issued = pass == 0 ? 1 : 0;                   // the redo pass starts over
-        for (; issued < NS - 1 && issued < nstages; ++issued) issue_stage(issued);
         int n_fast = 0;
         if (kHasFast && pass == 0) n_fast = max(0, min(nstages, (L - pos0) / SK));
+        if (pass == 1) issued = 0;                    // the redo pass starts over
+        // (the careful loop begins by filling the last slot itself)
+        for (const int fill = n_fast > 0 ? NS : NS - 1; issued < fill && issued < nstages; ++issued) issue_stage(issued);
         if (n_fast > 0) {
-            wait_stage(0);
-            __syncthreads();
             stamp(2);
-            if (issued < nstages) {                 // the slot beyond the prologue's stages is free
-                issue_stage(issued);
-                ++issued;
-            }
             f32x4 Sa[TPW][2];
             init_reference(0, wk, Sa);
             probe_spread(n_fast);
@@ -1040,7 +1018,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         for (int t = 0; t < TPW; ++t) {
             const int tg = rg * p.group_tiles + t * WR + wr;
             if (t * WR + wr >= p.group_tiles || tg >= p.RT) continue;
-            const size_t slot = (((size_t)b * p.Hkv + g) * p.max_splits + c) * p.RT + tg;
+            const size_t slot = pc.slot + tg;
             const float l = O[t][NT][0];
             if (kF32 || !p.half_partials) {                          // uniform over the launch
                 float4 *po = static_cast<float4 *>(p.part_o) + slot * (size_t)(NT * 64) + lane;
@@ -1078,6 +1056,111 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
                 }
             }
         }
+    }
+}
+
+template <typename T, int D, int TPW, int WR, int WK, bool TL>
+__global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+
+    // Workgroups go to the chip's eight XCDs round-robin in launch order, whether or not
+    // they have work.  KV heads (all with the same amount of work) vary fastest, so that
+    // splits that do not exist for a short sequence do not leave whole XCDs idle.
+    // n numbers the workgroups in launch order; a "stream" is one (KV head, share of the K/V).
+    // Row groups (workgroups that take different row tiles of the same stream, each reading its
+    // K/V) are laid out so that the groups of a stream follow each other on ONE XCD: stream u sits
+    // on XCD u mod 8, its groups in consecutive slots of that XCD, and all but the first find the
+    // K/V in that XCD's L2.  With a single row group this is the plain order (n = u).
+    // (the host keeps the workgroup count of a launch below 2^31)
+    uint32_t n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    int rg = 0;
+    if (p.row_groups > 1) {                          // the host pads the stream count to a multiple of 8
+        const uint32_t slot = n >> 3;
+        rg = (int)(slot % (uint32_t)p.row_groups);
+        n = ((slot / (uint32_t)p.row_groups) << 3) | (n & 7);
+    }
+    const uint32_t item = n / (uint32_t)p.Hkv;       // worker, or (split, sequence) with splits fastest
+    // The heads are rotated from one row of eight workgroups to the next, so that no XCD reads one head only.
+    const int g = (int)((n + item * (uint32_t)p.Hkv / 8) % (uint32_t)p.Hkv);
+    const size_t head_slots = (size_t)g * p.n_slots;
+
+    // timeline of this workgroup (profiling instantiations only; the production kernels
+    // carry neither the pointer nor a branch)
+    long long *tl = nullptr;
+    if constexpr (TL) {
+        const long long flat = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
+        tl = p.timeline + 10 * flat;
+        if (tid == 0) {
+            tl[0] = wall_clock64();
+            tl[1] = tl[2] = tl[3] = tl[4] = tl[5] = tl[8] = tl[9] = 0;
+            // XCC_ID register (bits 3:0) above the shader-engine / CU id: one value per compute unit
+            tl[6] = ((long long)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15) << 16) | __smid();
+            tl[7] = flat;
+        }
+    }
+    auto stamp = [&](int k) {                        // with several pieces: the last one's
+        if constexpr (TL) {
+            if (tid == 0) {
+                tl[k] = wall_clock64();
+                if (k == 2) tl[8] = clock64();        // shader cycles at both ends of the fast loop:
+                if (k == 3) tl[9] = clock64();        // their rate is the clock the chip really ran at
+            }
+        }
+    };
+
+    // The share: units [x, x1), the first of them in sequence b, which begins at unit `before`; the
+    // partials of its piece in sequence b go to slot `slot0 + b`.
+    int b = 0, before = 0, x, x1, slot0;
+    PageGuess guess;
+    if (!p.dealt) {                                   // equal splits of C tokens, of one sequence each
+        const int c = (int)(item % gridDim.y);
+        b = (int)(item / gridDim.y);
+        if (b >= p.B || c >= p.max_splits) return;    // padding of the grid
+        x = c * (p.C / kSplitQuantum);
+        x1 = x + p.C / kSplitQuantum;
+        slot0 = b * p.max_splits + c - b;
+        guess = guess_pages(p, b, x * kSplitQuantum);
+    } else {
+        const int worker = (int)item;
+        if (worker >= p.max_workers) return;          // padding of the grid
+        Deal deal;
+        if (p.B == 1) {
+            // most lone sequences are as long as announced: their pages are asked for along with the length
+            deal = Deal{p.full.workers, p.full.q, p.full.r};
+            guess = guess_pages(p, 0, deal_begin(deal, min(worker, deal.workers)) * kSplitQuantum);
+            const int N1 = load_n_draft(p.n_draft_seq, 0, p.N, nullptr);
+            const int T1 = N1 == 0 ? 0 : load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, nullptr) + N1;
+            if (T1 != p.max_ctx_len + p.N) deal = deal_units(p, max(seq_units(p, T1), 1));
+        } else {
+            const BatchUnits u = batch_units(p);
+            if (u.total == 0) return;                 // not one sequence has drafts
+            deal = deal_units(p, u.total);
+            if (worker < deal.workers) find_unit(p, u, deal_begin(deal, worker), &b, &before);
+            guess.pos0 = -1;
+        }
+        if (worker >= deal.workers) return;
+        x = deal_begin(deal, worker);
+        x1 = deal_begin(deal, worker + 1);
+        slot0 = worker;
+    }
+    for (bool again = false; b < p.B; ++b) {
+        const int Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status);
+        const int L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status);
+        const int T_b = Nb == 0 ? 0 : L + Nb;
+        const int s0 = x - before, s1 = min(x1 - before, stages_of(T_b));
+        if (s0 < s1) {
+            if (again) __syncthreads();               // LDS is free again
+            again = true;
+            const Piece pc{b, L, Nb, s0 * kSplitQuantum, min(s1 * kSplitQuantum, T_b),
+                           (head_slots + slot0 + b) * p.RT};
+            run_piece<T, D, TPW, WR, WK>(p, smem, g, rg, pc, guess, stamp);
+            guess.pos0 = -1;
+        }
+        before += seq_units(p, T_b);
+        if (before >= x1 || !p.dealt) break;
+        x = before;
     }
     if constexpr (TL) {
         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the partial stores have left

@@ -463,6 +463,33 @@ def test_batch_split_follows_the_lengths(oracle_mod, name, ctx, Hkv):
         assert_close(got3, want3, case.dtype, name + " (ragged counts)")
 
 
+@pytest.mark.parametrize("name,Hq,Hkv,D,ctx,n", [
+    ("more than one round of workers", 64, 64, 64, [200_000], 3),      # a share would outgrow the page list: 8 workers, not 4
+    ("shares of one stage", 8, 2, 128, [0, 1, 63, 64, 65, 127], 4),
+    ("few partials per sequence", 8, 2, 64, [1500 + 37 * k for k in range(40)], 6),
+    ("many partials per sequence", 8, 2, 128, [9000, 1, 14000], 6),
+])
+def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n):
+    """A library-chosen split size: equal shares of the sequences laid end to end, cut at their ends.  The
+    longest case reads a small pool through a table that repeats its pages."""
+    import dataclasses
+    r = _rng(sum(ctx) + n)
+    trees = [W.random_tree(n, 3, r) for _ in ctx]
+    case = W.make_case("dealt", 91, dtype=W.DT_BF16, Hq=Hq, Hkv=Hkv, D=D, ctx_lens=[min(L, 20000) for L in ctx], trees=trees)
+    if max(ctx) > 20000:
+        cols = (max(ctx) + n + 15) // 16
+        table = case.page_table[:, np.arange(cols) % (20000 // 16)]            # full pages only
+        case = dataclasses.replace(case, ctx_lens=np.array(ctx, np.int32), page_table=table, max_pages_per_seq=cols)
+    got, step = _run(case)
+    if max(ctx) > 20000:
+        rows = sample_rows(case, 40, seed=5, always=[(0, 0, 0), (0, n - 1, Hq - 1)])
+        want = oracle_mod.verify_attn_case(case, rows=rows)
+        got = np.stack([got[b, i, h] for b, i, h in rows])
+    else:
+        want = oracle_mod.verify_attn_case(case)
+    assert_close(got, want, case.dtype, f"{name} plan={step.plan.as_dict()}")
+
+
 @pytest.mark.parametrize("frac,gain,tag", [(0.05, 8.0, "frequent outliers: guarded reference"),
                                            (0.0007, 40.0, "rare late outliers: frozen reference, overflow, redo"),
                                            (0.02, 3.0, "mild tail: frozen reference holds")])
