@@ -172,27 +172,31 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     if (workers < 1) workers = 1;
     fp->max_workers = (int32_t)workers;
     fp->full = Deal{(int32_t)workers, (int32_t)(units_at_most / workers), (int32_t)(units_at_most % workers)};
-    const int64_t n_slots = fp->dealt ? workers + d->batch - 1 : (int64_t)d->batch * max_splits;
-    fp->n_slots = (int32_t)n_slots;
-
     // Workspace: the partials that are written, and never less than equal splits of half the planned size
-    // would need for a batch (the planned size for one sequence): what a caller's buffer holds and what
-    // owl_verify_attn_noalloc admits does not depend on how the work is dealt out.
-    int64_t sized_splits = max_splits;
-    if (fp->dealt && d->batch > 1) {
-        int64_t c_floor = align_up((size_t)(C / 2), kSplitQuantum);
-        if (c_floor < cmin) c_floor = cmin < C ? cmin : C;
-        max_splits = sized_splits = (T + c_floor - 1) / c_floor;
-    }
+    // would need for a batch (the planned size for one sequence).
     fp->half_partials = d->qkv_dtype != OWL_F32 && !(d->flags & OWL_FLAG_FP32_PARTIALS);
     const size_t o_bytes = (size_t)d->head_dim * kRowTile * (fp->half_partials ? 2 : 4), ml_bytes = kPartMl * sizeof(float);
-    const size_t slots = (size_t)d->n_kv_heads * (size_t)n_slots * RT;
-    const size_t sized = (size_t)d->batch * d->n_kv_heads * (size_t)sized_splits * RT;
-    fp->part_o_bytes = align_up(slots * o_bytes, 256);
-    fp->part_ml_bytes = align_up(slots * ml_bytes, 256);
-    size_t part_bytes = align_up(sized * o_bytes, 256) + align_up(sized * ml_bytes, 256);
-    if (part_bytes < fp->part_o_bytes + fp->part_ml_bytes) part_bytes = fp->part_o_bytes + fp->part_ml_bytes;
-    fp->info_offset = part_bytes;
+    auto bytes_of = [&](size_t slots, size_t unit) -> size_t { return align_up((size_t)d->n_kv_heads * slots * RT * unit, 256); };
+    auto partials = [&](size_t slots) -> size_t { return bytes_of(slots, o_bytes) + bytes_of(slots, ml_bytes); };
+    const size_t info_bytes = align_up(((size_t)d->batch + 3) * sizeof(int32_t), 256);                 // write_batch_info's words
+    int64_t sized_splits = max_splits;
+    if (d->split_tokens == 0 && d->batch > 1 && units_at_most < ((int64_t)1 << 30)) {
+        int64_t c_floor = align_up((size_t)(C / 2), kSplitQuantum);
+        if (c_floor < cmin) c_floor = cmin < C ? cmin : C;
+        sized_splits = (T + c_floor - 1) / c_floor;
+    }
+    const size_t sized = partials((size_t)d->batch * (size_t)sized_splits), dealt_bytes = partials((size_t)(workers + d->batch - 1));
+    // A dealt batch may leave one partial per worker and one per sequence, several times what few equal splits
+    // of short sequences leave.  What owl_verify_attn_noalloc admits must not depend on how the work is dealt
+    // out, so a launch that fits its scratch in equal splits only is cut that way.
+    if (fp->dealt && dealt_bytes + info_bytes > OWL_NOALLOC_SCRATCH_BYTES && sized + info_bytes <= OWL_NOALLOC_SCRATCH_BYTES)
+        fp->dealt = false;
+    const size_t n_slots = fp->dealt ? (size_t)(workers + d->batch - 1) : (size_t)d->batch * (size_t)max_splits;
+    fp->n_slots = (int32_t)n_slots;
+    if (fp->dealt) max_splits = sized_splits;
+    fp->part_o_bytes = bytes_of(n_slots, o_bytes);
+    fp->part_ml_bytes = bytes_of(n_slots, ml_bytes);
+    fp->info_offset = partials(n_slots) > sized ? partials(n_slots) : sized;
     fp->variant = v;
     owl_plan &pl = fp->pub;
     pl.reserved_ = 0;
@@ -213,7 +217,7 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     fp->grid = dim3(d->n_kv_heads * rgs, (unsigned)grid_y, (unsigned)grid_z);
     if ((int64_t)fp->grid.x * fp->grid.y * fp->grid.z >= ((int64_t)1 << 31)) return OWL_ERR_UNSUPPORTED;   // the kernel numbers them in 32 bits
     pl.n_workgroups = (int32_t)((int64_t)fp->grid.x * fp->grid.y * fp->grid.z);
-    pl.workspace_bytes = fp->info_offset + align_up(((size_t)d->batch + 3) * sizeof(int32_t), 256);     // + write_batch_info's words
+    pl.workspace_bytes = fp->info_offset + info_bytes;
     return OWL_OK;
 }
 

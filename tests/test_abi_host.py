@@ -274,6 +274,18 @@ def test_init_and_noalloc_reject_before_touching_a_device():
     assert f"#define OWL_NOALLOC_SCRATCH_BYTES ({B.OWL_NOALLOC_SCRATCH_BYTES >> 20}u << 20)" in header
 
 
+@pytest.mark.parametrize("hkv,group,n,d,batch,ctx,dtype,flags", [
+    (4, 7, 31, 128, 100, 3, B.OWL_F32, 0), (16, 8, 33, 128, 16, 27, B.OWL_F16, 1), (4, 64, 29, 64, 16, 7393, B.OWL_F16, 1),
+    (16, 64, 36, 64, 2, 7837, B.OWL_BF16, 1), (64, 7, 48, 64, 16, 1, B.OWL_BF16, 0), (2, 16, 56, 128, 100, 24, B.OWL_F16, 0)])
+def test_batches_of_short_sequences_fit_the_fixed_scratch(hkv, group, n, d, batch, ctx, dtype, flags):
+    """Shapes whose few equal splits fit the buffer of the entry point without a workspace, and one partial per
+    workgroup and sequence does not: the plan cuts them into equal splits."""
+    desc = _good(batch=batch, n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, max_ctx_len=ctx,
+                 max_pages_per_seq=(ctx + n + 15) // 16, qkv_dtype=dtype, flags=flags, kv_stride_page=hkv * 16 * d,
+                 kv_stride_head=16 * d, kv_stride_token=d)
+    assert B.owl_verify_attn_workspace_size(desc) <= B.OWL_NOALLOC_SCRATCH_BYTES
+
+
 def test_timeline_switch_checks_its_arguments():
     lib = B.lib()
     assert lib.owl_debug_set_timeline(0x10000, 0) == B.OWL_ERR_INVALID_ARG

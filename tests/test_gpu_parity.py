@@ -468,6 +468,7 @@ def test_batch_split_follows_the_lengths(oracle_mod, name, ctx, Hkv):
     ("shares of one stage", 8, 2, 128, [0, 1, 63, 64, 65, 127], 4),
     ("few partials per sequence", 8, 2, 64, [1500 + 37 * k for k in range(40)], 6),
     ("many partials per sequence", 8, 2, 128, [9000, 1, 14000], 6),
+    ("equal splits, to fit the fixed scratch", 28, 4, 128, [3 + k % 40 for k in range(100)], 31),
 ])
 def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n):
     """A library-chosen split size: equal shares of the sequences laid end to end, cut at their ends.  The
