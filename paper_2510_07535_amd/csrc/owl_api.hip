@@ -578,7 +578,7 @@ owl_status owl_drafter_cell_phases(const owl_drafter_desc *desc, const void *h, 
     float *proj = static_cast<float *>(workspace);
     if (phases & OWL_DRAFTER_PROJ)
         if (launch_drafter_proj(desc->dtype, h, w, desc->w_layout == OWL_W_TILED, proj, desc->n_states, desc->d_in,
-                                desc->d, s) != hipSuccess)
+                                desc->d, device_cus(), s) != hipSuccess)
             return OWL_ERR_HIP;
     if (phases & OWL_DRAFTER_GATES)
         if (launch_drafter_gates(desc->dtype, proj, z, tokens, parent_row, emb, gamma_c, beta_c, gamma_z, beta_z,

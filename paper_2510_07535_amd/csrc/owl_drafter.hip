@@ -12,6 +12,8 @@
 // into the MFMA operand registers: no element is used twice, so there is
 // nothing to stage in LDS.  The gates then need whole-row statistics twice (of
 // s^c and of z'): three small launches, see below.
+#include <type_traits>
+
 #include "owl_device.h"
 
 namespace owl {
@@ -35,8 +37,8 @@ __device__ __forceinline__ d_f32x4 mfma16(d_i32x4 a, d_i32x4 b, d_f32x4 c)
 // ---------------------------------------------------------------------------
 // Projection.  The four W^m, each [d][d_in] (one output channel's weights
 // contiguous), are one matrix of 4d rows.  A workgroup of four wavefronts owns
-// 64 consecutive rows (four 16-row MFMA tiles); every wavefront works on all
-// four tiles, so that a fragment of h is loaded once per four weight fragments,
+// GR groups of 64 consecutive rows (four 16-row MFMA tiles); every wavefront works on all
+// the tiles, so that a fragment of h is loaded once per 4 GR weight fragments,
 // and the wavefronts split the contraction dimension: wavefront w takes the
 // k-blocks w, w + 4, ... of 128 elements.  In MFMA terms A = h (rows = states),
 // B = W^T (columns = weight rows): lane l supplies the 8 consecutive k values of
@@ -51,102 +53,168 @@ __device__ __forceinline__ d_f32x4 mfma16(d_i32x4 a, d_i32x4 b, d_f32x4 c)
 //     granule(row, k) = ((row / 64 * KS + k / 32) * 4 + row % 64 / 16) * 64 + (k % 32 / 8) * 16 + row % 16
 // in units of 16 bytes (8 elements), KS = d_in / 32, rows padded with zeros to a
 // multiple of 64: one load instruction reads 1 KB contiguous, a workgroup reads
-// one contiguous run of 64 d_in elements from end to end, and the same kernel
-// reaches 5.6-5.9 TB/s, what a plain streaming read gets on this chip.
+// contiguous runs of 64 d_in elements from end to end, and the same kernel
+// reaches 6.7-6.9 TB/s, what a plain streaming read gets on this chip.
 // ---------------------------------------------------------------------------
 constexpr int kProjWaves = 4;
-constexpr int kProjTiles = 4;     // 16-row weight tiles per workgroup (fixed by the tiled layout)
-constexpr int kProjUnroll = 4;    // k-steps of 32 per wavefront and round
+constexpr int kProjTiles = 4;     // 16-row weight tiles per group of 64 rows (fixed by the tiled layout)
+constexpr int kProjUnroll = 4;    // consecutive k-steps of 32 that one wavefront takes
 static_assert(kProjTiles <= kProjWaves, "wavefront w adds up and stores weight tile w");
 
-template <bool kF16, int PT, bool kTiled>
-__global__ void __launch_bounds__(kProjWaves * 64) drafter_proj_kernel(const uint16_t *__restrict__ h,
-                                                                       const uint16_t *__restrict__ w,
-                                                                       float *__restrict__ s, int P, int d_in,
-                                                                       int n_rows)
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), unrolled at compile time.
+template <int N, typename F>
+__device__ __forceinline__ void each(F &&f)
 {
-    __shared__ d_f32x4 red[kProjWaves][kProjTiles][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if constexpr (N > 0) {
+        each<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
+// A wavefront works on GR groups of 64 weight rows at once: a fragment of h is then loaded once per 4 GR weight
+// fragments.  GR > 1 pays with more than 16 states (proj_wide).
+// k-steps (4 GR weight fragments and PT fragments of h each) that a wavefront keeps in flight: as many as leave room
+// for 4 - GR wavefronts per SIMD.
+// (The row layout has three more offsets to keep.)
+constexpr int proj_depth(int PT, bool tiled, int GR)
+{
+    if (GR == 3) return PT == 2 ? 5 : PT == 3 ? 4 : 3;
+    if (GR == 2) return PT == 2 ? 3 : 2;
+    return PT == 1 ? 6 : PT == 2 ? 4 : PT == 3 && tiled ? 3 : 2;
+}
+
+template <bool kF16, int PT, bool kTiled, int GR>
+__global__ void __launch_bounds__(kProjWaves * 64, 4 - GR) drafter_proj_kernel(const uint16_t *__restrict__ h,
+                                                                               const uint16_t *__restrict__ w,
+                                                                               float *__restrict__ s, int P, int d_in,
+                                                                               int n_rows)
+{
+    constexpr int kTiles = GR * kProjTiles;
+    __shared__ d_f32x4 red[kProjWaves][kTiles][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kg = lane >> 4;
     const int n_tiles = n_rows / 16;
-    const int tile0 = blockIdx.x * kProjTiles;
+    const int tile0 = blockIdx.x * kTiles;
     const int k_steps = d_in / 32;
 
-    // wp[nb] + ks * w_step is this lane's 16 bytes of k-step ks of weight tile nb.
-    const uint16_t *wp[kProjTiles];
-    int64_t w_step;
+    // w_base[q] + ks * w_step + w_off[nb] is this lane's 16 bytes of k-step ks of weight tile nb of group q (w_off in
+    // bytes, the rest in elements and uniform over the wavefront; d_in <= 2^20 keeps all offsets below 2^28).
+    // A tile or group past the end re-reads the last one (in bounds); its sums are not stored.
+    static_assert(kTiled || GR == 1, "the row layout comes one group at a time");
+    const uint16_t *w_base[GR];
+    int w_step;
+    uint32_t w_off[kProjTiles];
     if constexpr (kTiled) {
         w_step = kProjTiles * 512;
 #pragma unroll
-        for (int nb = 0; nb < kProjTiles; ++nb)
-            wp[nb] = w + ((int64_t)blockIdx.x * k_steps * kProjTiles + nb) * 512 + lane * 8;
+        for (int q = 0; q < GR; ++q) {
+            const int group = min((int)blockIdx.x * GR + q, (n_tiles + kProjTiles - 1) / kProjTiles - 1);
+            w_base[q] = w + (int64_t)group * k_steps * (kProjTiles * 512);
+        }
+#pragma unroll
+        for (int nb = 0; nb < kProjTiles; ++nb) w_off[nb] = nb * 1024 + lane * 16;
     } else {
         w_step = 32;
+        w_base[0] = w + (int64_t)tile0 * 16 * d_in;
 #pragma unroll
-        for (int nb = 0; nb < kProjTiles; ++nb) {
-            // A tile past the end re-reads the last tile (in bounds); its sums are not stored.
-            const int t = min(tile0 + nb, n_tiles - 1);
-            wp[nb] = w + (int64_t)(t * 16 + n) * d_in + kg * 8;
-        }
+        for (int nb = 0; nb < kProjTiles; ++nb) w_off[nb] = 2 * ((min(nb, n_tiles - 1 - tile0) * 16 + n) * d_in + kg * 8);
     }
-    // State rows past P read row P - 1 (in bounds) and are not stored either.
-    const uint16_t *hp[PT];
+    uint32_t h_off[PT];                                      // state rows past P read row P - 1 and are not stored either
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) hp[pt] = h + (int64_t)min(pt * 16 + n, P - 1) * d_in + kg * 8;
+    for (int pt = 0; pt < PT; ++pt) h_off[pt] = 2 * (min(pt * 16 + n, P - 1) * d_in + kg * 8);
 
-    d_f32x4 acc[PT][kProjTiles];
+    d_f32x4 acc[PT][kTiles];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-        for (int nb = 0; nb < kProjTiles; ++nb) acc[pt][nb] = d_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < kTiles; ++nb) acc[pt][nb] = d_f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // This wavefront's k-steps, in its own order: blocks of kProjUnroll consecutive ones, dealt out to the wavefronts.
     // With more than 16 state rows the h fragments weigh as much as the weights in the L1/L2
     // traffic, and every workgroup of the chip asks for the same lines of h at the same time if
     // all sweep k in the same order: each starts at a round of its own instead.
-    const int rounds = (k_steps + kProjWaves * kProjUnroll - 1) / (kProjWaves * kProjUnroll);
-    const int first = PT > 1 ? (int)((blockIdx.x * 7u) % (unsigned)rounds) : 0;
-    for (int it = 0; it < rounds; ++it) {
-        const int rr = it + first < rounds ? it + first : it + first - rounds;
-        const int ks0 = (rr * kProjWaves + wave) * kProjUnroll;
-        d_i32x4 b[kProjUnroll][kProjTiles], a[kProjUnroll][PT];
+    constexpr int kRound = kProjWaves * kProjUnroll;
+    const int rounds = k_steps / kRound;
+    const int n_mine = rounds * kProjUnroll + min(max(k_steps - rounds * kRound - wave * kProjUnroll, 0), kProjUnroll);
+    const int first = PT > 1 && rounds > 1 ? (int)((blockIdx.x * 7u) % (unsigned)rounds) * kProjUnroll : 0;
+    auto k_step_of = [&](int i) -> int {
+        i += first;
+        if (i >= n_mine) i -= n_mine;
+        return (i / kProjUnroll) * kRound + wave * kProjUnroll + i % kProjUnroll;
+    };
+
+    // The stream: a ring of kDepth k-steps in registers.  A slot's loads are issued as soon as the MFMAs
+    // have read it and are waited for kDepth - 1 steps later; the scheduling fences keep them apart (left to itself the
+    // compiler moved every load next to its use and waited for one after the other: with 40 states it kept 7 of a
+    // wavefront's 28 loads in flight; d = 4096, d_in = 12288, 40 states: 116 -> 83 us).
+    constexpr int kDepth = proj_depth(PT, kTiled, GR);
+    d_i32x4 b[kDepth][kTiles], a[kDepth][PT];
+    auto load = [&](auto slot, int i) {
+        constexpr int S = decltype(slot)::value;
+        const int ks = k_step_of(i);
+        const char *hk = reinterpret_cast<const char *>(h + ks * 32);
+        // every weight is used once: a non-temporal load, which leaves the caches to h (re-read by
+        // every workgroup) and is worth 11 % on this chip (square step: 206 -> 183 us)
 #pragma unroll
-        for (int u = 0; u < kProjUnroll; ++u) {
-            const bool live = ks0 + u < k_steps;            // uniform over the wavefront
-            const int ks = live ? ks0 + u : 0;
+        for (int q = 0; q < GR; ++q) {
+            const char *wk = reinterpret_cast<const char *>(w_base[q] + (int64_t)ks * w_step);
 #pragma unroll
-            for (int nb = 0; nb < kProjTiles; ++nb) {
-                // every weight is used once: a non-temporal load, which leaves the caches to h (re-read by
-                // every workgroup) and is worth 11 % on this chip (square step: 206 -> 183 us)
-                b[u][nb] = __builtin_nontemporal_load(reinterpret_cast<const d_i32x4 *>(wp[nb] + ks * w_step));
-                if (!live) b[u][nb] = d_i32x4{0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int pt = 0; pt < PT; ++pt) a[u][pt] = *reinterpret_cast<const d_i32x4 *>(hp[pt] + ks * 32);
+            for (int nb = 0; nb < kProjTiles; ++nb)
+                b[S][q * kProjTiles + nb] = __builtin_nontemporal_load(reinterpret_cast<const d_i32x4 *>(wk + w_off[nb]));
         }
 #pragma unroll
-        for (int u = 0; u < kProjUnroll; ++u)
+        for (int pt = 0; pt < PT; ++pt) a[S][pt] = *reinterpret_cast<const d_i32x4 *>(hk + h_off[pt]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto use = [&](auto slot) {
+        constexpr int S = decltype(slot)::value;
 #pragma unroll
-            for (int pt = 0; pt < PT; ++pt)
+        for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                for (int nb = 0; nb < kProjTiles; ++nb) acc[pt][nb] = mfma16<kF16>(a[u][pt], b[u][nb], acc[pt][nb]);
+            for (int nb = 0; nb < kTiles; ++nb) acc[pt][nb] = mfma16<kF16>(a[S][pt], b[S][nb], acc[pt][nb]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int i = 0;                                               // k-steps requested so far
+    if (n_mine >= kDepth) {
+        each<kDepth>([&](auto slot) { load(slot, i++); });
+        for (; i + kDepth <= n_mine; i += kDepth)
+            each<kDepth>([&](auto slot) {
+                use(slot);
+                load(slot, i + decltype(slot)::value);
+            });
+        const int rest = n_mine - i;                         // fewer than kDepth
+        each<kDepth>([&](auto slot) {
+            use(slot);
+            if (decltype(slot)::value < rest) load(slot, i + decltype(slot)::value);
+        });
+        each<kDepth - 1>([&](auto slot) {
+            if (decltype(slot)::value < rest) use(slot);
+        });
+    } else {
+        for (; i < n_mine; ++i) {
+            load(std::integral_constant<int, 0>{}, i);
+            use(std::integral_constant<int, 0>{});
+        }
     }
 
     // Accumulator layout: lane l holds, for weight row l % 16, the state rows 4 (l / 16) + i.
-    const int t_mine = tile0 + wave;
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) {
         if (pt) __syncthreads();
 #pragma unroll
-        for (int nb = 0; nb < kProjTiles; ++nb) red[wave][nb][lane] = acc[pt][nb];
+        for (int nb = 0; nb < kTiles; ++nb) red[wave][nb][lane] = acc[pt][nb];
         __syncthreads();
-        if (wave < kProjTiles && t_mine < n_tiles) {
-            d_f32x4 v = red[0][wave][lane];
 #pragma unroll
-            for (int ww = 1; ww < kProjWaves; ++ww) v += red[ww][wave][lane];
+        for (int q = 0; q < GR; ++q) {
+            const int mine = q * kProjTiles + wave, tile = tile0 + mine;
+            if (tile >= n_tiles) continue;
+            d_f32x4 v = red[0][mine][lane];
+#pragma unroll
+            for (int ww = 1; ww < kProjWaves; ++ww) v += red[ww][mine][lane];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int p = pt * 16 + kg * 4 + i;
-                if (p < P) s[(int64_t)p * n_rows + t_mine * 16 + n] = v[i];
+                if (p < P) s[(int64_t)p * n_rows + tile * 16 + n] = v[i];
             }
         }
     }
@@ -154,37 +222,58 @@ __global__ void __launch_bounds__(kProjWaves * 64) drafter_proj_kernel(const uin
 
 static int proj_groups(int d) { return (4 * d / 16 + kProjTiles - 1) / kProjTiles; }
 
-template <bool kF16, int PT>
-static hipError_t launch_proj_pt(const void *h, const void *w, bool tiled, float *s, int P, int d_in, int d,
-                                 hipStream_t st)
+// Groups per workgroup.  With more than 16 states the h fragments that every group asks L2 for weigh as much as its
+// weights; GR groups that share them cut that to a GRth (whole cell, us, one
+// group -> shared: d = d_in = 12288 with 20 / 40 / 64 states 199 -> 187 / 228 -> 190 / 281 -> 198; 9600 with 48 states 190 -> 137).  With up to 16 states the weights alone
+// fill the memory pipe (6.9 TB/s) and nothing is left to gain.  Taken where no compute unit is left with more groups than
+// it has when they come one by one: below that the lost balance costs more than the sharing gives.
+static int proj_wide(int P, int d, int n_cus)
 {
-    const int n_rows = 4 * d;
-    const dim3 grid(proj_groups(d)), block(kProjWaves * 64);
-    const uint16_t *hh = static_cast<const uint16_t *>(h), *ww = static_cast<const uint16_t *>(w);
-    if (tiled)
-        hipLaunchKernelGGL((drafter_proj_kernel<kF16, PT, true>), grid, block, 0, st, hh, ww, s, P, d_in, n_rows);
-    else
-        hipLaunchKernelGGL((drafter_proj_kernel<kF16, PT, false>), grid, block, 0, st, hh, ww, s, P, d_in, n_rows);
+    const int groups = proj_groups(d), most = (groups + n_cus - 1) / n_cus;
+    if (P <= 16) return 1;
+    for (int gr = 3; gr > 1; --gr)
+        if (gr * (((groups + gr - 1) / gr + n_cus - 1) / n_cus) <= most) return gr;
+    return 1;
+}
+
+template <bool kF16, int PT, bool kTiled, int GR>
+static hipError_t launch_proj_gr(const void *h, const void *w, float *s, int P, int d_in, int d, hipStream_t st)
+{
+    hipLaunchKernelGGL((drafter_proj_kernel<kF16, PT, kTiled, GR>), dim3((proj_groups(d) + GR - 1) / GR), dim3(kProjWaves * 64), 0, st,
+                       static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(w), s, P, d_in, 4 * d);
     return hipGetLastError();
 }
 
+template <bool kF16, int PT>
+static hipError_t launch_proj_pt(const void *h, const void *w, bool tiled, float *s, int P, int d_in, int d, int n_cus,
+                                 hipStream_t st)
+{
+    if (!tiled) return launch_proj_gr<kF16, PT, false, 1>(h, w, s, P, d_in, d, st);
+    if constexpr (PT > 1) {
+        const int gr = proj_wide(P, d, n_cus);
+        if (gr == 3) return launch_proj_gr<kF16, PT, true, 3>(h, w, s, P, d_in, d, st);
+        if (gr == 2) return launch_proj_gr<kF16, PT, true, 2>(h, w, s, P, d_in, d, st);
+    }
+    return launch_proj_gr<kF16, PT, true, 1>(h, w, s, P, d_in, d, st);
+}
+
 template <bool kF16>
-static hipError_t launch_proj_dt(const void *h, const void *w, bool tiled, float *s, int P, int d_in, int d,
+static hipError_t launch_proj_dt(const void *h, const void *w, bool tiled, float *s, int P, int d_in, int d, int n_cus,
                                  hipStream_t st)
 {
     switch ((P + 15) / 16) {
-    case 1: return launch_proj_pt<kF16, 1>(h, w, tiled, s, P, d_in, d, st);
-    case 2: return launch_proj_pt<kF16, 2>(h, w, tiled, s, P, d_in, d, st);
-    case 3: return launch_proj_pt<kF16, 3>(h, w, tiled, s, P, d_in, d, st);
-    default: return launch_proj_pt<kF16, 4>(h, w, tiled, s, P, d_in, d, st);
+    case 1: return launch_proj_pt<kF16, 1>(h, w, tiled, s, P, d_in, d, n_cus, st);
+    case 2: return launch_proj_pt<kF16, 2>(h, w, tiled, s, P, d_in, d, n_cus, st);
+    case 3: return launch_proj_pt<kF16, 3>(h, w, tiled, s, P, d_in, d, n_cus, st);
+    default: return launch_proj_pt<kF16, 4>(h, w, tiled, s, P, d_in, d, n_cus, st);
     }
 }
 
 hipError_t launch_drafter_proj(int dtype, const void *h, const void *w, bool tiled, float *s, int P, int d_in,
-                               int d, hipStream_t st)
+                               int d, int n_cus, hipStream_t st)
 {
-    return dtype == OWL_F16 ? launch_proj_dt<true>(h, w, tiled, s, P, d_in, d, st)
-                            : launch_proj_dt<false>(h, w, tiled, s, P, d_in, d, st);
+    return dtype == OWL_F16 ? launch_proj_dt<true>(h, w, tiled, s, P, d_in, d, n_cus, st)
+                            : launch_proj_dt<false>(h, w, tiled, s, P, d_in, d, n_cus, st);
 }
 
 // Bytes of the tiled copy of the weights: whole groups of 64 rows.

@@ -55,6 +55,19 @@ def test_cell_matches_oracle(dtype, d_in, d, P, M):
     _check(case, OD.drafter_alpha(8, d), tiled=False)    # the paper's alpha; weights as a plain [4d][d_in] matrix
 
 
+@pytest.mark.parametrize("d_in,d,P", [
+    # one group of 64 rows per workgroup; the wavefronts have fewer k-steps than their ring holds, as many, one round
+    # and a rest, none at all
+    (32 * 24, 80, 16), (32 * 27, 80, 5), (32 * 29, 80, 32), (32 * 13, 80, 33), (32 * 9, 80, 64), (32 * 115, 80, 49),
+    # two groups (320 and, the last one alone, 321 in all), then three (514 and 768) that share the states
+    (32 * 3, 5120, 17), (32 * 21, 5136, 32), (32 * 21, 5136, 40), (32 * 18, 5120, 64),
+    (32 * 3, 8224, 64), (32 * 21, 8224, 17), (32 * 37, 8224, 48), (32 * 21, 12288, 49),
+])
+def test_projection_ring_and_shared_states(d_in, d, P):
+    case = W.make_drafter_case("t", 300 + P, d_in=d_in, d=d, P=P, M=P, vocab=50)
+    _check(case, 1.0)
+
+
 def _tiled_by_definition(w_bits, d_in, d):
     """The tiled layout built from its definition in the header, granule by granule."""
     rows = w_bits.reshape(4 * d, d_in)
