@@ -11,7 +11,7 @@
 // beyond the vector ALUs at that rate.  Weights go from global memory straight
 // into the MFMA operand registers: no element is used twice, so there is
 // nothing to stage in LDS.  The gates then need whole-row statistics twice (of
-// s^c and of z'): three small launches, see below.
+// s^c and of z'): two small launches, see below.
 #include <type_traits>
 
 #include "owl_device.h"
@@ -313,12 +313,14 @@ hipError_t launch_drafter_tile_weights(const void *w_rows, void *w_tiled, int d_
 // Gates and state update.  f needs the mean and variance of a whole row twice
 // (of s^c, then of z'), and the transcendental work of one row (three sigmoids
 // and two GeLUs per channel) keeps a single compute unit busy for ~20 us, so a
-// row is spread over workgroups of 256 threads x 4 channels and the two row
-// statistics travel through memory between three small launches:
-//   1. per chunk of 1024 channels: count, mean and centred sum of squares of s^c
-//   2. merge those; z' = z g^f + f(s^c) g^i; the same partials of z'
-//   3. merge those; h' = f(z') g^o
-// Partials are (mean, M2) pairs merged with the pairwise update
+// row is spread over workgroups of 256 threads x 4 channels, in two launches:
+//   1. z' = z g^f + f(s^c) g^i, and per chunk of 1024 channels the mean and centred sum of squares of z'
+//   2. merge those; h' = f(z') g^o
+// The statistics of s^c need no transcendentals: every workgroup of launch 1 forms them from the whole row by itself, in
+// registers, while its own operands are on their way: 48 KB of s^c and 24 KB of embedding from L2 at d = 12288, against a launch
+// of its own with a round trip through memory (whole cell, us: d_in = 4096, 1 state, 10 rows 75.3 -> 73.7; d_in = 12288 with 10 / 40
+// states and rows 188.5 -> 186.9 / 189.5 -> 188.9).
+// The partials of z' are (mean, M2) pairs merged with the pairwise update
 //     M2 = sum_c M2_c + n_c (mean_c - mean)^2 ,
 // which keeps the variance as accurate as a two-pass sum.
 // ---------------------------------------------------------------------------
@@ -383,7 +385,7 @@ struct GateArgs {
     const float *gamma_c, *beta_c, *gamma_z, *beta_z;
     uint16_t *h_out;
     float *h_out_f32, *z_out;
-    float *part_c, *part_z;       // [M][kGateMaxChunks][2]: mean and centred sum of squares per chunk
+    float *part_z;                // [M][kGateMaxChunks][2]: mean and centred sum of squares per chunk
     int P, d, vocab;
     float alpha, eps;
     uint32_t *status;
@@ -444,32 +446,49 @@ __device__ __forceinline__ void merge_stats(const float *part, int d, float eps,
     *rstd_out = 1.0f / sqrtf(m2 / (float)d + eps);
 }
 
-template <bool kF16>
-__global__ void __launch_bounds__(kGateThreads) drafter_stats_kernel(GateArgs a)
+// Mean and 1 / sqrt(variance + eps) of s^c over a row of at most MAXC chunks, in two passes over registers; the same
+// in every workgroup of the row.
+template <bool kF16, int MAXC>
+__device__ __forceinline__ void row_stats(const GateArgs &a, const GateRow &g, float *scratch, float *mean_out, float *rstd_out)
+{
+    const int j0 = threadIdx.x * 4;
+    float4 v[MAXC];
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) {                        // past the end: the last channels once more, not counted
+        const int j = min(c * kGateChunk + j0, a.d - 4);
+        v[c] = add4(ld4(g.sp + 3 * a.d + j), scaled_emb4<kF16>(g.ep + j, g.alpha));
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c)
+        if (c * kGateChunk + j0 < a.d) sum += (v[c].x + v[c].y) + (v[c].z + v[c].w);
+    const float mean = block_sum(sum, scratch) / (float)a.d;
+    float sq = 0.f;
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c)
+        if (c * kGateChunk + j0 < a.d) {
+            const float4 x = make_float4(v[c].x - mean, v[c].y - mean, v[c].z - mean, v[c].w - mean);
+            sq += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
+        }
+    *mean_out = mean;
+    *rstd_out = 1.0f / sqrtf(block_sum(sq, scratch) / (float)a.d + a.eps);
+}
+
+template <bool kF16, int MAXC>
+__global__ void __launch_bounds__(kGateThreads) drafter_state_kernel(GateArgs a)
 {
     __shared__ float scratch[kGateThreads / 64];
     const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
     const GateRow g = gate_row(a, r, c == 0);
     const bool live = j < a.d;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) v = add4(ld4(g.sp + 3 * a.d + j), scaled_emb4<kF16>(g.ep + j, g.alpha));
-    chunk_stats(v, live, min(kGateChunk, a.d - c * kGateChunk), scratch, a.part_c + ((int64_t)r * kGateMaxChunks + c) * 2);
-}
-
-template <bool kF16>
-__global__ void __launch_bounds__(kGateThreads) drafter_state_kernel(GateArgs a)
-{
-    __shared__ float scratch[kGateThreads / 64];
-    const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
-    const GateRow g = gate_row(a, r, false);
+    const int jl = live ? j : 0;
+    const float4 e = scaled_emb4<kF16>(g.ep + jl, g.alpha);
+    const float4 sf = add4(ld4(g.sp + jl), e), si = add4(ld4(g.sp + a.d + jl), e), sc = add4(ld4(g.sp + 3 * a.d + jl), e);
+    const float4 zo = ld4(g.zp + jl), ga = ld4_or(a.gamma_c, jl, 1.f), be = ld4_or(a.beta_c, jl, 0.f);
     float mean, rstd;
-    merge_stats(a.part_c + (int64_t)r * kGateMaxChunks * 2, a.d, a.eps, &mean, &rstd);
-    const bool live = j < a.d;
+    row_stats<kF16, MAXC>(a, g, scratch, &mean, &rstd);
     float4 zn = make_float4(0.f, 0.f, 0.f, 0.f);
     if (live) {
-        const float4 e = scaled_emb4<kF16>(g.ep + j, g.alpha);
-        const float4 sf = add4(ld4(g.sp + j), e), si = add4(ld4(g.sp + a.d + j), e), sc = add4(ld4(g.sp + 3 * a.d + j), e);
-        const float4 zo = ld4(g.zp + j), ga = ld4_or(a.gamma_c, j, 1.f), be = ld4_or(a.beta_c, j, 0.f);
         zn.x = zo.x * sigmoid_f(sf.x) + gelu_f((sc.x - mean) * rstd * ga.x + be.x) * sigmoid_f(si.x);
         zn.y = zo.y * sigmoid_f(sf.y) + gelu_f((sc.y - mean) * rstd * ga.y + be.y) * sigmoid_f(si.y);
         zn.z = zo.z * sigmoid_f(sf.z) + gelu_f((sc.z - mean) * rstd * ga.z + be.z) * sigmoid_f(si.z);
@@ -503,13 +522,18 @@ __global__ void __launch_bounds__(kGateThreads) drafter_hidden_kernel(GateArgs a
     if (a.h_out_f32) *reinterpret_cast<float4 *>(a.h_out_f32 + (int64_t)r * a.d + j) = hn;
 }
 
+// (Half of it is used; the published workspace size stays what it was.)
 size_t drafter_gate_scratch_floats(int M) { return (size_t)2 * M * kGateMaxChunks * 2; }
 
 template <bool kF16> static hipError_t launch_gates_dt(const GateArgs &a, int M, hipStream_t st)
 {
     const dim3 grid((a.d + kGateChunk - 1) / kGateChunk, M), block(kGateThreads);
-    hipLaunchKernelGGL(drafter_stats_kernel<kF16>, grid, block, 0, st, a);
-    hipLaunchKernelGGL(drafter_state_kernel<kF16>, grid, block, 0, st, a);
+    switch ((grid.x + 3) / 4) {
+    case 1: hipLaunchKernelGGL((drafter_state_kernel<kF16, 4>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((drafter_state_kernel<kF16, 8>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((drafter_state_kernel<kF16, 12>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((drafter_state_kernel<kF16, kGateMaxChunks>), grid, block, 0, st, a); break;
+    }
     hipLaunchKernelGGL(drafter_hidden_kernel<kF16>, grid, block, 0, st, a);
     return hipGetLastError();
 }
@@ -524,7 +548,7 @@ hipError_t launch_drafter_gates(int dtype, const float *s, const float *z, const
     a.s = s, a.z = z, a.tokens = tokens, a.parent_row = parent_row, a.emb = static_cast<const uint16_t *>(emb);
     a.gamma_c = gamma_c, a.beta_c = beta_c, a.gamma_z = gamma_z, a.beta_z = beta_z;
     a.h_out = static_cast<uint16_t *>(h_out), a.h_out_f32 = h_out_f32, a.z_out = z_out;
-    a.part_c = gate_scratch, a.part_z = gate_scratch + (size_t)M * kGateMaxChunks * 2;
+    a.part_z = gate_scratch;
     a.P = P, a.d = d, a.vocab = vocab, a.alpha = alpha, a.eps = eps, a.status = status;
     return dtype == OWL_F16 ? launch_gates_dt<true>(a, M, st) : launch_gates_dt<false>(a, M, st);
 }

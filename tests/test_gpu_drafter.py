@@ -68,6 +68,13 @@ def test_projection_ring_and_shared_states(d_in, d, P):
     _check(case, 1.0)
 
 
+@pytest.mark.parametrize("d", [16, 1024, 1040, 4096, 4112, 8192, 8208, 12288, 12304, 16384])
+def test_row_statistics_at_the_edges_of_the_chunk_counts(d):
+    """One chunk of 1024 channels, one and a bit, and both sides of every number of chunks that a variant holds."""
+    case = W.make_drafter_case("t", 500 + d % 97, d_in=32, d=d, P=3, M=5, vocab=50)
+    _check(case, 1.0)
+
+
 def _tiled_by_definition(w_bits, d_in, d):
     """The tiled layout built from its definition in the header, granule by granule."""
     rows = w_bits.reshape(4 * d, d_in)
