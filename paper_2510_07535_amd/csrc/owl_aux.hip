@@ -75,8 +75,10 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     const bool late = p.dealt && p.B > 1;
     int s_first = p.dealt ? 0 : b * p.max_splits, limit = p.dealt ? p.max_workers : p.max_splits, ns = 0;
     if (!late) load(s_first, first, limit);
-    const int Nb = load_n_draft(p.n_draft_seq, b, p.N, nullptr);
-    const int T_b = Nb == 0 ? 0 : load_ctx_len(p.ctx_lens, b, p.max_ctx_len, nullptr) + Nb;
+    // (entries out of range are reported from here as well: every sequence has its workgroups in this grid, while the
+    // split-KV pass of a batch never gets to one that is left without drafts)
+    const int Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status), L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status);
+    const int T_b = Nb == 0 ? 0 : L + Nb;
     if (T_b > 0) {                                            // a sequence without drafts wrote no partials
         if (!p.dealt) {
             ns = min((T_b + p.C - 1) / p.C, p.max_splits);

@@ -598,6 +598,27 @@ def test_ragged_flags_bad_counts():
     assert np.isfinite(got).all() and (got[1] == 0).all()            # 9 -> 5 nodes, -1 -> none
 
 
+@pytest.mark.parametrize("split", [0, 128])
+@pytest.mark.parametrize("counts,lens,flags", [
+    ([5, -1], [300, 200], B.OWL_DEV_BAD_NDRAFT), ([-1, 5], [300, 200], B.OWL_DEV_BAD_NDRAFT), ([-1, -1], [300, 200], B.OWL_DEV_BAD_NDRAFT),
+    ([5, 6], [300, 200], B.OWL_DEV_BAD_NDRAFT), ([5, 0], [300, -7], B.OWL_DEV_BAD_CTX_LEN), ([0, 5], [301, 200], B.OWL_DEV_BAD_CTX_LEN),
+    ([5, 0], [300, 200], 0)])
+def test_ragged_flags_every_entry_out_of_range(counts, lens, flags, split):
+    """An entry out of range is reported whether or not it leaves its sequence anything to scan, whichever sequence it
+    belongs to, with a caller-chosen and a library-chosen split size."""
+    case = W.make_case("ragged_bad", 77, dtype=W.DT_BF16, Hq=8, Hkv=2, D=128, ctx_lens=[300, 200],
+                       trees=[W.chain_tree(5) for _ in range(2)])
+    step = VerifyStep(case, split_tokens=split)
+    step.ctx_lens = torch.tensor(lens, dtype=torch.int32, device=step.device)
+    nd = torch.tensor(counts, dtype=torch.int32, device=step.device)
+    B.owl_verify_attn_ragged(step.desc, step.q, step.k, step.v, step.page_table, step.ctx_lens,
+                             step.tree_parent, nd, step.out, step.workspace, step.status)
+    got = step.result()
+    assert step.dev_status() == flags
+    for b, n in enumerate(counts):
+        assert np.isfinite(got[b]).all() and (got[b, max(0, n):] == 0).all()
+
+
 # ---------------------------------------------------------------------------
 # a single sequence much shorter than the length the plan was made for
 # ---------------------------------------------------------------------------
