@@ -120,7 +120,9 @@ typedef struct owl_plan {
                              /* many workers per KV head (and row group) as run at a time, each    */
                              /* with an equal run of 64-token stages of the sequences laid end to  */
                              /* end                                                                */
-    int32_t max_splits;      /* splits of the plan in the longest sequence it admits        */
+    int32_t max_splits;      /* splits that the workspace has room for in every sequence; of        */
+                             /* split_tokens each in the longest one, in a batch with a             */
+                             /* library-chosen size of half as many                                 */
     int32_t rows_per_kv;     /* R = (Hq/Hkv) * N query rows packed against one KV stream   */
     int32_t row_tiles;       /* 16-row MFMA tiles covering R                               */
     int32_t row_groups;      /* workgroups sharing one KV split, each owning some tiles    */

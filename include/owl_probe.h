@@ -104,6 +104,18 @@ owl_status owl_probe_event_destroy(void *event);
 owl_status owl_probe_event_elapsed_ms(void *start_event, void *stop_event, float *ms_host);
 
 /*
+ * How owl_verify_attn cuts sequences of the given lengths into pieces of work, computed on the host with
+ * the arithmetic that the kernels use.  Launches nothing; host pointers.
+ *   tokens   [batch] cached rows to scan of each sequence, prefix and drafts (0: no drafts)
+ *   pieces   [capacity][5]: worker, sequence, first row, row behind the last one, slot of its partial
+ *   ranges   [batch][2]: first slot and number of slots that the merge reads for each sequence
+ *   info     [4]: pieces in all (more than capacity: the rest is not written), slots per KV head, 1 if the
+ *            work is dealt out by the lengths (0: equal splits), workers per KV head and row group
+ */
+owl_status owl_probe_deal(const owl_verify_desc *desc, const int32_t *tokens, int32_t capacity, int32_t *pieces,
+                          int32_t *ranges, int32_t *info);
+
+/*
  * Per-workgroup timeline of the split-KV pass.  With a device buffer of
  * 10 * n_workgroups int64, later owl_verify_attn calls whose split-KV grid has
  * at most n_workgroups workgroups (owl_plan.n_workgroups) and whose shape has a

@@ -42,7 +42,7 @@ EXPORTS = (
 PROBE_EXPORTS = (
     "owl_stream_read_probe", "owl_gather_read_probe", "owl_mfma_probe", "owl_selftest_quad_max",
     "owl_debug_set_timeline", "owl_step_probe", "owl_verify_attn_split_timed", "owl_probe_event_create",
-    "owl_probe_event_destroy", "owl_probe_event_elapsed_ms",
+    "owl_probe_event_destroy", "owl_probe_event_elapsed_ms", "owl_probe_deal",
 )
 OWL_NOALLOC_SCRATCH_BYTES = 48 << 20
 
@@ -135,6 +135,8 @@ def lib() -> ctypes.CDLL:
         l.owl_verify_attn_split_timed.restype = ctypes.c_int
         l.owl_verify_attn_split_timed.argtypes = [ctypes.POINTER(VerifyDesc), vp, vp, vp, vp, vp, vp, vp,
                                                   vp, ctypes.c_size_t, vp, vp, vp, vp]
+        l.owl_probe_deal.restype = ctypes.c_int
+        l.owl_probe_deal.argtypes = [ctypes.POINTER(VerifyDesc), vp, i32, vp, vp, vp]
         l.owl_probe_event_create.restype = ctypes.c_int
         l.owl_probe_event_create.argtypes = [ctypes.POINTER(ctypes.c_void_p)]
         l.owl_probe_event_destroy.restype = ctypes.c_int
@@ -274,6 +276,22 @@ def owl_debug_set_timeline(buffer) -> None:
     number of workgroups it has room for), or None to switch the recording off."""
     n = 0 if buffer is None else int(buffer.numel()) // 10
     _check(lib().owl_debug_set_timeline(_ptr(buffer), n), "owl_debug_set_timeline")
+
+
+def owl_probe_deal(desc: VerifyDesc, tokens):
+    """How owl_verify_attn cuts sequences of `tokens` cached rows each into pieces: (pieces [n][5]: worker, sequence, first
+    row, end row, slot; ranges [batch][2]: first slot and slots merged; slots per KV head; dealt by length; workers)."""
+    import numpy as np
+    tokens = np.ascontiguousarray(tokens, dtype=np.int32)
+    ranges, info = np.zeros((len(tokens), 2), np.int32), np.zeros(4, np.int32)
+    pieces = np.zeros((1 << 12, 5), np.int32)
+    for _ in range(2):
+        _check(lib().owl_probe_deal(ctypes.byref(desc), tokens.ctypes.data, len(pieces), pieces.ctypes.data,
+                                    ranges.ctypes.data, info.ctypes.data), "owl_probe_deal")
+        if info[0] <= len(pieces):
+            break
+        pieces = np.zeros((int(info[0]), 5), np.int32)
+    return pieces[:info[0]], ranges, int(info[1]), bool(info[2]), int(info[3])
 
 
 class KernelTimer:

@@ -59,11 +59,12 @@ owl_status check_desc(const owl_verify_desc *d)
 struct FullPlan {
     owl_plan pub;
     const Variant *variant;
-    size_t part_o_bytes, part_ml_bytes, info_offset;
+    size_t part_o_bytes;
     bool half_partials;       // normalised fp16 partials (16-bit inputs unless the caller asks for fp32 ones)
     int32_t group_tiles;
     bool dealt;               // the kernels cut the work by the actual lengths (deal_units)
-    int32_t min_units, round_workers, max_workers, seq_extra, n_slots;
+    DealRule rule;
+    int32_t n_slots;
     Deal full;                // one sequence of the greatest length
     dim3 grid;                // of the split-KV pass
 };
@@ -149,8 +150,8 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     // one with a set-up and an empty ring (0 instead of 8: 284 against 259 us on four sequences of 3K-16K
     // tokens with 240 rows in four layers; 4: 268, 10: 260), and 1-2 for the masked steps of a lone sequence.
     const int64_t stages_at_most = (T + kSplitQuantum - 1) / kSplitQuantum;
-    fp->seq_extra = d->batch == 1 ? (RT > 4 ? 2 : 1) : 8;
-    const int64_t units_at_most = (int64_t)d->batch * (stages_at_most + fp->seq_extra);
+    fp->rule.seq_extra = d->batch == 1 ? (RT > 4 ? 2 : 1) : 8;
+    const int64_t units_at_most = (int64_t)d->batch * (stages_at_most + fp->rule.seq_extra);
     fp->dealt = d->split_tokens == 0 && units_at_most < ((int64_t)1 << 30);
     const int64_t head_groups = (int64_t)d->n_kv_heads * rgs;
     int64_t per_round = 1;
@@ -164,13 +165,13 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
         if (per_round > 4) break;
     }
     if (per_round < 1) per_round = 1;
-    fp->round_workers = (int32_t)per_round;
-    fp->min_units = (R + kSplitQuantum - 1) / kSplitQuantum;
+    fp->rule.round_workers = (int32_t)per_round;
+    fp->rule.min_units = (R + kSplitQuantum - 1) / kSplitQuantum;
     const int64_t rounds = 1 + (units_at_most - 1) / (per_round * kMaxPieceUnits);
-    int64_t workers = units_at_most / fp->min_units;
+    int64_t workers = units_at_most / fp->rule.min_units;
     if (workers > per_round * rounds) workers = per_round * rounds;
     if (workers < 1) workers = 1;
-    fp->max_workers = (int32_t)workers;
+    fp->rule.max_workers = (int32_t)workers;
     fp->full = Deal{(int32_t)workers, (int32_t)(units_at_most / workers), (int32_t)(units_at_most % workers)};
     // Workspace: the partials that are written, and never less than equal splits of half the planned size
     // would need for a batch (the planned size for one sequence).
@@ -178,7 +179,6 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     const size_t o_bytes = (size_t)d->head_dim * kRowTile * (fp->half_partials ? 2 : 4), ml_bytes = kPartMl * sizeof(float);
     auto bytes_of = [&](size_t slots, size_t unit) -> size_t { return align_up((size_t)d->n_kv_heads * slots * RT * unit, 256); };
     auto partials = [&](size_t slots) -> size_t { return bytes_of(slots, o_bytes) + bytes_of(slots, ml_bytes); };
-    const size_t info_bytes = align_up(((size_t)d->batch + 3) * sizeof(int32_t), 256);                 // write_batch_info's words
     int64_t sized_splits = max_splits;
     if (d->split_tokens == 0 && d->batch > 1 && units_at_most < ((int64_t)1 << 30)) {
         int64_t c_floor = align_up((size_t)(C / 2), kSplitQuantum);
@@ -189,14 +189,12 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     // A dealt batch may leave one partial per worker and one per sequence, several times what few equal splits
     // of short sequences leave.  What owl_verify_attn_noalloc admits must not depend on how the work is dealt
     // out, so a launch that fits its scratch in equal splits only is cut that way.
-    if (fp->dealt && dealt_bytes + info_bytes > OWL_NOALLOC_SCRATCH_BYTES && sized + info_bytes <= OWL_NOALLOC_SCRATCH_BYTES)
+    if (fp->dealt && dealt_bytes > OWL_NOALLOC_SCRATCH_BYTES && sized <= OWL_NOALLOC_SCRATCH_BYTES)
         fp->dealt = false;
     const size_t n_slots = fp->dealt ? (size_t)(workers + d->batch - 1) : (size_t)d->batch * (size_t)max_splits;
     fp->n_slots = (int32_t)n_slots;
     if (fp->dealt) max_splits = sized_splits;
     fp->part_o_bytes = bytes_of(n_slots, o_bytes);
-    fp->part_ml_bytes = bytes_of(n_slots, ml_bytes);
-    fp->info_offset = partials(n_slots) > sized ? partials(n_slots) : sized;
     fp->variant = v;
     owl_plan &pl = fp->pub;
     pl.reserved_ = 0;
@@ -217,7 +215,7 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     fp->grid = dim3(d->n_kv_heads * rgs, (unsigned)grid_y, (unsigned)grid_z);
     if ((int64_t)fp->grid.x * fp->grid.y * fp->grid.z >= ((int64_t)1 << 31)) return OWL_ERR_UNSUPPORTED;   // the kernel numbers them in 32 bits
     pl.n_workgroups = (int32_t)((int64_t)fp->grid.x * fp->grid.y * fp->grid.z);
-    pl.workspace_bytes = fp->info_offset + info_bytes;
+    pl.workspace_bytes = partials(n_slots) > sized ? partials(n_slots) : sized;
     return OWL_OK;
 }
 
@@ -356,7 +354,7 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     st = ensure_lds_attr(variant);
     if (st != OWL_OK) return st;
 
-    // workspace: partial O | partial (m, l, s) | ... | write_batch_info's words
+    // workspace: partial O | partial (m, l, s)
     char *ws = static_cast<char *>(workspace);
     KParams p;
     memset(&p, 0, sizeof p);
@@ -366,7 +364,6 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     p.part_o = ws;
     p.half_partials = fp.half_partials ? 1 : 0;
     p.part_ml = reinterpret_cast<float *>(ws + fp.part_o_bytes);
-    p.batch_info = fp.dealt && desc->batch > 1 ? reinterpret_cast<int32_t *>(ws + fp.info_offset) : nullptr;
     p.out = out;
     p.out_dtype = desc->out_dtype;
     p.dev_status = dev_status;
@@ -374,8 +371,7 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     p.G = p.Hq / p.Hkv; p.R = fp.pub.rows_per_kv;
     p.max_pages = desc->max_pages_per_seq; p.max_ctx_len = desc->max_ctx_len;
     p.C = fp.pub.split_tokens; p.max_splits = fp.pub.max_splits;
-    p.dealt = fp.dealt ? 1 : 0; p.min_units = fp.min_units; p.round_workers = fp.round_workers;
-    p.max_workers = fp.max_workers; p.seq_extra = fp.seq_extra; p.n_slots = fp.n_slots;
+    p.dealt = fp.dealt ? 1 : 0; p.rule = fp.rule; p.n_slots = fp.n_slots;
     p.full = fp.full;
     p.RT = fp.pub.row_tiles; p.row_groups = fp.pub.row_groups; p.group_tiles = fp.group_tiles;
     p.stride_page = desc->kv_stride_page; p.stride_head = desc->kv_stride_head;
@@ -403,6 +399,65 @@ owl_status owl_verify_attn_split_timed(const owl_verify_desc *desc, const void *
     return verify_impl(desc, q, k_cache, v_cache, page_table, ctx_lens, tree_parent, nullptr, out, workspace,
                        workspace_bytes, dev_status, stream, OWL_PHASE_SPLIT, static_cast<hipEvent_t>(start_event),
                        static_cast<hipEvent_t>(stop_event));
+}
+
+owl_status owl_probe_deal(const owl_verify_desc *desc, const int32_t *tokens, int32_t capacity, int32_t *pieces,
+                          int32_t *ranges, int32_t *info)
+{
+    if (!tokens || !pieces || !ranges || !info || capacity < 0) return OWL_ERR_INVALID_ARG;
+    FullPlan fp;
+    const owl_status st = make_plan(desc, &fp);
+    if (st != OWL_OK) return st;
+    int64_t total = 0;
+    for (int b = 0; b < desc->batch; ++b) {
+        if (tokens[b] < 0 || tokens[b] > (int64_t)desc->max_ctx_len + desc->n_draft) return OWL_ERR_INVALID_ARG;
+        if (fp.dealt) total += seq_units(fp.rule, tokens[b]);
+    }
+    int32_t n = 0;
+    auto piece = [&](int worker, int b, int first, int end, int slot) {
+        if (n < capacity) {
+            const int32_t row[5] = {worker, b, first, end, slot};
+            memcpy(pieces + 5 * (size_t)n, row, sizeof row);
+        }
+        ++n;
+    };
+    info[1] = fp.n_slots;
+    info[2] = fp.dealt ? 1 : 0;
+    info[3] = fp.dealt ? fp.rule.max_workers : desc->batch * fp.pub.max_splits;
+    if (!fp.dealt) {
+        for (int b = 0; b < desc->batch; ++b) {
+            const int splits = (int)(((int64_t)tokens[b] + fp.pub.split_tokens - 1) / fp.pub.split_tokens);
+            for (int c = 0; c < splits; ++c) {
+                const int64_t end = ((int64_t)c + 1) * fp.pub.split_tokens;
+                piece(b * fp.pub.max_splits + c, b, c * fp.pub.split_tokens, (int)(end < tokens[b] ? end : tokens[b]),
+                      b * fp.pub.max_splits + c);
+            }
+            ranges[2 * b] = b * fp.pub.max_splits;
+            ranges[2 * b + 1] = splits;
+        }
+        info[0] = n;
+        return OWL_OK;
+    }
+    const Deal deal = desc->batch == 1 && tokens[0] == desc->max_ctx_len + desc->n_draft
+                          ? fp.full : deal_units(fp.rule, total > 0 ? (int)total : 1);
+    for (int w = 0; w < deal.workers && total > 0; ++w) {
+        const int x0 = deal_begin(deal, w), x1 = deal_begin(deal, w + 1);
+        for (int b = 0, before = 0; b < desc->batch; before += seq_units(fp.rule, tokens[b]), ++b) {
+            const int s0 = (x0 > before ? x0 : before) - before;
+            const int s1 = x1 - before < stages_of(tokens[b]) ? x1 - before : stages_of(tokens[b]);
+            if (s0 < s1)
+                piece(w, b, s0 * kSplitQuantum, s1 * kSplitQuantum < tokens[b] ? s1 * kSplitQuantum : tokens[b], w + b);
+        }
+    }
+    for (int b = 0, before = 0; b < desc->batch; before += seq_units(fp.rule, tokens[b]), ++b) {
+        ranges[2 * b] = ranges[2 * b + 1] = 0;
+        if (tokens[b] == 0) continue;
+        const int w0 = deal_worker(deal, before);
+        ranges[2 * b] = w0 + b;
+        ranges[2 * b + 1] = deal_worker(deal, before + stages_of(tokens[b]) - 1) - w0 + 1;
+    }
+    info[0] = n;
+    return OWL_OK;
 }
 
 owl_status owl_probe_event_create(void **event)

@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     // The partials of this row tile: `ns` slots from s_first on (wave-uniform).  Where they begin depends on
     // the lengths only in a batch; otherwise the first ones are requested before the length is known.
     const bool late = p.dealt && p.B > 1;
-    int s_first = p.dealt ? 0 : b * p.max_splits, limit = p.dealt ? p.max_workers : p.max_splits, ns = 0;
+    int s_first = p.dealt ? 0 : b * p.max_splits, limit = p.dealt ? p.rule.max_workers : p.max_splits, ns = 0;
     if (!late) load(s_first, first, limit);
     // (entries out of range are reported from here as well: every sequence has its workgroups in this grid, while the
     // split-KV pass of a batch never gets to one that is left without drafts)
@@ -126,13 +126,11 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
         s0 += kStride * kInFlight;
         if (s0 < ns) load(s_first, s0, limit);
     }
-    const bool last_block = p.batch_info && blockIdx.x + blockIdx.y + blockIdx.z == 0;
     float lsum = lw;
     float4 tot[UPW];
     if constexpr (BY_CHANNEL) {
 #pragma unroll
         for (int u = 0; u < UPW; ++u) tot[u] = acc[u];
-        if (last_block && w == 0) write_batch_info(p);
     } else {
         __shared__ float4 s_acc[WAVES][UPW][64];
         __shared__ float s_m[WAVES][64], s_l[WAVES][64];
@@ -141,7 +139,6 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
         s_m[w][lane] = mw;
         s_l[w][lane] = lw;
         __syncthreads();
-        if (last_block && w == 1) write_batch_info(p);
         if (w != 0) return;
         float M = s_m[0][lane];
 #pragma unroll
@@ -185,7 +182,7 @@ template <int D>
 static void launch_combine_d(const KParams &p, bool half_partials, hipStream_t s)
 {
     // Partials per sequence on average, if all sequences are alike.
-    const int per_seq = p.dealt ? (p.max_workers + p.B - 1) / p.B : p.max_splits;
+    const int per_seq = p.dealt ? (p.rule.max_workers + p.B - 1) / p.B : p.max_splits;
     if (p.B > 1 && per_seq <= 8) {
         launch_combine_as<D, D / 32, true>(p, half_partials, dim3(p.RT, p.Hkv, p.B), s);
         return;

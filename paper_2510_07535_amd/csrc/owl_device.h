@@ -74,54 +74,8 @@ __device__ __forceinline__ int seq_tokens(const KParams &p, int b)
     return n == 0 ? 0 : L + n;
 }
 
-// ---------------------------------------------------------------------------
-// How the K/V of a launch is dealt out when the caller leaves the split size to
-// the library.  A KV head (and row group) has `workers` workgroups, all resident
-// at once, one per compute unit; the sequences' stages of 64 tokens are laid end
-// to end and every worker takes an equal run of them, crossing from one sequence
-// into the next where its share asks for it.  Each run is cut at the sequence
-// boundaries into pieces, one partial per piece.  So every compute unit gets the
-// same work whatever the lengths are, and pays for set-up and epilogue once or
-// twice instead of once per split.  (Equal splits in 4-5 rounds of workgroups, the
-// alternative, left 9 % of the compute units idle in the last round and 9 % of
-// the time in set-up and epilogues on 16 sequences of 8K-64K tokens.)
-//
-// A sequence counts `seq_extra` units beyond its stages, at its end: what the masked
-// steps over its drafts and the set-up of the following piece cost.
-// ---------------------------------------------------------------------------
-// a / b for 0 <= a, 0 < b and quotients below 2^20: a multiplication and a correction instead of the
-// thirty dependent instructions of an integer division (four of them cost a workgroup half a microsecond).
-__device__ __forceinline__ int quotient(int a, int b)
-{
-    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
-    int r = a - q * b;
-    if (r < 0) --q, r += b;
-    if (r >= b) ++q;
-    return __builtin_amdgcn_readfirstlane(q);
-}
-
-__device__ __forceinline__ Deal deal_units(const KParams &p, int units)
-{
-    // more than one round only where a share would outgrow the page list in LDS
-    int n = p.round_workers;
-    if (units > n * kMaxPieceUnits) n *= quotient(units + n * kMaxPieceUnits - 1, n * kMaxPieceUnits);
-    n = min(n, p.max_workers);
-    if (units < n * p.min_units) n = max(1, quotient(units, p.min_units));
-    const int q = quotient(units, n);
-    return Deal{n, q, units - q * n};
-}
-__device__ __forceinline__ int deal_begin(const Deal &d, int worker) { return worker * d.q + min(worker, d.r); }
-__device__ __forceinline__ int deal_worker(const Deal &d, int unit)
-{
-    const int cut = d.r * (d.q + 1);
-    return unit < cut ? quotient(unit, d.q + 1) : d.r + quotient(unit - cut, d.q);
-}
-
-__device__ __forceinline__ int stages_of(int tokens) { return (tokens + kSplitQuantum - 1) / kSplitQuantum; }
-__device__ __forceinline__ int seq_units(const KParams &p, int tokens)
-{
-    return tokens == 0 ? 0 : stages_of(tokens) + p.seq_extra;
-}
+__device__ __forceinline__ Deal deal_units(const KParams &p, int units) { return deal_units(p.rule, units); }
+__device__ __forceinline__ int seq_units(const KParams &p, int tokens) { return seq_units(p.rule, tokens); }
 
 // Inclusive sum over the lanes of the wavefront.
 __device__ __forceinline__ int lane_scan(int v)
@@ -185,27 +139,6 @@ __device__ __forceinline__ int units_before(const KParams &p, const BatchUnits &
     }
     const int l = b & 63;
     return base + (l > 0 ? __builtin_amdgcn_readlane(scan, max(l - 1, 0)) : 0);
-}
-
-// The last words of a batch's workspace say what equal splits of the planned size would make of it
-// (int32): [0] that size C, [1] the number of (sequence, split) pairs, [2 + b] the pairs of the
-// sequences before b (b = 0 .. B).  For inspection; no kernel reads it.  One wavefront.
-__device__ __forceinline__ void write_batch_info(const KParams &p)
-{
-    const int lane = threadIdx.x & 63;
-    int base = 0;
-    for (int b0 = 0; b0 < p.B; b0 += 64) {
-        const bool live = b0 + lane < p.B;
-        const int n = live ? (seq_tokens(p, b0 + lane) + p.C - 1) / p.C : 0;
-        const int scan = lane_scan(n);
-        if (live) p.batch_info[2 + b0 + lane] = base + scan - n;
-        base += __builtin_amdgcn_readlane(scan, 63);
-    }
-    if (lane == 0) {
-        p.batch_info[2 + p.B] = base;
-        p.batch_info[0] = p.C;
-        p.batch_info[1] = base;
-    }
 }
 
 // Physical page of logical page lp of sequence b; an id outside the pool (or a

@@ -6,17 +6,12 @@
 #include <stdint.h>
 
 #include "owl.h"
+#include "owl_deal.h"
 
 namespace owl {
 
-constexpr int kPage = 16;                 // tokens per cache page
 constexpr int kRowTile = 16;              // query rows per MFMA tile
 constexpr int kMaxSplitTokens = 16384;    // largest split of a plan with equal splits
-constexpr int kSplitQuantum = 64;         // split_tokens is a multiple of every stage size
-// The page list of one piece of work sits in LDS (12 KB beside the 128 KB ring); one worker's share of
-// a launch whose work is dealt out evenly never exceeds it (see deal_units).
-constexpr int kMaxPiecePages = 3072;
-constexpr int kMaxPieceUnits = kMaxPiecePages * kPage / kSplitQuantum - 1;
 
 // Format of a split's partial, per 16-row tile ("slot").
 //   fp32 inputs, and 16-bit inputs with OWL_FLAG_FP32_PARTIALS:
@@ -27,11 +22,6 @@ constexpr int kMaxPieceUnits = kMaxPiecePages * kPage / kSplitQuantum - 1;
 //                  bytes to write and to read back; a value is stored to 2^-12 of its row's largest
 //                  component whatever the magnitude of V, far below the bf16 rounding of P.
 constexpr int kPartMl = 48;               // floats of part_ml per slot: m[16], l[16], s[16]
-
-// `units` stages of work dealt out evenly: the first r workers take q + 1 of them, the others q.
-struct Deal {
-    int32_t workers, q, r;
-};
 
 // Everything a kernel needs, passed by value.
 struct KParams {
@@ -47,15 +37,11 @@ struct KParams {
     int32_t B, N, Hq, Hkv, G, R;
     int32_t max_pages, max_ctx_len;
     int32_t C;            // tokens per split of the plan
-    int32_t max_splits;   // splits of C tokens in the longest sequence the plan admits
+    int32_t max_splits;   // not dealt: splits of C tokens in the longest sequence the plan admits
     int32_t dealt;        // 1: the library cuts the work by the actual lengths (deal_units); 0: equal splits of C tokens
-    int32_t min_units;    // dealt: least units (stages of 64 tokens) worth a worker
-    int32_t round_workers;// dealt: workers per (KV head, row group) that run at the same time
-    int32_t max_workers;  // dealt: workers per (KV head, row group) of the launched grid
+    DealRule rule;        // dealt: how
     Deal full;            // dealt, B == 1: deal_units of the longest sequence the plan admits
-    int32_t seq_extra;    // dealt: units a sequence counts beyond its stages (set-up, masked steps)
     int32_t n_slots;      // partials per (KV head, row tile)
-    int32_t *batch_info;  // a dealt batch: what equal splits of C tokens would make of it (write_batch_info), else null
     int32_t RT;           // row tiles covering R
     int32_t row_groups;
     int32_t group_tiles;  // row tiles per row group (the last group may hold fewer)

@@ -1126,7 +1126,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         guess = guess_pages(p, b, x * kSplitQuantum);
     } else {
         const int worker = (int)item;
-        if (worker >= p.max_workers) return;          // padding of the grid
+        if (worker >= p.rule.max_workers) return;          // padding of the grid
         Deal deal;
         if (p.B == 1) {
             // most lone sequences are as long as announced: their pages are asked for along with the length

@@ -286,6 +286,48 @@ def test_batches_of_short_sequences_fit_the_fixed_scratch(hkv, group, n, d, batc
     assert B.owl_verify_attn_workspace_size(desc) <= B.OWL_NOALLOC_SCRATCH_BYTES
 
 
+def _check_pieces(desc, tokens):
+    """Every cached row of every sequence lies in exactly one piece, every piece has a slot of its own, and the merge of a
+    sequence reads exactly the slots of its pieces.  Returns (pieces, dealt by length, workers)."""
+    pieces, ranges, n_slots, dealt, workers = B.owl_probe_deal(desc, tokens)
+    assert len(set(pieces[:, 4].tolist())) == len(pieces) and len(set(map(tuple, pieces[:, :2].tolist()))) == len(pieces)
+    per_seq = {}
+    for w, b, first, end, slot in pieces.tolist():
+        assert 0 <= w < workers and 0 <= slot < n_slots
+        assert first % 64 == 0 and first < end and (end - first + 15) // 16 <= 3072          # the page list in LDS
+        per_seq.setdefault(b, []).append((first, end, slot))
+    for b, t in enumerate(tokens):
+        mine = sorted(per_seq.get(b, []))
+        assert [f for f, _, _ in mine] == [0] * (t > 0) + [e for _, e, _ in mine][:-1]
+        assert not mine or mine[-1][1] == t
+        assert [s for _, _, s in mine] == list(range(ranges[b, 0], ranges[b, 0] + ranges[b, 1]))
+        assert len(mine) == ranges[b, 1]
+    bytes_per_slot = desc.n_kv_heads * (-(-desc.n_q_heads // desc.n_kv_heads * desc.n_draft // 16)) * (desc.head_dim * 16 * 2 + 192)
+    assert n_slots * bytes_per_slot <= B.owl_verify_attn_workspace_size(desc)
+    return pieces, dealt, workers
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_dealt_pieces_cover_every_sequence_once(seed):
+    """The arithmetic by which the kernels share out a launch, over random shapes, lengths (empty sequences among them),
+    announced lengths and split sizes."""
+    r = np.random.Generator(np.random.Philox(key=seed))
+    for _ in range(25):
+        hkv, group = [(8, 4), (8, 8), (1, 8), (1, 4), (2, 8), (4, 8), (64, 1), (3, 7), (96, 2)][r.integers(9)]
+        batch = 1 if r.random() < 0.4 else int(2 ** r.uniform(1, 8))
+        n = int(r.integers(1, 65))
+        ctx = int(2 ** r.uniform(0, 17 if batch > 1 else 22))
+        lens = r.integers(0, ctx + 1, size=batch) if r.random() < 0.7 else np.minimum(ctx, r.integers(0, 200, size=batch))
+        if r.random() < 0.5:
+            lens[r.integers(batch)] = ctx
+        counts = np.full(batch, n) if r.random() < 0.6 else r.integers(0, n + 1, size=batch)
+        desc = _good(batch=batch, n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, max_ctx_len=ctx,
+                     max_pages_per_seq=(ctx + n + 15) // 16, split_tokens=int(r.choice([0, 0, 0, 64, 1000, 20000])),
+                     kv_stride_page=hkv * 16 * 128, qkv_dtype=int(r.choice([B.OWL_BF16, B.OWL_F32])),
+                     flags=int(r.random() < 0.2) * B.OWL_FLAG_FP32_PARTIALS)
+        _check_pieces(desc, [int(l + c) if c else 0 for l, c in zip(lens, counts)])
+
+
 def test_timeline_switch_checks_its_arguments():
     lib = B.lib()
     assert lib.owl_debug_set_timeline(0x10000, 0) == B.OWL_ERR_INVALID_ARG
