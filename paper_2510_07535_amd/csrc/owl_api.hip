@@ -167,12 +167,12 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     if (per_round < 1) per_round = 1;
     fp->rule.round_workers = (int32_t)per_round;
     fp->rule.min_units = (R + kSplitQuantum - 1) / kSplitQuantum;
-    const int64_t rounds = 1 + (units_at_most - 1) / (per_round * kMaxPieceUnits);
-    int64_t workers = units_at_most / fp->rule.min_units;
-    if (workers > per_round * rounds) workers = per_round * rounds;
-    if (workers < 1) workers = 1;
-    fp->rule.max_workers = (int32_t)workers;
-    fp->full = Deal{(int32_t)workers, (int32_t)(units_at_most / workers), (int32_t)(units_at_most % workers)};
+    fp->rule.merge = d->batch == 1 && RT <= 4 && d->qkv_dtype != OWL_F32 ? kMergeUnits : 0;
+    int64_t workers = 1;
+    if (fp->dealt) {                                // (no shorter length asks for more workers than the greatest)
+        fp->rule.max_workers = workers = most_workers(fp->rule, (int)units_at_most);
+        fp->full = deal_units(fp->rule, (int)units_at_most);
+    }
     // Workspace: the partials that are written, and never less than equal splits of half the planned size
     // would need for a batch (the planned size for one sequence).
     fp->half_partials = d->qkv_dtype != OWL_F32 && !(d->flags & OWL_FLAG_FP32_PARTIALS);

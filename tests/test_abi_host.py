@@ -328,6 +328,22 @@ def test_dealt_pieces_cover_every_sequence_once(seed):
         _check_pieces(desc, [int(l + c) if c else 0 for l, c in zip(lens, counts)])
 
 
+@pytest.mark.parametrize("hkv,group,n,d,dtype,announced,tokens,most,longest", [
+    (1, 4, 1, 128, B.OWL_BF16, 20000, 20001, 86, 4),       # sqrt(24 * 314): shares of at most four stages
+    (1, 4, 9, 128, B.OWL_F16, 131072, 20009, 86, 4),       # announced longer than it is
+    (1, 4, 16, 64, B.OWL_BF16, 41000, 41016, 124, 6),
+    (2, 4, 1, 128, B.OWL_BF16, 10000, 10001, 64, 3),
+    (4, 4, 1, 128, B.OWL_BF16, 5000, 5001, 40, 2),         # 64 compute units a head, but shares of two stages all the same
+    (1, 4, 1, 128, B.OWL_BF16, 3000, 3001, 48, 1),         # up to 64 partials are free
+])
+def test_a_lone_sequence_with_few_rows_leaves_few_partials(hkv, group, n, d, dtype, announced, tokens, most, longest):
+    """Every partial lengthens the merge, so the compute units are not all used where that does not pay for itself."""
+    desc = _good(n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, max_ctx_len=announced, qkv_dtype=dtype,
+                 max_pages_per_seq=(announced + n + 15) // 16, kv_stride_page=hkv * 16 * d, kv_stride_head=16 * d, kv_stride_token=d)
+    pieces, dealt, _ = _check_pieces(desc, [tokens])
+    assert dealt and len(pieces) <= most and max(end - first for _, _, first, end, _ in pieces.tolist()) <= 64 * longest
+
+
 def test_timeline_switch_checks_its_arguments():
     lib = B.lib()
     assert lib.owl_debug_set_timeline(0x10000, 0) == B.OWL_ERR_INVALID_ARG

@@ -459,6 +459,7 @@ def test_batch_split_follows_the_lengths(oracle_mod, name, ctx, Hkv):
 
 @pytest.mark.parametrize("name,Hq,Hkv,D,ctx,n", [
     ("more than one round of workers", 64, 64, 64, [200_000], 3),      # a share would outgrow the page list: 8 workers, not 4
+    ("fewer workers than compute units", 4, 1, 128, [19950], 4),
     ("shares of one stage", 8, 2, 128, [0, 1, 63, 64, 65, 127], 4),
     ("few partials per sequence", 8, 2, 64, [1500 + 37 * k for k in range(40)], 6),
     ("many partials per sequence", 8, 2, 128, [9000, 1, 14000], 6),
