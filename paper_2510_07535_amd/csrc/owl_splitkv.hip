@@ -193,8 +193,25 @@ __device__ __forceinline__ PageGuess guess_pages(const KParams &p, int b, int po
     return gs;
 }
 
+// The kernel's arguments for one piece.  In fp16, whose second (guarded) loop takes more scalar registers, they are read
+// again from the kernel-argument segment: kept across the pieces they made 36-79 scalar registers spill (0-13 now) and
+// cost a call of 3K-7K tokens 0.2-0.4 us of 11-13 (head_dim 64, 8 KV heads, 4 rows, 3K: 11.5 -> 11.1 us).  The bf16
+// kernels spill half of that and lose by reading again (16 sequences of 8K-64K, 104 rows: 452 -> 457 us).
+template <typename T>
+__device__ __forceinline__ const KParams &piece_args(const KParams &launch_args)
+{
+    if constexpr (std::is_same<T, _Float16>::value) {
+        typedef const __attribute__((address_space(4))) KParams KernelArgs;
+        KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        return *(const KParams *)args;
+    } else {
+        return launch_args;
+    }
+}
+
 template <typename T, int D, int TPW, int WR, int WK, typename Stamp>
-__device__ __forceinline__ void run_piece(const KParams &p, unsigned char *smem, int g, int rg, const Piece &pc,
+__device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned char *smem, int g, int rg, const Piece &pc,
                                           const PageGuess &guess, Stamp &&stamp)
 {
     using GEO = Geo<T, D, TPW, WR, WK>;
@@ -215,6 +232,7 @@ __device__ __forceinline__ void run_piece(const KParams &p, unsigned char *smem,
     // pieces of a share (as the compiler would by itself) it does not fit the registers of the loops.
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
+    const KParams &p = piece_args<T>(launch_args);
     asm volatile("" : "+s"(g), "+s"(rg));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % WR, wk = wave / WR;
