@@ -1113,10 +1113,10 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         n = ((slot / (uint32_t)p.row_groups) << 3) | (n & 7);
     }
     const uint32_t item = n / (uint32_t)p.Hkv;       // worker, or (split, sequence) with splits fastest
-    // The heads are rotated from one row of eight workgroups to the next, so that no XCD reads one head only.  Not with
-    // row groups: those are short contexts with many rows, where an XCD that stays with its heads finds their query
-    // rows in its L2 (240 rows on 16K / 5K tokens 31.7 -> 30.7 / 20.4 -> 19.8 us, 320 rows on 16K 37.6 -> 36.0 us).
-    const int g = (int)((n + (p.row_groups > 1 ? 0u : item * (uint32_t)p.Hkv / 8)) % (uint32_t)p.Hkv);
+    // An XCD stays with its heads, and finds their query rows in its L2.  (Rotating the heads from one row of eight
+    // workgroups to the next: 24 rows, 8 heads, 5K tokens 13.1 -> 13.2 us, four sequences of 3K-16K, 240 rows, 52.5 -> 53.7,
+    // eight of 2K-9K, 4 heads, 39.6 -> 40.5.)
+    const int g = (int)(n % (uint32_t)p.Hkv);
     const size_t head_slots = (size_t)g * p.n_slots;
 
     // timeline of this workgroup (profiling instantiations only; the production kernels
