@@ -168,7 +168,8 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     fp->rule.round_workers = (int32_t)per_round;
     fp->rule.min_units = (R + kSplitQuantum - 1) / kSplitQuantum;
     fp->rule.merge = d->batch == 1 && RT <= 4 && d->qkv_dtype != OWL_F32 ? kMergeUnits : 0;
-    int64_t workers = 1;
+    int64_t workers = fp->rule.max_workers = 1;
+    fp->full = Deal{1, 0, 0};
     if (fp->dealt) {                                // (no shorter length asks for more workers than the greatest)
         fp->rule.max_workers = workers = most_workers(fp->rule, (int)units_at_most);
         fp->full = deal_units(fp->rule, (int)units_at_most);
@@ -186,11 +187,19 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
         sized_splits = (T + c_floor - 1) / c_floor;
     }
     const size_t sized = partials((size_t)d->batch * (size_t)sized_splits), dealt_bytes = partials((size_t)(workers + d->batch - 1));
-    // A dealt batch may leave one partial per worker and one per sequence, several times what few equal splits
-    // of short sequences leave.  What owl_verify_attn_noalloc admits must not depend on how the work is dealt
-    // out, so a launch that fits its scratch in equal splits only is cut that way.
-    if (fp->dealt && dealt_bytes > OWL_NOALLOC_SCRATCH_BYTES && sized <= OWL_NOALLOC_SCRATCH_BYTES)
-        fp->dealt = false;
+    // A dealt launch leaves one partial per worker, in a batch also one per sequence: that may be several times what few
+    // equal splits of short sequences leave.  What owl_verify_attn_noalloc admits must not depend on how the work is
+    // dealt out, so a launch that fits its scratch in equal splits only has as many workers as fit, or, where those
+    // would be fewer than the splits, equal splits.
+    if (fp->dealt && dealt_bytes > OWL_NOALLOC_SCRATCH_BYTES && sized <= OWL_NOALLOC_SCRATCH_BYTES) {
+        int64_t room = (int64_t)(OWL_NOALLOC_SCRATCH_BYTES / partials(1)) - (d->batch - 1);      // partials(1) is rounded up
+        if (room >= (int64_t)d->batch * max_splits && (units_at_most + room - 1) / room <= kMaxPieceUnits) {
+            fp->rule.max_workers = workers = room;
+            fp->full = deal_units(fp->rule, (int)units_at_most);
+        } else {
+            fp->dealt = false;
+        }
+    }
     const size_t n_slots = fp->dealt ? (size_t)(workers + d->batch - 1) : (size_t)d->batch * (size_t)max_splits;
     fp->n_slots = (int32_t)n_slots;
     if (fp->dealt) max_splits = sized_splits;

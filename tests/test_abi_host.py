@@ -279,11 +279,29 @@ def test_init_and_noalloc_reject_before_touching_a_device():
     (16, 64, 36, 64, 2, 7837, B.OWL_BF16, 1), (64, 7, 48, 64, 16, 1, B.OWL_BF16, 0), (2, 16, 56, 128, 100, 24, B.OWL_F16, 0)])
 def test_batches_of_short_sequences_fit_the_fixed_scratch(hkv, group, n, d, batch, ctx, dtype, flags):
     """Shapes whose few equal splits fit the buffer of the entry point without a workspace, and one partial per
-    workgroup and sequence does not: the plan cuts them into equal splits."""
+    workgroup and sequence does not: the plan cuts them into equal splits, unless as many workers as splits would fit."""
     desc = _good(batch=batch, n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, max_ctx_len=ctx,
                  max_pages_per_seq=(ctx + n + 15) // 16, qkv_dtype=dtype, flags=flags, kv_stride_page=hkv * 16 * d,
                  kv_stride_head=16 * d, kv_stride_token=d)
     assert B.owl_verify_attn_workspace_size(desc) <= B.OWL_NOALLOC_SCRATCH_BYTES
+    _, dealt, workers = _check_pieces(desc, [ctx + n] * batch)
+    plan = B.owl_verify_attn_plan(desc)
+    splits = -(-(ctx + n) // plan.split_tokens)
+    assert dealt == (batch == 2) and plan.n_workgroups >= hkv * plan.row_groups * workers
+    assert workers >= batch * splits and (dealt or workers == batch * splits)
+
+
+@pytest.mark.parametrize("ctx,n,hkv,group,batch,most", [(40000, 48, 8, 8, 1, 31), (8000, 48, 8, 8, 4, 28)])
+def test_a_launch_that_outgrows_the_fixed_scratch_has_fewer_workers(ctx, n, hkv, group, batch, most):
+    """fp32 partials of every compute unit would not fit, those of somewhat fewer workers do: the work is still shared out
+    by the actual lengths, so that one shorter than announced keeps all workers busy."""
+    desc = _good(batch=batch, n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, max_ctx_len=ctx, flags=B.OWL_FLAG_FP32_PARTIALS,
+                 max_pages_per_seq=(ctx + n + 15) // 16)
+    assert B.owl_verify_attn_workspace_size(desc) <= B.OWL_NOALLOC_SCRATCH_BYTES
+    for tokens in (ctx + n, ctx // 4 + n, n + 1):
+        pieces, dealt, workers = _check_pieces(desc, [tokens] * batch)
+        assert dealt and workers == most
+    assert len({w for w, *_ in _check_pieces(desc, [ctx // 4 + n] * batch)[0].tolist()}) > most * 3 // 4
 
 
 def _check_pieces(desc, tokens):
@@ -302,7 +320,9 @@ def _check_pieces(desc, tokens):
         assert not mine or mine[-1][1] == t
         assert [s for _, _, s in mine] == list(range(ranges[b, 0], ranges[b, 0] + ranges[b, 1]))
         assert len(mine) == ranges[b, 1]
-    bytes_per_slot = desc.n_kv_heads * (-(-desc.n_q_heads // desc.n_kv_heads * desc.n_draft // 16)) * (desc.head_dim * 16 * 2 + 192)
+    size = 4 if desc.qkv_dtype == B.OWL_F32 or desc.flags & B.OWL_FLAG_FP32_PARTIALS else 2
+    row_tiles = (desc.n_q_heads // desc.n_kv_heads * desc.n_draft + 15) // 16
+    bytes_per_slot = desc.n_kv_heads * row_tiles * (desc.head_dim * 16 * size + 192)
     assert n_slots * bytes_per_slot <= B.owl_verify_attn_workspace_size(desc)
     return pieces, dealt, workers
 

@@ -457,17 +457,18 @@ def test_batch_split_follows_the_lengths(oracle_mod, name, ctx, Hkv):
         assert_close(got3, want3, case.dtype, name + " (ragged counts)")
 
 
-@pytest.mark.parametrize("name,Hq,Hkv,D,ctx,n", [
-    ("more than one round of workers", 64, 64, 64, [200_000], 3),      # a share would outgrow the page list: 8 workers, not 4
-    ("fewer workers than compute units", 4, 1, 128, [19950], 4),
-    ("shares of one stage", 8, 2, 128, [0, 1, 63, 64, 65, 127], 4),
-    ("few partials per sequence", 8, 2, 64, [1500 + 37 * k for k in range(40)], 6),
-    ("many partials per sequence", 8, 2, 128, [9000, 1, 14000], 6),
-    ("equal splits, to fit the fixed scratch", 28, 4, 128, [3 + k % 40 for k in range(100)], 31),
+@pytest.mark.parametrize("name,Hq,Hkv,D,ctx,n,dealt", [
+    ("more than one round of workers", 64, 64, 64, [200_000], 3, True),    # a share would outgrow the page list: 8 workers, not 4
+    ("fewer workers than compute units", 4, 1, 128, [19950], 4, True),
+    ("shares of one stage", 8, 2, 128, [0, 1, 63, 64, 65, 127], 4, True),
+    ("few partials per sequence", 8, 2, 64, [1500 + 37 * k for k in range(40)], 6, True),
+    ("many partials per sequence", 8, 2, 128, [9000, 1, 14000], 6, True),
+    ("fewer workers, to fit the fixed scratch", 64, 8, 128, [2900, 40, 8000, 700], 48, True),
+    ("equal splits, to fit the fixed scratch", 28, 4, 128, [3 + k % 40 for k in range(100)], 31, False),
 ])
-def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n):
-    """A library-chosen split size: equal shares of the sequences laid end to end, cut at their ends.  The
-    longest case reads a small pool through a table that repeats its pages."""
+def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n, dealt):
+    """A library-chosen split size: equal shares of the sequences laid end to end, cut at their ends (or
+    equal splits, where the partials would not fit).  The longest case reads a small pool through a table that repeats its pages."""
     import dataclasses
     r = _rng(sum(ctx) + n)
     trees = [W.random_tree(n, 3, r) for _ in ctx]
@@ -476,8 +477,10 @@ def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n):
         cols = (max(ctx) + n + 15) // 16
         table = case.page_table[:, np.arange(cols) % (20000 // 16)]            # full pages only
         case = dataclasses.replace(case, ctx_lens=np.array(ctx, np.int32), page_table=table, max_pages_per_seq=cols)
-    got, step = _run(case)
-    if max(ctx) > 20000:
+    # (fp32 partials where the fixed scratch of the entry point without a workspace is to be what limits the launch)
+    got, step = _run(case, flags=B.OWL_FLAG_FP32_PARTIALS if "scratch" in name else 0)
+    assert B.owl_probe_deal(step.desc, [L + n for L in ctx])[3] == dealt
+    if sum(ctx) * n * Hq > 2e7:
         rows = sample_rows(case, 40, seed=5, always=[(0, 0, 0), (0, n - 1, Hq - 1)])
         want = oracle_mod.verify_attn_case(case, rows=rows)
         got = np.stack([got[b, i, h] for b, i, h in rows])
