@@ -375,9 +375,11 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     };
     // Every worker of a head reads the same rows, so they stay in the caches, except where one worker takes the whole
     // sequence (non-temporal against cached, us: 24 rows, 8 heads, 5K tokens 14.0 -> 13.2, 320 rows, 1 head, 10K 15.3 -> 14.3,
-    // 104 rows, 8 heads, 64K 55.0 -> 54.0; but 512 sequences of 125-500 tokens, 104 rows, 440 -> 448).
+    // 104 rows, 8 heads, 64K 55.0 -> 54.0; but 512 sequences of 125-500 tokens, 104 rows, 440 -> 448).  With three tiles a
+    // wavefront, whose registers are all taken, both the choice and the cached form cost more (320 rows, 64 sequences of
+    // 250-1000 tokens: 125.5 us, 131.4 with the choice, 128.4 cached; one of 128K 170-173 in every form).
     auto issue_queries = [&]() {
-        const bool once = pos0 == 0 && pos1 == Ttot;
+        const bool once = TPW == 3 || (pos0 == 0 && pos1 == Ttot);
         if constexpr (!kF32) {
 #pragma unroll
             for (int t = 0; t < TPW; ++t) {
