@@ -201,19 +201,16 @@ hipError_t launch_combine(const KParams &p, int D, bool half_partials, hipStream
 }
 
 // ---------------------------------------------------------------------------
-// Tree mask: one wavefront per sequence, lane i walks node i's root path.
+// Tree mask: one wavefront per sequence, lane i = node i.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) tree_mask_kernel(const int32_t *parent, int N, uint64_t *anc,
                                                        int32_t *depth, uint32_t *status)
 {
-    __shared__ int32_t s_parent[64];
     const int b = blockIdx.x, i = threadIdx.x;
-    if (i < N) s_parent[i] = parent[(int64_t)b * N + i];
-    __syncthreads();
+    const uint64_t set = ancestor_sets(parent[(int64_t)b * N + min(i, N - 1)], i, N, status);
     if (i < N) {
-        int d;
-        anc[(int64_t)b * N + i] = ancestor_set(s_parent, i, &d, status);
-        if (depth) depth[(int64_t)b * N + i] = d;
+        anc[(int64_t)b * N + i] = set;
+        if (depth) depth[(int64_t)b * N + i] = __popcll(set);
     }
 }
 

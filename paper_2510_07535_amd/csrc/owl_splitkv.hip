@@ -969,7 +969,10 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         issue_queries();
         for (issued = 1; issued < kQSlot0 && issued < nstages; ++issued) issue_stage(issued);
     }
-    if (has_drafts && tid < Nb) s_anc[tid] = ancestor_set(s_parent, tid, nullptr, p.dev_status);
+    if (has_drafts && wave == 0) {
+        const uint64_t set = ancestor_sets(s_parent[min(lane, p.N - 1)], lane, Nb, p.dev_status);
+        if (lane < Nb) s_anc[lane] = set;
+    }
     if constexpr (!kF32) {
         wait_stage(0);                                // the queries were requested before stage 1: they are in as well
         take_queries();

@@ -11,22 +11,18 @@ namespace owl {
 // ---------------------------------------------------------------------------
 // Prepare: one workgroup per sequence, thread i < 2n owns token i of the verify
 // input.  Tokens 0..n-1 are the tree nodes, token n+k is the extra token of node
-// k: its parent is k, so the ordinary root-path walk gives its mask and depth.
+// k: its parent is k, so it is one more node of the tree, with a mask and depth like any other.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) prepare_kernel(const int32_t *parent, const int32_t *ctx_lens, int n,
                                                      int32_t *parent2, uint64_t *anc, int32_t *depth,
                                                      int32_t *pos, uint32_t *status)
 {
-    __shared__ int32_t s_parent[64];
     const int b = blockIdx.x, i = threadIdx.x, n2 = 2 * n;
-    if (i < n) s_parent[i] = parent[(int64_t)b * n + i];
-    else if (i < n2) s_parent[i] = i - n;
-    __syncthreads();
+    int p = i < n ? parent[(int64_t)b * n + i] : i - n;
+    const uint64_t a = ancestor_sets(p, i, n2, status);
     if (i < n2) {
-        int d;
-        const uint64_t a = ancestor_set(s_parent, i, &d, status);
-        int p = s_parent[i];
-        if (p < -1 || p >= i) p = -1;                      // flagged by the walk; keep the output a valid tree
+        if (p < -1 || p >= i) p = -1;                      // flagged above; keep the output a valid tree
+        const int d = __popcll(a);
         const int64_t o = (int64_t)b * n2 + i;
         parent2[o] = p;
         anc[o] = a;

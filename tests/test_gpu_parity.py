@@ -240,6 +240,31 @@ def test_quad_max_lane_semantics():
 # ---------------------------------------------------------------------------
 # mask builder and paging: bit-exact
 # ---------------------------------------------------------------------------
+@pytest.mark.parametrize("n", [1, 2, 32, 33, 63, 64])
+def test_deep_and_malformed_trees(oracle_mod, n):
+    """The root paths as deep as they come (a chain of n), and parents that are no parents: such a node is a root, as in
+    the same tree with -1 in its place, and is flagged."""
+    chain, cut = W.chain_tree(n), W.chain_tree(n)
+    bad = chain.copy()
+    for i, p in ((n // 3, n // 3), (n // 2, -7), (n - 1, 64)):
+        bad[i], cut[i] = p, -1
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).cuda()
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for given, meant, flag in ((chain, chain, 0), (bad, cut, B.OWL_DEV_BAD_PARENT)):
+        want_anc, want_dep = oracle_mod.tree_mask(meant)
+        anc, dep = torch.zeros((1, n), dtype=torch.int64, device="cuda"), torch.zeros((1, n), dtype=torch.int32, device="cuda")
+        st.zero_()
+        B.owl_build_tree_mask(dev(given[None]), anc, dep, st)
+        assert np.array_equal(anc.cpu().numpy().view(np.uint64)[0], want_anc) and np.array_equal(dep.cpu().numpy()[0], want_dep)
+        assert int(st.item()) == flag
+        case = W.make_case("deep", 40 + n, dtype=W.DT_BF16, Hq=8, Hkv=2, D=128, ctx_lens=[150], trees=[meant])
+        step = VerifyStep(case)
+        step.tree_parent.copy_(dev(given[None]))
+        step.run()
+        assert_close(step.result(), oracle_mod.verify_attn_case(case), case.dtype, f"n={n}")
+        assert step.dev_status() == flag
+
+
 def test_tree_mask_bit_exact(oracle_mod):
     r = _rng(10)
     trees64 = [W.random_tree(64, md, r) for md in (None, 2, 8)] + [W.chain_tree(64), np.full(64, -1, np.int32)]
