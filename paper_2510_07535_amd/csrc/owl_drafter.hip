@@ -48,7 +48,7 @@ __device__ __forceinline__ d_f32x4 mfma16(d_i32x4 a, d_i32x4 b, d_f32x4 c)
 //
 // Two weight layouts.  OWL_W_ROWS is the matrix as it stands: a load instruction
 // then touches 16 rows with 64 bytes each and the chip holds ~50 000 row streams
-// open at once, which DRAM serves at 4.6-4.9 TB/s.  OWL_W_TILED stores the same
+// open at once, which DRAM serves at 4.4-4.9 TB/s.  OWL_W_TILED stores the same
 // numbers in the order the kernel consumes them,
 //     granule(row, k) = ((row / 64 * KS + k / 32) * 4 + row % 64 / 16) * 64 + (k % 32 / 8) * 16 + row % 16
 // in units of 16 bytes (8 elements), KS = d_in / 32, rows padded with zeros to a
@@ -75,12 +75,11 @@ __device__ __forceinline__ void each(F &&f)
 // fragments.  GR > 1 pays with more than 16 states (proj_wide).
 // k-steps (4 GR weight fragments and PT fragments of h each) that a wavefront keeps in flight: as many as leave room
 // for 4 - GR wavefronts per SIMD.
-// (The row layout has three more offsets to keep.)
-constexpr int proj_depth(int PT, bool tiled, int GR)
+constexpr int proj_depth(int PT, int GR)
 {
     if (GR == 3) return PT == 2 ? 5 : PT == 3 ? 4 : 3;
     if (GR == 2) return PT == 2 ? 3 : 2;
-    return PT == 1 ? 6 : PT == 2 ? 4 : PT == 3 && tiled ? 3 : 2;
+    return PT == 1 ? 6 : PT == 2 ? 4 : PT == 3 ? 3 : 2;
 }
 
 template <bool kF16, int PT, bool kTiled, int GR>
@@ -143,57 +142,95 @@ __global__ void __launch_bounds__(kProjWaves * 64, 4 - GR) drafter_proj_kernel(c
         return (i / kProjUnroll) * kRound + wave * kProjUnroll + i % kProjUnroll;
     };
 
-    // The stream: a ring of kDepth k-steps in registers.  A slot's loads are issued as soon as the MFMAs
-    // have read it and are waited for kDepth - 1 steps later; the scheduling fences keep them apart (left to itself the
-    // compiler moved every load next to its use and waited for one after the other: with 40 states it kept 7 of a
-    // wavefront's 28 loads in flight; d = 4096, d_in = 12288, 40 states: 116 -> 83 us).
-    constexpr int kDepth = proj_depth(PT, kTiled, GR);
-    d_i32x4 b[kDepth][kTiles], a[kDepth][PT];
-    auto load = [&](auto slot, int i) {
-        constexpr int S = decltype(slot)::value;
-        const int ks = k_step_of(i);
-        const char *hk = reinterpret_cast<const char *>(h + ks * 32);
-        // every weight is used once: a non-temporal load, which leaves the caches to h (re-read by
-        // every workgroup) and is worth 11 % on this chip (square step: 206 -> 183 us)
+    if constexpr (!kTiled) {
+        // A k-step is 64 bytes of a row here, half a memory line, and the weights are not kept in the caches: several k-steps
+        // at a time, asked for row by row, so that the two halves of a line are asked for one right after the other.
+        // (Through the ring below, one k-step after the other, lines were fetched twice; whole cell, us: d = d_in = 12288
+        // with 10 / 40 states 361 -> 271 / 398 -> 316, 8192 with 20 180 -> 124, 4096 with 1 52 -> 39; rings of pairs or
+        // fours gain nothing more.)
+        constexpr int kStep = PT <= 2 ? 4 : 2;
+        auto steps = [&](auto count, int i) {
+            constexpr int n_steps = decltype(count)::value;
+            d_i32x4 b[n_steps][kTiles], a[n_steps][PT];
+            int ks[n_steps];
 #pragma unroll
-        for (int q = 0; q < GR; ++q) {
-            const char *wk = reinterpret_cast<const char *>(w_base[q] + (int64_t)ks * w_step);
+            for (int u = 0; u < n_steps; ++u) ks[u] = k_step_of(i + u);
 #pragma unroll
-            for (int nb = 0; nb < kProjTiles; ++nb)
-                b[S][q * kProjTiles + nb] = __builtin_nontemporal_load(reinterpret_cast<const d_i32x4 *>(wk + w_off[nb]));
-        }
+            for (int nb = 0; nb < kTiles; ++nb)
 #pragma unroll
-        for (int pt = 0; pt < PT; ++pt) a[S][pt] = *reinterpret_cast<const d_i32x4 *>(hk + h_off[pt]);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto use = [&](auto slot) {
-        constexpr int S = decltype(slot)::value;
+                for (int u = 0; u < n_steps; ++u)
+                    b[u][nb] = __builtin_nontemporal_load(reinterpret_cast<const d_i32x4 *>(
+                        reinterpret_cast<const char *>(w_base[0] + (int64_t)ks[u] * w_step) + w_off[nb]));
 #pragma unroll
-        for (int pt = 0; pt < PT; ++pt)
+            for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-            for (int nb = 0; nb < kTiles; ++nb) acc[pt][nb] = mfma16<kF16>(a[S][pt], b[S][nb], acc[pt][nb]);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    int i = 0;                                               // k-steps requested so far
-    if (n_mine >= kDepth) {
-        each<kDepth>([&](auto slot) { load(slot, i++); });
-        for (; i + kDepth <= n_mine; i += kDepth)
+                for (int u = 0; u < n_steps; ++u)
+                    a[u][pt] = *reinterpret_cast<const d_i32x4 *>(reinterpret_cast<const char *>(h + ks[u] * 32) + h_off[pt]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < n_steps; ++u)
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                    for (int nb = 0; nb < kTiles; ++nb) acc[pt][nb] = mfma16<kF16>(a[u][pt], b[u][nb], acc[pt][nb]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        int i = 0;
+        for (; i + kStep <= n_mine; i += kStep) steps(std::integral_constant<int, kStep>{}, i);
+        for (; i < n_mine; ++i) steps(std::integral_constant<int, 1>{}, i);
+    } else {
+        // The stream: a ring of kDepth k-steps in registers.  A slot's loads are issued as soon as the MFMAs
+        // have read it and are waited for kDepth - 1 steps later; the scheduling fences keep them apart (left to itself the
+        // compiler moved every load next to its use and waited for one after the other: with 40 states it kept 7 of a
+        // wavefront's 28 loads in flight; d = 4096, d_in = 12288, 40 states: 116 -> 83 us).
+        constexpr int kDepth = proj_depth(PT, GR);
+        d_i32x4 b[kDepth][kTiles], a[kDepth][PT];
+        auto load = [&](auto slot, int i) {
+            constexpr int S = decltype(slot)::value;
+            const int ks = k_step_of(i);
+            const char *hk = reinterpret_cast<const char *>(h + ks * 32);
+            // every weight is used once: a non-temporal load, which leaves the caches to h (re-read by
+            // every workgroup) and is worth 11 % on this chip (square step: 206 -> 183 us)
+#pragma unroll
+            for (int q = 0; q < GR; ++q) {
+                const char *wk = reinterpret_cast<const char *>(w_base[q] + (int64_t)ks * w_step);
+#pragma unroll
+                for (int nb = 0; nb < kProjTiles; ++nb)
+                    b[S][q * kProjTiles + nb] = __builtin_nontemporal_load(reinterpret_cast<const d_i32x4 *>(wk + w_off[nb]));
+            }
+#pragma unroll
+            for (int pt = 0; pt < PT; ++pt) a[S][pt] = *reinterpret_cast<const d_i32x4 *>(hk + h_off[pt]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto use = [&](auto slot) {
+            constexpr int S = decltype(slot)::value;
+#pragma unroll
+            for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                for (int nb = 0; nb < kTiles; ++nb) acc[pt][nb] = mfma16<kF16>(a[S][pt], b[S][nb], acc[pt][nb]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        int i = 0;                                               // k-steps requested so far
+        if (n_mine >= kDepth) {
+            each<kDepth>([&](auto slot) { load(slot, i++); });
+            for (; i + kDepth <= n_mine; i += kDepth)
+                each<kDepth>([&](auto slot) {
+                    use(slot);
+                    load(slot, i + decltype(slot)::value);
+                });
+            const int rest = n_mine - i;                         // fewer than kDepth
             each<kDepth>([&](auto slot) {
                 use(slot);
-                load(slot, i + decltype(slot)::value);
+                if (decltype(slot)::value < rest) load(slot, i + decltype(slot)::value);
             });
-        const int rest = n_mine - i;                         // fewer than kDepth
-        each<kDepth>([&](auto slot) {
-            use(slot);
-            if (decltype(slot)::value < rest) load(slot, i + decltype(slot)::value);
-        });
-        each<kDepth - 1>([&](auto slot) {
-            if (decltype(slot)::value < rest) use(slot);
-        });
-    } else {
-        for (; i < n_mine; ++i) {
-            load(std::integral_constant<int, 0>{}, i);
-            use(std::integral_constant<int, 0>{});
+            each<kDepth - 1>([&](auto slot) {
+                if (decltype(slot)::value < rest) use(slot);
+            });
+        } else {
+            for (; i < n_mine; ++i) {
+                load(std::integral_constant<int, 0>{}, i);
+                use(std::integral_constant<int, 0>{});
+            }
         }
     }
 

@@ -66,6 +66,7 @@ def test_cell_matches_oracle(dtype, d_in, d, P, M):
 def test_projection_ring_and_shared_states(d_in, d, P):
     case = W.make_drafter_case("t", 300 + P, d_in=d_in, d=d, P=P, M=P, vocab=50)
     _check(case, 1.0)
+    _check(case, 1.0, tiled=False)                       # slots of two or four k-steps, and what does not fill one
 
 
 @pytest.mark.parametrize("d", [16, 1024, 1040, 4096, 4112, 8192, 8208, 12288, 12304, 16384])
