@@ -298,7 +298,7 @@ def evidence(rot, case):
     cyc, clk, us, span, phases = [], [], [], [], []
     for i in range(n):
         t = bufs[i].cpu().numpy().reshape(nwg, 10)
-        t = t[t[:, 0] > 0]
+        t = t[t[:, 5] > 0]                                # workgroups that had work
         if len(t) == 0:
             continue
         rel = (t[:, :6] - t[:, 0].min()) * 0.01

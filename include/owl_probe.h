@@ -120,12 +120,15 @@ owl_status owl_probe_deal(const owl_verify_desc *desc, const int32_t *tokens, in
  * 10 * n_workgroups int64, later owl_verify_attn calls whose split-KV grid has
  * at most n_workgroups workgroups (owl_plan.n_workgroups) and whose shape has a
  * profiling copy of the kernel (bf16, head_dim 128) run that copy; every
- * workgroup records the GPU's constant-rate (100 MHz) wall clock at: [0] entry,
- * [1] page list and tree mask ready, [2] first stage in LDS, [3] end of the fast
+ * workgroup with work records the GPU's constant-rate (100 MHz) wall clock at: [0] entry,
+ * [1] page list ready, [2] first stage in LDS, [3] end of the fast
  * loop, [4] end of the careful loop, [5] partials written; [6] = (XCC id << 16) |
  * CU id, [7] = its flat workgroup index; [8], [9] = the shader cycle counter at
  * [2] and [3], so that ([9] - [8]) / ([3] - [2]) / 10 is the shader clock in GHz
- * the workgroup really ran its main loop at.  Calls that do not qualify (larger
+ * the workgroup really ran its main loop at.  A workgroup whose share has several
+ * pieces records them as if they had run phase by phase: [1] - [0] is the time it
+ * spent on setting up all of them, [2] - [1] on their first stages, and so on.  One
+ * without work leaves [5] at 0.  Calls that do not qualify (larger
  * grid, other type) run the ordinary kernel and record nothing.  buffer = NULL
  * switches recording off (the default); the ordinary kernels contain no trace of
  * the hook.  One switch per process; set it from the measuring thread.

@@ -1126,24 +1126,30 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
 
     // timeline of this workgroup (profiling instantiations only; the production kernels
     // carry neither the pointer nor a branch)
-    long long *tl = nullptr;
+    long long *tl = nullptr, last = 0, loop_clock = 0;
     if constexpr (TL) {
         const long long flat = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
         tl = p.timeline + 10 * flat;
         if (tid == 0) {
-            tl[0] = wall_clock64();
+            last = wall_clock64();
+            tl[0] = last;
             tl[1] = tl[2] = tl[3] = tl[4] = tl[5] = tl[8] = tl[9] = 0;
             // XCC_ID register (bits 3:0) above the shader-engine / CU id: one value per compute unit
             tl[6] = ((long long)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15) << 16) | __smid();
             tl[7] = flat;
         }
     }
-    auto stamp = [&](int k) {                        // with several pieces: the last one's
+    // tl[k] sums, over the pieces of the share, the time from the stamp before to stamp k, tl[9] the shader cycles of the
+    // fast loops (their rate is the clock the chip really ran at); the last lines of the kernel turn them into points in time.
+    auto add = [&](int k, long long v) { atomicAdd(reinterpret_cast<unsigned long long *>(tl + k), (unsigned long long)v); };
+    auto stamp = [&](int k) {
         if constexpr (TL) {
             if (tid == 0) {
-                tl[k] = wall_clock64();
-                if (k == 2) tl[8] = clock64();        // shader cycles at both ends of the fast loop:
-                if (k == 3) tl[9] = clock64();        // their rate is the clock the chip really ran at
+                const long long now = wall_clock64();
+                add(k, now - last);
+                last = now;
+                if (k == 2) loop_clock = clock64();
+                if (k == 3) add(9, clock64() - loop_clock);
             }
         }
     };
@@ -1194,6 +1200,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
             const Piece pc{b, L, Nb, s0 * kSplitQuantum, min(s1 * kSplitQuantum, T_b),
                            (head_slots + slot0 + b) * p.RT};
             run_piece<T, D, TPW, WR, WK>(p, smem, g, rg, pc, guess, stamp);
+            stamp(5);
             guess.pos0 = -1;
         }
         before += seq_units(p, T_b);
@@ -1203,6 +1210,15 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     if constexpr (TL) {
         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the partial stores have left
         stamp(5);
+        if (tid == 0) {
+            long long at = tl[0];
+            for (int k = 1; k <= 5; ++k) {
+                at += (long long)atomicAdd(reinterpret_cast<unsigned long long *>(tl + k), 0ull);     // read where it was added
+                tl[k] = at;
+            }
+            tl[8] = loop_clock;
+            add(9, loop_clock);
+        }
     }
 }
 

@@ -354,6 +354,27 @@ def test_measurement_aids():
     assert sorted(ran[:, 7]) == sorted(set(ran[:, 7]))
     assert (ran[:, 9] >= ran[:, 8]).all() and (ran[:, 8] > 0).all()   # shader cycles at both ends of the fast loop
 
+    # a workgroup whose share has two pieces: its phases are summed over them, set-up does not swallow the first piece's loop
+    two = W.make_case("tl2", 80, dtype=W.DT_BF16, Hq=64, Hkv=64, D=128, ctx_lens=[2200, 2500], trees=[W.chain_tree(6)] * 2)
+    step2 = VerifyStep(two)
+    pieces, _, _, dealt, _ = B.owl_probe_deal(step2.desc, [2206, 2506])
+    crossing = [w for w in set(pieces[:, 0].tolist()) if (pieces[:, 0] == w).sum() == 2]
+    step2.run()
+    tl = torch.zeros(10 * step2.plan.n_workgroups, dtype=torch.int64, device="cuda")
+    B.owl_debug_set_timeline(tl)
+    try:
+        step2.run()
+        step2.result()
+    finally:
+        B.owl_debug_set_timeline(None)
+    t = tl.cpu().numpy().reshape(-1, 10)
+    t = t[t[:, 5] > 0]
+    of_two = np.isin(t[:, 7] // 64, crossing)                         # KV heads vary fastest, one row group
+    assert dealt and step2.plan.row_groups == 1 and len(crossing) == 1 and of_two.sum() == 64
+    assert (np.diff(t[:, :6], axis=1) >= 0).all() and (t[:, 9] > t[:, 8]).all()
+    setup = np.diff(t[:, :2], axis=1)[:, 0] / (t[:, 5] - t[:, 0])
+    assert np.median(setup[of_two]) < 0.45, (np.median(setup[of_two]), np.median(setup[~of_two]))
+
     # the split-KV launch with events attached to its dispatch: same result, a plausible duration
     timer = B.KernelTimer()
     step.out.fill_(float("nan"))
