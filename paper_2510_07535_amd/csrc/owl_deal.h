@@ -95,9 +95,9 @@ __host__ __device__ inline Deal deal_units(const DealRule &p, int units)
 {
     int n = min(most_workers(p, units), p.max_workers);
     if (p.merge > 0 && units > n) {                  // no more than the longest share makes necessary: the rest only adds
-                                                     // partials (4 heads, 4 rows, 5K: 64 -> 40 workers, 13.0 -> 12.4 us)
-        const int longest = quotient(units + n - 1, n);
-        n = quotient(units + longest - 1, longest);
+        const int longest = quotient(units + n - 1, n);      // partials (4 heads, 4 rows, 5K: 64 -> 40 workers, 13.0 -> 12.4 us);
+        const int enough = quotient(units + longest - 1, longest);
+        if (16 * (n - enough) > n) n = enough;       // one or two fewer are not worth other shares (8 heads, 32K: 32 and 31 alike)
     }
     const int q = quotient(units, n);
     return Deal{n, q, units - q * n};
