@@ -179,7 +179,7 @@ __device__ __forceinline__ uint64_t ancestor_sets(int parent, int i, int n, uint
     int up = i < n ? parent : -1;
     uint64_t set = (uint64_t)1 << i;
 #pragma unroll 1                                     // (unrolled, it costs the fp32 kernel registers and 5 % of its time)
-    for (int round = 0; round < 6; ++round) {
+    for (int round = 0; round < 6 && __ballot(up >= 0); ++round) {       // (short paths need fewer)
         const int from = up < 0 ? i : up;
         const uint32_t lo = __shfl((uint32_t)set, from), hi = __shfl((uint32_t)(set >> 32), from);
         const int next = __shfl(up, from);
