@@ -40,9 +40,9 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     constexpr int NUG = NT / UPW;
     static_assert(!BY_CHANNEL || WAVES == NUG, "one wavefront per pair of channel tiles");
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tg = BY_CHANNEL ? blockIdx.x : blockIdx.x / NUG;
-    const int u0 = (BY_CHANNEL ? w : (int)(blockIdx.x % NUG)) * UPW;
-    const int g = blockIdx.y, b = blockIdx.z;
+    const int tg = BY_CHANNEL ? blockIdx.y : blockIdx.y / NUG;
+    const int u0 = (BY_CHANNEL ? w : (int)(blockIdx.y % NUG)) * UPW;
+    const int g = blockIdx.x, b = blockIdx.z;
     const int j = lane & 15, qd = lane >> 4;
     constexpr int kStride = BY_CHANNEL ? 1 : WAVES;  // this wavefront's partials: first, first + kStride, ...
     const int first = BY_CHANNEL ? 0 : w;
@@ -184,10 +184,10 @@ static void launch_combine_d(const KParams &p, bool half_partials, hipStream_t s
     // Partials per sequence on average, if all sequences are alike.
     const int per_seq = p.dealt ? (p.rule.max_workers + p.B - 1) / p.B : p.max_splits;
     if (p.B > 1 && per_seq <= 8) {
-        launch_combine_as<D, D / 32, true>(p, half_partials, dim3(p.RT, p.Hkv, p.B), s);
+        launch_combine_as<D, D / 32, true>(p, half_partials, dim3(p.Hkv, p.RT, p.B), s);
         return;
     }
-    const dim3 grid(p.RT * (D / 32), p.Hkv, p.B);
+    const dim3 grid(p.Hkv, p.RT * (D / 32), p.B);
     // a wavefront merges its splits as a chain, 8 loads in flight: beyond 32 splits more wavefronts share them
     if (per_seq > 32) launch_combine_as<D, 8, false>(p, half_partials, grid, s);
     else launch_combine_as<D, 4, false>(p, half_partials, grid, s);
