@@ -39,6 +39,7 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     constexpr int NT = D / 16, UPW = 2;              // channel tiles per wavefront
     constexpr int NUG = NT / UPW;
     static_assert(!BY_CHANNEL || WAVES == NUG, "one wavefront per pair of channel tiles");
+    fetch_args<KParams>();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tg = BY_CHANNEL ? blockIdx.y : blockIdx.y / NUG;
     const int u0 = (BY_CHANNEL ? w : (int)(blockIdx.y % NUG)) * UPW;

@@ -33,6 +33,20 @@ __device__ __forceinline__ void store_out4(void *out, int64_t e, float4 v, int o
     *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + e) = w;
 }
 
+// Asks for every line of the launch's arguments at once and waits for them.  They are cold in each launch, and left to
+// itself the compiler loads them in several rounds, close to their uses, each a memory round trip of its own
+// (set-up of a split-KV workgroup 1.12 -> 0.98 us).
+template <typename Args>
+__device__ __forceinline__ void fetch_args()
+{
+    typedef const __attribute__((address_space(4))) int32_t *Line;
+    const Line at = (Line)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int n = (sizeof(Args) + 63) / 64;
+    static_assert(n <= 4, "four lines of arguments");
+    const int32_t a = at[0], b = at[n > 1 ? 16 : 0], c = at[n > 2 ? 32 : 0], d = at[n > 3 ? 48 : 0];
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+}
+
 // Reads through the scalar cache; for arrays no kernel of the launch writes, uniform index.
 __device__ __forceinline__ int load_uniform(const int32_t *a, int i)
 {

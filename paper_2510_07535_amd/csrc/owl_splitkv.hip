@@ -167,7 +167,8 @@ struct Geo {
     static constexpr int QREGS = kF32 ? D / 4 : D / 32; // Q fragment slots per tile
     static constexpr int KSWZ = (PPR - 1) & 15;         // K rows: piece ^= key & KSWZ
     static constexpr int VSWM = PPR >= 16 ? 7 : PPR / 2 - 1;   // V rows: piece ^= (key & VSWM) << 1
-    static constexpr size_t LDS = (size_t)NS * 2 * STAGE + kMaxPiecePages * 4 + 64 * 8 + 64 * 4;
+    static constexpr size_t PAGES = (size_t)NS * 2 * STAGE;           // page list, behind the ring
+    static constexpr size_t LDS = PAGES + kMaxPiecePages * 4 + 64 * 8 + 64 * 4 + 2 * kWaves * 4;
     static_assert(WR * WK == kWaves && (WK == 1 || WK == 2), "eight wavefronts per workgroup");
     static_assert(NS * LPS < 64, "loads in flight must fit vmcnt");
     static_assert((WK - 1) * WR * TPW * (4 * (NT + 1) + 1) * 256 <= NS * 2 * STAGE,
@@ -181,23 +182,46 @@ struct Piece {
     size_t slot;                                     // where the partials of row tile 0 go
 };
 
-// Page-table entries requested for a window that begins at pos0, before the context length that
-// decides about the window was known (pos0 < 0: none).
+// This lane's number in its wavefront, formed anew: not to be kept across the pieces of a share, where the loops leave no
+// register for it.  (In the three-tile kernel what was kept went to scratch memory, and every reload between the requests
+// of the first stages waited for all of them: 128K hybrid, 320 rows, 171.2 -> 168 us.)
+__device__ __forceinline__ int fresh_lane()
+{
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
+// A page list in LDS that was brought before the length which decides about the window was known: `n` pages from token pos0
+// on (pos0 < 0: none), as far as this wavefront's own entries go all of them pages of the pool.
 struct PageGuess {
-    int pos0;
-    int page[2];
+    int pos0, n;
 };
 
-__device__ __forceinline__ PageGuess guess_pages(const KParams &p, int b, int pos0)
+// Page-table entries first + tid and first + kThreads + tid of the window of sequence b that begins at pos0: f(entry, page)
+// (no branch: an entry past the table re-reads its last one and is not used).
+template <typename F>
+__device__ __forceinline__ void for_pages(const KParams &p, int tid, int b, int pos0, int first, F &&f)
 {
-    PageGuess gs;
-    gs.pos0 = pos0;
+    int pg[2];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {                    // no branch: an entry past the window is simply not used
-        const int lp = pos0 / kPage + (int)threadIdx.x + r * kThreads;
-        gs.page[r] = p.page_table ? p.page_table[(int64_t)b * p.max_pages + min(lp, p.max_pages - 1)] : lp;
+    for (int r = 0; r < 2; ++r) {
+        const int lp = pos0 / kPage + first + tid + r * kThreads;
+        pg[r] = p.page_table ? p.page_table[(int64_t)b * p.max_pages + min(lp, p.max_pages - 1)] : lp;
     }
-    return gs;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) f(first + tid + r * kThreads, pg[r]);
+}
+
+__device__ __forceinline__ PageGuess guess_pages(const KParams &p, int32_t *s_pages, int tid, int b, int pos0, int tokens)
+{
+    const int n = min((min(tokens, p.max_ctx_len + p.N - pos0) + kPage - 1) / kPage, 2 * kThreads);
+    bool bad = false;
+    for_pages(p, tid, b, pos0, 0, [&](int idx, int pg) {
+        bad |= idx < n && (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages));
+        s_pages[idx] = pg;
+    });
+    return PageGuess{__builtin_amdgcn_ballot_w64(bad) ? -1 : pos0, n};
 }
 
 // The kernel's arguments for one piece.  In fp16, whose second (guarded) loop takes more scalar registers, they are read
@@ -217,8 +241,20 @@ __device__ __forceinline__ const KParams &piece_args(const KParams &launch_args)
     }
 }
 
+// Whether `v` holds in any thread of the workgroup; `words`: kWaves words of LDS that nothing else uses for the piece.
+__device__ __forceinline__ bool workgroup_any(bool v, int wave, int lane, int32_t *words)
+{
+    const int any = __builtin_amdgcn_ballot_w64(v) != 0;
+    if (lane == 0) words[wave] = any;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) all |= words[w];
+    return __builtin_amdgcn_readfirstlane(all) != 0;
+}
+
 template <typename T, int D, int TPW, int WR, int WK, typename Stamp>
-__device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned char *smem, int g, int rg, const Piece &pc,
+__device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned char *smem, int wave, int g, int rg, const Piece &pc,
                                           const PageGuess &guess, Stamp &&stamp)
 {
     using GEO = Geo<T, D, TPW, WR, WK>;
@@ -229,19 +265,18 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     constexpr int KSWZ = GEO::KSWZ, VSWM = GEO::VSWM, VREG = GEO::VREG;
     constexpr int KQ = kF32 ? 1 : QREGS;             // K/Q fragment slots of the 16-bit paths
 
-    int32_t *s_pages = reinterpret_cast<int32_t *>(smem + NS * 2 * STAGE);
+    int32_t *s_pages = reinterpret_cast<int32_t *>(smem + GEO::PAGES);
     uint64_t *s_anc = reinterpret_cast<uint64_t *>(s_pages + kMaxPiecePages);
     int32_t *s_parent = reinterpret_cast<int32_t *>(s_anc + 64);
+    int32_t *s_any = s_parent + 64;
     const uint32_t lds0 =
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
 
     // What follows from the thread's number and the KV head is derived once per piece: kept across the
     // pieces of a share (as the compiler would by itself) it does not fit the registers of the loops.
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
     const KParams &p = piece_args<T>(launch_args);
-    asm volatile("" : "+s"(g), "+s"(rg));
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    asm volatile("" : "+s"(g), "+s"(rg), "+s"(wave));
+    const int lane = fresh_lane(), tid = wave * 64 + lane;
     const int wr = wave % WR, wk = wave / WR;
     const int j = lane & 15, qd = lane >> 4;
 
@@ -251,14 +286,14 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
 
     // ---- set-up: page list, parents and query rows are requested together, one memory round trip ----
     const int npg = (pos1 - pos0 + kPage - 1) / kPage;
-    PageGuess pages = guess;
-    if (guess.pos0 != pos0) pages = guess_pages(p, b, pos0);
     int parent = 0;
     if (has_drafts) parent = p.parent[(int64_t)b * p.N + min(tid, p.N - 1)];
     // ---- this wave's query rows: tiles wr, wr + WR, ... of the row group ----
     // Row `row` belongs to node row / G; the quotient is exact: rows stay below 2^12, where the error of
     // the product is far below the half that is added.
-    const float inv_g = __builtin_amdgcn_rcpf((float)p.G);
+    int heads = p.G;
+    asm volatile("" : "+s"(heads));
+    const float inv_g = __builtin_amdgcn_rcpf((float)heads);
     auto node_of = [&](int row) -> int { return (int)(((float)row + 0.5f) * inv_g); };
     const unsigned char *q_head = static_cast<const unsigned char *>(p.q) + ((int64_t)b * p.N * p.Hq + (int64_t)g * p.G) * D * ES;
     auto row_offset = [&](int row) -> int64_t { return ((int64_t)node_of(row) * (p.Hq - p.G) + row) * ROWB; };
@@ -283,20 +318,16 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         }
     }
 
-    auto keep_page = [&](int idx, int pg) {
-        if (idx >= npg) return;
-        if (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages)) {
-            flag_status(p.dev_status, OWL_DEV_BAD_PAGE);
-            pg = 0;
-        }
-        s_pages[idx] = pg;
-    };
-#pragma unroll
-    for (int r = 0; r < 2; ++r) keep_page(tid + r * kThreads, pages.page[r]);
-    for (int first = 2 * kThreads; first < npg; first += 2 * kThreads) {       // more than 16K tokens in one piece
-        const PageGuess more = guess_pages(p, b, pos0 + first * kPage);
-#pragma unroll
-        for (int r = 0; r < 2; ++r) keep_page(first + tid + r * kThreads, more.page[r]);
+    if (guess.pos0 != pos0 || npg > guess.n) {       // uniform over the wavefront
+        for (int first = 0; first < npg; first += 2 * kThreads)                 // (up to 16K tokens: once)
+            for_pages(p, tid, b, pos0, first, [&](int idx, int pg) {
+                if (idx >= npg) return;
+                if (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages)) {
+                    flag_status(p.dev_status, OWL_DEV_BAD_PAGE);
+                    pg = 0;
+                }
+                s_pages[idx] = pg;
+            });
     }
     if (has_drafts && tid < p.N) s_parent[tid] = parent;
     __syncthreads();
@@ -635,7 +666,11 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // ---- reference m of every row tile from one unmasked step (before the fast loop) ----
     auto init_reference = [&](int buf, int ks, f32x4 (&keep)[TPW][2]) {
         if constexpr (!kF32) {
-            const unsigned char *Kb = smem + buf * STAGE + ks * 32 * ROWB;
+            // (Formed here: as an address that the compiler kept from before the stages were requested, it came back from
+            // scratch memory in the three-tile kernel, and the wait for it drained the whole ring before the first step.)
+            int off = buf * STAGE + ks * 32 * ROWB;
+            asm volatile("" : "+s"(off));
+            const unsigned char *Kb = smem + off;
             uint4 kf[2][KQ];
             load_k_frags(Kb, kf);
 #pragma unroll
@@ -927,7 +962,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             bool wide = false;
 #pragma unroll
             for (int t = 0; t < TPW; ++t) wide |= (hi[t] - lo[t]) * p.c_log2 > 14.0f;
-            use_guard = __syncthreads_or(wide ? 1 : 0) != 0;
+            use_guard = workgroup_any(wide, wave, lane, s_any);
         }
     };
     // the fast loop is compiled once per possible tile count of a wave, so that
@@ -1000,7 +1035,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         bool bad = false;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) bad |= !(O[t][NT][0] < 1.0e30f);
-        if (!__syncthreads_or(bad ? 1 : 0)) break;
+        if (!workgroup_any(bad, wave, lane, s_any + kWaves)) break;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
             m[t] = kMInit;
@@ -1098,8 +1133,10 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
 template <typename T, int D, int TPW, int WR, int WK, bool TL>
 __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
 {
+    using GEO = Geo<T, D, TPW, WR, WK>;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x;
+    fetch_args<KParams>();
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // Workgroups go to the chip's eight XCDs round-robin in launch order, whether or not
     // they have work.  KV heads (all with the same amount of work) vary fastest, so that
@@ -1157,7 +1194,8 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     // The share: units [x, x1), the first of them in sequence b, which begins at unit `before`; the
     // partials of its piece in sequence b go to slot `slot0 + b`.
     int b = 0, before = 0, x, x1, slot0;
-    PageGuess guess;
+    PageGuess guess{-1, 0};
+    int32_t *const s_pages = reinterpret_cast<int32_t *>(smem + GEO::PAGES);
     if (!p.dealt) {                                   // equal splits of C tokens, of one sequence each
         const int c = (int)(item % gridDim.y);
         b = (int)(item / gridDim.y);
@@ -1165,7 +1203,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         x = c * (p.C / kSplitQuantum);
         x1 = x + p.C / kSplitQuantum;
         slot0 = b * p.max_splits + c - b;
-        guess = guess_pages(p, b, x * kSplitQuantum);
+        guess = guess_pages(p, s_pages, tid, b, x * kSplitQuantum, p.C);
     } else {
         const int worker = (int)item;
         if (worker >= p.rule.max_workers) return;          // padding of the grid
@@ -1173,9 +1211,10 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         if (p.B == 1) {
             // most lone sequences are as long as announced: their pages are asked for along with the length
             deal = Deal{p.full.workers, p.full.q, p.full.r};
-            guess = guess_pages(p, 0, deal_begin(deal, min(worker, deal.workers)) * kSplitQuantum);
-            const int N1 = load_n_draft(p.n_draft_seq, 0, p.N, nullptr);
-            const int T1 = N1 == 0 ? 0 : load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, nullptr) + N1;
+            const int N1 = load_n_draft(p.n_draft_seq, 0, p.N, nullptr), L1 = load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, nullptr);
+            const int guessed = min(worker, deal.workers - 1);
+            guess = guess_pages(p, s_pages, tid, 0, deal_begin(deal, guessed) * kSplitQuantum, (deal.q + 1) * kSplitQuantum);
+            const int T1 = N1 == 0 ? 0 : L1 + N1;
             if (T1 != p.max_ctx_len + p.N) deal = deal_units(p, max(seq_units(p, T1), 1));
         } else {
             const BatchUnits u = batch_units(p);
@@ -1199,7 +1238,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
             again = true;
             const Piece pc{b, L, Nb, s0 * kSplitQuantum, min(s1 * kSplitQuantum, T_b),
                            (head_slots + slot0 + b) * p.RT};
-            run_piece<T, D, TPW, WR, WK>(p, smem, g, rg, pc, guess, stamp);
+            run_piece<T, D, TPW, WR, WK>(p, smem, wave, g, rg, pc, guess, stamp);
             stamp(5);
             guess.pos0 = -1;
         }
