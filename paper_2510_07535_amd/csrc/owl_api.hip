@@ -104,7 +104,15 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
         rgs = (RT + caps[li] - 1) / caps[li];
         group_tiles = (RT + rgs - 1) / rgs;
         rgs = (RT + group_tiles - 1) / group_tiles;
+        // Seven or eight tiles: eight wavefronts with one each, or four pairs with two each, a pair splitting the steps of a
+        // stage.  That halves the fragments read from LDS, and with them the power that limits the loop, but a workgroup then
+        // has a merge of its own and no pipelined loop: it pays on long shares, the sooner the fuller the pairs are.  us, one
+        // tile -> two: 128 rows, shares of 33 / 64 / 125 / 300 / 512 stages 54.4 -> 55.2 / 97.0 -> 93.8 / 129.4 -> 126.2 / 301.9
+        // -> 287.2 / 498.5 -> 470.0; 104 rows, 96 / 125 / 300 / 512 stages 122.9 -> 123.8 / 125.4 -> 125.3 / 285.5 -> 283.4 /
+        // 473.1 -> 453.9.  Five and six tiles gain nothing (80 rows, 512 stages 442 -> 441).
+        const int64_t share = (int64_t)d->batch * ((T + kSplitQuantum - 1) / kSplitQuantum) * d->n_kv_heads * rgs / device_cus();
         if (caps[li] == 4) { tpw = 1; wr = 4; wk = 2; }
+        else if (caps[li] == 8 && group_tiles >= 7 && share >= (group_tiles == 8 ? 64 : 256)) { tpw = 2; wr = 4; wk = 2; }
         else { wr = 8; wk = 1; tpw = (group_tiles + 7) / 8; }
     }
     const Variant *v = find_variant(d->qkv_dtype, d->head_dim, tpw, wr, wk);

@@ -167,11 +167,12 @@ struct Geo {
     static constexpr int QREGS = kF32 ? D / 4 : D / 32; // Q fragment slots per tile
     static constexpr int KSWZ = (PPR - 1) & 15;         // K rows: piece ^= key & KSWZ
     static constexpr int VSWM = PPR >= 16 ? 7 : PPR / 2 - 1;   // V rows: piece ^= (key & VSWM) << 1
-    static constexpr size_t PAGES = (size_t)NS * 2 * STAGE;           // page list, behind the ring
-    static constexpr size_t LDS = PAGES + kMaxPiecePages * 4 + 64 * 8 + 64 * 4 + 2 * kWaves * 4;
+    static constexpr size_t PAGES = (size_t)NS * 2 * STAGE;           // behind the ring: page list, ancestor sets, parents, votes
+    static constexpr size_t ANC = PAGES + kMaxPiecePages * 4, PARENT = ANC + 64 * 8, ANY = PARENT + 64 * 4;
+    static constexpr size_t LDS = ANY + 2 * kWaves * 4;
     static_assert(WR * WK == kWaves && (WK == 1 || WK == 2), "eight wavefronts per workgroup");
     static_assert(NS * LPS < 64, "loads in flight must fit vmcnt");
-    static_assert((WK - 1) * WR * TPW * (4 * (NT + 1) + 1) * 256 <= NS * 2 * STAGE,
+    static_assert((WK - 1) * WR * TPW * (NT * 1024 + 512) <= NS * 2 * STAGE,
                   "cross-wave merge buffer must fit in the stage ring");
 };
 
@@ -192,37 +193,33 @@ __device__ __forceinline__ int fresh_lane()
     return lane;
 }
 
-// A page list in LDS that was brought before the length which decides about the window was known: `n` pages from token pos0
-// on (pos0 < 0: none), as far as this wavefront's own entries go all of them pages of the pool.
-struct PageGuess {
-    int pos0, n;
+// Page-table entries first + tid and first + kThreads + tid of the window of sequence b that begins at pos0 (no branch: an
+// entry past the table re-reads its last one and is not used).
+struct PagePair {
+    int page[2];
 };
 
-// Page-table entries first + tid and first + kThreads + tid of the window of sequence b that begins at pos0: f(entry, page)
-// (no branch: an entry past the table re-reads its last one and is not used).
-template <typename F>
-__device__ __forceinline__ void for_pages(const KParams &p, int tid, int b, int pos0, int first, F &&f)
+__device__ __forceinline__ PagePair load_pages(const KParams &p, int tid, int b, int pos0, int first)
 {
-    int pg[2];
+    PagePair pg;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int lp = pos0 / kPage + first + tid + r * kThreads;
-        pg[r] = p.page_table ? p.page_table[(int64_t)b * p.max_pages + min(lp, p.max_pages - 1)] : lp;
+        pg.page[r] = p.page_table ? p.page_table[(int64_t)b * p.max_pages + min(lp, p.max_pages - 1)] : lp;
     }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) f(first + tid + r * kThreads, pg[r]);
+    return pg;
 }
 
-__device__ __forceinline__ PageGuess guess_pages(const KParams &p, int32_t *s_pages, int tid, int b, int pos0, int tokens)
-{
-    const int n = min((min(tokens, p.max_ctx_len + p.N - pos0) + kPage - 1) / kPage, 2 * kThreads);
-    bool bad = false;
-    for_pages(p, tid, b, pos0, 0, [&](int idx, int pg) {
-        bad |= idx < n && (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages));
-        s_pages[idx] = pg;
-    });
-    return PageGuess{__builtin_amdgcn_ballot_w64(bad) ? -1 : pos0, n};
-}
+// What was asked for before the length that decides about the window was known: the parents of the sequence, and the first
+// entries of the page list from token pos0 on (pos0 < 0: none).  They wait in registers for the set-up of the piece, which
+// asks for the rest meanwhile; the three-tile kernel, which has none to spare across its loops, puts them in LDS at once
+// (`kept` entries, as far as this wavefront's own go all of them pages of the pool).
+struct Ahead {
+    int pos0, kept;
+    bool parents;
+    PagePair pages;
+    int parent;
+};
 
 // The kernel's arguments for one piece.  In fp16, whose second (guarded) loop takes more scalar registers, they are read
 // again from the kernel-argument segment: kept across the pieces they made 36-79 scalar registers spill (0-13 now) and
@@ -255,7 +252,7 @@ __device__ __forceinline__ bool workgroup_any(bool v, int wave, int lane, int32_
 
 template <typename T, int D, int TPW, int WR, int WK, typename Stamp>
 __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned char *smem, int wave, int g, int rg, const Piece &pc,
-                                          const PageGuess &guess, Stamp &&stamp)
+                                          const Ahead &ahead, Stamp &&stamp)
 {
     using GEO = Geo<T, D, TPW, WR, WK>;
     constexpr bool kF32 = GEO::kF32;
@@ -266,9 +263,9 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     constexpr int KQ = kF32 ? 1 : QREGS;             // K/Q fragment slots of the 16-bit paths
 
     int32_t *s_pages = reinterpret_cast<int32_t *>(smem + GEO::PAGES);
-    uint64_t *s_anc = reinterpret_cast<uint64_t *>(s_pages + kMaxPiecePages);
-    int32_t *s_parent = reinterpret_cast<int32_t *>(s_anc + 64);
-    int32_t *s_any = s_parent + 64;
+    uint64_t *s_anc = reinterpret_cast<uint64_t *>(smem + GEO::ANC);
+    int32_t *s_parent = reinterpret_cast<int32_t *>(smem + GEO::PARENT);
+    int32_t *s_any = reinterpret_cast<int32_t *>(smem + GEO::ANY);
     const uint32_t lds0 =
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
 
@@ -286,8 +283,13 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
 
     // ---- set-up: page list, parents and query rows are requested together, one memory round trip ----
     const int npg = (pos1 - pos0 + kPage - 1) / kPage;
-    int parent = 0;
-    if (has_drafts) parent = p.parent[(int64_t)b * p.N + min(tid, p.N - 1)];
+    constexpr bool kKeptEarly = TPW == 3;
+    const bool have = ahead.pos0 == pos0 && (!kKeptEarly || npg <= ahead.kept);      // uniform over the wavefront
+    PagePair pages{};
+    if (!have) pages = load_pages(p, tid, b, pos0, 0);
+    else if (!kKeptEarly) pages = ahead.pages;
+    int parent = kKeptEarly ? 0 : ahead.parent;
+    if (has_drafts && !ahead.parents) parent = p.parent[(int64_t)b * p.N + min(tid, p.N - 1)];
     // ---- this wave's query rows: tiles wr, wr + WR, ... of the row group ----
     // Row `row` belongs to node row / G; the quotient is exact: rows stay below 2^12, where the error of
     // the product is far below the half that is added.
@@ -318,18 +320,23 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         }
     }
 
-    if (guess.pos0 != pos0 || npg > guess.n) {       // uniform over the wavefront
-        for (int first = 0; first < npg; first += 2 * kThreads)                 // (up to 16K tokens: once)
-            for_pages(p, tid, b, pos0, first, [&](int idx, int pg) {
-                if (idx >= npg) return;
-                if (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages)) {
-                    flag_status(p.dev_status, OWL_DEV_BAD_PAGE);
-                    pg = 0;
-                }
-                s_pages[idx] = pg;
-            });
-    }
-    if (has_drafts && tid < p.N) s_parent[tid] = parent;
+    auto keep_pages = [&](const PagePair &from, int first) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int idx = first + tid + r * kThreads;
+            int pg = from.page[r];
+            if (idx >= npg) continue;
+            if (pg < 0 || pg >= p.n_pool_pages || (p.page_table && pos0 / kPage + idx >= p.max_pages)) {
+                flag_status(p.dev_status, OWL_DEV_BAD_PAGE);
+                pg = 0;
+            }
+            s_pages[idx] = pg;
+        }
+    };
+    if (!kKeptEarly || !have) keep_pages(pages, 0);
+    for (int first = 2 * kThreads; first < npg; first += 2 * kThreads)           // more than 16K tokens in one piece
+        keep_pages(load_pages(p, tid, b, pos0, first), first);
+    if (has_drafts && !(kKeptEarly && ahead.parents) && tid < p.N) s_parent[tid] = parent;
     __syncthreads();
     stamp(1);
 
@@ -998,20 +1005,37 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // an fp16 P overflows 12 above it (and the redo is then the price).  fp32 is
     // the small correctness shape and has no fast loop.
     constexpr bool kHasFast = !kF32;
+    // With one tile a wavefront the piece is bound by its K/V, and all that the ring holds is requested at once.  With more it
+    // is bound by the loop, which should begin early: when every workgroup asks for its whole ring at the same time, stage 0
+    // arrives in the middle of 33 MB (4 us), so the first stages go out one after the other, behind the queries (320 rows,
+    // 20K tokens 41.5 -> 40.6 us, 240 rows, 64K 79.7 -> 79.3).
+    constexpr bool kPaced = !kF32 && TPW >= 2;
     if constexpr (!kF32) {
-        // stage 0 (a piece is not empty), the queries, and the stages whose slots the queries leave free
-        issue_stage(0);
-        issue_queries();
-        for (issued = 1; issued < kQSlot0 && issued < nstages; ++issued) issue_stage(issued);
+        if constexpr (kPaced) {
+            issue_queries();
+            issue_stage(0);                           // (a piece is not empty)
+            issued = 1;
+        } else {
+            // stage 0, the queries, and the stages whose slots the queries leave free
+            issue_stage(0);
+            issue_queries();
+            for (issued = 1; issued < kQSlot0 && issued < nstages; ++issued) issue_stage(issued);
+        }
     }
     if (has_drafts && wave == 0) {
         const uint64_t set = ancestor_sets(s_parent[min(lane, p.N - 1)], lane, Nb, p.dev_status);
         if (lane < Nb) s_anc[lane] = set;
     }
     if constexpr (!kF32) {
-        wait_stage(0);                                // the queries were requested before stage 1: they are in as well
+        if constexpr (kPaced) wait_vmcnt<LPS>();
+        else wait_stage(0);                           // the queries were requested before stage 1: they are in as well
         take_queries();
         __syncthreads();                              // everyone has; their slots are free
+        if constexpr (kPaced) {
+            if (nstages > 1) issue_stage(issued++);
+            wait_stage(0);
+            __syncthreads();
+        }
     }
     for (int pass = 0; pass < 2; ++pass) {
         int n_fast = 0;
@@ -1044,39 +1068,39 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         }
     }
 
-    // ---- merge the key groups of a row group through LDS (reuses the ring) ----
-    if constexpr (WK > 1) {
+    // ---- merge the two key groups of a row group through LDS (reuses the ring), 16 bytes a lane ----
+    // With one tile a wavefront the second group hands its tile to the first.  With two, each hands one over and finishes
+    // the other, so that all eight wavefronts write partials.
+    constexpr int kGive = WK == 2 ? TPW : 0;
+    const int mine = kGive == 2 ? wk : 0;                             // the tile this wavefront finishes
+    if constexpr (WK == 2) {
+        static_assert(TPW <= 2, "a tile for each key group");
         __syncthreads();
-        float *mb = reinterpret_cast<float *>(smem);
-        constexpr int PER_TILE = 4 * (NT + 1) + 1;
-        if (wk > 0) {
+        constexpr int PER_TILE = NT * 64 * 16 + 64 * 8;
+        auto tile_of = [&](int w) -> unsigned char * { return smem + (w * WR + wr) * PER_TILE; };
+        if (kGive == 2 || wk == 1) {
+            unsigned char *dst = tile_of(kGive == 2 ? wk : 0);
 #pragma unroll
-            for (int t = 0; t < TPW; ++t) {
-                float *dst = mb + ((size_t)(((wk - 1) * WR + wr) * TPW + t) * PER_TILE) * 64 + lane;
-#pragma unroll
-                for (int u = 0; u <= NT; ++u)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) dst[(u * 4 + r) * 64] = O[t][u][r];
-                dst[4 * (NT + 1) * 64] = m[t];
-            }
+            for (int u = 0; u < NT; ++u)
+                reinterpret_cast<f32x4 *>(dst)[u * 64 + lane] = kGive == 2 && wk == 0 ? O[TPW - 1][u] : O[0][u];
+            reinterpret_cast<float2 *>(dst + NT * 1024)[lane] = kGive == 2 && wk == 0 ? make_float2(m[TPW - 1], O[TPW - 1][NT][0])
+                                                                                      : make_float2(m[0], O[0][NT][0]);
         }
         __syncthreads();
-        if (wk == 0) {
-            for (int w2 = 1; w2 < WK; ++w2) {
+        if (kGive == 2 || wk == 0) {
+            const unsigned char *src = tile_of(kGive == 2 ? 1 - wk : 0);
+            if (kGive == 2 && wk == 1) {                              // from here on the tile sits in the first place
+                m[0] = m[TPW - 1];
 #pragma unroll
-                for (int t = 0; t < TPW; ++t) {
-                    const float *src = mb + ((size_t)(((w2 - 1) * WR + wr) * TPW + t) * PER_TILE) * 64 + lane;
-                    const float m2 = src[4 * (NT + 1) * 64];
-                    const float mn = fmaxf(m[t], m2);
-                    const float a1 = fast_exp2(m[t] - mn), a2 = fast_exp2(m2 - mn);
-                    m[t] = mn;
-#pragma unroll
-                    for (int u = 0; u <= NT; ++u)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            O[t][u][r] = O[t][u][r] * a1 + src[(u * 4 + r) * 64] * a2;
-                }
+                for (int u = 0; u <= NT; ++u) O[0][u] = O[TPW - 1][u];
             }
+            const float2 ml = reinterpret_cast<const float2 *>(src + NT * 1024)[lane];
+            const float mn = fmaxf(m[0], ml.x);
+            const float a1 = fast_exp2(m[0] - mn), a2 = fast_exp2(ml.x - mn);
+            m[0] = mn;
+#pragma unroll
+            for (int u = 0; u < NT; ++u) O[0][u] = O[0][u] * a1 + reinterpret_cast<const f32x4 *>(src)[u * 64 + lane] * a2;
+            O[0][NT][0] = O[0][NT][0] * a1 + ml.y * a2;
         }
     }
 
@@ -1084,11 +1108,11 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // fp32 partials (fp32 inputs, or on request): the accumulator fragments as they are, float4 [slot][u][lane] =
     // channels 16*u + 4*quad .. +3 of row lane%16.  Otherwise: each row normalised by its row sum and by its largest magnitude s, as fp16,
     // uint4 [slot][u/2][lane] = the four halves of channel tile u (even) and of u + 1; (m, l, s) beside it.
-    if (wk == 0) {
+    if (wk == 0 || kGive == 2) {
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-            const int tg = rg * p.group_tiles + t * WR + wr;
-            if (t * WR + wr >= p.group_tiles || tg >= p.RT) continue;
+        for (int t = 0; t < (WK == 2 ? 1 : TPW); ++t) {
+            const int tile = (t + mine) * WR + wr, tg = rg * p.group_tiles + tile;
+            if (tile >= p.group_tiles || tg >= p.RT) continue;
             const size_t slot = pc.slot + tg;
             const float l = O[t][NT][0];
             if (kF32 || !p.half_partials) {                          // uniform over the launch
@@ -1194,8 +1218,9 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
     // The share: units [x, x1), the first of them in sequence b, which begins at unit `before`; the
     // partials of its piece in sequence b go to slot `slot0 + b`.
     int b = 0, before = 0, x, x1, slot0;
-    PageGuess guess{-1, 0};
-    int32_t *const s_pages = reinterpret_cast<int32_t *>(smem + GEO::PAGES);
+    Ahead ahead{-1, 0, false, {}, 0};
+    Deal deal = p.full;
+    int window = p.C;                                 // tokens of the window that is asked for ahead
     if (!p.dealt) {                                   // equal splits of C tokens, of one sequence each
         const int c = (int)(item % gridDim.y);
         b = (int)(item / gridDim.y);
@@ -1203,30 +1228,54 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         x = c * (p.C / kSplitQuantum);
         x1 = x + p.C / kSplitQuantum;
         slot0 = b * p.max_splits + c - b;
-        guess = guess_pages(p, s_pages, tid, b, x * kSplitQuantum, p.C);
     } else {
+        if ((int)item >= p.rule.max_workers) return;  // padding of the grid
+        x = deal_begin(deal, min((int)item, deal.workers - 1));
+        window = (deal.q + 1) * kSplitQuantum;
+    }
+    // Most lone sequences are as long as announced: their pages and parents are asked for along with the length.
+    PagePair pages{};
+    int parent = 0;
+    if (!p.dealt || p.B == 1) {
+        ahead.pos0 = x * kSplitQuantum;
+        ahead.parents = true;
+        pages = load_pages(p, tid, b, ahead.pos0, 0);
+        parent = p.parent[(int64_t)b * p.N + min(tid, p.N - 1)];
+    }
+    if (p.dealt) {
         const int worker = (int)item;
-        if (worker >= p.rule.max_workers) return;          // padding of the grid
-        Deal deal;
         if (p.B == 1) {
-            // most lone sequences are as long as announced: their pages are asked for along with the length
-            deal = Deal{p.full.workers, p.full.q, p.full.r};
-            const int N1 = load_n_draft(p.n_draft_seq, 0, p.N, nullptr), L1 = load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, nullptr);
-            const int guessed = min(worker, deal.workers - 1);
-            guess = guess_pages(p, s_pages, tid, 0, deal_begin(deal, guessed) * kSplitQuantum, (deal.q + 1) * kSplitQuantum);
-            const int T1 = N1 == 0 ? 0 : L1 + N1;
+            const int N1 = load_n_draft(p.n_draft_seq, 0, p.N, nullptr);
+            const int T1 = N1 == 0 ? 0 : load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, nullptr) + N1;
             if (T1 != p.max_ctx_len + p.N) deal = deal_units(p, max(seq_units(p, T1), 1));
         } else {
             const BatchUnits u = batch_units(p);
             if (u.total == 0) return;                 // not one sequence has drafts
             deal = deal_units(p, u.total);
             if (worker < deal.workers) find_unit(p, u, deal_begin(deal, worker), &b, &before);
-            guess.pos0 = -1;
         }
         if (worker >= deal.workers) return;
         x = deal_begin(deal, worker);
         x1 = deal_begin(deal, worker + 1);
         slot0 = worker;
+    }
+    if constexpr (TPW == 3) {
+        if (ahead.parents) {
+            int32_t *s_pages = reinterpret_cast<int32_t *>(smem + GEO::PAGES), *s_parent = reinterpret_cast<int32_t *>(smem + GEO::PARENT);
+            ahead.kept = min((min(window, p.max_ctx_len + p.N - ahead.pos0) + kPage - 1) / kPage, 2 * kThreads);
+            bool bad = false;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int idx = tid + r * kThreads, pg = pages.page[r];
+                bad |= idx < ahead.kept && (pg < 0 || pg >= p.n_pool_pages || (p.page_table && ahead.pos0 / kPage + idx >= p.max_pages));
+                s_pages[idx] = pg;
+            }
+            if (__builtin_amdgcn_ballot_w64(bad)) ahead.pos0 = -1;
+            if (tid < p.N) s_parent[tid] = parent;
+        }
+    } else {
+        ahead.pages = pages;
+        ahead.parent = parent;
     }
     for (bool again = false; b < p.B; ++b) {
         const int Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status);
@@ -1238,9 +1287,10 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
             again = true;
             const Piece pc{b, L, Nb, s0 * kSplitQuantum, min(s1 * kSplitQuantum, T_b),
                            (head_slots + slot0 + b) * p.RT};
-            run_piece<T, D, TPW, WR, WK>(p, smem, wave, g, rg, pc, guess, stamp);
+            run_piece<T, D, TPW, WR, WK>(p, smem, wave, g, rg, pc, ahead, stamp);
             stamp(5);
-            guess.pos0 = -1;
+            ahead.pos0 = -1;
+            ahead.parents = false;
         }
         before += seq_units(p, T_b);
         if (before >= x1 || !p.dealt) break;
@@ -1281,7 +1331,7 @@ static void launch_variant(const KParams &p, dim3 grid, hipStream_t s, hipEvent_
 
 #define OWL_VARIANTS_16BIT(DT, T, D, TL)                                                \
     OWL_VARIANT(DT, T, D, 1, 4, 2, TL), OWL_VARIANT(DT, T, D, 1, 8, 1, TL),             \
-    OWL_VARIANT(DT, T, D, 2, 8, 1, TL), OWL_VARIANT(DT, T, D, 3, 8, 1, TL)
+    OWL_VARIANT(DT, T, D, 2, 4, 2, TL), OWL_VARIANT(DT, T, D, 2, 8, 1, TL), OWL_VARIANT(DT, T, D, 3, 8, 1, TL)
 
 static const Variant kVariants[] = {
     OWL_VARIANTS_16BIT(OWL_BF16, __bf16, 128, false),
