@@ -78,21 +78,28 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     if (!late) load(s_first, first, limit);
     // (entries out of range are reported from here as well: every sequence has its workgroups in this grid, while the
     // split-KV pass of a batch never gets to one that is left without drafts)
-    const int Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status), L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status);
-    const int T_b = Nb == 0 ? 0 : L + Nb;
-    if (T_b > 0) {                                            // a sequence without drafts wrote no partials
-        if (!p.dealt) {
-            ns = min((T_b + p.C - 1) / p.C, p.max_splits);
-        } else if (p.B == 1) {
-            const Deal deal = T_b == p.max_ctx_len + p.N ? p.full : deal_units(p, seq_units(p, T_b));
-            ns = deal_worker(deal, stages_of(T_b) - 1) + 1;
-        } else {
-            const BatchUnits u = batch_units(p);
+    int Nb, L;
+    if (late) {
+        const BatchUnits u = batch_units(p);
+        const SeqSize size = size_of(p, u, b);
+        Nb = size.drafts;
+        L = size.len;
+        if (Nb > 0 && L + Nb > 0) {
             const Deal deal = deal_units(p, u.total);
             const int before = units_before(p, u, b), w0 = deal_worker(deal, before);
             s_first = w0 + b;
-            limit = ns = deal_worker(deal, before + stages_of(T_b) - 1) - w0 + 1;
+            limit = ns = deal_worker(deal, before + stages_of(L + Nb) - 1) - w0 + 1;
             load(s_first, first, limit);
+        }
+    } else {
+        Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status);
+        L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status);
+        const int T_b = Nb == 0 ? 0 : L + Nb;                 // a sequence without drafts wrote no partials
+        if (T_b > 0 && !p.dealt) {
+            ns = min((T_b + p.C - 1) / p.C, p.max_splits);
+        } else if (T_b > 0) {
+            const Deal deal = T_b == p.max_ctx_len + p.N ? p.full : deal_units(p, seq_units(p, T_b));
+            ns = deal_worker(deal, stages_of(T_b) - 1) + 1;
         }
     }
 

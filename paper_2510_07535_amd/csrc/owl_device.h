@@ -78,50 +78,66 @@ __device__ __forceinline__ int load_n_draft(const int32_t *n_draft_seq, int b, i
     return n;
 }
 
-// Cached rows of sequence b that the pass has to scan: 0 for a sequence without drafts.
-__device__ __forceinline__ int seq_tokens(const KParams &p, int b)
-{
-    int L = p.ctx_lens[b];
-    L = L < 0 ? 0 : (L > p.max_ctx_len ? p.max_ctx_len : L);        // flagged where the sequence is processed
-    int n = p.n_draft_seq ? p.n_draft_seq[b] : p.N;
-    n = n < 0 ? 0 : (n > p.N ? p.N : n);
-    return n == 0 ? 0 : L + n;
-}
-
 __device__ __forceinline__ Deal deal_units(const KParams &p, int units) { return deal_units(p.rule, units); }
 __device__ __forceinline__ int seq_units(const KParams &p, int tokens) { return seq_units(p.rule, tokens); }
 
-// Inclusive sum over the lanes of the wavefront.
+// Inclusive sum over the lanes of the wavefront, without LDS: within rows of 16 lanes by shifts of 1, 2, 4 and 8, then the
+// last lane of a row to the next one, then lane 31 to the upper half.  (By shuffles through LDS, six
+// round trips, and with each sequence's size read once more behind it, a batch took 0.5-1 us longer in both kernels: 16 rows,
+// 24 sequences of 400-2K, head_dim 64, 19.7 -> 19.1 us; 64 rows, 100 of 100-1K 71.8 -> 68.6; 320 rows, 8 of 500-3K 43.0 -> 41.4.)
 __device__ __forceinline__ int lane_scan(int v)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(v, off);
-        if (lane >= off) v += up;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return v;
 }
 
-// The units of a batch: lane l of the calling wavefront keeps the running sum through sequence l;
+// Length and draft count of a sequence, forced into range (and flagged).
+struct SeqSize {
+    int len, drafts;
+};
+
+// The units of a batch: lane l of the calling wavefront keeps sequence l's size and the running sum through it;
 // sequences from 64 on are read again when they are asked for.
 struct BatchUnits {
     int scan, total;
+    SeqSize size;
 };
 
-__device__ __forceinline__ int chunk_scan(const KParams &p, int b0)
+// Sequences b0 .. b0 + 63, one a lane: their sizes and the running sum of their units.
+__device__ __forceinline__ int chunk_scan(const KParams &p, int b0, SeqSize *size)
 {
     const int b = b0 + (threadIdx.x & 63);
-    return lane_scan(b < p.B ? seq_units(p, seq_tokens(p, b)) : 0);
+    int L = 0, n = 0;
+    if (b < p.B) {
+        const int len = p.ctx_lens[b], drafts = p.n_draft_seq ? p.n_draft_seq[b] : p.N;
+        L = len < 0 ? 0 : min(len, p.max_ctx_len);
+        n = drafts < 0 ? 0 : min(drafts, p.N);
+        if (L != len) flag_status(p.dev_status, OWL_DEV_BAD_CTX_LEN);
+        if (n != drafts) flag_status(p.dev_status, OWL_DEV_BAD_NDRAFT);
+    }
+    if (size) *size = SeqSize{L, n};
+    return lane_scan(n == 0 ? 0 : seq_units(p, L + n));
 }
 
 __device__ __forceinline__ BatchUnits batch_units(const KParams &p)
 {
     BatchUnits u;
-    u.scan = chunk_scan(p, 0);
+    u.scan = chunk_scan(p, 0, &u.size);
     u.total = __builtin_amdgcn_readlane(u.scan, 63);
-    for (int b0 = 64; b0 < p.B; b0 += 64) u.total += __builtin_amdgcn_readlane(chunk_scan(p, b0), 63);
+    for (int b0 = 64; b0 < p.B; b0 += 64) u.total += __builtin_amdgcn_readlane(chunk_scan(p, b0, nullptr), 63);
     return u;
+}
+
+// Size of sequence b, which lane b holds if b < 64: no second round trip for it.  Wave-uniform.
+__device__ __forceinline__ SeqSize size_of(const KParams &p, const BatchUnits &u, int b)
+{
+    if (b < 64) return SeqSize{__builtin_amdgcn_readlane(u.size.len, b), __builtin_amdgcn_readlane(u.size.drafts, b)};
+    return SeqSize{load_ctx_len(p.ctx_lens, b, p.max_ctx_len, nullptr), load_n_draft(p.n_draft_seq, b, p.N, nullptr)};
 }
 
 // Sequence that unit x falls into (0 <= x < total) and the units before it.  Wave-uniform.
@@ -138,7 +154,7 @@ __device__ __forceinline__ void find_unit(const KParams &p, const BatchUnits &u,
         }
         base += __builtin_amdgcn_readlane(scan, 63);
         b0 += 64;
-        scan = chunk_scan(p, b0);
+        scan = chunk_scan(p, b0, nullptr);
     }
 }
 
@@ -149,7 +165,7 @@ __device__ __forceinline__ int units_before(const KParams &p, const BatchUnits &
     for (int b0 = 0; b >= b0 + 64;) {
         base += __builtin_amdgcn_readlane(scan, 63);
         b0 += 64;
-        scan = chunk_scan(p, b0);
+        scan = chunk_scan(p, b0, nullptr);
     }
     const int l = b & 63;
     return base + (l > 0 ? __builtin_amdgcn_readlane(scan, max(l - 1, 0)) : 0);

@@ -825,11 +825,17 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 ++issued;
             }
             const int sbase = pos0 + s * SK;
-#pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) {
-                if (ks % WK != wk) continue;
-                if (sbase + ks * 32 >= pos1) continue;       // uniform: nothing left in this step
+            auto step = [&](int ks) {
+                if (ks % WK != wk) return;
+                if (sbase + ks * 32 >= pos1) return;         // uniform: nothing left in this step
                 careful_step(s % NS, ks, sbase + ks * 32);
+            };
+            if constexpr (kF32) {
+#pragma unroll 1                                             // (two copies of the step spill at head_dim 128: 32 rows, 2K 18.5 -> 15.4 us)
+                for (int ks = 0; ks < KSTEPS; ++ks) step(ks);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < KSTEPS; ++ks) step(ks);
             }
         }
     };
@@ -1242,18 +1248,22 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         pages = load_pages(p, tid, b, ahead.pos0, 0);
         parent = p.parent[(int64_t)b * p.N + min(tid, p.N - 1)];
     }
+    SeqSize size{0, 0};                               // of the first sequence, once known
+    bool sized = false;
     if (p.dealt) {
         const int worker = (int)item;
         if (p.B == 1) {
-            const int N1 = load_n_draft(p.n_draft_seq, 0, p.N, nullptr);
-            const int T1 = N1 == 0 ? 0 : load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, nullptr) + N1;
+            size = SeqSize{load_ctx_len(p.ctx_lens, 0, p.max_ctx_len, p.dev_status), load_n_draft(p.n_draft_seq, 0, p.N, p.dev_status)};
+            const int T1 = size.drafts == 0 ? 0 : size.len + size.drafts;
             if (T1 != p.max_ctx_len + p.N) deal = deal_units(p, max(seq_units(p, T1), 1));
         } else {
             const BatchUnits u = batch_units(p);
             if (u.total == 0) return;                 // not one sequence has drafts
             deal = deal_units(p, u.total);
             if (worker < deal.workers) find_unit(p, u, deal_begin(deal, worker), &b, &before);
+            size = size_of(p, u, b);
         }
+        sized = true;
         if (worker >= deal.workers) return;
         x = deal_begin(deal, worker);
         x1 = deal_begin(deal, worker + 1);
@@ -1278,8 +1288,9 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
         ahead.parent = parent;
     }
     for (bool again = false; b < p.B; ++b) {
-        const int Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status);
-        const int L = load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status);
+        if (!sized) size = SeqSize{load_ctx_len(p.ctx_lens, b, p.max_ctx_len, p.dev_status), load_n_draft(p.n_draft_seq, b, p.N, p.dev_status)};
+        sized = false;
+        const int L = size.len, Nb = size.drafts;
         const int T_b = Nb == 0 ? 0 : L + Nb;
         const int s0 = x - before, s1 = min(x1 - before, stages_of(T_b));
         if (s0 < s1) {
