@@ -36,16 +36,17 @@ __device__ __forceinline__ void store_out4(void *out, int64_t e, float4 v, int o
 // Asks for every line of the launch's arguments at once and waits for them.  They are cold in each launch, and left to
 // itself the compiler loads them in several rounds, close to their uses, each a memory round trip of its own
 // (set-up of a split-KV workgroup 1.12 -> 0.98 us).
-template <typename Args>
-__device__ __forceinline__ void fetch_args()
+template <int bytes>
+__device__ __forceinline__ void fetch_arg_bytes()
 {
     typedef const __attribute__((address_space(4))) int32_t *Line;
     const Line at = (Line)__builtin_amdgcn_kernarg_segment_ptr();
-    constexpr int n = (sizeof(Args) + 63) / 64;
+    constexpr int n = (bytes + 63) / 64;
     static_assert(n <= 4, "four lines of arguments");
     const int32_t a = at[0], b = at[n > 1 ? 16 : 0], c = at[n > 2 ? 32 : 0], d = at[n > 3 ? 48 : 0];
     asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
 }
+template <typename Args> __device__ __forceinline__ void fetch_args() { fetch_arg_bytes<sizeof(Args)>(); }
 
 // Reads through the scalar cache; for arrays no kernel of the launch writes, uniform index.
 __device__ __forceinline__ int load_uniform(const int32_t *a, int i)
@@ -94,6 +95,21 @@ __device__ __forceinline__ int lane_scan(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return v;
+}
+
+// The same steps for a sum of floats, which lane 63 ends up with and every lane gets.
+__device__ __forceinline__ float wave_sum(float v)
+{
+#define OWL_DPP_ADD(ctrl, rows)                                                                                              \
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, rows, 0xf, false))
+    OWL_DPP_ADD(0x111, 0xf);
+    OWL_DPP_ADD(0x112, 0xf);
+    OWL_DPP_ADD(0x114, 0xf);
+    OWL_DPP_ADD(0x118, 0xf);
+    OWL_DPP_ADD(0x142, 0xa);
+    OWL_DPP_ADD(0x143, 0xc);
+#undef OWL_DPP_ADD
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 // Length and draft count of a sequence, forced into range (and flagged).

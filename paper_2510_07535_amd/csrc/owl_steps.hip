@@ -17,7 +17,9 @@ __global__ void __launch_bounds__(64) prepare_kernel(const int32_t *parent, cons
                                                      int32_t *parent2, uint64_t *anc, int32_t *depth,
                                                      int32_t *pos, uint32_t *status)
 {
+    fetch_arg_bytes<64>();
     const int b = blockIdx.x, i = threadIdx.x, n2 = 2 * n;
+    const int L = pos ? load_uniform(ctx_lens, b) : 0;
     int p = i < n ? parent[(int64_t)b * n + i] : i - n;
     const uint64_t a = ancestor_sets(p, i, n2, status);
     if (i < n2) {
@@ -27,7 +29,7 @@ __global__ void __launch_bounds__(64) prepare_kernel(const int32_t *parent, cons
         parent2[o] = p;
         anc[o] = a;
         if (depth) depth[o] = d;
-        if (pos) pos[o] = ctx_lens[b] + d - 1;
+        if (pos) pos[o] = L + d - 1;
     }
 }
 
@@ -53,24 +55,21 @@ __global__ void __launch_bounds__(64) accept_kernel(const int32_t *tokens, const
                                                     int N, int n_cand, int32_t *accepted, int32_t *n_accept,
                                                     int32_t *bonus, int32_t *last, uint32_t *status)
 {
-    __shared__ int32_t s_parent[64];
+    fetch_arg_bytes<80>();
     const int b = blockIdx.x, i = threadIdx.x;
     const int64_t row = (int64_t)b * N;
-    int p = -1;
-    bool agrees = false;
-    if (i < N) {
-        p = parent[row + i];
-        if (p < -1 || p >= i) {
-            flag_status(status, OWL_DEV_BAD_PARENT);
-            p = -1;
-        }
-        s_parent[i] = p;
-        if (i < n_cand && p < n_cand) {
-            const int want = p < 0 ? target_root[b] : target_next[row + p];
-            agrees = tokens[row + i] == want;
-        }
+    // everything in one memory round trip; what the target says after the parent comes from the parent's lane
+    const int64_t at = row + min(i, N - 1);
+    int p = parent[at];
+    const int token = tokens[at], next = target_next[at], root = load_uniform(target_root, b);
+    if (i >= N) {
+        p = -1;
+    } else if (p < -1 || p >= i) {
+        flag_status(status, OWL_DEV_BAD_PARENT);
+        p = -1;
     }
-    __syncthreads();
+    const int said = __shfl(next, max(p, 0));
+    const bool agrees = i < N && i < n_cand && p < n_cand && token == (p < 0 ? root : said);
     uint64_t reach = 0;
     int depth = 0;                                          // depth of lane's node once reached
     for (int round = 1; round <= N; ++round) {              // uniform: `reach` is the same in every lane
@@ -84,19 +83,19 @@ __global__ void __launch_bounds__(64) accept_kernel(const int32_t *tokens, const
     int key = ((reach >> i) & 1) ? depth * 64 + (63 - i) : -1;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off));
+    key = __builtin_amdgcn_readfirstlane(key);
     const int best = key < 0 ? -1 : 63 - (key & 63);
     const int na = key < 0 ? 0 : key >> 6;
-    if (i < N) accepted[row + i] = -1;
-    __syncthreads();
+    // The path is walked in scalar registers; the node at depth k goes to place k - 1, the places behind it get -1.
+    uint64_t path = 0;
+    for (int node = best; node >= 0; node = __builtin_amdgcn_readlane(p, node)) path |= (uint64_t)1 << node;   // decreasing indices
+    const int after = __builtin_amdgcn_readlane(next, max(best, 0));
+    if ((path >> i) & 1) accepted[row + depth - 1] = i;
+    if (i >= na && i < N) accepted[row + i] = -1;
     if (i == 0) {
         n_accept[b] = na;
         last[b] = best;
-        bonus[b] = best < 0 ? target_root[b] : target_next[row + best];
-        int jn = best;
-        for (int k = na - 1; k >= 0 && jn >= 0; --k) {       // walks strictly decreasing indices
-            accepted[row + k] = jn;
-            jn = s_parent[jn];
-        }
+        bonus[b] = best < 0 ? root : after;
     }
 }
 
@@ -135,32 +134,39 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
     __shared__ int32_t s_src[64];
     __shared__ int64_t s_src_page[64], s_dst_page[64];
     __shared__ int s_bad, s_bad_page;
+    fetch_arg_bytes<128>();
     const int g = blockIdx.x, b = blockIdx.y;
     unsigned char *cache = blockIdx.z ? v_cache : k_cache;
     const int tid = threadIdx.x;
+    // length, count and path in one memory round trip, the pages in the next (one after the other: 4.6 -> 4.1 us a launch)
+    int a = 0;
+    if (tid < 64) a = accepted[(int64_t)b * N + min(tid, N - 1)];
+    int na = load_uniform(n_accept, b);
     const int L = load_ctx_len(ctx_lens, b, max_ctx_len, status);
-    int na = n_accept[b];
-    if (tid == 0) s_bad = s_bad_page = 0;
-    __syncthreads();
     if (na < 0 || na > N) {
         if (tid == 0) flag_status(status, OWL_DEV_BAD_ACCEPT);
         na = 0;
     }
-    if (tid < na) {
-        const int a = accepted[(int64_t)b * N + tid];
-        const int prev = tid > 0 ? accepted[(int64_t)b * N + tid - 1] : -1;
-        if (a < 0 || a >= N || a <= prev) s_bad = 1;
-        s_src[tid] = a;
-        // physical pages of the row's source and destination, unchecked ids; -1 = not in the table
-        auto page_of = [&](int pos) -> int64_t {
-            const int lp = pos / kPage;
-            if (!page_table) return lp;
-            return lp < max_pages ? (int64_t)page_table[(int64_t)b * max_pages + lp] : -1;
-        };
-        const int64_t sp = (a >= 0 && a < N) ? page_of(L + a) : 0, dp = page_of(L + tid);
-        if (sp < 0 || sp >= n_pool_pages || dp < 0 || dp >= n_pool_pages) s_bad_page = 1;
-        s_src_page[tid] = sp;
-        s_dst_page[tid] = dp;
+    if (tid < 64) {                                         // one wavefront, lane = row of the path
+        const int prev = __shfl_up(a, 1);
+        const bool mine = tid < na;
+        bool bad = false, bad_page = false;
+        if (mine) {
+            bad = a < 0 || a >= N || (tid > 0 && a <= prev);
+            s_src[tid] = a;
+            // physical pages of the row's source and destination, unchecked ids; -1 = not in the table
+            auto page_of = [&](int pos) -> int64_t {
+                const int lp = pos / kPage;
+                if (!page_table) return lp;
+                return lp < max_pages ? (int64_t)page_table[(int64_t)b * max_pages + lp] : -1;
+            };
+            const int64_t sp = (a >= 0 && a < N) ? page_of(L + a) : 0, dp = page_of(L + tid);
+            bad_page = sp < 0 || sp >= n_pool_pages || dp < 0 || dp >= n_pool_pages;
+            s_src_page[tid] = sp;
+            s_dst_page[tid] = dp;
+        }
+        const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0, any_page = __builtin_amdgcn_ballot_w64(bad_page) != 0;
+        if (tid == 0) s_bad = any_bad, s_bad_page = any_page;
     }
     __syncthreads();
     if (s_bad) {                                            // uniform over the workgroup
@@ -178,7 +184,7 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
 #pragma unroll
     for (int r = 0; r < kCommitMaxPieces; ++r) {
         const int id = tid + r * kCommitThreads;
-        if (id < total) {
+        if (id < total && s_src[id / ppr] != id / ppr) {    // a row already in place is left alone
             const int i = id / ppr, piece = id % ppr;
             const int pos = L + s_src[i];
             const int64_t off = (s_src_page[i] * stride_page + g * stride_head + (pos % kPage) * stride_token) * es;
@@ -191,7 +197,7 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
         const int id = tid + r * kCommitThreads;
         if (id < total) {
             const int i = id / ppr, piece = id % ppr;
-            if (s_src[i] != i) {                            // a row already in place is left alone
+            if (s_src[i] != i) {
                 const int pos = L + i;
                 const int64_t off = (s_dst_page[i] * stride_page + g * stride_head + (pos % kPage) * stride_token) * es;
                 *reinterpret_cast<uint4 *>(cache + off + piece * 16) = held[r];
