@@ -685,6 +685,30 @@ def test_context_shorter_than_planned(oracle_mod, L, planned):
     assert_close(got, exact.astype(np.float64), case.dtype, "planned-for-longer vs planned-exactly")
 
 
+@pytest.mark.parametrize("dtype,D,G,N,frac,gain", [
+    (W.DT_BF16, 128, 8, 13, 0.0, 1.0),        # 104 rows: seven tiles, the fourth pair has one
+    (W.DT_BF16, 128, 8, 15, 0.05, 8.0),       # 120 rows: eight tiles, the last one half empty
+    (W.DT_BF16, 64, 4, 32, 0.0, 1.0),         # 128 rows, exactly eight tiles
+    (W.DT_F16, 128, 4, 26, 0.0007, 40.0),     # a frozen reference that overflows: the piece is redone
+    (W.DT_F16, 64, 8, 16, 0.05, 8.0),         # the guarded reference
+])
+def test_two_tiles_a_pair_of_wavefronts(oracle_mod, dtype, D, G, N, frac, gain):
+    """Seven and eight row tiles, planned for long shares: pairs of wavefronts hold two tiles each, split the steps of a
+    stage and hand each other a tile at the end.  The lengths are short (none, one stage, ragged ends, several stages), the
+    announced length is what makes the plan choose this layout."""
+    import dataclasses
+    lens, planned = [0, 3000, 64, 1, 63, 700, 128, 5001], 131072
+    trees = [W.random_tree(N, 5, _rng(N + 10 * b)) for b in range(len(lens))]
+    case = W.make_case("pairs", 870 + N, dtype=dtype, Hq=4 * G, Hkv=4, D=D, ctx_lens=lens, trees=trees, outlier_frac=frac, outlier_gain=gain)
+    table = np.zeros((len(lens), (planned + N + 15) // 16), dtype=np.int32)
+    table[:, :case.page_table.shape[1]] = np.maximum(case.page_table, 0)
+    wide = dataclasses.replace(case, page_table=table, max_pages_per_seq=table.shape[1])
+    got, step = _run(wide, max_ctx_len=planned)
+    plan = step.plan.as_dict()
+    assert plan["row_tiles"] in (7, 8) and plan["row_groups"] == 1 and plan["tiles_per_wave"] == 2, plan
+    assert_close(got, oracle_mod.verify_attn_case(case), case.dtype, f"plan={plan}")
+
+
 # ---------------------------------------------------------------------------
 # the largest shapes the entry point takes
 # ---------------------------------------------------------------------------
