@@ -95,12 +95,18 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     } else {
         static const int caps[4] = {24, 16, 8, 4};
         int li = RT <= 4 ? 3 : (RT <= 8 ? 2 : (RT <= 16 ? 1 : 0));
-        const int64_t splits_at_most = d->split_tokens > 0
-            ? (T + (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum) - 1) / (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum)
-            : (T + cmin - 1) / cmin;
-        const int64_t streams = (int64_t)d->batch * d->n_kv_heads * (splits_at_most < 1 ? 1 : splits_at_most);
-        // (three quarters of the compute units will do: larger groups do more per K/V byte they read)
-        while (li < 3 && 4 * streams * ((RT + caps[li] - 1) / caps[li]) < 3 * (int64_t)device_cus()) ++li;
+        // (three quarters of the compute units will do: larger groups do more per K/V byte they read.  Two groups are kept as long
+        // as splits of 2 R tokens reach that, one group or more than two as long as splits of 4 R do.  us with 4 R -> 2 R: from
+        // four groups to two 240 rows, 9K tokens 24.9 -> 22.7, from three to two 320 rows, 12K 32.7 -> 30.1, 2 KV heads, 40K
+        // 29.0 -> 27.6; but from two to one 240 rows, 16K 30.5 -> 31.3, 320 rows, 1 head, 128K 37.2 -> 41.9, 104 rows, 5K
+        // 14.7 -> 15.2.  With R, four to two: 240 rows, 5K 18.6 -> 20.8.)
+        auto fills = [&](int groups) {
+            const int64_t least = d->split_tokens > 0 ? (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum)
+                                                      : (groups == 2 ? (cmin + 1) / 2 : cmin);
+            const int64_t splits = (T + least - 1) / least;
+            return 4 * (int64_t)d->batch * d->n_kv_heads * (splits < 1 ? 1 : splits) * groups >= 3 * (int64_t)device_cus();
+        };
+        while (li < 3 && !fills((RT + caps[li] - 1) / caps[li])) ++li;
         rgs = (RT + caps[li] - 1) / caps[li];
         group_tiles = (RT + rgs - 1) / rgs;
         rgs = (RT + group_tiles - 1) / group_tiles;

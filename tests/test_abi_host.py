@@ -59,6 +59,19 @@ def test_plan_matches_shapes():
     assert p.row_groups == 5 and p.tiles_per_wave == 1
 
 
+@pytest.mark.parametrize("n,group,hkv,batch,ctx,groups,tiles", [
+    (60, 4, 8, 1, 5003, 4, 1), (60, 4, 8, 1, 9000, 2, 1), (60, 4, 8, 1, 16000, 2, 1), (60, 4, 8, 1, 28000, 1, 2),   # 240 rows
+    (40, 8, 8, 1, 12000, 2, 2), (40, 8, 2, 1, 40000, 2, 2), (40, 8, 1, 1, 131072, 2, 2),                             # 320 rows
+    (32, 4, 8, 1, 130976, 1, 1), (32, 4, 8, 1, 130977, 1, 2),          # eight tiles: shares of 63 and of 64 stages
+    (26, 4, 8, 16, 32678, 1, 1), (26, 4, 8, 16, 32679, 1, 2),          # seven tiles: 255 and 256 stages
+    (24, 4, 8, 16, 65536, 1, 1),                                       # six tiles: one a wavefront
+])
+def test_plan_row_groups_and_tiles_a_wavefront(n, group, hkv, batch, ctx, groups, tiles):
+    p = B.owl_verify_attn_plan(_good(n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, batch=batch, max_ctx_len=ctx,
+                                     max_pages_per_seq=(ctx + n + 15) // 16))
+    assert (p.row_groups, p.tiles_per_wave) == (groups, tiles), p.as_dict()
+
+
 @pytest.mark.parametrize("over,code", [
     (dict(batch=0), B.OWL_ERR_INVALID_ARG),
     (dict(n_draft=0), B.OWL_ERR_INVALID_ARG),
