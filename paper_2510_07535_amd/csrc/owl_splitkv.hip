@@ -402,9 +402,9 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     };
     auto issue_stage = [&](int s) { issue_stage_pg(s, stage_page(s)); };
 
-    // The query rows travel like K pages: by DMA, 16 bytes a lane, rows contiguous, into the ring slots
-    // behind the stages that are requested with them (TPW slots, one tile of every wavefront each), from
-    // where each wavefront picks its own fragments.  (Loaded straight into registers they took 2 us for
+    // The query rows travel like K pages: by DMA, 16 bytes a lane, rows contiguous, into the last TPW ring
+    // slots (one tile of every wavefront each), before the stages that belong there are requested; from
+    // there each wavefront picks its own fragments.  (Loaded straight into registers they took 2 us for
     // 20 row tiles, as 64-byte pieces of 16 rows per instruction, and the compiler, which does not see the
     // ring's transfers in the wait counter, drained the whole ring before it used them.)
     constexpr int kQSlot0 = NS - TPW;                // first ring slot the queries occupy
