@@ -35,7 +35,7 @@ __device__ __forceinline__ void store_out4(void *out, int64_t e, float4 v, int o
 
 // Asks for every line of the launch's arguments at once and waits for them.  They are cold in each launch, and left to
 // itself the compiler loads them in several rounds, close to their uses, each a memory round trip of its own
-// (set-up of a split-KV workgroup 1.12 -> 0.98 us).
+// (set-up of a split-KV workgroup 1.12 -> 0.98 us; the drafter kernels gain nothing by it).
 template <int bytes>
 __device__ __forceinline__ void fetch_arg_bytes()
 {

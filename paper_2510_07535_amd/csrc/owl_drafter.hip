@@ -512,7 +512,6 @@ template <bool kF16, int MAXC>
 __global__ void __launch_bounds__(kGateThreads) drafter_state_kernel(GateArgs a)
 {
     __shared__ float scratch[4 * kGateWaves];
-    fetch_args<GateArgs>();
     const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
     const GateRow g = gate_row(a, r, c == 0);
     const bool live = j < a.d;
@@ -536,7 +535,6 @@ __global__ void __launch_bounds__(kGateThreads) drafter_state_kernel(GateArgs a)
 template <bool kF16>
 __global__ void __launch_bounds__(kGateThreads) drafter_hidden_kernel(GateArgs a)
 {
-    fetch_args<GateArgs>();
     const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
     // (everything is asked for before the statistics are merged; lanes past the last chunk read chunk 0 and do not count)
     const int n_chunks = (a.d + kGateChunk - 1) / kGateChunk, chunk = (int)(threadIdx.x & 63) < n_chunks ? threadIdx.x & 63 : 0;
