@@ -39,7 +39,6 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     constexpr int NT = D / 16, UPW = 2;              // channel tiles per wavefront
     constexpr int NUG = NT / UPW;
     static_assert(!BY_CHANNEL || WAVES == NUG, "one wavefront per pair of channel tiles");
-    fetch_args<KParams>();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // KV heads vary fastest, as in the split-KV pass: with eight heads the partials of a head were written on XCD (head mod 8) and
     // are found in its L2 (row tiles fastest: 240 rows, four sequences 6.6 -> 5.4 us, 320 rows, 128K 7.5 -> 6.8; lone 240 rows, 5K
