@@ -183,11 +183,16 @@ struct Piece {
     size_t slot;                                     // where the partials of row tile 0 go
 };
 
-// This lane's number in its wavefront, formed anew: not to be kept across the pieces of a share, where the loops leave no
-// register for it.  (In the three-tile kernel what was kept went to scratch memory, and every reload between the requests
-// of the first stages waited for all of them: 128K hybrid, 320 rows, 171.2 -> 168 us.)
-__device__ __forceinline__ int fresh_lane()
+// This lane's number in its wavefront.  Formed anew in each piece (kAnew) it is not kept across the pieces of a share, where
+// the loops of some kernels leave no register for it: in the three-tile kernel it went to scratch memory, and every reload
+// between the requests of the first stages waited for all of them (128K hybrid, 320 rows 167.5 us against 172.3 with the
+// number kept, 8 sequences of 500-3K 39.0 against 47.7; fp32, head_dim 128, 512 tokens 13.6 against 16.3).  With one tile of 16
+// bits there is room, and what follows from the number is then not derived again in the loops (320 rows, 1 head, 10K tokens, in
+// row groups of one tile a wavefront 14.39 us anew, 14.22 kept; 160 rows 12.98 and 12.82).  Two tiles: within 1 % either way.
+template <bool kAnew>
+__device__ __forceinline__ int lane_number()
 {
+    if constexpr (!kAnew) return threadIdx.x & 63;
     int lane;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
     return lane;
@@ -273,7 +278,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // pieces of a share (as the compiler would by itself) it does not fit the registers of the loops.
     const KParams &p = piece_args<T>(launch_args);
     asm volatile("" : "+s"(g), "+s"(rg), "+s"(wave));
-    const int lane = fresh_lane(), tid = wave * 64 + lane;
+    const int lane = lane_number<(TPW > 1) || kF32>(), tid = wave * 64 + lane;
     const int wr = wave % WR, wk = wave / WR;
     const int j = lane & 15, qd = lane >> 4;
 
