@@ -112,13 +112,21 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
         rgs = (RT + group_tiles - 1) / group_tiles;
         // Seven or eight tiles: eight wavefronts with one each, or four pairs with two each, a pair splitting the steps of a
         // stage.  That halves the fragments read from LDS, and with them the power that limits the loop, but a workgroup then
-        // has a merge of its own and no pipelined loop: it pays on long shares, the sooner the fuller the pairs are.  us, one
-        // tile -> two: 128 rows, shares of 33 / 64 / 125 / 300 / 512 stages 54.4 -> 55.2 / 97.0 -> 93.8 / 129.4 -> 126.2 / 301.9
-        // -> 287.2 / 498.5 -> 470.0; 104 rows, 96 / 125 / 300 / 512 stages 122.9 -> 123.8 / 125.4 -> 125.3 / 285.5 -> 283.4 /
-        // 473.1 -> 453.9.  Five and six tiles gain nothing (80 rows, 512 stages 442 -> 441).
-        const int64_t share = (int64_t)d->batch * ((T + kSplitQuantum - 1) / kSplitQuantum) * d->n_kv_heads * rgs / device_cus();
+        // has a merge of its own in every piece and no pipelined loop: it pays where a worker has many stages and its pieces are
+        // not short, the sooner the fuller the pairs are.  us, one tile -> two, 8 KV heads, bf16, sequences of S stages each, a
+        // worker's share 256 stages (64 where it says so): 104 rows, S = 8 / 32 / 128 / 512 / 2048 1004 -> 1020 / 477 -> 476 /
+        // 377 -> 370 / 361 -> 343 / 358 -> 341, but with shares of 64 121 -> 121 / 102.4 -> 103.0 / 98.1 -> 99.0 / 96.4 -> 93.9
+        // from S = 32 on; 128 rows 1093 -> 1109 / 498 -> 497 / 396 -> 382 / 381 -> 360 / 378 -> 356, and with 64 126 -> 126 /
+        // 104.7 -> 104.4 / 102.5 -> 99.5 / 101.2 -> 96.8.  A caller's splits of 1 / 4 / 16 / 64 stages, 104 rows: 1858 -> 2089 /
+        // 717 -> 750 / 460 -> 464 / 390 -> 388.  fp16 and head_dim 64 gain more from S = 32 on (1-7 %) and lose as much at S = 8
+        // (1-4 %).  What is known here is the greatest length: 128 rows announced as 128K and 4K long take 16.1 instead of
+        // 15.6.  Five and six tiles gain nothing (80 rows, share 512: 442 -> 441).
+        const int64_t stages = (T + kSplitQuantum - 1) / kSplitQuantum;
+        const int64_t share = (int64_t)d->batch * stages * d->n_kv_heads * rgs / device_cus();
+        const int64_t split = (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum) / kSplitQuantum;
+        const int64_t piece = d->split_tokens > 0 && split < stages ? split : stages;
         if (caps[li] == 4) { tpw = 1; wr = 4; wk = 2; }
-        else if (caps[li] == 8 && group_tiles >= 7 && share >= (group_tiles == 8 ? 64 : 256)) { tpw = 2; wr = 4; wk = 2; }
+        else if (caps[li] == 8 && group_tiles >= 7 && piece >= 32 && share >= (group_tiles == 8 ? 64 : 256)) { tpw = 2; wr = 4; wk = 2; }
         else { wr = 8; wk = 1; tpw = (group_tiles + 7) / 8; }
     }
     const Variant *v = find_variant(d->qkv_dtype, d->head_dim, tpw, wr, wk);

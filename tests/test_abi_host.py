@@ -72,6 +72,19 @@ def test_plan_row_groups_and_tiles_a_wavefront(n, group, hkv, batch, ctx, groups
     assert (p.row_groups, p.tiles_per_wave) == (groups, tiles), p.as_dict()
 
 
+@pytest.mark.parametrize("n,batch,ctx,split,tiles", [
+    (32, 256, 480, 0, 1), (26, 1000, 486, 0, 1), (32, 512, 500, 0, 1),     # shares of many short sequences
+    (32, 256, 1952, 0, 1), (32, 256, 1953, 0, 2),                          # pieces of 31 and of 32 stages
+    (26, 16, 32742, 64, 1), (32, 16, 65000, 256, 1), (32, 16, 65000, 1024, 1),
+    (32, 16, 65000, 1984, 1), (32, 512, 500, 16384, 1), (32, 16, 65000, 1985, 2), (26, 16, 65000, 2048, 2), (26, 16, 16000, 2048, 1),
+])
+def test_two_tiles_a_wavefront_need_long_pieces(n, batch, ctx, split, tiles):
+    """Seven and eight row tiles: the layout with pairs of wavefronts pays a merge in every piece, so a caller's short splits
+    and short sequences keep the one without, however much work a compute unit has in all."""
+    p = B.owl_verify_attn_plan(_good(n_draft=n, batch=batch, max_ctx_len=ctx, split_tokens=split, max_pages_per_seq=(ctx + n + 15) // 16))
+    assert (p.row_groups, p.tiles_per_wave) == (1, tiles), p.as_dict()
+
+
 @pytest.mark.parametrize("over,code", [
     (dict(batch=0), B.OWL_ERR_INVALID_ARG),
     (dict(n_draft=0), B.OWL_ERR_INVALID_ARG),
