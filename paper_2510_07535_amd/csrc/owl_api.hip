@@ -82,8 +82,8 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
     if (cmin < 256) cmin = 256;
     // Eight wavefronts per workgroup: WR of them split the row tiles, WK the
     // 32-key steps of a stage; a wave holds up to three tiles in accumulators.
-    // A workgroup takes up to 4 (WK = 2) or 8, 16, 24 (WK = 1) row tiles; more
-    // tiles than that go to further row groups, workgroups that read the same
+    // A workgroup takes up to 4 (WK = 2) or 8, 16, 24 (WK = 1; 7 and 8 on long
+    // shares WK = 2) row tiles; more tiles than that go to further row groups, workgroups that read the same
     // split.  Few KV streams (one or two KV heads of a tensor-parallel shard, one
     // sequence) cannot fill the chip by splits alone without the partials
     // outgrowing the K/V they summarise: then the rows are cut into more, smaller
@@ -94,19 +94,40 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
         group_tiles = (RT + rgs - 1) / rgs;
     } else {
         static const int caps[4] = {24, 16, 8, 4};
-        int li = RT <= 4 ? 3 : (RT <= 8 ? 2 : (RT <= 16 ? 1 : 0));
-        // (three quarters of the compute units will do: larger groups do more per K/V byte they read.  Two groups are kept as long
-        // as splits of 2 R tokens reach that, one group or more than two as long as splits of 4 R do.  us with 4 R -> 2 R: from
-        // four groups to two 240 rows, 9K tokens 24.9 -> 22.7, from three to two 320 rows, 12K 32.7 -> 30.1, 2 KV heads, 40K
-        // 29.0 -> 27.6; but from two to one 240 rows, 16K 30.5 -> 31.3, 320 rows, 1 head, 128K 37.2 -> 41.9, 104 rows, 5K
-        // 14.7 -> 15.2.  With R, four to two: 240 rows, 5K 18.6 -> 20.8.)
-        auto fills = [&](int groups) {
-            const int64_t least = d->split_tokens > 0 ? (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum)
-                                                      : (groups == 2 ? (cmin + 1) / 2 : cmin);
-            const int64_t splits = (T + least - 1) / least;
-            return 4 * (int64_t)d->batch * d->n_kv_heads * (splits < 1 ? 1 : splits) * groups >= 3 * (int64_t)device_cus();
+        auto groups_of = [&](int l) { return (RT + caps[l] - 1) / caps[l]; };
+        auto splits_of = [&](int64_t least) { return T <= least ? (int64_t)1 : (T + least - 1) / least; };
+        // (three quarters of the compute units will do: larger groups do more per K/V byte they read)
+        auto fills = [&](int groups, int64_t least) {
+            return 4 * (int64_t)d->batch * d->n_kv_heads * splits_of(least) * groups >= 3 * (int64_t)device_cus();
         };
-        while (li < 3 && !fills((RT + caps[li] - 1) / caps[li])) ++li;
+        const int largest = RT <= 4 ? 3 : (RT <= 8 ? 2 : (RT <= 16 ? 1 : 0));
+        int li = largest;
+        while (li < 3 && !fills(groups_of(li), d->split_tokens > 0 ? (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum) : cmin)) ++li;
+        // Where splits of 4 R tokens reach that only with more than two groups, a lone sequence takes two all the same if splits
+        // of `least` tokens reach it: more groups re-read the K/V from L2 more often than the longer shares cost.  How far below
+        // 4 R that holds was measured in bf16 against the plan by 4 R (two groups / that plan, at 2 R, 2.5 R, 3.2 R and 4 R):
+        //   9-12 tiles, from three groups: 6 heads 1.03 1.02 0.99 0.99, but 1 head 1.04 1.04 1.01 1.00, 3 heads 1.05 1.04 1.02
+        //   1.01 (two groups leave a SIMD two tiles, three groups one; with 1 head a row has 128 partials to merge, not 80);
+        //   13-16, from four: 6 heads 0.97 0.94 0.93 0.90, 1 head 1.03 0.99 0.97 0.94, 3 heads 1.02 0.97 0.96 0.93;
+        //   17-32, from three to six: 0.96 0.94 0.92 0.90, never above 1.006 but for one run;
+        //   37-40, and all from five or six: 0.95 0.94 0.92 0.91;
+        //   33-36 and 41-48, from three groups of two tiles a wavefront, head_dim 128: 1.05 1.04 1.03 1.02 and 1.01 1.00 1.00 1.00
+        //   (a SIMD has two times five or six tiles against three times three or four, in the kernel that spills; with 37-40 it is
+        //   two times five against three times four); head_dim 64: 0.96.
+        // In a batch the lengths are bounds, and how sequences fall on the workers decides: 340 plans 0.83 to 1.25, 1.009 on average
+        // (worst: 8 heads, eight sequences of 0.3K-1K, where four groups have a worker for each sequence), so it keeps 4 R.
+        const int more = groups_of(li);
+        if (d->split_tokens == 0 && d->batch == 1 && more > 2) {
+            const bool level = RT >= 37 && RT <= 40, many_heads = d->n_kv_heads >= 6;
+            int eighths = 8;                            // of 4 R
+            if (RT <= 12) eighths = many_heads ? 6 : 8;
+            else if (RT <= 16) eighths = many_heads ? 4 : 5;
+            else if (RT <= 32 || more > 3 || level || d->head_dim == 64) eighths = 4;
+            int two = largest;
+            while (groups_of(two) < 2) ++two;
+            const int64_t least = cmin * eighths / 8;
+            if (groups_of(two) == 2 && fills(2, least)) li = two;
+        }
         rgs = (RT + caps[li] - 1) / caps[li];
         group_tiles = (RT + rgs - 1) / rgs;
         rgs = (RT + group_tiles - 1) / group_tiles;

@@ -72,6 +72,24 @@ def test_plan_row_groups_and_tiles_a_wavefront(n, group, hkv, batch, ctx, groups
     assert (p.row_groups, p.tiles_per_wave) == (groups, tiles), p.as_dict()
 
 
+@pytest.mark.parametrize("n,group,hkv,d,batch,ctx,groups", [
+    (18, 8, 8, 128, 1, 4000, 3), (18, 8, 8, 128, 1, 4600, 3), (18, 8, 8, 128, 1, 5000, 2), (20, 8, 3, 128, 1, 19000, 3),   # 9, 10 tiles
+    (60, 4, 8, 128, 1, 5300, 2), (60, 4, 1, 128, 1, 46500, 4), (60, 4, 1, 128, 1, 58200, 2),                                # 15
+    (60, 4, 8, 128, 2, 3400, 4), (60, 4, 8, 128, 8, 900, 4), (60, 4, 8, 128, 8, 700, 4),
+    (40, 8, 8, 128, 1, 7200, 2), (40, 8, 8, 128, 1, 9000, 2), (40, 8, 8, 128, 2, 3300, 5), (40, 8, 8, 128, 4, 1800, 3),     # 20
+    (40, 8, 8, 128, 8, 900, 3), (60, 8, 8, 128, 8, 1300, 4), (60, 8, 8, 128, 1, 15000, 2),                                  # 30
+    (33, 16, 8, 128, 1, 12000, 2), (33, 16, 8, 128, 1, 18000, 3), (33, 16, 8, 64, 1, 18000, 2), (33, 16, 8, 128, 1, 26000, 2),
+    (40, 16, 8, 128, 1, 18000, 2), (40, 16, 8, 128, 2, 10000, 3), (40, 16, 8, 128, 8, 2000, 3), (48, 16, 8, 128, 1, 27000, 3),
+])
+def test_two_row_groups_where_they_gain(n, group, hkv, d, batch, ctx, groups):
+    """Two row groups are preferred to more below splits of 4 R tokens in a lone sequence, except where they leave the matrix
+    cores more to do than three (9-12 row tiles, 33-36 and 41-48 with head_dim 128), and never in a batch."""
+    p = B.owl_verify_attn_plan(_good(n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, batch=batch, max_ctx_len=ctx,
+                                     max_pages_per_seq=(ctx + n + 15) // 16, kv_stride_page=hkv * 16 * d, kv_stride_head=16 * d,
+                                     kv_stride_token=d))
+    assert p.row_groups == groups, p.as_dict()
+
+
 @pytest.mark.parametrize("n,batch,ctx,split,tiles", [
     (32, 256, 480, 0, 1), (26, 1000, 486, 0, 1), (32, 512, 500, 0, 1),     # shares of many short sequences
     (32, 256, 1952, 0, 1), (32, 256, 1953, 0, 2),                          # pieces of 31 and of 32 stages
