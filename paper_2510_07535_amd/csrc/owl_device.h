@@ -39,9 +39,20 @@ __device__ __forceinline__ void store_out4(void *out, int64_t e, float4 v, int o
 // 11.44 -> 11.33 us; a decoding iteration of one sequence of 1000 tokens, four layers, with it in its small steps 58.5 -> 57.8).
 // The combine asks for a lone sequence's partials with a few of them, and waiting for the rest first cost every call 0.2-0.35 us
 // (320 rows, 1 head, 10K tokens 14.03 -> 14.39, 56 rows, 8 heads, 2000 tokens 11.33 -> 11.68); the drafter kernels gain nothing.
-template <int bytes>
-__device__ __forceinline__ void fetch_arg_bytes()
+template <typename Kernel> struct ArgBytes;
+template <typename... A> struct ArgBytes<void(A...)> {      // of a kernel's type: its arguments one after the other, each aligned
+    static constexpr int end_of()
+    {
+        size_t at = 0;
+        ((at = (at + alignof(A) - 1) / alignof(A) * alignof(A) + sizeof(A)), ...);
+        return (int)at;
+    }
+    static constexpr int value = end_of();
+};
+template <typename Kernel>
+__device__ __forceinline__ void fetch_args()
 {
+    constexpr int bytes = ArgBytes<Kernel>::value;
     typedef const __attribute__((address_space(4))) int32_t *Line;
     const Line at = (Line)__builtin_amdgcn_kernarg_segment_ptr();
     constexpr int n = (bytes + 63) / 64;
@@ -49,7 +60,6 @@ __device__ __forceinline__ void fetch_arg_bytes()
     const int32_t a = at[0], b = at[n > 1 ? 16 : 0], c = at[n > 2 ? 32 : 0], d = at[n > 3 ? 48 : 0];
     asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
 }
-template <typename Args> __device__ __forceinline__ void fetch_args() { fetch_arg_bytes<sizeof(Args)>(); }
 
 // Reads through the scalar cache; for arrays no kernel of the launch writes, uniform index.
 __device__ __forceinline__ int load_uniform(const int32_t *a, int i)

@@ -1170,7 +1170,7 @@ __global__ void __launch_bounds__(kThreads) splitkv_kernel(const KParams p)
 {
     using GEO = Geo<T, D, TPW, WR, WK>;
     extern __shared__ __align__(16) unsigned char smem[];
-    fetch_args<KParams>();
+    fetch_args<void(KParams)>();
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // Workgroups go to the chip's eight XCDs round-robin in launch order, whether or not

@@ -17,7 +17,7 @@ __global__ void __launch_bounds__(64) prepare_kernel(const int32_t *parent, cons
                                                      int32_t *parent2, uint64_t *anc, int32_t *depth,
                                                      int32_t *pos, uint32_t *status)
 {
-    fetch_arg_bytes<64>();
+    fetch_args<decltype(prepare_kernel)>();
     const int b = blockIdx.x, i = threadIdx.x, n2 = 2 * n;
     const int L = pos ? load_uniform(ctx_lens, b) : 0;
     int p = i < n ? parent[(int64_t)b * n + i] : i - n;
@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(64) accept_kernel(const int32_t *tokens, const
                                                     int N, int n_cand, int32_t *accepted, int32_t *n_accept,
                                                     int32_t *bonus, int32_t *last, uint32_t *status)
 {
-    fetch_arg_bytes<80>();
+    fetch_args<decltype(accept_kernel)>();
     const int b = blockIdx.x, i = threadIdx.x;
     const int64_t row = (int64_t)b * N;
     // everything in one memory round trip; what the target says after the parent comes from the parent's lane
@@ -134,7 +134,7 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
     __shared__ int32_t s_src[64];
     __shared__ int64_t s_src_page[64], s_dst_page[64];
     __shared__ int s_bad, s_bad_page;
-    fetch_arg_bytes<128>();
+    fetch_args<decltype(commit_kernel)>();
     const int g = blockIdx.x, b = blockIdx.y;
     unsigned char *cache = blockIdx.z ? v_cache : k_cache;
     const int tid = threadIdx.x;
