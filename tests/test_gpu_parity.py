@@ -709,6 +709,78 @@ def test_two_tiles_a_pair_of_wavefronts(oracle_mod, dtype, D, G, N, frac, gain):
     assert_close(got, oracle_mod.verify_attn_case(case), case.dtype, f"plan={plan}")
 
 
+def _announced(case, planned):
+    """The case with a page table wide enough for ``planned`` tokens; the entries behind the sequences hold -1."""
+    import dataclasses
+    table = np.full((case.B, (planned + case.N + 15) // 16), -1, dtype=np.int32)
+    table[:, :case.page_table.shape[1]] = case.page_table
+    return dataclasses.replace(case, page_table=table, max_pages_per_seq=table.shape[1])
+
+
+def _close_to_oracle(oracle_mod, case, got, what):
+    """All rows, or forty of them where all would keep the oracle busy for long."""
+    if int(case.ctx_lens.sum()) * case.N * case.Hq > 2e7:
+        rows = sample_rows(case, 40, seed=5, always=[(0, 0, 0), (case.B - 1, case.N - 1, case.Hq - 1)])
+        assert np.isfinite(got).all(), what
+        assert_close(np.stack([got[b, i, h] for b, i, h in rows]), oracle_mod.verify_attn_case(case, rows=rows), case.dtype, what)
+    else:
+        assert_close(got, oracle_mod.verify_attn_case(case), case.dtype, what)
+
+
+@pytest.mark.parametrize("dtype,D,G,N,Hkv,lens,split,flags,groups", [
+    (W.DT_BF16, 128, 8, 13, 4, [0, 3000, 64, 1, 63, 700, 128, 5001], 0, B.OWL_FLAG_FP32_PARTIALS, 1),
+    (W.DT_F16, 64, 4, 30, 4, [0, 3000, 64, 1, 63, 700, 128, 5001], 0, B.OWL_FLAG_FP32_PARTIALS, 1),
+    (W.DT_BF16, 128, 8, 31, 2, [20000, 16353, 16354, 0, 500, 1], 16384, 0, 2),     # a caller's splits, two groups of eight tiles
+    (W.DT_BF16, 64, 16, 60, 1, [2900], 0, 0, 8),                                    # eight groups, the last of four tiles
+    (W.DT_F16, 128, 16, 60, 1, [100], 0, 0, 8),
+    (W.DT_F16, 64, 4, 32, 8, [131040], 0, 0, 1),                                    # a lone sequence as long as announced
+    (W.DT_BF16, 64, 4, 32, 8, [131039], 0, 0, 1),
+])
+def test_pairs_of_wavefronts_by_other_routes(oracle_mod, dtype, D, G, N, Hkv, lens, split, flags, groups):
+    """Pairs with two tiles each and fp32 partials, a caller's split size, several row groups, and lone sequences whose page
+    list and parents are asked for along with the length."""
+    planned = 131040 if lens[0] > 130000 else 131072
+    case = W.make_case("pairs", 40 + N + len(lens), dtype=dtype, Hq=Hkv * G, Hkv=Hkv, D=D, ctx_lens=lens,
+                       trees=[W.random_tree(N, 5, _rng(N + 10 * b)) for b in range(len(lens))])
+    got, step = _run(_announced(case, planned), max_ctx_len=planned, split_tokens=split, flags=flags)
+    plan = step.plan.as_dict()
+    assert (plan["row_groups"], plan["tiles_per_wave"]) == (groups, 2) and plan["row_tiles"] <= 8 * groups, plan
+    _close_to_oracle(oracle_mod, case, got, f"plan={plan}")
+
+
+@pytest.mark.parametrize("split", [0, 1024])
+@pytest.mark.parametrize("dtype,L", [(W.DT_BF16, 0), (W.DT_BF16, 100), (W.DT_F16, 9001), (W.DT_BF16, 31999), (W.DT_BF16, 32000)])
+def test_three_tiles_and_a_length_short_of_the_announced(oracle_mod, dtype, L, split):
+    """The three-tile kernel puts the page list that a lone sequence would have if it were as long as announced, and the
+    parents, into LDS before it knows the length.  Shorter sequences have other windows, and entries of -1 in the list."""
+    planned = 32000
+    case = W.make_case("three", 300 + L % 89, dtype=dtype, Hq=64, Hkv=8, D=128, ctx_lens=[L], trees=[W.hybrid_tree(32, 8, _rng(L + 3))])
+    got, step = _run(_announced(case, planned), max_ctx_len=planned, split_tokens=split)
+    plan = step.plan.as_dict()
+    assert (plan["row_groups"], plan["tiles_per_wave"]) == (1, 3), plan
+    _close_to_oracle(oracle_mod, case, got, f"L={L} plan={plan}")
+
+
+@pytest.mark.parametrize("split", [0, 1024])
+@pytest.mark.parametrize("entry,bad", [(0, -1), (63, 10 ** 6), (1100, -7), (2002, 10 ** 6)])
+def test_three_tiles_and_a_page_out_of_the_pool(oracle_mod, entry, bad, split):
+    """One wavefront finds the entry in its part of the list asked for ahead and reads the list again: the flag is set, and the
+    rest of the result is that of a table with page 0 in the entry's place."""
+    import dataclasses
+    L = 32000
+    case = W.make_case("three_bad", 77, dtype=W.DT_BF16, Hq=64, Hkv=8, D=128, ctx_lens=[L], trees=[W.hybrid_tree(32, 8, _rng(5))])
+    table = case.page_table.copy()
+    table[0, entry] = bad
+    step = VerifyStep(dataclasses.replace(case, page_table=table), split_tokens=split)
+    assert step.plan.as_dict()["tiles_per_wave"] == 3
+    step.run()
+    got = step.result()
+    assert step.dev_status() == B.OWL_DEV_BAD_PAGE
+    table = table.copy()
+    table[0, entry] = 0
+    _close_to_oracle(oracle_mod, dataclasses.replace(case, page_table=table), got, f"entry {entry} = {bad}")
+
+
 # ---------------------------------------------------------------------------
 # the largest shapes the entry point takes
 # ---------------------------------------------------------------------------
