@@ -508,8 +508,12 @@ __device__ __forceinline__ void row_stats(const GateArgs &a, const GateRow &g, f
     *rstd_out = 1.0f / sqrtf(block_sum(sq, scratch + kGateWaves) / (float)a.d + a.eps);
 }
 
+// (64 rows of 12 chunks are three wavefronts a SIMD: the compiler need not aim for more.  Where it did, it loaded the row in
+// rounds, each a trip to L2.  us of this launch, rows loaded in rounds -> all at once: bf16, 12 chunks, 10 rows 8.0 -> 5.8, 40 rows
+// 9.7 -> 8.3; 16 chunks, 10 rows bf16 9.2 -> 6.2, fp16 6.8 -> 6.0, 64 rows bf16 13.6 -> 12.4.  Others had all of it in flight already
+// and stay as they are: fp16, 12 chunks, 10 rows 5.3.)
 template <bool kF16, int MAXC>
-__global__ void __launch_bounds__(kGateThreads) drafter_state_kernel(GateArgs a)
+__global__ void __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(1, 3))) drafter_state_kernel(GateArgs a)
 {
     __shared__ float scratch[4 * kGateWaves];
     const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
