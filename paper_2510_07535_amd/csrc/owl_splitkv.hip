@@ -506,6 +506,12 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                        auto ntag, auto gtag) {
         constexpr int NA = decltype(ntag)::value;    // tiles this wave really owns
         constexpr bool kGuarded = decltype(gtag)::value;
+        // One tile of bf16 a wavefront: half of the V^T fragments are asked for behind the scores, so that they arrive while P is
+        // formed; the fence keeps the compiler from gathering all of them behind P, which only the exponentials may pass.  us, all
+        // behind P -> half before it: 408 rows, 1 head, 52K / 70K tokens 27.7 -> 27.0 / 33.2 -> 32.3, 496 rows, 60K 30.2 -> 29.5, 240 rows,
+        // 8 heads, 5K 17.1 -> 16.9; up to 64 rows and 8 heads within 0.2 %.  (All of them before it: 33.2 -> 33.1, and 64 rows 0.5 %
+        // longer; fp16's kernel orders them like this by itself.)
+        constexpr bool kEarlyV = TPW == 1 && !kGuard;
         if constexpr (!kF32 && NA > 0) {
             // The score -> softmax -> P chain is the latency-critical part of a step; O += V^T P
             // is throughput work without dependents.  Raising this wave's priority for the
@@ -521,6 +527,11 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 for (int kk = 0; kk < KQ; ++kk) {
                     s0 = mfma16<T>(kf[0][kk], qf[t][kk], s0);
                     s1 = mfma16<T>(kf[1][kk], qf[t][kk], s1);
+                }
+                if constexpr (kEarlyV) {
+#pragma unroll
+                    for (int u = 0; u < NT / 2; ++u) vf[u] = load_v_frag(Vb, u);
+                    __builtin_amdgcn_sched_barrier(0x400);
                 }
                 if constexpr (kGuarded) {
                     // fp16 holds 2^(x - m) only up to 2^16.  The reference stays frozen as long as no
@@ -549,7 +560,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 pf[t].w = pack2<T>(s1[2], s1[3]);
             }
 #pragma unroll
-            for (int u = 0; u < NT; ++u) vf[u] = load_v_frag(Vb, u);
+            for (int u = kEarlyV ? NT / 2 : 0; u < NT; ++u) vf[u] = load_v_frag(Vb, u);
         }
     };
     auto fast_pv = [&](const uint4 (&pf)[TPW], const uint4 (&vf)[NT], auto ntag) {
