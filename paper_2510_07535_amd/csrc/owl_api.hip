@@ -103,24 +103,33 @@ owl_status make_plan(const owl_verify_desc *d, FullPlan *fp)
         const int largest = RT <= 4 ? 3 : (RT <= 8 ? 2 : (RT <= 16 ? 1 : 0));
         int li = largest;
         while (li < 3 && !fills(groups_of(li), d->split_tokens > 0 ? (int64_t)align_up((size_t)d->split_tokens, kSplitQuantum) : cmin)) ++li;
-        // Where splits of 4 R tokens reach that only with more than two groups, a lone sequence takes two all the same if splits
-        // of `least` tokens reach it: more groups re-read the K/V from L2 more often than the longer shares cost.  How far below
-        // 4 R that holds was measured in bf16 against the plan by 4 R (two groups / that plan, at 2 R, 2.5 R, 3.2 R and 4 R):
+        // Where splits of 4 R tokens reach that only with more than two groups, two are taken all the same if splits of `least`
+        // tokens reach it: more groups re-read the K/V from L2 more often than the longer shares cost.  How far below
+        // 4 R that holds was measured against the plan by 4 R.  Lone sequences in bf16, two groups / that plan, at 2 R, 2.5 R, 3.2 R and 4 R:
         //   9-12 tiles, from three groups: 6 heads 1.03 1.02 0.99 0.99, but 1 head 1.04 1.04 1.01 1.00, 3 heads 1.05 1.04 1.02
-        //   1.01 (two groups leave a SIMD two tiles, three groups one; with 1 head a row has 128 partials to merge, not 80);
+        //   1.01 (two groups leave a SIMD two tiles, three groups one; with 1 head a row has 128 partials to merge, not 80).  With 6 to
+        //   8 heads, bf16 and fp16, between 2.75 R and 3.75 R: 9 tiles 0.96-1.02 with no trend, 10 to 12 tiles 0.95-1.02 below and
+        //   0.95-1.00 from 3.3 R on but for one of 30 (1.026);
         //   13-16, from four: 6 heads 0.97 0.94 0.93 0.90, 1 head 1.03 0.99 0.97 0.94, 3 heads 1.02 0.97 0.96 0.93;
+        //   13-20, 1 head, head_dim 64, at 2 R, 2.5 R, 3 R and 3.5 R: 1.03 1.02 0.99 0.97 (few bytes, and again the merge; 22 tiles 0.92);
         //   17-32, from three to six: 0.96 0.94 0.92 0.90, never above 1.006 but for one run;
         //   37-40, and all from five or six: 0.95 0.94 0.92 0.91;
         //   33-36 and 41-48, from three groups of two tiles a wavefront, head_dim 128: 1.05 1.04 1.03 1.02 and 1.01 1.00 1.00 1.00
         //   (a SIMD has two times five or six tiles against three times three or four, in the kernel that spills; with 37-40 it is
         //   two times five against three times four); head_dim 64: 0.96.
-        // In a batch the lengths are bounds, and how sequences fall on the workers decides: 340 plans 0.83 to 1.25, 1.009 on average
-        // (worst: 8 heads, eight sequences of 0.3K-1K, where four groups have a worker for each sequence), so it keeps 4 R.
+        // In a batch the lengths are bounds, and how sequences fall on the workers decides.  500 random batches of 2 to 16, two groups at
+        // 2 R / the plan by 4 R: from three groups 1.02 on average (0.88-1.18), from five 1.01, from six 0.93 (0.81-1.03 but for one
+        // of very uneven lengths 1.13); from four 0.99 (0.86-1.14), but 0.96 (1.05 at most) where the batch in all, without
+        // rounding each sequence up, comes to splits of 3 R.
         const int more = groups_of(li);
-        if (d->split_tokens == 0 && d->batch == 1 && more > 2) {
+        if (d->split_tokens == 0 && more > 2) {
             const bool level = RT >= 37 && RT <= 40, many_heads = d->n_kv_heads >= 6;
             int eighths = 8;                            // of 4 R
-            if (RT <= 12) eighths = many_heads ? 6 : 8;
+            if (d->batch > 1) {
+                const bool enough = 4 * (int64_t)d->batch * T * d->n_kv_heads * 2 >= 3 * (int64_t)device_cus() * (cmin * 6 / 8);
+                if (more >= 6 || (more == 4 && enough)) eighths = 4;
+            } else if (RT <= 12) eighths = !many_heads || RT == 9 ? 8 : 7;
+            else if (RT <= 20 && d->head_dim == 64 && d->n_kv_heads == 1) eighths = 6;
             else if (RT <= 16) eighths = many_heads ? 4 : 5;
             else if (RT <= 32 || more > 3 || level || d->head_dim == 64) eighths = 4;
             int two = largest;

@@ -73,17 +73,21 @@ def test_plan_row_groups_and_tiles_a_wavefront(n, group, hkv, batch, ctx, groups
 
 
 @pytest.mark.parametrize("n,group,hkv,d,batch,ctx,groups", [
-    (18, 8, 8, 128, 1, 4000, 3), (18, 8, 8, 128, 1, 4600, 3), (18, 8, 8, 128, 1, 5000, 2), (20, 8, 3, 128, 1, 19000, 3),   # 9, 10 tiles
+    (18, 8, 8, 128, 1, 4000, 3), (18, 8, 8, 128, 1, 6200, 3), (18, 8, 8, 128, 1, 6400, 2), (20, 8, 8, 128, 1, 6000, 3),     # 9, 10 tiles
+    (20, 8, 8, 128, 1, 6400, 2), (20, 8, 3, 128, 1, 19000, 3),
     (60, 4, 8, 128, 1, 5300, 2), (60, 4, 1, 128, 1, 46500, 4), (60, 4, 1, 128, 1, 58200, 2),                                # 15
-    (60, 4, 8, 128, 2, 3400, 4), (60, 4, 8, 128, 8, 900, 4), (60, 4, 8, 128, 8, 700, 4),
+    (60, 4, 1, 64, 1, 58200, 4), (60, 4, 1, 64, 1, 70000, 2),
+    (60, 4, 8, 128, 2, 3400, 4), (60, 4, 8, 128, 2, 4600, 2), (60, 4, 8, 128, 8, 900, 4), (60, 4, 8, 128, 8, 1100, 2), (60, 4, 8, 128, 8, 700, 4),
     (40, 8, 8, 128, 1, 7200, 2), (40, 8, 8, 128, 1, 9000, 2), (40, 8, 8, 128, 2, 3300, 5), (40, 8, 8, 128, 4, 1800, 3),     # 20
-    (40, 8, 8, 128, 8, 900, 3), (60, 8, 8, 128, 8, 1300, 4), (60, 8, 8, 128, 1, 15000, 2),                                  # 30
+    (40, 8, 1, 64, 1, 80000, 5), (40, 8, 1, 64, 1, 93000, 2),
+    (43, 8, 8, 128, 3, 2000, 6), (43, 8, 8, 128, 3, 2421, 2), (44, 8, 1, 64, 1, 70000, 2),                                  # 22
+    (40, 8, 8, 128, 8, 900, 3), (60, 8, 8, 128, 8, 1300, 4), (60, 8, 8, 128, 8, 2200, 2), (60, 8, 8, 128, 1, 15000, 2),     # 30
     (33, 16, 8, 128, 1, 12000, 2), (33, 16, 8, 128, 1, 18000, 3), (33, 16, 8, 64, 1, 18000, 2), (33, 16, 8, 128, 1, 26000, 2),
     (40, 16, 8, 128, 1, 18000, 2), (40, 16, 8, 128, 2, 10000, 3), (40, 16, 8, 128, 8, 2000, 3), (48, 16, 8, 128, 1, 27000, 3),
 ])
 def test_two_row_groups_where_they_gain(n, group, hkv, d, batch, ctx, groups):
-    """Two row groups are preferred to more below splits of 4 R tokens in a lone sequence, except where they leave the matrix
-    cores more to do than three (9-12 row tiles, 33-36 and 41-48 with head_dim 128), and never in a batch."""
+    """Two row groups are preferred to more below splits of 4 R tokens, in a lone sequence except where they leave the matrix
+    cores more to do than three (9-12 row tiles, 33-36 and 41-48 with head_dim 128), in a batch only to four and to six."""
     p = B.owl_verify_attn_plan(_good(n_draft=n, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, batch=batch, max_ctx_len=ctx,
                                      max_pages_per_seq=(ctx + n + 15) // 16, kv_stride_page=hkv * 16 * d, kv_stride_head=16 * d,
                                      kv_stride_token=d))
