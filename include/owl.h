@@ -136,7 +136,8 @@ typedef struct owl_plan {
 /* Fill *plan for `desc` on the current device.  Host only, no launch. */
 owl_status owl_verify_attn_plan(const owl_verify_desc *desc, owl_plan *plan);
 
-/* Bytes of device scratch owl_verify_attn needs for `desc` (split partials). */
+/* Bytes of device scratch owl_verify_attn needs for `desc` (split partials).
+ * They follow from the plan: ask again for another `desc` or another build. */
 owl_status owl_verify_attn_workspace_size(const owl_verify_desc *desc, size_t *bytes);
 
 /*

@@ -227,9 +227,9 @@ struct Ahead {
 };
 
 // The kernel's arguments for one piece.  In fp16, whose second (guarded) loop takes more scalar registers, they are read
-// again from the kernel-argument segment: kept across the pieces they made 36-79 scalar registers spill (0-13 now) and
+// again from the kernel-argument segment: kept across the pieces they made 36-79 scalar registers spill (3-16 so) and
 // cost a call of 3K-7K tokens 0.2-0.4 us of 11-13 (head_dim 64, 8 KV heads, 4 rows, 3K: 11.5 -> 11.1 us).  The bf16
-// kernels spill half of that and lose by reading again (16 sequences of 8K-64K, 104 rows: 452 -> 457 us).
+// kernels spill 21-58 and lose by reading again (16 sequences of 8K-64K, 104 rows: 452 -> 457 us).
 template <typename T>
 __device__ __forceinline__ const KParams &piece_args(const KParams &launch_args)
 {
