@@ -187,8 +187,10 @@ struct Piece {
 // the loops of some kernels leave no register for it: in the three-tile kernel it went to scratch memory, and every reload
 // between the requests of the first stages waited for all of them (128K hybrid, 320 rows 167.5 us against 172.3 with the
 // number kept, 8 sequences of 500-3K 39.0 against 47.7; fp32, head_dim 128, 512 tokens 13.6 against 16.3).  With one tile of 16
-// bits there is room, and what follows from the number is then not derived again in the loops (320 rows, 1 head, 10K tokens, in
-// row groups of one tile a wavefront 14.39 us anew, 14.22 kept; 160 rows 12.98 and 12.82).  Two tiles: within 1 % either way.
+// bits and two key groups there is room, and what follows from the number is then not derived again in the loop (320 rows, 1 head,
+// 10K tokens, in row groups 14.39 us anew, 14.22 kept; 160 rows 12.98 and 12.82).  With one tile and the pipelined loop keeping it loses in
+// batches, more the more pieces a share has (96 rows, 8 sequences of 1K-6.4K 18.5 us anew, 19.3 kept; 116 rows, 8 of 1.2K-2.5K 24.4
+// and 25.0; fp16, 100 rows, 16 of 700-2K 21.5 and 21.7).  Two tiles: within 1 % either way.
 template <bool kAnew>
 __device__ __forceinline__ int lane_number()
 {
@@ -278,7 +280,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // pieces of a share (as the compiler would by itself) it does not fit the registers of the loops.
     const KParams &p = piece_args<T>(launch_args);
     asm volatile("" : "+s"(g), "+s"(rg), "+s"(wave));
-    const int lane = lane_number<(TPW > 1) || kF32>(), tid = wave * 64 + lane;
+    const int lane = lane_number<(TPW > 1) || WK == 1>(), tid = wave * 64 + lane;
     const int wr = wave % WR, wk = wave / WR;
     const int j = lane & 15, qd = lane >> 4;
 
