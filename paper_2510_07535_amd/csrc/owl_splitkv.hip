@@ -344,6 +344,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     for (int first = 2 * kThreads; first < npg; first += 2 * kThreads)           // more than 16K tokens in one piece
         keep_pages(load_pages(p, tid, b, pos0, first), first);
     if (has_drafts && !(kKeptEarly && ahead.parents) && tid < p.N) s_parent[tid] = parent;
+    if (std::is_same<T, _Float16>::value && tid < 2) s_any[tid] = 0;
     __syncthreads();
     stamp(1);
 
@@ -362,6 +363,11 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     const int ld_piece = lane % PPR, ld_row = lane / PPR;
     const int64_t head_off = (int64_t)g * p.stride_head * ES;
     const int64_t tok_bytes = p.stride_token * ES;
+    // (Held in their registers: fp16's arguments are in memory, and left to the compiler every stage of its loops loaded the
+    // stride again, every masked step the scale, and waited for it, and with it for all LDS reads under way.)
+    int64_t page_bytes = p.stride_page * ES;
+    float c_log2 = p.c_log2;
+    if constexpr (std::is_same<T, _Float16>::value) asm volatile("" : "+s"(page_bytes), "+s"(c_log2));
 
     // A whole page (every stage but the split's last page) needs no clamping:
     // the lane's byte offsets inside the page are fixed, only the page base
@@ -387,7 +393,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         const uint32_t lds_dst = ld_lds + buf * STAGE;
         if (pgx_raw < last_pgx && ld_off_ok) {           // uniform over the wave
             const int64_t pg = __builtin_amdgcn_readfirstlane(pg_lane);
-            const uint64_t sb = (uint64_t)(uintptr_t)ld_base + (uint64_t)(pg * p.stride_page * ES + head_off);
+            const uint64_t sb = (uint64_t)(uintptr_t)ld_base + (uint64_t)(pg * page_bytes + head_off);
             const uint64_t sbase = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(sb >> 32)) << 32) |
                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sb);
 #pragma unroll
@@ -397,7 +403,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             return;
         }
         const int slot_max = pgx_raw >= last_pgx ? last_slot : kPage - 1;
-        const int64_t base = (int64_t)pg_lane * p.stride_page * ES + head_off;
+        const int64_t base = (int64_t)pg_lane * page_bytes + head_off;
 #pragma unroll
         for (int it = 0; it < LPS; ++it) {
             const int row = it * RPI + ld_row;
@@ -493,11 +499,9 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     };
 
     // ---- fast step: no mask, fixed reference m, accumulators touched by MFMA only ----
-    // fp16 storage: a workgroup whose first step shows a wide spread of scores takes the plain loop
-    // with a guarded reference (see fast_sx) instead of the frozen one; the choice only affects
-    // speed (a frozen reference that overflows is caught by the row sums and the split redone)
+    // fp16 storage: a frozen reference that overflows shows in the row sums.  The loops look for it at a few stages (see
+    // `watched`) and give way to the plain loop with a guarded reference (see fast_sx).
     constexpr bool kGuard = std::is_same<T, _Float16>::value;
-    bool use_guard = false;
     // p = 2^(x - m) is exact in relative terms whatever m is; with m frozen at
     // the first step's row maximum, p overflows only if a later score exceeds
     // it by more than ~100 (log2 units), which the row sum exposes afterwards.
@@ -508,12 +512,12 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                        auto ntag, auto gtag) {
         constexpr int NA = decltype(ntag)::value;    // tiles this wave really owns
         constexpr bool kGuarded = decltype(gtag)::value;
-        // One tile of bf16 a wavefront: half of the V^T fragments are asked for behind the scores, so that they arrive while P is
+        // One tile a wavefront: half of the V^T fragments are asked for behind the scores, so that they arrive while P is
         // formed; the fence keeps the compiler from gathering all of them behind P, which only the exponentials may pass.  us, all
         // behind P -> half before it: 408 rows, 1 head, 52K / 70K tokens 27.7 -> 27.0 / 33.2 -> 32.3, 496 rows, 60K 30.2 -> 29.5, 240 rows,
         // 8 heads, 5K 17.1 -> 16.9; up to 64 rows and 8 heads within 0.2 %.  (All of them before it: 33.2 -> 33.1, and 64 rows 0.5 %
-        // longer; fp16's kernel orders them like this by itself.)
-        constexpr bool kEarlyV = TPW == 1 && !kGuard;
+        // longer.  fp16 with the frozen reference: 7K 20.5 -> 20.4.)
+        constexpr bool kEarlyV = TPW == 1 && !kGuarded;
         if constexpr (!kF32 && NA > 0) {
             // The score -> softmax -> P chain is the latency-critical part of a step; O += V^T P
             // is throughput work without dependents.  Raising this wave's priority for the
@@ -542,8 +546,8 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                     const float tm = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
                                            fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
                     // detection needs no cross-lane step: any lane's own keys can raise the alarm
-                    if (__builtin_amdgcn_ballot_w64(__builtin_fmaf(tm, p.c_log2, -m[t]) > 11.0f) != 0) {
-                        const float sc = quad_column_max(tm) * p.c_log2;
+                    if (__builtin_amdgcn_ballot_w64(__builtin_fmaf(tm, c_log2, -m[t]) > 11.0f) != 0) {
+                        const float sc = quad_column_max(tm) * c_log2;
                         const float mn = sc > m[t] + 11.0f ? sc + 4.0f : m[t];
                         const float alpha = fast_exp2(m[t] - mn);
                         m[t] = mn;
@@ -553,8 +557,8 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    s0[r] = fast_exp2(__builtin_fmaf(s0[r], p.c_log2, -m[t]));
-                    s1[r] = fast_exp2(__builtin_fmaf(s1[r], p.c_log2, -m[t]));
+                    s0[r] = fast_exp2(__builtin_fmaf(s0[r], c_log2, -m[t]));
+                    s1[r] = fast_exp2(__builtin_fmaf(s1[r], c_log2, -m[t]));
                 }
                 pf[t].x = pack2<T>(s0[0], s0[1]);
                 pf[t].y = pack2<T>(s0[2], s0[3]);
@@ -669,7 +673,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 static_for<done1, done2>([&](auto ii) {
                     constexpr int idx = decltype(ii)::value;
                     constexpr int t = idx >> 3, kt = (idx >> 2) & 1, r = idx & 3;
-                    float e = fast_exp2(__builtin_fmaf(Sc[t][kt][r], p.c_log2, -m[t]));
+                    float e = fast_exp2(__builtin_fmaf(Sc[t][kt][r], c_log2, -m[t]));
                     asm volatile("" : "+v"(e));          // pins the computation of the value to this group
                     Sc[t][kt][r] = e;
                 });
@@ -688,6 +692,38 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         }
     };
 
+    // ---- fp16 only: is the frozen reference good? ----
+    // A wavefront that finds it is not raises an alarm, which all read behind a later barrier: before the loops, if the scores of
+    // its first step span more than 2^14 in some lane (ten standard deviations of the scores of unit-variance inputs: a long
+    // tail, and a later score is likely to pass the head room above the first step's maximum); in the pipelined loop, also if those
+    // of the second do; and at the barriers of stages 4, 16, 64, ... of a frozen loop, if a row sum has overflowed.  A guarded
+    // loop then takes over, from the start.  What the last look misses the check behind the loops finds.  (Two words, one for before the loops and one for within: no
+    // wavefront writes a word that another may still have to read.)  Before, every piece formed the scores of its first one
+    // to three stages twice to measure their spread, and an overflow was redone with the exact loop.  us, 8 heads: 24 rows, 2.5K tokens
+    // 10.8 -> 10.5, 64 rows, 20K 24.8 -> 21.6, 240 rows, 5K / 20K 18.0 -> 17.9 / 34.9 -> 34.1, four sequences of 900-9K 35.0 -> 33.2; with one
+    // key in twenty eight times as long, 240 rows, 5K / 20K 19.4 -> 19.1 / 40.6 -> 40.8, 16 sequences of 900-4K 109 -> 81, but 320
+    // rows, 64K 112 -> 116: the three-tile kernel sees 32 keys before its loop, where it saw 192.  (Looks at 8, 32, ... as well:
+    // 240 rows, 5K 17.9 -> 18.0.)
+    auto alarm = [&](bool bad, int word) {
+        if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_any[word] = 1;
+    };
+    auto alarmed = [&](int word) -> bool { return __builtin_amdgcn_readfirstlane(s_any[word]) != 0; };
+    auto watch_sums = [&]() {
+        bool bad = false;
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) bad |= !(O[t][NT][0] < 1.0e30f);
+        alarm(bad, 1);
+    };
+    auto watched = [](int s) { return (s & (s - 1)) == 0 && (s & 0x2AAAAAAB) == 0; };       // 0, 4, 16, 64, ...
+    auto is_wide = [&](const f32x4 &s0, const f32x4 &s1, float high) {
+        const float low = fminf(fminf(fminf(s0[0], s0[1]), fminf(s0[2], s0[3])),
+                                fminf(fminf(s1[0], s1[1]), fminf(s1[2], s1[3])));
+        return (high - low) * c_log2 > 14.0f;
+    };
+    auto highest = [](const f32x4 &s0, const f32x4 &s1) {
+        return fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])), fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
+    };
+
     // ---- reference m of every row tile from one unmasked step (before the fast loop) ----
     auto init_reference = [&](int buf, int ks, f32x4 (&keep)[TPW][2]) {
         if constexpr (!kF32) {
@@ -698,6 +734,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             const unsigned char *Kb = smem + off;
             uint4 kf[2][KQ];
             load_k_frags(Kb, kf);
+            bool wide = false;
 #pragma unroll
             for (int t = 0; t < TPW; ++t) {
                 f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -708,12 +745,13 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 }
                 keep[t][0] = s0;
                 keep[t][1] = s1;
-                const float tm = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                                       fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
+                const float tm = highest(s0, s1);
                 // fp16 holds 2^(x - m) only up to 2^16: its reference sits a little above the
                 // first step's maximum, which trades low-end resolution for head room
-                m[t] = quad_column_max(tm) * p.c_log2 + (std::is_same<T, _Float16>::value ? 4.0f : 0.0f);
+                m[t] = quad_column_max(tm) * c_log2 + (kGuard ? 4.0f : 0.0f);
+                if constexpr (kGuard) wide |= is_wide(s0, s1, tm);
             }
+            if constexpr (kGuard) alarm(wide, 0);
         }
     };
 
@@ -738,15 +776,15 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         float tm = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
                          fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
         tm = quad_column_max(tm);
-        const float mn = fmaxf(m[t], tm * p.c_log2);
+        const float mn = fmaxf(m[t], tm * c_log2);
         const float alpha = fast_exp2(m[t] - mn);
         m[t] = mn;
 #pragma unroll
         for (int u = 0; u <= NT; ++u) O[t][u] *= alpha;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            s0[r] = fast_exp2(__builtin_fmaf(s0[r], p.c_log2, -m[t]));
-            s1[r] = fast_exp2(__builtin_fmaf(s1[r], p.c_log2, -m[t]));
+            s0[r] = fast_exp2(__builtin_fmaf(s0[r], c_log2, -m[t]));
+            s1[r] = fast_exp2(__builtin_fmaf(s1[r], c_log2, -m[t]));
         }
     };
 
@@ -857,6 +895,8 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             }
         }
     };
+    // A fast loop returns n_fast, or the stage at whose barrier the alarm was seen: its last.
+
     // fast stages [0, n_fast); the caller has admitted stage 0.
     // The two waves of a SIMD (w and w + 4) would run in lockstep if both took
     // the per-stage barrier at the same place in their instruction stream, and
@@ -866,22 +906,28 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // ring slot is free all the same) across the barrier.  After every barrier
     // the two waves of a SIMD are then half a step apart, and one's matrix work
     // overlaps the other's vector work.
-    auto run_fast_n = [&](int n_fast, auto ntag, auto gtag) {
+    auto run_fast_n = [&](int n_fast, auto ntag, auto gtag) -> int {
         if constexpr (!kF32) {
+            constexpr bool kWatch = kGuard && !decltype(gtag)::value;
             const bool late = wave >= kWaves / 2;
             auto kptr = [&](int s, int ks) -> const unsigned char * {
                 return smem + (s % NS) * STAGE + ks * 32 * ROWB;
             };
+            int end = n_fast;
             auto admit = [&](int s) {
+                if constexpr (kWatch)
+                    if (watched(s)) watch_sums();
                 wait_stage(s);
                 __syncthreads();     // stage s is in; all LDS reads of stage s-1 have completed
+                if constexpr (kWatch)
+                    if (watched(s) && alarmed(1)) end = s;
                 if (issued < nstages) {
                     issue_stage(issued);
                     ++issued;
                 }
             };
             uint4 pf[TPW], vf[NT];
-            for (int s = 0; s < n_fast; ++s) {
+            auto stage = [&](int s) {
                 if constexpr (WK == 1) {
                     if (s > 0) {
                         if (!late) fast_pv(pf, vf, ntag);       // early waves finish stage s-1 first
@@ -899,15 +945,25 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                     }
                     fast_sx(kptr(s, wk), kptr(s, wk) + VREG, pf, vf, ntag, gtag);
                 }
+            };
+            if constexpr (kGuard && (TPW > 1 || !kWatch)) {
+#pragma unroll 1                                             // (with their first stages peeled off, these loops' kernels spill)
+                for (int s = 0; s < end; ++s) stage(s);
+            } else {
+                for (int s = 0; s < end; ++s) stage(s);
             }
             fast_pv(pf, vf, ntag);
+            return end;
+        } else {
+            return 0;
         }
     };
     // Pipelined fast stages [0, n_fast); the caller has admitted stage 0 and Sa
     // holds the scores of step 0.  V of a step is read one iteration after its
     // K, so a ring slot is refilled one stage later than in the plain loop: at
     // the barrier in front of step 2s+1 every wave is done with stage s-1.
-    auto run_pipe_n = [&](int n_fast, f32x4 (&Sa)[TPW][2], auto ntag) {
+    auto run_pipe_n = [&](int n_fast, f32x4 (&Sa)[TPW][2], auto ntag) -> int {
+        int end = n_fast;
         if constexpr (kPipe) {
             constexpr int NA = decltype(ntag)::value;
             using yes = std::true_type;
@@ -924,17 +980,28 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             // step 0: P of step 0, scores of step 1; no V^T P yet
             pipe_iter(Sa, Sb, Pb, Pa, vpre, std::integral_constant<uint32_t, 0>{},
                       std::integral_constant<uint32_t, 32 * ROWB>{}, std::integral_constant<uint32_t, 0>{}, no{}, ntag);
-            for (int s4 = 0; s4 < n_fast; s4 += NS) {
+            if constexpr (kGuard) {
+                bool wide = false;
+#pragma unroll
+                for (int t = 0; t < NA; ++t) wide |= is_wide(Sb[t][0], Sb[t][1], highest(Sb[t][0], Sb[t][1]));
+                alarm(wide, 1);
+            }
+            for (int s4 = 0; s4 < end; s4 += NS) {
                 static_for<0, NS>([&](auto bb) {
                     constexpr uint32_t B = decltype(bb)::value, B1 = (B + 1) % NS;
                     constexpr uint32_t cur0 = B * STAGE, cur1 = B * STAGE + 32 * ROWB;
                     constexpr uint32_t nxt0 = B1 * STAGE, nxt1 = B1 * STAGE + 32 * ROWB;
                     const int s = s4 + (int)B;
-                    if (s < n_fast) {                                   // uniform
+                    if (s < end) {                                      // uniform
                         // stage s+1 in; every wave is done with stage s-1: refill its slot
                         const int pg = stage_page(issued);
+                        constexpr bool kLook = kGuard && B == 0;
+                        if constexpr (kLook)
+                            if (s > 0 && watched(s)) watch_sums();
                         wait_stage(s + 1);
                         __syncthreads();
+                        if constexpr (kLook)
+                            if (watched(s) && alarmed(1)) end = s;
                         if (issued < nstages && issued <= s + NS - 1) {
                             issue_stage_pg(issued, pg);
                             ++issued;
@@ -953,68 +1020,26 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 });
             }
         }
-    };
-    // fp16 only: which fast loop?  The scores of the stages already requested (up to 192 keys)
-    // are formed once more, without the softmax; if some lane's keys span more than 2^14 (ten
-    // standard deviations of the scores of unit-variance inputs: no false alarm in 10^5 lanes) the
-    // scores have a long tail, a later one is likely to pass the head room above the first
-    // step's maximum, and the workgroup takes the guarded loop.  A wrong guess costs time only.
-    auto probe_spread = [&](int n_fast) {
-        if constexpr (kGuard) {
-            float lo[TPW], hi[TPW];
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) lo[t] = INFINITY, hi[t] = -INFINITY;
-            // stage `issued - 1` may still be in flight; a short split is probed less
-            const int n_probe = min(min(n_fast, issued - 1), max(1, n_fast / 16));
-            for (int sb = 0; sb < n_probe; ++sb) {
-                if (sb > 0) {
-                    wait_stage(sb);
-                    __syncthreads();
-                }
-#pragma unroll
-                for (int ks = 0; ks < KSTEPS; ++ks) {
-                    uint4 kf[2][KQ];
-                    load_k_frags(smem + sb * STAGE + ks * 32 * ROWB, kf);
-#pragma unroll
-                    for (int t = 0; t < TPW; ++t) {
-                        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int kk = 0; kk < KQ; ++kk) {
-                            s0 = mfma16<T>(kf[0][kk], qf[t][kk], s0);
-                            s1 = mfma16<T>(kf[1][kk], qf[t][kk], s1);
-                        }
-                        hi[t] = fmaxf(hi[t], fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                                                   fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3]))));
-                        lo[t] = fminf(lo[t], fminf(fminf(fminf(s0[0], s0[1]), fminf(s0[2], s0[3])),
-                                                   fminf(fminf(s1[0], s1[1]), fminf(s1[2], s1[3]))));
-                    }
-                }
-            }
-            bool wide = false;
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) wide |= (hi[t] - lo[t]) * p.c_log2 > 14.0f;
-            use_guard = workgroup_any(wide, wave, lane, s_any);
-        }
+        return end;
     };
     // the fast loop is compiled once per possible tile count of a wave, so that
     // its body has no per-tile branches
-    auto run_fast_tag = [&](int n_fast, f32x4 (&Sa)[TPW][2], auto ntag) {
-        if constexpr (kGuard) {
-            if (use_guard) {                          // uniform over the workgroup
-                run_fast_n(n_fast, ntag, std::true_type{});
-                return;
-            }
+    auto run_fast_tag = [&](int n_fast, bool guarded, f32x4 (&Sa)[TPW][2], auto ntag) -> int {
+        if constexpr (kGuard)
+            if (guarded) return run_fast_n(n_fast, ntag, std::true_type{});      // uniform over the workgroup
+        if constexpr (kPipe) {
+            return run_pipe_n(n_fast, Sa, ntag);
+        } else {
+            return run_fast_n(n_fast, ntag, std::false_type{});
         }
-        if constexpr (kPipe) run_pipe_n(n_fast, Sa, ntag);
-        else run_fast_n(n_fast, ntag, std::false_type{});
     };
-    auto run_fast = [&](int n_fast, f32x4 (&Sa)[TPW][2]) {
-        if (my_nt == TPW) run_fast_tag(n_fast, Sa, std::integral_constant<int, TPW>{});
-        else if (TPW > 1 && my_nt == TPW - 1)
-            run_fast_tag(n_fast, Sa, std::integral_constant<int, (TPW > 1 ? TPW - 1 : 0)>{});
-        else if (TPW > 2 && my_nt == TPW - 2)
-            run_fast_tag(n_fast, Sa, std::integral_constant<int, (TPW > 2 ? TPW - 2 : 0)>{});
-        else run_fast_tag(n_fast, Sa, std::integral_constant<int, 0>{});
+    auto run_fast = [&](int n_fast, bool guarded, f32x4 (&Sa)[TPW][2]) -> int {
+        if (my_nt == TPW) return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, TPW>{});
+        if (TPW > 1 && my_nt == TPW - 1)
+            return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, (TPW > 1 ? TPW - 1 : 0)>{});
+        if (TPW > 2 && my_nt == TPW - 2)
+            return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, (TPW > 2 ? TPW - 2 : 0)>{});
+        return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, 0>{});
     };
     static_assert(TPW <= 3, "run_fast dispatches on at most three tile counts");
 
@@ -1023,12 +1048,13 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
 
     // Pass 0: stages that lie wholly inside the prefix run the fast step with a
     // frozen reference; the rest (drafts, ragged end) run the careful step.
-    // Pass 1 happens only if a row sum of pass 0 is not a modest finite number:
-    // the whole split is redone with the careful step.  bf16 shares fp32's
-    // exponent range, so that happens only for scores ~100 above the reference;
-    // an fp16 P overflows 12 above it (and the redo is then the price).  fp32 is
-    // the small correctness shape and has no fast loop.
+    // The last pass happens only if a row sum of the one before is not a modest finite
+    // number: the whole split is redone with the careful step.  bf16 shares fp32's
+    // exponent range, so that happens only for scores ~100 above the reference.
+    // An fp16 P overflows 16 above it: fp16 has a pass between the two, the fast loop
+    // with a guarded reference.  fp32 is the small correctness shape and has no fast loop.
     constexpr bool kHasFast = !kF32;
+    constexpr int kPasses = kGuard ? 3 : 2;
     // With one tile a wavefront the piece is bound by its K/V, and all that the ring holds is requested at once.  With more it
     // is bound by the loop, which should begin early: when every workgroup asks for its whole ring at the same time, stage 0
     // arrives in the middle of 33 MB (4 us), so the first stages go out one after the other, behind the queries (320 rows,
@@ -1061,25 +1087,51 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             __syncthreads();
         }
     }
-    for (int pass = 0; pass < 2; ++pass) {
+    [[maybe_unused]] bool kept = false;               // (fp16) the ring still holds the first stages
+    for (int pass = 0; pass < kPasses; ++pass) {
+        if constexpr (kGuard) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                m[t] = kMInit;
+#pragma unroll
+                for (int u = 0; u <= NT; ++u) O[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
         int n_fast = 0;
-        if (kHasFast && pass == 0) n_fast = max(0, min(nstages, (L - pos0) / SK));
-        if (pass == 1) issued = 0;                    // the redo pass starts over
+        if (kHasFast && pass < kPasses - 1) n_fast = max(0, min(nstages, (L - pos0) / SK));
+        if (pass > 0 && !(kGuard && kept)) issued = 0;        // a redo starts over
         // (the careful loop begins by filling the last slot itself)
         for (const int fill = n_fast > 0 ? NS : NS - 1; issued < fill && issued < nstages; ++issued) issue_stage(issued);
         if (n_fast > 0) {
             stamp(2);
             f32x4 Sa[TPW][2];
+            if constexpr (kGuard) {
+                if (pass == 1 && !kept) {
+                    wait_stage(0);
+                    __syncthreads();
+                }
+            }
             init_reference(0, wk, Sa);
-            probe_spread(n_fast);
-            run_fast(n_fast, Sa);
+            if constexpr (kGuard) {
+                __syncthreads();
+                if (alarmed(0)) pass = 1;              // uniform over the workgroup
+            }
+            [[maybe_unused]] const int end = run_fast(n_fast, pass == 1, Sa);
+            if constexpr (kGuard) {
+                kept = end == 0;
+                if (end < n_fast) {                   // a redo begins once no transfer is under way and no wavefront reads the ring
+                    if (!kept) wait_vmcnt<0>();
+                    __syncthreads();
+                    continue;
+                }
+            }
         } else {
             stamp(2);
         }
         stamp(3);
         run_careful(n_fast, nstages);
         stamp(4);
-        if (!kHasFast || pass == 1) break;
+        if (!kHasFast || pass == kPasses - 1) break;
         bool bad = false;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) bad |= !(O[t][NT][0] < 1.0e30f);

@@ -540,15 +540,38 @@ def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n, dealt):
                                            (0.02, 3.0, "mild tail: frozen reference holds")])
 @pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # 2 / 15 / 20 row tiles: all three fast loops
 def test_fp16_score_range_paths(oracle_mod, frac, gain, tag, N, G):
-    """fp16 probabilities overflow 2^16 above their reference.  The kernel probes the first stages of
-    a split and takes a loop with a guarded (moving) reference if the scores already show a long
-    tail; otherwise it freezes the reference and, should a later score overflow it after all,
-    redoes the split with the exact loop.  All three routes must give the oracle's result."""
+    """fp16 probabilities overflow 2^16 above their reference.  The kernel takes a loop with a guarded (moving) reference if the
+    scores of a split's first keys already show a long tail; otherwise it freezes the reference and, should a later score
+    overflow it after all, redoes the split with the guarded loop.  All routes must give the oracle's result."""
     r = _rng(77 + N)
     case = W.make_case("f16range", 910 + N, dtype=W.DT_F16, Hq=2 * G, Hkv=2, D=128, ctx_lens=[9000, 700],
                        trees=[W.random_tree(N, 6, r) for _ in range(2)], outlier_frac=frac, outlier_gain=gain)
     got, step = _run(case)
     assert_close(got, oracle_mod.verify_attn_case(case), case.dtype, f"{tag}, N={N} G={G}")
+
+
+@pytest.mark.parametrize("N,G,D", [(6, 4, 128), (60, 4, 64), (26, 4, 128), (60, 4, 128), (40, 8, 128)])     # 2, 15, 7, 15, 20 row tiles
+def test_fp16_overflow_found_at_every_look(oracle_mod, N, G, D):
+    """A frozen fp16 loop looks for overflowed row sums at stages 4, 16, 64, ..., and once more behind its last stage.  Each split here has one key that overflows the reference, in another place: the second step, the stages
+    around a look, the last fast stage.  The first split has none."""
+    C, L = 1280, 8 * 1280 + 100
+    hot = [s * C + 64 * stage + slot for s, (stage, slot) in enumerate([(0, 40), (1, 9), (3, 63), (4, 0), (15, 40), (16, 3), (19, 63)], 1)]
+    case = W.make_case("f16_looks", 950 + N + D, dtype=W.DT_F16, Hq=2 * G, Hkv=2, D=D, ctx_lens=[L], trees=[W.random_tree(N, 6, _rng(N))])
+    for pos in hot:
+        page = int(case.page_table[0, pos // 16])
+        row = W.widen(case.k_pool[page, :, pos % 16, :], W.DT_F16) * 32.0
+        case.k_pool[page, :, pos % 16, :] = W.store(row.astype(np.float32), W.DT_F16)
+    # the premise, from the stored values: some row's score lies 2^20 or more above its reference (4 above the first keys)
+    q, c = W.widen(case.q[0], W.DT_F16), case.scale * 1.4426950408889634
+    for pos in hot[1:]:
+        at = np.append(np.arange(pos // C * C, pos // C * C + 64), pos)
+        keys = W.widen(case.k_pool[case.page_table[0, at // 16], :, at % 16, :], W.DT_F16)          # [65, Hkv, D]
+        x = np.stack([c * q[:, h] @ keys[:, h // G].T for h in range(case.Hq)])                       # [Hq, N, 65]
+        assert (x[..., -1] - x[..., :-1].max(axis=-1)).max() > 21.0
+    want = oracle_mod.verify_attn_case(case)
+    for split in (C, 0):
+        got, step = _run(case, split_tokens=split)
+        assert_close(got, want, case.dtype, f"N={N} G={G} D={D} split={split} plan={step.plan.as_dict()}")
 
 
 @pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # 2 / 15 / 20 row tiles: all three fast loops
