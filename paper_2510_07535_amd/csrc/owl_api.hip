@@ -434,6 +434,7 @@ static owl_status verify_impl(const owl_verify_desc *desc, const void *q, const 
     p.C = fp.pub.split_tokens; p.max_splits = fp.pub.max_splits;
     p.dealt = fp.dealt ? 1 : 0; p.rule = fp.rule; p.n_slots = fp.n_slots;
     p.full = fp.full;
+    p.full_pieces = fp.dealt ? deal_worker(fp.full, stages_of((int)(desc->max_ctx_len + desc->n_draft)) - 1) + 1 : 0;
     p.RT = fp.pub.row_tiles; p.row_groups = fp.pub.row_groups; p.group_tiles = fp.group_tiles;
     p.stride_page = desc->kv_stride_page; p.stride_head = desc->kv_stride_head;
     p.stride_token = desc->kv_stride_token; p.n_pool_pages = desc->n_pool_pages;

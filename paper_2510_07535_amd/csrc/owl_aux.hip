@@ -14,7 +14,7 @@ namespace owl {
 // [slot][u][lane] = channels 16*u + 4*quad .. +3 of row lane%16.  For 16-bit
 // inputs (HALF) a row of a partial is stored normalised, O_s / (l_s s_s) with s_s
 // its largest magnitude, as fp16: uint4 [slot][u/2][lane] holds the lane's four
-// channels of tiles u and u + 1; the weight of split s is then 2^(m_s - M) l_s s_s.
+// channels of tiles u and u + 1; the weight of split s is then 2^(m_s - M) w_s, w_s = l_s s_s.
 //
 // Two ways to spread the work, chosen by the launch:
 //   few sequences  One workgroup per (sequence, KV head, 16-row tile, pair of channel tiles); its WAVES
@@ -27,13 +27,39 @@ namespace owl {
 // ---------------------------------------------------------------------------
 typedef _Float16 c_f16x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ float2 unpack_half2(uint32_t w)
+struct RowStats {                                    // of a row of a partial, as the split-KV pass leaves them (kPartMl)
+    float m, l, w;
+};
+
+// acc += c * (the four values of one channel tile), each product and sum in fp32.
+__device__ __forceinline__ void add_scaled(float4 &acc, float c, uint32_t lo, uint32_t hi)
 {
-    const c_f16x2 h = __builtin_bit_cast(c_f16x2, w);
-    return make_float2((float)h[0], (float)h[1]);
+    const c_f16x2 a = __builtin_bit_cast(c_f16x2, lo), b = __builtin_bit_cast(c_f16x2, hi);
+    acc.x = __builtin_fmaf((float)a[0], c, acc.x);
+    acc.y = __builtin_fmaf((float)a[1], c, acc.y);
+    acc.z = __builtin_fmaf((float)b[0], c, acc.z);
+    acc.w = __builtin_fmaf((float)b[1], c, acc.w);
+}
+__device__ __forceinline__ void add_scaled(float4 &acc, float c, float4 x)
+{
+    acc.x = __builtin_fmaf(x.x, c, acc.x);
+    acc.y = __builtin_fmaf(x.y, c, acc.y);
+    acc.z = __builtin_fmaf(x.z, c, acc.z);
+    acc.w = __builtin_fmaf(x.w, c, acc.w);
+}
+__device__ __forceinline__ void scale(float4 &acc, float a)
+{
+    acc.x *= a; acc.y *= a; acc.z *= a; acc.w *= a;
 }
 
-template <int D, bool HALF, int WAVES, bool BY_CHANNEL>
+// This kernel is a chain: arguments, partials, merge, store.  One wavefront takes about 3.6 ns from one instruction to the next, so beside the round
+// trips the number of instructions between them counts (it was 1000 for 32 partials and is 400): addresses advance by a
+// constant instead of a product for each partial, a row's three statistics come in one load, the greatest reference of the partials
+// in flight is found first (one rescale for all of them instead of one each), the halves enter the sums as they are (v_fma_mix), four
+// wavefronts share the end, and what a batch needs to find its partials (LATE) is a kernel of its own.  us per call, 8 heads, bf16: 24 rows,
+// 5K / 32K tokens 11.65 -> 11.2 / 27.7 -> 27.25, 240 rows, 5K 16.85 -> 16.5, 320 rows, 1 head, 128K 34.7 -> 34.0, four sequences
+// of 900-9K, 48 rows 19.85 -> 19.35.
+template <int D, bool HALF, int WAVES, bool BY_CHANNEL, bool LATE>
 __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
 {
     constexpr int NT = D / 16, UPW = 2;              // channel tiles per wavefront
@@ -50,38 +76,52 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
     constexpr int kStride = BY_CHANNEL ? 1 : WAVES;  // this wavefront's partials: first, first + kStride, ...
     const int first = BY_CHANNEL ? 0 : w;
 
-    // The merge is a chain (each partial rescales the running sums), the loads are not: the
-    // partials of kInFlight splits are requested together, so that a wavefront pays the
-    // memory latency once per batch rather than once per split (up to 32 splits: once).
+    // The merge is a chain, the loads are not: the partials of kInFlight splits are requested together, so that a wavefront
+    // pays the memory latency once per batch rather than once per split (up to 32 splits: once).
     constexpr int kInFlight = 8;
-    float ms[kInFlight], ls[kInFlight], ss[kInFlight];
+    constexpr uint32_t kMlBytes = kPartMl * sizeof(float), kTileBytes = HALF ? 512 : 1024, kPartBytes = NT * kTileBytes;
+    RowStats st[kInFlight];
     uint4 raw[kInFlight][HALF ? 1 : UPW];                    // fp16 or fp32 values as they are stored
-    auto load = [&](int s_first, int s0, int limit) {        // past the end: re-read the last one, not merged
-        const size_t slot0 = ((size_t)g * p.n_slots + s_first) * p.RT + tg;
+    const uint32_t ml_lane = j * sizeof(RowStats), po_lane = lane * 16 + u0 * kTileBytes;
+    const char *ml = nullptr, *po = nullptr;                 // of this wavefront's next partial (wave-uniform)
+    int at = 0;                                              // its number in the sequence
+    auto start = [&](int s_first, int s0) {
+        const uint32_t slot = ((uint32_t)g * (uint32_t)p.n_slots + (uint32_t)(s_first + s0)) * (uint32_t)p.RT + (uint32_t)tg;
+        ml = reinterpret_cast<const char *>(p.part_ml) + (size_t)slot * kMlBytes;
+        po = static_cast<const char *>(p.part_o) + (size_t)slot * kPartBytes;
+        at = s0;
+    };
+    const uint32_t step = (uint32_t)kStride * (uint32_t)p.RT;
+    const uint64_t ml_step = (uint64_t)step * kMlBytes, po_step = (uint64_t)step * kPartBytes;
+    auto load = [&](int limit) {                             // past the end: re-read the last one, not merged
 #pragma unroll
         for (int k = 0; k < kInFlight; ++k) {
-            const size_t slot = slot0 + (size_t)min(s0 + kStride * k, limit - 1) * p.RT;
-            ms[k] = p.part_ml[slot * kPartMl + j];
-            ls[k] = p.part_ml[slot * kPartMl + 16 + j];
-            ss[k] = HALF ? p.part_ml[slot * kPartMl + 32 + j] : 1.f;
-            const uint4 *po = static_cast<const uint4 *>(p.part_o) + slot * (size_t)(NT / (HALF ? 2 : 1) * 64) + lane;
+            st[k] = *reinterpret_cast<const RowStats *>(ml + ml_lane);
             static_assert(UPW == 2, "one 16-byte piece per lane holds a pair of channel tiles");
-            if constexpr (HALF) raw[k][0] = po[(u0 / 2) * 64];
-            else
 #pragma unroll
-                for (int u = 0; u < UPW; ++u) raw[k][u] = po[(u0 + u) * 64];
+            for (int u = 0; u < (HALF ? 1 : UPW); ++u) raw[k][u] = *reinterpret_cast<const uint4 *>(po + po_lane + u * kTileBytes);
+            const bool more = at + kStride < limit;
+            at += kStride;
+            ml += more ? ml_step : 0;
+            po += more ? po_step : 0;
         }
     };
 
     // The partials of this row tile: `ns` slots from s_first on (wave-uniform).  Where they begin depends on
     // the lengths only in a batch; otherwise the first ones are requested before the length is known.
-    const bool late = p.dealt && p.B > 1;
-    int s_first = p.dealt ? 0 : b * p.max_splits, limit = p.dealt ? p.rule.max_workers : p.max_splits, ns = 0;
-    if (!late) load(s_first, first, limit);
+    int limit = LATE ? 0 : (p.dealt ? p.rule.max_workers : p.max_splits), ns = 0;
+    if constexpr (!LATE) {
+        start(p.dealt ? 0 : b * p.max_splits, min(first, limit - 1));
+        load(limit);
+    }
+    // Row r of the tile belongs to node r / G, which the product with the reciprocal gives exactly (see the split-KV pass).
+    const int row = tg * kRowTile + j;
+    const int i = (int)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)p.G)), hh = row - i * p.G;
+    const int64_t o = (((int64_t)b * p.N + i) * p.Hq + g * p.G + hh) * D + 4 * qd + 16 * u0;
     // (entries out of range are reported from here as well: every sequence has its workgroups in this grid, while the
     // split-KV pass of a batch never gets to one that is left without drafts)
     int Nb, L;
-    if (late) {
+    if constexpr (LATE) {
         const BatchUnits u = batch_units(p);
         const SeqSize size = size_of(p, u, b);
         Nb = size.drafts;
@@ -89,9 +129,9 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
         if (Nb > 0 && L + Nb > 0) {
             const Deal deal = deal_units(p, u.total);
             const int before = units_before(p, u, b), w0 = deal_worker(deal, before);
-            s_first = w0 + b;
             limit = ns = deal_worker(deal, before + stages_of(L + Nb) - 1) - w0 + 1;
-            load(s_first, first, limit);
+            start(w0 + b, min(first, limit - 1));
+            load(limit);
         }
     } else {
         Nb = load_n_draft(p.n_draft_seq, b, p.N, p.dev_status);
@@ -99,9 +139,10 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
         const int T_b = Nb == 0 ? 0 : L + Nb;                 // a sequence without drafts wrote no partials
         if (T_b > 0 && !p.dealt) {
             ns = min((T_b + p.C - 1) / p.C, p.max_splits);
+        } else if (T_b == p.max_ctx_len + p.N) {
+            ns = p.full_pieces;
         } else if (T_b > 0) {
-            const Deal deal = T_b == p.max_ctx_len + p.N ? p.full : deal_units(p, seq_units(p, T_b));
-            ns = deal_worker(deal, stages_of(T_b) - 1) + 1;
+            ns = deal_worker(deal_units(p, seq_units(p, T_b)), stages_of(T_b) - 1) + 1;
         }
     }
 
@@ -110,103 +151,103 @@ __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
 #pragma unroll
     for (int u = 0; u < UPW; ++u) acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = first; s0 < ns;) {
+        float top = mw;
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+            if (s0 + kStride * k < ns) top = fmaxf(top, st[k].m);    // uniform over the wavefront
+        if (s0 != first) {
+            const float a = __builtin_amdgcn_exp2f(mw - top);
+            lw *= a;
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) scale(acc[u], a);
+        }
+        mw = top;
 #pragma unroll
         for (int k = 0; k < kInFlight; ++k) {
-            if (s0 + kStride * k < ns) {                     // uniform over the wavefront
-                const float mn = fmaxf(mw, ms[k]);
-                const float a = __builtin_amdgcn_exp2f(mw - mn);     // 0 on the first round (mw = -inf)
-                const float c = __builtin_amdgcn_exp2f(ms[k] - mn);
-                mw = mn;
-                lw = lw * a + ls[k] * c;
-                const float co = HALF ? c * (ls[k] * ss[k]) : c;     // the stored rows are O / (l s)
+            if (s0 + kStride * k < ns) {
+                const float c = __builtin_amdgcn_exp2f(st[k].m - top);
+                lw = __builtin_fmaf(st[k].l, c, lw);
+                if constexpr (HALF) {
+                    const float co = c * st[k].w;                    // the stored rows are O / w, w = l s
+                    add_scaled(acc[0], co, raw[k][0].x, raw[k][0].y);
+                    add_scaled(acc[1], co, raw[k][0].z, raw[k][0].w);
+                } else {
 #pragma unroll
-                for (int u = 0; u < UPW; ++u) {
-                    float4 x;
-                    if constexpr (HALF) {
-                        const float2 lo = unpack_half2(u ? raw[k][0].z : raw[k][0].x), hi = unpack_half2(u ? raw[k][0].w : raw[k][0].y);
-                        x = make_float4(lo.x, lo.y, hi.x, hi.y);
-                    } else {
-                        x = __builtin_bit_cast(float4, raw[k][u]);
-                    }
-                    acc[u].x = acc[u].x * a + x.x * co; acc[u].y = acc[u].y * a + x.y * co;
-                    acc[u].z = acc[u].z * a + x.z * co; acc[u].w = acc[u].w * a + x.w * co;
+                    for (int u = 0; u < UPW; ++u) add_scaled(acc[u], c, __builtin_bit_cast(float4, raw[k][u]));
                 }
             }
         }
         s0 += kStride * kInFlight;
-        if (s0 < ns) load(s_first, s0, limit);
+        if (s0 < ns) load(limit);
     }
-    float lsum = lw;
-    float4 tot[UPW];
     if constexpr (BY_CHANNEL) {
+        if (row >= p.R) return;
+        const float inv = i < Nb ? 1.0f / lw : 0.f;                  // rows of absent nodes come out as zeros
 #pragma unroll
-        for (int u = 0; u < UPW; ++u) tot[u] = acc[u];
+        for (int u = 0; u < UPW; ++u) {
+            scale(acc[u], inv);
+            store_out4(p.out, o + 16 * u, i < Nb ? acc[u] : make_float4(0.f, 0.f, 0.f, 0.f), p.out_dtype);
+        }
     } else {
+        // The first four wavefronts finish two of a lane's eight channels each.
+        static_assert(WAVES >= 4 && UPW == 2, "four wavefronts, two channels of one tile each");
         __shared__ float4 s_acc[WAVES][UPW][64];
-        __shared__ float s_m[WAVES][64], s_l[WAVES][64];
+        __shared__ float2 s_ml[WAVES][64];
 #pragma unroll
         for (int u = 0; u < UPW; ++u) s_acc[w][u][lane] = acc[u];
-        s_m[w][lane] = mw;
-        s_l[w][lane] = lw;
+        s_ml[w][lane] = make_float2(mw, lw);
         __syncthreads();
-        if (w != 0) return;
-        float M = s_m[0][lane];
-#pragma unroll
-        for (int k = 1; k < WAVES; ++k) M = fmaxf(M, s_m[k][lane]);
-        lsum = 0.f;
-#pragma unroll
-        for (int u = 0; u < UPW; ++u) tot[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (w >= 4 || row >= p.R) return;
+        const int u = w >> 1, half = w & 1;
+        float2 ml_of[WAVES];
+        float M = -INFINITY, lsum = 0.f;
 #pragma unroll
         for (int k = 0; k < WAVES; ++k) {
-            const float wk = s_m[k][lane] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[k][lane] - M);
-            lsum += wk * s_l[k][lane];
-#pragma unroll
-            for (int u = 0; u < UPW; ++u) {
-                const float4 y = s_acc[k][u][lane];
-                tot[u].x += wk * y.x; tot[u].y += wk * y.y; tot[u].z += wk * y.z; tot[u].w += wk * y.w;
-            }
+            ml_of[k] = s_ml[k][lane];
+            M = fmaxf(M, ml_of[k].x);
         }
-    }
-    const int row = tg * kRowTile + j;
-    if (row >= p.R) return;
-    const int i = row / p.G, hh = row % p.G;
-    const float inv = i < Nb ? 1.0f / lsum : 0.f;                   // rows of absent nodes come out as zeros
-    const int64_t o = (((int64_t)b * p.N + i) * p.Hq + g * p.G + hh) * D + 4 * qd;
+        float2 tot = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int u = 0; u < UPW; ++u)
-        store_out4(p.out, o + 16 * (u0 + u),
-                   i < Nb ? make_float4(tot[u].x * inv, tot[u].y * inv, tot[u].z * inv, tot[u].w * inv)
-                          : make_float4(0.f, 0.f, 0.f, 0.f),
-                   p.out_dtype);
+        for (int k = 0; k < WAVES; ++k) {
+            const float wk = __builtin_amdgcn_exp2f(ml_of[k].x - M);        // 0 for a wavefront without partials
+            lsum = __builtin_fmaf(ml_of[k].y, wk, lsum);
+            const float2 y = reinterpret_cast<const float2 *>(&s_acc[k][u][lane])[half];
+            tot.x = __builtin_fmaf(y.x, wk, tot.x);
+            tot.y = __builtin_fmaf(y.y, wk, tot.y);
+        }
+        const float inv = 1.0f / lsum;
+        store_out2(p.out, o + 16 * u + 2 * half, i < Nb ? make_float2(tot.x * inv, tot.y * inv) : make_float2(0.f, 0.f), p.out_dtype);
+    }
 }
 
-template <int D, int WAVES, bool BY_CHANNEL>
+template <int D, int WAVES, bool BY_CHANNEL, bool LATE>
 static void launch_combine_as(const KParams &p, bool half_partials, dim3 grid, hipStream_t s)
 {
     const dim3 block(64 * WAVES);
-    if (half_partials) hipLaunchKernelGGL((combine_kernel<D, true, WAVES, BY_CHANNEL>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((combine_kernel<D, false, WAVES, BY_CHANNEL>), grid, block, 0, s, p);
+    if (half_partials) hipLaunchKernelGGL((combine_kernel<D, true, WAVES, BY_CHANNEL, LATE>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((combine_kernel<D, false, WAVES, BY_CHANNEL, LATE>), grid, block, 0, s, p);
 }
 
-template <int D>
+template <int D, bool LATE>
 static void launch_combine_d(const KParams &p, bool half_partials, hipStream_t s)
 {
     // Partials per sequence on average, if all sequences are alike.
     const int per_seq = p.dealt ? (p.rule.max_workers + p.B - 1) / p.B : p.max_splits;
     if (p.B > 1 && per_seq <= 8) {
-        launch_combine_as<D, D / 32, true>(p, half_partials, dim3(p.Hkv, p.RT, p.B), s);
+        launch_combine_as<D, D / 32, true, LATE>(p, half_partials, dim3(p.Hkv, p.RT, p.B), s);
         return;
     }
     const dim3 grid(p.Hkv, p.RT * (D / 32), p.B);
     // a wavefront merges its splits as a chain, 8 loads in flight: beyond 32 splits more wavefronts share them
-    if (per_seq > 32) launch_combine_as<D, 8, false>(p, half_partials, grid, s);
-    else launch_combine_as<D, 4, false>(p, half_partials, grid, s);
+    if (per_seq > 32) launch_combine_as<D, 8, false, LATE>(p, half_partials, grid, s);
+    else launch_combine_as<D, 4, false, LATE>(p, half_partials, grid, s);
 }
 
 hipError_t launch_combine(const KParams &p, int D, bool half_partials, hipStream_t s)
 {
-    if (D == 128) launch_combine_d<128>(p, half_partials, s);
-    else launch_combine_d<64>(p, half_partials, s);
+    const bool late = p.dealt && p.B > 1;                    // where a sequence's partials begin depends on the lengths
+    if (D == 128) late ? launch_combine_d<128, true>(p, half_partials, s) : launch_combine_d<128, false>(p, half_partials, s);
+    else late ? launch_combine_d<64, true>(p, half_partials, s) : launch_combine_d<64, false>(p, half_partials, s);
     return hipGetLastError();
 }
 
@@ -278,22 +319,30 @@ hipError_t launch_gather(const owl_verify_desc &d, const void *cache, const int3
 
 // Makes the runtime resolve the combine kernels now, so that their first launch may happen
 // inside a stream capture.
-hipError_t load_aux_kernels()
+template <int D, bool HALF, bool LATE>
+static hipError_t load_combine()
 {
+    const void *fns[] = {
+        reinterpret_cast<const void *>(&combine_kernel<D, HALF, 4, false, LATE>),
+        reinterpret_cast<const void *>(&combine_kernel<D, HALF, 8, false, LATE>),
+        reinterpret_cast<const void *>(&combine_kernel<D, HALF, D / 32, true, LATE>),
+    };
     hipFuncAttributes a;
     hipError_t e = hipSuccess;
-    const void *fns[] = {
-        reinterpret_cast<const void *>(&combine_kernel<128, true, 4, false>), reinterpret_cast<const void *>(&combine_kernel<128, true, 8, false>),
-        reinterpret_cast<const void *>(&combine_kernel<128, true, 4, true>),
-        reinterpret_cast<const void *>(&combine_kernel<128, false, 4, false>), reinterpret_cast<const void *>(&combine_kernel<128, false, 8, false>),
-        reinterpret_cast<const void *>(&combine_kernel<128, false, 4, true>),
-        reinterpret_cast<const void *>(&combine_kernel<64, true, 4, false>), reinterpret_cast<const void *>(&combine_kernel<64, true, 8, false>),
-        reinterpret_cast<const void *>(&combine_kernel<64, true, 2, true>),
-        reinterpret_cast<const void *>(&combine_kernel<64, false, 4, false>), reinterpret_cast<const void *>(&combine_kernel<64, false, 8, false>),
-        reinterpret_cast<const void *>(&combine_kernel<64, false, 2, true>),
-    };
     for (const void *f : fns)
         if (e == hipSuccess) e = hipFuncGetAttributes(&a, f);
+    return e;
+}
+
+hipError_t load_aux_kernels()
+{
+    hipError_t (*const loads[])() = {
+        &load_combine<128, true, false>, &load_combine<128, true, true>, &load_combine<128, false, false>, &load_combine<128, false, true>,
+        &load_combine<64, true, false>, &load_combine<64, true, true>, &load_combine<64, false, false>, &load_combine<64, false, true>,
+    };
+    hipError_t e = hipSuccess;
+    for (auto load : loads)
+        if (e == hipSuccess) e = load();
     return e;
 }
 

@@ -33,6 +33,22 @@ __device__ __forceinline__ void store_out4(void *out, int64_t e, float4 v, int o
     *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + e) = w;
 }
 
+// Two channels, likewise.
+__device__ __forceinline__ void store_out2(void *out, int64_t e, float2 v, int out_dtype)
+{
+    typedef float o_f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 o_bf16x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 o_f16x2 __attribute__((ext_vector_type(2)));
+    if (out_dtype == OWL_F32) {
+        *reinterpret_cast<float2 *>(static_cast<float *>(out) + e) = v;
+        return;
+    }
+    const o_f32x2 x = {v.x, v.y};
+    *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(out) + e) =
+        out_dtype == OWL_BF16 ? __builtin_bit_cast(uint32_t, __builtin_convertvector(x, o_bf16x2))
+                              : __builtin_bit_cast(uint32_t, __builtin_convertvector(x, o_f16x2));
+}
+
 // Asks for every line of the launch's arguments at once and waits for them.  They are cold in each launch, and left to
 // itself the compiler loads them in several rounds, close to their uses, each a memory round trip of its own.  It pays where
 // most of them are needed before the first load (split-KV pass: 56 rows, 8 heads, 600 / 2000 tokens 9.85 -> 9.78,

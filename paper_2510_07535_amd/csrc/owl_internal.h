@@ -15,13 +15,13 @@ constexpr int kMaxSplitTokens = 16384;    // largest split of a plan with equal 
 
 // Format of a split's partial, per 16-row tile ("slot").
 //   fp32 inputs, and 16-bit inputs with OWL_FLAG_FP32_PARTIALS:
-//                  O fragments as they stand, float4 [slot][channel tile][lane]; (m, l) in part_ml.
+//                  O fragments as they stand, float4 [slot][channel tile][lane]; (m, l, 1) in part_ml.
 //   16-bit inputs: the NORMALISED output O / l of each row (a convex combination of V rows, so bounded by
 //                  them), divided by s = its largest magnitude over the row's channels, as fp16:
-//                  uint4 [slot][pair of channel tiles][lane] = 2 x 4 halves; (m, l, s) in part_ml.  Half the
+//                  uint4 [slot][pair of channel tiles][lane] = 2 x 4 halves; (m, l, l s) in part_ml.  Half the
 //                  bytes to write and to read back; a value is stored to 2^-12 of its row's largest
 //                  component whatever the magnitude of V, far below the bf16 rounding of P.
-constexpr int kPartMl = 48;               // floats of part_ml per slot: m[16], l[16], s[16]
+constexpr int kPartMl = 48;               // floats of part_ml per slot: three for each of its 16 rows, one 12-byte load
 
 // Everything a kernel needs, passed by value.
 struct KParams {
@@ -30,7 +30,7 @@ struct KParams {
     const int32_t *n_draft_seq;   // optional [B]: drafted tokens of each sequence (<= N), else null = N everywhere
     void *part_o;         // split partials: accumulator fragments (see kPartMl below)
     int32_t half_partials;// 1: normalised fp16 partials (16-bit inputs, the default), 0: raw fp32 fragments
-    float *part_ml;       // split partials: per row reference m, row sum l and, for 16-bit partials, scale s
+    float *part_ml;       // split partials: per row reference m, row sum l and, for 16-bit partials, l times the scale s
     void *out;            // [B][N][Hq][D] in out_dtype
     int32_t out_dtype;    // OWL_F32, OWL_BF16 or OWL_F16
     uint32_t *dev_status;
@@ -41,6 +41,7 @@ struct KParams {
     int32_t dealt;        // 1: the library cuts the work by the actual lengths (deal_units); 0: equal splits of C tokens
     DealRule rule;        // dealt: how
     Deal full;            // dealt, B == 1: deal_units of the longest sequence the plan admits
+    int32_t full_pieces;  // dealt, B == 1: the partials that sequence leaves per (KV head, row tile)
     int32_t n_slots;      // partials per (KV head, row tile)
     int32_t RT;           // row tiles covering R
     int32_t row_groups;

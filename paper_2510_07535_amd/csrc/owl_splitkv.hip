@@ -1183,7 +1183,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // ---- write this split's partial ----
     // fp32 partials (fp32 inputs, or on request): the accumulator fragments as they are, float4 [slot][u][lane] =
     // channels 16*u + 4*quad .. +3 of row lane%16.  Otherwise: each row normalised by its row sum and by its largest magnitude s, as fp16,
-    // uint4 [slot][u/2][lane] = the four halves of channel tile u (even) and of u + 1; (m, l, s) beside it.
+    // uint4 [slot][u/2][lane] = the four halves of channel tile u (even) and of u + 1; (m, l, l s) beside it.
     if (wk == 0 || kGive == 2) {
 #pragma unroll
         for (int t = 0; t < (WK == 2 ? 1 : TPW); ++t) {
@@ -1197,9 +1197,10 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 for (int u = 0; u < NT; ++u)
                     po[u * 64] = make_float4(O[t][u][0], O[t][u][1], O[t][u][2], O[t][u][3]);
                 if (qd == 0) {
-                    p.part_ml[slot * kPartMl + j] = m[t];
-                    p.part_ml[slot * kPartMl + 16 + j] = l;
-                    p.part_ml[slot * kPartMl + 32 + j] = 1.0f;
+                    float *stats = p.part_ml + slot * kPartMl + 3 * j;
+                    stats[0] = m[t];
+                    stats[1] = l;
+                    stats[2] = 1.0f;
                 }
             } else {
                 const float inv_l = l > 0.f ? 1.0f / l : 0.f;          // a row that saw no key: all zeros
@@ -1221,9 +1222,10 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                                                    pack2<_Float16>(O[t][u + 1][0] * inv_s, O[t][u + 1][1] * inv_s),
                                                    pack2<_Float16>(O[t][u + 1][2] * inv_s, O[t][u + 1][3] * inv_s));
                 if (qd == 0) {
-                    p.part_ml[slot * kPartMl + j] = m[t];
-                    p.part_ml[slot * kPartMl + 16 + j] = l;
-                    p.part_ml[slot * kPartMl + 32 + j] = big;
+                    float *stats = p.part_ml + slot * kPartMl + 3 * j;
+                    stats[0] = m[t];
+                    stats[1] = l;
+                    stats[2] = l * big;
                 }
             }
         }
