@@ -126,6 +126,18 @@ __device__ __forceinline__ int lane_scan(int v)
     return v;
 }
 
+// The same steps for the greatest of the lanes' numbers, none below -1.
+__device__ __forceinline__ int wave_max(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // The same steps for a sum of floats, which lane 63 ends up with and every lane gets.
 __device__ __forceinline__ float wave_sum(float v)
 {

@@ -4,6 +4,8 @@
 // (Sec. 1 / Sec. 2: the target keeps the longest drafted path that agrees with
 // its own next tokens), and the commit of that path's K/V rows into the
 // context (Algorithm 1: l <- l;d, N <- N + |d|).  All results are exact.
+#include <type_traits>
+
 #include "owl_device.h"
 
 namespace owl {
@@ -46,7 +48,8 @@ hipError_t launch_prepare(const int32_t *parent, const int32_t *ctx_lens, int B,
 // if its token is the target's next token at its parent (at the context end for
 // a root); it is reachable if it and all its ancestors agree.  Parents precede
 // children, so reachability spreads one tree level per round of a ballot loop
-// that ends when a round adds nothing (at most depth rounds).  The answer is the
+// that ends when a round adds nothing (at most depth rounds; ten instructions a
+// round, a wavefront takes 3.6 ns for one).  The answer is the
 // reachable node of greatest depth, smallest index on ties; its root path is
 // written from the root down.
 // ---------------------------------------------------------------------------
@@ -62,28 +65,23 @@ __global__ void __launch_bounds__(64) accept_kernel(const int32_t *tokens, const
     const int64_t at = row + min(i, N - 1);
     int p = parent[at];
     const int token = tokens[at], next = target_next[at], root = load_uniform(target_root, b);
-    if (i >= N) {
-        p = -1;
-    } else if (p < -1 || p >= i) {
-        flag_status(status, OWL_DEV_BAD_PARENT);
-        p = -1;
-    }
+    const bool bad = i < N && (p < -1 || p >= i);
+    if (bad) flag_status(status, OWL_DEV_BAD_PARENT);
+    p = i < N && !bad ? p : -1;
     const int said = __shfl(next, max(p, 0));
     const bool agrees = i < N && i < n_cand && p < n_cand && token == (p < 0 ? root : said);
-    uint64_t reach = 0;
-    int depth = 0;                                          // depth of lane's node once reached
-    for (int round = 1; round <= N; ++round) {              // uniform: `reach` is the same in every lane
-        const bool now = agrees && !((reach >> i) & 1) && (p < 0 ? round == 1 : ((reach >> p) & 1));
-        const uint64_t add = __builtin_amdgcn_ballot_w64(now);
+    // `fresh`: the nodes that the last round reached, each in one round only
+    uint64_t fresh = __builtin_amdgcn_ballot_w64(agrees && p < 0), reach = fresh;
+    const uint64_t up = agrees && p >= 0 ? (uint64_t)1 << p : 0;
+    int depth = 1;                                          // of the lane's node, once reached
+    for (int round = 2; fresh; ++round) {                   // uniform; a parent precedes its children, so it ends
+        const bool now = (up & fresh) != 0;
         if (now) depth = round;
-        if (add == 0) break;
-        reach |= add;
+        fresh = __builtin_amdgcn_ballot_w64(now);
+        reach |= fresh;
     }
     // deepest reachable node, smallest index on ties: key = depth * 64 + (63 - i)
-    int key = ((reach >> i) & 1) ? depth * 64 + (63 - i) : -1;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off));
-    key = __builtin_amdgcn_readfirstlane(key);
+    const int key = wave_max(((reach >> i) & 1) ? depth * 64 + (63 - i) : -1);
     const int best = key < 0 ? -1 : 63 - (key & 63);
     const int na = key < 0 ? 0 : key >> 6;
     // The path is walked in scalar registers; the node at depth k goes to place k - 1, the places behind it get -1.
@@ -121,89 +119,83 @@ hipError_t launch_accept(const int32_t *tokens, const int32_t *parent, const int
 // position beyond the table) means OWL_DEV_BAD_PAGE, no row of that sequence
 // moves, and its new length equals the old one.  A kernel that writes must not
 // replace a bad page by some other page.
+// Every wavefront looks the path up for itself, lane = row (length, count and path in one memory round trip, the pages in the next),
+// and hands the byte offsets of a row's source and destination to the lanes that move it: one barrier, and nothing of it in
+// scratch memory: what remains of 4.65 us are four cold round trips.  (One wavefront for all by way of LDS, two barriers, divisions
+// by the pieces of a row and the moved rows in scratch memory: 5.03.)
 // ---------------------------------------------------------------------------
 constexpr int kCommitThreads = 256;
 constexpr int kCommitMaxPieces = 8;                         // 64 rows x 32 pieces / 256 threads
 
+__device__ __forceinline__ int64_t shfl64(int64_t v, int lane)
+{
+    const uint32_t lo = __shfl((uint32_t)v, lane), hi = __shfl((uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
     unsigned char *k_cache, unsigned char *v_cache, const int32_t *page_table, const int32_t *ctx_lens,
     const int32_t *accepted, const int32_t *n_accept, int N, int max_pages, int max_ctx_len,
-    int64_t n_pool_pages, int row_bytes, int es, int64_t stride_page, int64_t stride_head,
+    int64_t n_pool_pages, int log_pieces, int es, int64_t stride_page, int64_t stride_head,
     int64_t stride_token, int32_t *new_ctx_lens, uint32_t *status)
 {
-    __shared__ int32_t s_src[64];
-    __shared__ int64_t s_src_page[64], s_dst_page[64];
-    __shared__ int s_bad, s_bad_page;
     fetch_args<decltype(commit_kernel)>();
     const int g = blockIdx.x, b = blockIdx.y;
-    unsigned char *cache = blockIdx.z ? v_cache : k_cache;
-    const int tid = threadIdx.x;
-    // length, count and path in one memory round trip, the pages in the next (one after the other: 4.6 -> 4.1 us a launch)
-    int a = 0;
-    if (tid < 64) a = accepted[(int64_t)b * N + min(tid, N - 1)];
-    int na = load_uniform(n_accept, b);
-    const int L = load_ctx_len(ctx_lens, b, max_ctx_len, status);
+    unsigned char *cache = (blockIdx.z ? v_cache : k_cache) + g * stride_head * es;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int a = accepted[(int64_t)b * N + min(lane, N - 1)];
+    int na = load_uniform(n_accept, b), L = load_uniform(ctx_lens, b);
+    asm volatile("" : "+s"(na), "+s"(L));                   // (both asked for before either is looked at)
+    if (L < 0 || L > max_ctx_len) {
+        if (tid == 0) flag_status(status, OWL_DEV_BAD_CTX_LEN);
+        L = L < 0 ? 0 : max_ctx_len;
+    }
     if (na < 0 || na > N) {
         if (tid == 0) flag_status(status, OWL_DEV_BAD_ACCEPT);
         na = 0;
     }
-    if (tid < 64) {                                         // one wavefront, lane = row of the path
-        const int prev = __shfl_up(a, 1);
-        const bool mine = tid < na;
-        bool bad = false, bad_page = false;
-        if (mine) {
-            bad = a < 0 || a >= N || (tid > 0 && a <= prev);
-            s_src[tid] = a;
-            // physical pages of the row's source and destination, unchecked ids; -1 = not in the table
-            auto page_of = [&](int pos) -> int64_t {
-                const int lp = pos / kPage;
-                if (!page_table) return lp;
-                return lp < max_pages ? (int64_t)page_table[(int64_t)b * max_pages + lp] : -1;
-            };
-            const int64_t sp = (a >= 0 && a < N) ? page_of(L + a) : 0, dp = page_of(L + tid);
-            bad_page = sp < 0 || sp >= n_pool_pages || dp < 0 || dp >= n_pool_pages;
-            s_src_page[tid] = sp;
-            s_dst_page[tid] = dp;
-        }
-        const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0, any_page = __builtin_amdgcn_ballot_w64(bad_page) != 0;
-        if (tid == 0) s_bad = any_bad, s_bad_page = any_page;
+    // row `lane` of the path: physical pages of its source and destination, unchecked ids
+    const int before = __shfl_up(a, 1), from = L + min(max(a, 0), N - 1), to = L + lane;
+    const int from_lp = from / kPage, to_lp = to / kPage;
+    int from_page = from_lp, to_page = to_lp;
+    if (page_table) {
+        const int32_t *pages = page_table + (int64_t)b * max_pages;
+        from_page = pages[min(from_lp, max_pages - 1)];
+        to_page = pages[min(to_lp, max_pages - 1)];
     }
-    __syncthreads();
-    if (s_bad) {                                            // uniform over the workgroup
-        if (tid == 0) flag_status(status, OWL_DEV_BAD_ACCEPT);
-        na = 0;
-    } else if (s_bad_page) {
-        if (tid == 0) flag_status(status, OWL_DEV_BAD_PAGE);
+    const bool bad_page = (page_table && max(from_lp, to_lp) >= max_pages) || min(from_page, to_page) < 0 || max(from_page, to_page) >= n_pool_pages;
+    const bool mine = lane < na, bad = a < 0 || a >= N || (lane > 0 && a <= before);
+    const bool any_bad = __builtin_amdgcn_ballot_w64(mine && bad) != 0;          // the same in every wavefront
+    if (any_bad || __builtin_amdgcn_ballot_w64(mine && bad_page) != 0) {
+        if (tid == 0) flag_status(status, any_bad ? OWL_DEV_BAD_ACCEPT : OWL_DEV_BAD_PAGE);
         na = 0;
     }
     if (g == 0 && blockIdx.z == 0 && tid == 0 && new_ctx_lens) new_ctx_lens[b] = L + na;
 
-    const int ppr = row_bytes / 16;
-    const int total = na * ppr;
-    uint4 held[kCommitMaxPieces];
+    const int64_t src = ((int64_t)from_page * stride_page + from % kPage * stride_token) * es;
+    const int64_t dst = ((int64_t)to_page * stride_page + to % kPage * stride_token) * es;
+    // 16-byte piece `id` of the moved rows belongs to row id >> log_pieces; past the end: the last row once more, not stored
+    const int total = na << log_pieces, piece = (tid & ((1 << log_pieces) - 1)) * 16;
+    typedef uint32_t Piece __attribute__((ext_vector_type(4)));          // (an array of the struct uint4 goes to scratch memory)
+    auto move = [&](auto pieces) {
+        constexpr int n = decltype(pieces)::value;
+        Piece held[n];
+        int64_t at[n];
 #pragma unroll
-    for (int r = 0; r < kCommitMaxPieces; ++r) {
-        const int id = tid + r * kCommitThreads;
-        if (id < total && s_src[id / ppr] != id / ppr) {    // a row already in place is left alone
-            const int i = id / ppr, piece = id % ppr;
-            const int pos = L + s_src[i];
-            const int64_t off = (s_src_page[i] * stride_page + g * stride_head + (pos % kPage) * stride_token) * es;
-            held[r] = *reinterpret_cast<const uint4 *>(cache + off + piece * 16);
+        for (int r = 0; r < n; ++r) {
+            const int id = tid + r * kCommitThreads, i = min(id >> log_pieces, na - 1);
+            const int64_t s = shfl64(src, i), d = shfl64(dst, i);
+            at[r] = id < total && s != d ? d + piece : -1;  // (a row already in place is left alone)
+            held[r] = *reinterpret_cast<const Piece *>(cache + s + piece);
         }
-    }
-    __syncthreads();                                        // all reads done before the first write
+        __syncthreads();                                    // all reads done before the first write
 #pragma unroll
-    for (int r = 0; r < kCommitMaxPieces; ++r) {
-        const int id = tid + r * kCommitThreads;
-        if (id < total) {
-            const int i = id / ppr, piece = id % ppr;
-            if (s_src[i] != i) {
-                const int pos = L + i;
-                const int64_t off = (s_dst_page[i] * stride_page + g * stride_head + (pos % kPage) * stride_token) * es;
-                *reinterpret_cast<uint4 *>(cache + off + piece * 16) = held[r];
-            }
-        }
-    }
+        for (int r = 0; r < n; ++r)
+            if (at[r] >= 0) *reinterpret_cast<Piece *>(cache + at[r]) = held[r];
+    };
+    if (total == 0) return;                                 // uniform over the workgroup, as are the others
+    if (total <= kCommitThreads) move(std::integral_constant<int, 1>{});
+    else move(std::integral_constant<int, kCommitMaxPieces>{});
 }
 
 hipError_t launch_commit(const owl_verify_desc &d, void *k_cache, void *v_cache, const int32_t *page_table,
@@ -211,12 +203,13 @@ hipError_t launch_commit(const owl_verify_desc &d, void *k_cache, void *v_cache,
                          int32_t *new_ctx_lens, uint32_t *status, hipStream_t s)
 {
     const int es = d.qkv_dtype == OWL_F32 ? 4 : 2;
-    const int row_bytes = d.head_dim * es;
     static_assert(64 * 32 <= kCommitThreads * kCommitMaxPieces, "64 rows of up to 512 bytes fit the held pieces");
+    int log_pieces = 3;                                     // rows of 128, 256 or 512 bytes
+    while (16 << log_pieces < d.head_dim * es) ++log_pieces;
     hipLaunchKernelGGL(commit_kernel, dim3(d.n_kv_heads, d.batch, 2), dim3(kCommitThreads), 0, s,
                        static_cast<unsigned char *>(k_cache), static_cast<unsigned char *>(v_cache), page_table,
                        ctx_lens, accepted, n_accept, d.n_draft, d.max_pages_per_seq, d.max_ctx_len,
-                       d.n_pool_pages, row_bytes, es, d.kv_stride_page, d.kv_stride_head, d.kv_stride_token,
+                       d.n_pool_pages, log_pieces, es, d.kv_stride_page, d.kv_stride_head, d.kv_stride_token,
                        new_ctx_lens, status);
     return hipGetLastError();
 }
