@@ -350,8 +350,8 @@ hipError_t launch_drafter_tile_weights(const void *w_rows, void *w_tiled, int d_
 // Gates and state update.  f needs the mean and variance of a whole row twice
 // (of s^c, then of z'), and the transcendental work of one row (three sigmoids
 // and two GeLUs per channel) keeps a single compute unit busy for ~20 us, so a
-// row is spread over workgroups of 256 threads x 4 channels, in two launches:
-//   1. z' = z g^f + f(s^c) g^i, and per chunk of 1024 channels the mean and centred sum of squares of z'
+// row is spread over workgroups of 256 threads x C channels, in two launches:
+//   1. z' = z g^f + f(s^c) g^i, and per chunk of 256 C channels the mean and centred sum of squares of z'
 //   2. merge those; h' = f(z') g^o
 // The statistics of s^c need no transcendentals: every workgroup of launch 1 forms them from the whole row by itself, in
 // registers, while its own operands are on their way: 48 KB of s^c and 24 KB of embedding from L2 at d = 12288, against a launch
@@ -362,8 +362,10 @@ hipError_t launch_drafter_tile_weights(const void *w_rows, void *w_tiled, int d_
 // which keeps the variance as accurate as a two-pass sum.
 // ---------------------------------------------------------------------------
 constexpr int kGateThreads = 256;
-constexpr int kGateChunk = kGateThreads * 4;               // channels per workgroup
-constexpr int kGateMaxChunks = 16;                         // d <= 16384
+constexpr int kRowChunk = kGateThreads * 4;                // channels that a workgroup reads at a time for a whole row
+constexpr int kRowMaxChunks = 16;                          // d <= 16384
+constexpr int kGateMaxChunks = 32;                         // chunks of a row: one lane of a wavefront each, and what the scratch holds
+constexpr int kGateWorkgroups = 256;                       // see launch_gates_dt
 
 // Sum over the workgroup, the same in every thread.  Each call of a kernel has words of its own in `scratch`, so that one
 // barrier is enough.  (Shuffles through LDS and two barriers a sum, and a loop over the chunks' partials in the hidden kernel:
@@ -401,20 +403,45 @@ template <bool kF16> __device__ __forceinline__ uint16_t narrow16(float x)
     }
 }
 
-// alpha * (four consecutive channels of a 16-bit embedding row)
-template <bool kF16> __device__ __forceinline__ float4 scaled_emb4(const uint16_t *p, float alpha)
+// C consecutive channels (1, 2 or 4), and how they are read and written in one piece.
+template <int C> struct Chan {
+    float x[C];
+};
+template <int C> struct Bits16 {
+    uint16_t x[C];
+};
+template <int C> __device__ __forceinline__ Chan<C> ld(const float *p)
 {
-    const uint2 raw = *reinterpret_cast<const uint2 *>(p);
-    return make_float4(alpha * widen16<kF16>((uint16_t)(raw.x & 0xffffu)), alpha * widen16<kF16>((uint16_t)(raw.x >> 16)),
-                       alpha * widen16<kF16>((uint16_t)(raw.y & 0xffffu)), alpha * widen16<kF16>((uint16_t)(raw.y >> 16)));
+    typedef float V __attribute__((ext_vector_type(C)));
+    return __builtin_bit_cast(Chan<C>, *reinterpret_cast<const V *>(p));
 }
-
-__device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-__device__ __forceinline__ float4 ld4_or(const float *p, int j, float fill)
+template <> __device__ __forceinline__ Chan<1> ld<1>(const float *p) { return Chan<1>{{*p}}; }
+template <int C> __device__ __forceinline__ void st(float *p, const Chan<C> &v)
 {
-    return p ? ld4(p + j) : make_float4(fill, fill, fill, fill);
+    typedef float V __attribute__((ext_vector_type(C)));
+    *reinterpret_cast<V *>(p) = __builtin_bit_cast(V, v);
 }
-__device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+template <> __device__ __forceinline__ void st<1>(float *p, const Chan<1> &v) { *p = v.x[0]; }
+template <int C> __device__ __forceinline__ Chan<C> ld_or(const float *p, int j, float fill)
+{
+    if (p) return ld<C>(p + j);
+    Chan<C> v;
+#pragma unroll
+    for (int i = 0; i < C; ++i) v.x[i] = fill;
+    return v;
+}
+// s + alpha * (a 16-bit embedding row), C consecutive channels
+template <bool kF16, int C> __device__ __forceinline__ Chan<C> add_emb(const float *s, const uint16_t *e, float alpha)
+{
+    typedef uint16_t V __attribute__((ext_vector_type(C == 1 ? 2 : C)));
+    Bits16<C == 1 ? 2 : C> raw;
+    if constexpr (C == 1) raw.x[0] = *e;
+    else raw = __builtin_bit_cast(Bits16<C>, *reinterpret_cast<const V *>(e));
+    Chan<C> v = ld<C>(s);
+#pragma unroll
+    for (int i = 0; i < C; ++i) v.x[i] += alpha * widen16<kF16>(raw.x[i]);
+    return v;
+}
 
 struct GateArgs {
     const float *s, *z;
@@ -455,24 +482,23 @@ __device__ __forceinline__ GateRow gate_row(const GateArgs &a, int r, bool flag)
 }
 
 // Mean and centred sum of squares of the live channels of this workgroup's chunk.
-__device__ __forceinline__ void chunk_stats(float4 v, bool live, int n_live, float *scratch, float *out2)
+template <int C> __device__ __forceinline__ void chunk_stats(Chan<C> v, bool live, int n_live, float *scratch, float *out2)
 {
-    const float sum = block_sum(live ? (v.x + v.y) + (v.z + v.w) : 0.f, scratch);
-    const float mean = sum / (float)n_live;
-    float sq = 0.f;
-    if (live) {
-        v.x -= mean, v.y -= mean, v.z -= mean, v.w -= mean;
-        sq = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-    }
-    const float m2 = block_sum(sq, scratch + kGateWaves);
+    float sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < C; ++i) sum += v.x[i];
+    const float mean = block_sum(live ? sum : 0.f, scratch) / (float)n_live;
+#pragma unroll
+    for (int i = 0; i < C; ++i) sq += (v.x[i] - mean) * (v.x[i] - mean);
+    const float m2 = block_sum(live ? sq : 0.f, scratch + kGateWaves);
     if (threadIdx.x == 0) out2[0] = mean, out2[1] = m2;
 }
 
 // Mean and 1 / sqrt(variance + eps) of a row from its chunks' partials, one chunk a lane: a loop over them waits for each.
-__device__ __forceinline__ void merge_stats(const float2 part, int d, float eps, float *mean_out, float *rstd_out)
+__device__ __forceinline__ void merge_stats(const float2 part, int chunk, int d, float eps, float *mean_out, float *rstd_out)
 {
     const int c = threadIdx.x & 63;
-    const float n = (float)max(min(kGateChunk, d - c * kGateChunk), 0);      // channels of the lane's chunk
+    const float n = (float)max(min(chunk, d - c * chunk), 0);                // channels of the lane's chunk
     const float mean = wave_sum(n > 0.f ? part.x * n : 0.f) / (float)d;
     const float dm = part.x - mean;
     const float m2 = wave_sum(n > 0.f ? part.y + n * dm * dm : 0.f);
@@ -480,28 +506,28 @@ __device__ __forceinline__ void merge_stats(const float2 part, int d, float eps,
     *rstd_out = 1.0f / sqrtf(m2 / (float)d + eps);
 }
 
-// Mean and 1 / sqrt(variance + eps) of s^c over a row of at most MAXC chunks, in two passes over registers; the same
-// in every workgroup of the row.
+// Mean and 1 / sqrt(variance + eps) of s^c over a row of at most MAXC pieces of kRowChunk channels, in two passes over registers; the
+// same in every workgroup of the row.
 template <bool kF16, int MAXC>
 __device__ __forceinline__ void row_stats(const GateArgs &a, const GateRow &g, float *scratch, float *mean_out, float *rstd_out)
 {
     const int j0 = threadIdx.x * 4;
-    float4 v[MAXC];
+    Chan<4> v[MAXC];
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {                        // past the end: the last channels once more, not counted
-        const int j = min(c * kGateChunk + j0, a.d - 4);
-        v[c] = add4(ld4(g.sp + 3 * a.d + j), scaled_emb4<kF16>(g.ep + j, g.alpha));
+        const int j = min(c * kRowChunk + j0, a.d - 4);
+        v[c] = add_emb<kF16, 4>(g.sp + 3 * a.d + j, g.ep + j, g.alpha);
     }
     float sum = 0.f;
 #pragma unroll
     for (int c = 0; c < MAXC; ++c)
-        if (c * kGateChunk + j0 < a.d) sum += (v[c].x + v[c].y) + (v[c].z + v[c].w);
+        if (c * kRowChunk + j0 < a.d) sum += (v[c].x[0] + v[c].x[1]) + (v[c].x[2] + v[c].x[3]);
     const float mean = block_sum(sum, scratch) / (float)a.d;
     float sq = 0.f;
 #pragma unroll
     for (int c = 0; c < MAXC; ++c)
-        if (c * kGateChunk + j0 < a.d) {
-            const float4 x = make_float4(v[c].x - mean, v[c].y - mean, v[c].z - mean, v[c].w - mean);
+        if (c * kRowChunk + j0 < a.d) {
+            const float4 x = make_float4(v[c].x[0] - mean, v[c].x[1] - mean, v[c].x[2] - mean, v[c].x[3] - mean);
             sq += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
         }
     *mean_out = mean;
@@ -512,72 +538,95 @@ __device__ __forceinline__ void row_stats(const GateArgs &a, const GateRow &g, f
 // rounds, each a trip to L2.  us of this launch, rows loaded in rounds -> all at once: bf16, 12 chunks, 10 rows 8.0 -> 5.8, 40 rows
 // 9.7 -> 8.3; 16 chunks, 10 rows bf16 9.2 -> 6.2, fp16 6.8 -> 6.0, 64 rows bf16 13.6 -> 12.4.  Others had all of it in flight already
 // and stay as they are: fp16, 12 chunks, 10 rows 5.3.)
-template <bool kF16, int MAXC>
+template <bool kF16, int MAXC, int C>
 __global__ void __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(1, 3))) drafter_state_kernel(GateArgs a)
 {
     __shared__ float scratch[4 * kGateWaves];
-    const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
+    constexpr int kChunk = kGateThreads * C;
+    const int c = blockIdx.x, r = blockIdx.y, j = c * kChunk + threadIdx.x * C;
     const GateRow g = gate_row(a, r, c == 0);
     const bool live = j < a.d;
     const int jl = live ? j : 0;
-    const float4 e = scaled_emb4<kF16>(g.ep + jl, g.alpha);
-    const float4 sf = add4(ld4(g.sp + jl), e), si = add4(ld4(g.sp + a.d + jl), e), sc = add4(ld4(g.sp + 3 * a.d + jl), e);
-    const float4 zo = ld4(g.zp + jl), ga = ld4_or(a.gamma_c, jl, 1.f), be = ld4_or(a.beta_c, jl, 0.f);
+    const Chan<C> sf = add_emb<kF16, C>(g.sp + jl, g.ep + jl, g.alpha), si = add_emb<kF16, C>(g.sp + a.d + jl, g.ep + jl, g.alpha),
+                  sc = add_emb<kF16, C>(g.sp + 3 * a.d + jl, g.ep + jl, g.alpha);
+    const Chan<C> zo = ld<C>(g.zp + jl), ga = ld_or<C>(a.gamma_c, jl, 1.f), be = ld_or<C>(a.beta_c, jl, 0.f);
     float mean, rstd;
     row_stats<kF16, MAXC>(a, g, scratch, &mean, &rstd);
-    float4 zn = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) {
-        zn.x = zo.x * sigmoid_f(sf.x) + gelu_f((sc.x - mean) * rstd * ga.x + be.x) * sigmoid_f(si.x);
-        zn.y = zo.y * sigmoid_f(sf.y) + gelu_f((sc.y - mean) * rstd * ga.y + be.y) * sigmoid_f(si.y);
-        zn.z = zo.z * sigmoid_f(sf.z) + gelu_f((sc.z - mean) * rstd * ga.z + be.z) * sigmoid_f(si.z);
-        zn.w = zo.w * sigmoid_f(sf.w) + gelu_f((sc.w - mean) * rstd * ga.w + be.w) * sigmoid_f(si.w);
-        *reinterpret_cast<float4 *>(a.z_out + (int64_t)r * a.d + j) = zn;
-    }
-    chunk_stats(zn, live, min(kGateChunk, a.d - c * kGateChunk), scratch + 2 * kGateWaves, a.part_z + ((int64_t)r * kGateMaxChunks + c) * 2);
+    Chan<C> zn;
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+        zn.x[i] = zo.x[i] * sigmoid_f(sf.x[i]) + gelu_f((sc.x[i] - mean) * rstd * ga.x[i] + be.x[i]) * sigmoid_f(si.x[i]);
+    if (live) st<C>(a.z_out + (int64_t)r * a.d + j, zn);
+    chunk_stats<C>(zn, live, min(kChunk, a.d - c * kChunk), scratch + 2 * kGateWaves, a.part_z + ((int64_t)r * kGateMaxChunks + c) * 2);
 }
 
-template <bool kF16>
+template <bool kF16, int C>
 __global__ void __launch_bounds__(kGateThreads) drafter_hidden_kernel(GateArgs a)
 {
-    const int c = blockIdx.x, r = blockIdx.y, j = c * kGateChunk + threadIdx.x * 4;
+    constexpr int kChunk = kGateThreads * C;
+    const int c = blockIdx.x, r = blockIdx.y, j = c * kChunk + threadIdx.x * C;
     // (everything is asked for before the statistics are merged; lanes past the last chunk read chunk 0 and do not count)
-    const int n_chunks = (a.d + kGateChunk - 1) / kGateChunk, chunk = (int)(threadIdx.x & 63) < n_chunks ? threadIdx.x & 63 : 0;
+    const int n_chunks = (a.d + kChunk - 1) / kChunk, chunk = (int)(threadIdx.x & 63) < n_chunks ? threadIdx.x & 63 : 0;
     const float2 part = reinterpret_cast<const float2 *>(a.part_z)[(int64_t)r * kGateMaxChunks + chunk];
     const bool live = j < a.d;
     const int jl = live ? j : 0;
-    const float4 zn = ld4(a.z_out + (int64_t)r * a.d + jl), ga = ld4_or(a.gamma_z, jl, 1.f), be = ld4_or(a.beta_z, jl, 0.f);
+    const Chan<C> zn = ld<C>(a.z_out + (int64_t)r * a.d + jl), ga = ld_or<C>(a.gamma_z, jl, 1.f), be = ld_or<C>(a.beta_z, jl, 0.f);
     const GateRow g = gate_row(a, r, false);
-    const float4 so = add4(ld4(g.sp + 2 * a.d + jl), scaled_emb4<kF16>(g.ep + jl, g.alpha));
+    const Chan<C> so = add_emb<kF16, C>(g.sp + 2 * a.d + jl, g.ep + jl, g.alpha);
     float mean, rstd;
-    merge_stats(part, a.d, a.eps, &mean, &rstd);
+    merge_stats(part, kChunk, a.d, a.eps, &mean, &rstd);
     if (!live) return;
-    float4 hn;
-    hn.x = gelu_f((zn.x - mean) * rstd * ga.x + be.x) * sigmoid_f(so.x);
-    hn.y = gelu_f((zn.y - mean) * rstd * ga.y + be.y) * sigmoid_f(so.y);
-    hn.z = gelu_f((zn.z - mean) * rstd * ga.z + be.z) * sigmoid_f(so.z);
-    hn.w = gelu_f((zn.w - mean) * rstd * ga.w + be.w) * sigmoid_f(so.w);
-    if (a.h_out) {
-        uint2 pk;
-        pk.x = (uint32_t)narrow16<kF16>(hn.x) | ((uint32_t)narrow16<kF16>(hn.y) << 16);
-        pk.y = (uint32_t)narrow16<kF16>(hn.z) | ((uint32_t)narrow16<kF16>(hn.w) << 16);
-        *reinterpret_cast<uint2 *>(a.h_out + (int64_t)r * a.d + j) = pk;
+    Chan<C> hn;
+    Bits16<C> out;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        hn.x[i] = gelu_f((zn.x[i] - mean) * rstd * ga.x[i] + be.x[i]) * sigmoid_f(so.x[i]);
+        out.x[i] = narrow16<kF16>(hn.x[i]);
     }
-    if (a.h_out_f32) *reinterpret_cast<float4 *>(a.h_out_f32 + (int64_t)r * a.d + j) = hn;
+    if (a.h_out) {
+        if constexpr (C == 1) {
+            a.h_out[(int64_t)r * a.d + j] = out.x[0];
+        } else {
+            typedef uint16_t V __attribute__((ext_vector_type(C)));
+            *reinterpret_cast<V *>(a.h_out + (int64_t)r * a.d + j) = __builtin_bit_cast(V, out);
+        }
+    }
+    if (a.h_out_f32) st<C>(a.h_out_f32 + (int64_t)r * a.d + j, hn);
 }
 
-// (Half of it is used; the published workspace size stays what it was.)
-size_t drafter_gate_scratch_floats(int M) { return (size_t)2 * M * kGateMaxChunks * 2; }
+size_t drafter_gate_scratch_floats(int M) { return (size_t)M * kGateMaxChunks * 2; }
 
+template <bool kF16, int MAXC, int C> static void launch_gates_as(const GateArgs &a, int M, hipStream_t st)
+{
+    const dim3 grid((a.d + kGateThreads * C - 1) / (kGateThreads * C), M), block(kGateThreads);
+    hipLaunchKernelGGL((drafter_state_kernel<kF16, MAXC, C>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((drafter_hidden_kernel<kF16, C>), grid, block, 0, st, a);
+}
+
+template <bool kF16, int C> static void launch_gates_c(const GateArgs &a, int M, hipStream_t st)
+{
+    const int rounds = (a.d + 4 * kRowChunk - 1) / (4 * kRowChunk);
+    if (rounds == 1) launch_gates_as<kF16, 4, C>(a, M, st);
+    else if (rounds == 2) launch_gates_as<kF16, 8, C>(a, M, st);
+    else if constexpr (C > 1) {                             // (with one channel a lane a row of this width has too many chunks)
+        if (rounds == 3) launch_gates_as<kF16, 12, C>(a, M, st);
+        else launch_gates_as<kF16, kRowMaxChunks, C>(a, M, st);
+    }
+}
+
+// Channels a lane: a lane's sigmoids and GeLUs follow each other, about 100 instructions a channel, so it takes as few as leave no more
+// than one workgroup a compute unit (each reads its whole row) and no more chunks than the scratch holds.  us per cell, four a lane -> as
+// few as that (up to 512 workgroups, up to 1024): bf16, 10 rows, 2048 from 2048 15.4 -> 13.9 (13.9, 14.4), 4096 from 4096 31.3 -> 30.0 (30.0, 30.0),
+// 12288 from 4096 72.7 -> 71.6 (71.6, 71.6); fp16, 16384 from 4096 92.6 -> 92.8 (93.4, 93.4); 40 rows, 12288 77.4 -> 77.5 (77.6, 78.9).
 template <bool kF16> static hipError_t launch_gates_dt(const GateArgs &a, int M, hipStream_t st)
 {
-    const dim3 grid((a.d + kGateChunk - 1) / kGateChunk, M), block(kGateThreads);
-    switch ((grid.x + 3) / 4) {
-    case 1: hipLaunchKernelGGL((drafter_state_kernel<kF16, 4>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((drafter_state_kernel<kF16, 8>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((drafter_state_kernel<kF16, 12>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((drafter_state_kernel<kF16, kGateMaxChunks>), grid, block, 0, st, a); break;
-    }
-    hipLaunchKernelGGL(drafter_hidden_kernel<kF16>, grid, block, 0, st, a);
+    auto fits = [&](int channels) {
+        const int chunks = (a.d + kGateThreads * channels - 1) / (kGateThreads * channels);
+        return chunks <= kGateMaxChunks && chunks * M <= kGateWorkgroups;
+    };
+    if (fits(1)) launch_gates_c<kF16, 1>(a, M, st);
+    else if (fits(2)) launch_gates_c<kF16, 2>(a, M, st);
+    else launch_gates_c<kF16, 4>(a, M, st);
     return hipGetLastError();
 }
 

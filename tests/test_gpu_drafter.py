@@ -76,6 +76,18 @@ def test_row_statistics_at_the_edges_of_the_chunk_counts(d):
     _check(case, 1.0)
 
 
+@pytest.mark.parametrize("dtype,d,M", [
+    (W.DT_BF16, 8192, 8), (W.DT_F16, 8192, 9),              # 256 workgroups of one channel a lane, and one row more: two
+    (W.DT_F16, 8208, 5),                                    # more chunks of one channel a lane than the scratch holds
+    (W.DT_BF16, 1040, 51), (W.DT_F16, 1040, 52),            # a last chunk of 16 channels, one and two a lane
+    (W.DT_BF16, 4112, 28), (W.DT_F16, 4112, 29),            # two a lane and four
+    (W.DT_BF16, 16384, 8), (W.DT_F16, 16384, 9),            # the widest row: 32 chunks, and 16
+])
+def test_gates_by_channels_a_lane(dtype, d, M):
+    case = W.make_drafter_case("t", 700 + d % 89 + M, dtype=dtype, d_in=32, d=d, P=3, M=M, vocab=50)
+    _check(case, 1.0)
+
+
 def _tiled_by_definition(w_bits, d_in, d):
     """The tiled layout built from its definition in the header, granule by granule."""
     rows = w_bits.reshape(4 * d, d_in)
