@@ -318,11 +318,15 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         const int row = tg * kRowTile + j, i = node_of(row);
         irow[t] = tile_ok && row < p.R && i < Nb ? i : -1;
         if constexpr (kF32) {
-            const float *qp = reinterpret_cast<const float *>(q_head + row_offset(min(row, p.R - 1)));
+            const float4 *qp = reinterpret_cast<const float4 *>(q_head + row_offset(min(row, p.R - 1)));
 #pragma unroll
-            for (int kk = 0; kk < QREGS; ++kk) {
-                const float x = qp[4 * kk + qd];
-                qs[t][kk] = irow[t] >= 0 ? x : 0.f;
+            for (int c = 0; c < QREGS / 4; ++c) {            // (the channels that a quad of lanes takes, see careful_step)
+                const float4 x = qp[4 * c + qd];
+                const bool on = irow[t] >= 0;
+                qs[t][4 * c] = on ? x.x : 0.f;
+                qs[t][4 * c + 1] = on ? x.y : 0.f;
+                qs[t][4 * c + 2] = on ? x.z : 0.f;
+                qs[t][4 * c + 3] = on ? x.w : 0.f;
             }
         }
     }
@@ -794,42 +798,44 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         const unsigned char *Kb = smem + buf * STAGE + ks * 32 * ROWB;
         const unsigned char *Vb = Kb + VREG;
         if constexpr (kF32) {
-            // fp32 path: 16x16x4 MFMA, one channel (QK) / one key (PV) per quad and step
+            // fp32 path: 16x16x4 MFMA, one channel (QK) / one key (PV) per quad and instruction; one softmax for both halves of the
+            // step.  The order of the channels is free as long as both operands agree, so an LDS read brings a lane four at once:
+            // K and Q take channels 16 c + 4 quad .. +3 one after the other, and tile u, lane j of V^T is channel
+            // 64 (u / 4) + 4 j + u % 4 (the epilogue puts them back).  The loop is bound by the LDS and its instructions.  us, one value a
+            // read and a softmax for each half -> now: head_dim 64, 16 rows, 512 tokens 10.1 -> 9.5, 128 rows, 2K 21.4 -> 17.4, head_dim 128, 16
+            // rows, 2K 14.4 -> 13.05, 64 rows 17.4 -> 14.05, 128 rows 33.9 -> 26.9.  (One softmax alone 21.4 -> 20.7 and 33.7 -> 32.6.)
+            static_assert(TPW == 1 && NT % 4 == 0, "one tile a wavefront, channels in blocks of 64");
+            f32x4 sc[2];
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
-                float kf[QREGS];
+                f32x4 kf[QREGS / 4];
                 const int key = kt * 16 + j;
 #pragma unroll
+                for (int c = 0; c < QREGS / 4; ++c)
+                    kf[c] = *reinterpret_cast<const f32x4 *>(Kb + key * ROWB + (((4 * c + qd) ^ (key & KSWZ)) << 4));
+                sc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
                 for (int kk = 0; kk < QREGS; ++kk)
-                    kf[kk] = *reinterpret_cast<const float *>(
-                        Kb + key * ROWB + ((kk ^ (key & KSWZ)) << 4) + qd * 4);
-                float vraw[4][NT];
+                    sc[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk / 4][kk % 4], qs[0][kk], sc[kt], 0, 0, 0);
+            }
+            softmax_step(sc[0], sc[1], 0, step_pos);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                f32x4 vf[4][NT / 4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int vkey = kt * 16 + 4 * qd + r;
                     const int vs = (vkey & VSWM) << 1;
 #pragma unroll
-                    for (int u = 0; u < NT; ++u)
-                        vraw[r][u] = *reinterpret_cast<const float *>(
-                            Vb + vkey * ROWB + (((4 * u + (j >> 2)) ^ vs) << 4) + (j & 3) * 4);
+                    for (int b4 = 0; b4 < NT / 4; ++b4)
+                        vf[r][b4] = *reinterpret_cast<const f32x4 *>(Vb + vkey * ROWB + (((16 * b4 + j) ^ vs) << 4));
                 }
 #pragma unroll
-                for (int t = 0; t < TPW; ++t) {
-                    f32x4 s0 = {0.f, 0.f, 0.f, 0.f};
+                for (int r = 0; r < 4; ++r) {
 #pragma unroll
-                    for (int kk = 0; kk < QREGS; ++kk)
-                        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk], qs[t][kk], s0, 0, 0, 0);
-                    // the other 16 keys of the step come with the next kt: give
-                    // the softmax a fully masked second half
-                    f32x4 s1 = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-                    softmax_step(s0, s1, t, step_pos + kt * 16);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-                        for (int u = 0; u < NT; ++u)
-                            O[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(vraw[r][u], s0[r], O[t][u], 0, 0, 0);
-                        O[t][NT] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, s0[r], O[t][NT], 0, 0, 0);
-                    }
+                    for (int u = 0; u < NT; ++u)
+                        O[0][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][u / 4][u % 4], sc[kt][r], O[0][u], 0, 0, 0);
+                    O[0][NT] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sc[kt][r], O[0][NT], 0, 0, 0);
                 }
             }
         } else {
@@ -1192,10 +1198,19 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             const size_t slot = pc.slot + tg;
             const float l = O[t][NT][0];
             if (kF32 || !p.half_partials) {                          // uniform over the launch
-                float4 *po = static_cast<float4 *>(p.part_o) + slot * (size_t)(NT * 64) + lane;
+                float4 *po = static_cast<float4 *>(p.part_o) + slot * (size_t)(NT * 64);
+                if constexpr (kF32) {
+                    // element r of tile u is channel 64 (u / 4) + 4 (4 quad + r) + u % 4: element u % 4 of lane 16 r + j, tile 4 (u / 4) + quad
 #pragma unroll
-                for (int u = 0; u < NT; ++u)
-                    po[u * 64] = make_float4(O[t][u][0], O[t][u][1], O[t][u][2], O[t][u][3]);
+                    for (int u = 0; u < NT; u += 4)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            po[(u + qd) * 64 + 16 * r + j] = make_float4(O[t][u][r], O[t][u + 1][r], O[t][u + 2][r], O[t][u + 3][r]);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < NT; ++u)
+                        po[u * 64 + lane] = make_float4(O[t][u][0], O[t][u][1], O[t][u][2], O[t][u][3]);
+                }
                 if (qd == 0) {
                     float *stats = p.part_ml + slot * kPartMl + 3 * j;
                     stats[0] = m[t];
