@@ -234,12 +234,17 @@ def owl_verify_attn(desc: VerifyDesc, q, k_cache, v_cache, page_table, ctx_lens,
                     workspace, dev_status=None, stream: Optional[int] = None) -> None:
     """All tensor arguments are torch CUDA tensors (or None where the C ABI
     allows NULL); nothing is copied or allocated here."""
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    rc = lib().owl_verify_attn(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                               _ptr(page_table), _ptr(ctx_lens), _ptr(tree_parent), _ptr(out),
-                               _ptr(workspace), ws_bytes, _ptr(dev_status),
-                               _stream() if stream is None else stream)
-    _check(rc, "owl_verify_attn")
+    # (The pointers are taken in place: a call with little work is bound by what the host does for it, and nine calls of _ptr
+    # were 1 us of that: 4 fp32 rows on 512 tokens 9.65 -> 9.25 us a call.)
+    rc = lib().owl_verify_attn(
+        ctypes.byref(desc), None if q is None else q.data_ptr(), None if k_cache is None else k_cache.data_ptr(),
+        None if v_cache is None else v_cache.data_ptr(), None if page_table is None else page_table.data_ptr(),
+        None if ctx_lens is None else ctx_lens.data_ptr(), None if tree_parent is None else tree_parent.data_ptr(),
+        None if out is None else out.data_ptr(), None if workspace is None else workspace.data_ptr(),
+        0 if workspace is None else workspace.nbytes, None if dev_status is None else dev_status.data_ptr(),
+        _stream() if stream is None else stream)
+    if rc != OWL_OK:
+        raise OwlError(rc, "owl_verify_attn")
 
 
 def owl_verify_attn_init(desc: VerifyDesc) -> None:
