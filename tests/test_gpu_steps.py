@@ -170,6 +170,34 @@ def test_commit_matches_oracle(dtype, D, head_major, paged):
         assert np.array_equal(new_ctx.cpu().numpy(), want_ctx)
 
 
+@pytest.mark.parametrize("dtype,D", [(W.DT_BF16, 64), (W.DT_F16, 128), (W.DT_F32, 128)])
+def test_commit_around_one_piece_a_thread(dtype, D):
+    """256 threads hold one 16-byte piece each up to 256 pieces of moved rows and eight beyond: counts on both sides
+    of that line (8, 16 and 32 pieces a row), and the largest, with lists that overlap what they write."""
+    r = _rng(D + dtype)
+    line = 256 * 16 // (D * (4 if dtype == W.DT_F32 else 2))
+    na = np.array([line - 1, line, line + 1, 64, 63, 1], dtype=np.int32)
+    N = 64
+    ctx = [37, 1000, 0, 16, 5, 33]
+    case = W.make_case("commit-line", 41, dtype=dtype, Hq=4, Hkv=2, D=D, ctx_lens=ctx,
+                       trees=[W.random_tree(N, 6, r) for _ in ctx])
+    acc = np.full((case.B, N), -1, dtype=np.int32)
+    for b, n in enumerate(na):
+        acc[b, :n] = np.sort(r.choice(N, size=n, replace=False))
+    step = VerifyStep(case)
+    new_ctx = torch.zeros(case.B, dtype=torch.int32, device=DEV)
+    B.owl_commit_kv(step.desc, step.k, step.v, step.page_table, step.ctx_lens, _i32(acc), _i32(na), new_ctx,
+                    step.status)
+    torch.cuda.synchronize()
+    assert step.dev_status() == 0
+    for name, pool, dev in (("k", case.k_pool, step.k), ("v", case.v_pool, step.v)):
+        want, want_ctx = S.commit_kv(pool, case.page_table, case.ctx_lens, acc, na, case.stride_page,
+                                     case.stride_head, case.stride_token, case.Hkv, case.D)
+        got = dev.cpu().numpy().view(pool.dtype).reshape(pool.shape)
+        assert np.array_equal(got.view(np.uint8), want.view(np.uint8)), name
+        assert np.array_equal(new_ctx.cpu().numpy(), want_ctx)
+
+
 def test_commit_then_verify_sees_the_committed_rows():
     """After the commit, a verify step over the longer context reads the moved rows:
     compare with the oracle run on the oracle-committed cache."""
