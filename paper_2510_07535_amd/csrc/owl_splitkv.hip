@@ -700,14 +700,15 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // A wavefront that finds it is not raises an alarm, which all read behind a later barrier: before the loops, if the scores of
     // its first step span more than 2^14 in some lane (ten standard deviations of the scores of unit-variance inputs: a long
     // tail, and a later score is likely to pass the head room above the first step's maximum); in the pipelined loop, also if those
-    // of the second do; and at the barriers of stages 4, 16, 64, ... of a frozen loop, if a row sum has overflowed.  A guarded
+    // of the second do; and at the barriers of stages 4, 16, 64, ... of a frozen loop, if a row sum has overflowed (with three tiles a wavefront, whose plain
+    // loop has seen 32 keys by then, of stage 1 as well; looks lie two barriers apart or more, and the plain loops have none at stage 0).  A guarded
     // loop then takes over, from the start.  What the last look misses the check behind the loops finds.  (Two words, one for before the loops and one for within: no
     // wavefront writes a word that another may still have to read.)  Before, every piece formed the scores of its first one
     // to three stages twice to measure their spread, and an overflow was redone with the exact loop.  us, 8 heads: 24 rows, 2.5K tokens
     // 10.8 -> 10.5, 64 rows, 20K 24.8 -> 21.6, 240 rows, 5K / 20K 18.0 -> 17.9 / 34.9 -> 34.1, four sequences of 900-9K 35.0 -> 33.2; with one
-    // key in twenty eight times as long, 240 rows, 5K / 20K 19.4 -> 19.1 / 40.6 -> 40.8, 16 sequences of 900-4K 109 -> 81, but 320
-    // rows, 64K 112 -> 116: the three-tile kernel sees 32 keys before its loop, where it saw 192.  (Looks at 8, 32, ... as well:
-    // 240 rows, 5K 17.9 -> 18.0.)
+    // key in twenty eight times as long, 240 rows, 5K / 20K 19.4 -> 19.1 / 40.6 -> 40.8, 16 sequences of 900-4K 109 -> 81; 320
+    // rows, 16K / 64K / 128K 61.6 -> 47.3 / 107.5 -> 107.8 / 199 -> 198, without the look at stage 1 48.5 / 112.8 / 201.  (Looks at 8, 32, ... as
+    // well: 240 rows, 5K 17.9 -> 18.0.)
     auto alarm = [&](bool bad, int word) {
         if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_any[word] = 1;
     };
@@ -718,7 +719,9 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         for (int t = 0; t < TPW; ++t) bad |= !(O[t][NT][0] < 1.0e30f);
         alarm(bad, 1);
     };
-    auto watched = [](int s) { return (s & (s - 1)) == 0 && (s & 0x2AAAAAAB) == 0; };       // 0, 4, 16, 64, ...
+    auto watched = [](int s) {                       // 0, 4, 16, 64, ..., and 1 with three tiles a wavefront
+        return (s & (s - 1)) == 0 && (s & (TPW > 2 ? 0x2AAAAAAA : 0x2AAAAAAB)) == 0;
+    };
     auto is_wide = [&](const f32x4 &s0, const f32x4 &s1, float high) {
         const float low = fminf(fminf(fminf(s0[0], s0[1]), fminf(s0[2], s0[3])),
                                 fminf(fminf(s1[0], s1[1]), fminf(s1[2], s1[3])));

@@ -552,7 +552,8 @@ def test_fp16_score_range_paths(oracle_mod, frac, gain, tag, N, G):
 
 @pytest.mark.parametrize("N,G,D", [(6, 4, 128), (60, 4, 64), (26, 4, 128), (60, 4, 128), (40, 8, 128)])     # 2, 15, 7, 15, 20 row tiles
 def test_fp16_overflow_found_at_every_look(oracle_mod, N, G, D):
-    """A frozen fp16 loop looks for overflowed row sums at stages 4, 16, 64, ..., and once more behind its last stage.  Each split here has one key that overflows the reference, in another place: the second step, the stages
+    """A frozen fp16 loop looks for overflowed row sums at stages 4, 16, 64, ... (with three tiles a wavefront at stage 1
+    too), and once more behind its last stage.  Each split here has one key that overflows the reference, in another place: the second step, the stages
     around a look, the last fast stage.  The first split has none."""
     C, L = 1280, 8 * 1280 + 100
     hot = [s * C + 64 * stage + slot for s, (stage, slot) in enumerate([(0, 40), (1, 9), (3, 63), (4, 0), (15, 40), (16, 3), (19, 63)], 1)]
