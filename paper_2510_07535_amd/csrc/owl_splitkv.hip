@@ -62,6 +62,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 512;        // 8 wavefronts
 constexpr int kWaves = kThreads / 64;
 constexpr float kMInit = -1.0e30f;   // "no key seen yet"; finite so that m - m is 0
+constexpr float kGuardRoom = 11.0f;  // fp16: how far a score may lie above a guarded reference (2^16 is the limit)
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -506,6 +507,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // fp16 storage: a frozen reference that overflows shows in the row sums.  The loops look for it at a few stages (see
     // `watched`) and give way to the plain loop with a guarded reference (see fast_sx).
     constexpr bool kGuard = std::is_same<T, _Float16>::value;
+    constexpr bool kExactRedo = kGuard && TPW == 1 && WK == 2;       // see the passes
     // p = 2^(x - m) is exact in relative terms whatever m is; with m frozen at
     // the first step's row maximum, p overflows only if a later score exceeds
     // it by more than ~100 (log2 units), which the row sum exposes afterwards.
@@ -513,7 +515,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // the V^T fragments already in registers (fast_pv), so that the stage loop
     // can put a barrier between them.
     auto fast_sx = [&](const unsigned char *Kb, const unsigned char *Vb, uint4 (&pf)[TPW], uint4 (&vf)[NT],
-                       auto ntag, auto gtag) {
+                       auto ntag, auto gtag, [[maybe_unused]] float room) {
         constexpr int NA = decltype(ntag)::value;    // tiles this wave really owns
         constexpr bool kGuarded = decltype(gtag)::value;
         // One tile a wavefront: half of the V^T fragments are asked for behind the scores, so that they arrive while P is
@@ -544,15 +546,16 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                     __builtin_amdgcn_sched_barrier(0x400);
                 }
                 if constexpr (kGuarded) {
-                    // fp16 holds 2^(x - m) only up to 2^16.  The reference stays frozen as long as no
-                    // score of the step comes within 2^5 of that; a row that does moves its reference
-                    // 4 above the offender and rescales its accumulators (rare; uniform branch).
+                    // The reference stays until a score lies more than `room` above it.  The row then moves it to
+                    // its highest score, as the exact loop does, and rescales its accumulators (rare; uniform branch).
+                    // Not above that: fp16 has nothing below 2^-25, and the many small weights would pay for the
+                    // head room (one score 20.5 above the rest of 16K: error 9e-6, with 4 of head room 7e-4).
                     const float tm = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
                                            fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
                     // detection needs no cross-lane step: any lane's own keys can raise the alarm
-                    if (__builtin_amdgcn_ballot_w64(__builtin_fmaf(tm, c_log2, -m[t]) > 11.0f) != 0) {
+                    if (__builtin_amdgcn_ballot_w64(__builtin_fmaf(tm, c_log2, -m[t]) > room) != 0) {
                         const float sc = quad_column_max(tm) * c_log2;
-                        const float mn = sc > m[t] + 11.0f ? sc + 4.0f : m[t];
+                        const float mn = sc > m[t] + room ? sc : m[t];
                         const float alpha = fast_exp2(m[t] - mn);
                         m[t] = mn;
 #pragma unroll
@@ -697,18 +700,19 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     };
 
     // ---- fp16 only: is the frozen reference good? ----
-    // A wavefront that finds it is not raises an alarm, which all read behind a later barrier: before the loops, if the scores of
-    // its first step span more than 2^14 in some lane (ten standard deviations of the scores of unit-variance inputs: a long
-    // tail, and a later score is likely to pass the head room above the first step's maximum); in the pipelined loop, also if those
-    // of the second do; and at the barriers of stages 4, 16, 64, ... of a frozen loop, if a row sum has overflowed (with three tiles a wavefront, whose plain
-    // loop has seen 32 keys by then, of stage 1 as well; looks lie two barriers apart or more, and the plain loops have none at stage 0).  A guarded
-    // loop then takes over, from the start.  What the last look misses the check behind the loops finds.  (Two words, one for before the loops and one for within: no
-    // wavefront writes a word that another may still have to read.)  Before, every piece formed the scores of its first one
-    // to three stages twice to measure their spread, and an overflow was redone with the exact loop.  us, 8 heads: 24 rows, 2.5K tokens
-    // 10.8 -> 10.5, 64 rows, 20K 24.8 -> 21.6, 240 rows, 5K / 20K 18.0 -> 17.9 / 34.9 -> 34.1, four sequences of 900-9K 35.0 -> 33.2; with one
-    // key in twenty eight times as long, 240 rows, 5K / 20K 19.4 -> 19.1 / 40.6 -> 40.8, 16 sequences of 900-4K 109 -> 81; 320
-    // rows, 16K / 64K / 128K 61.6 -> 47.3 / 107.5 -> 107.8 / 199 -> 198, without the look at stage 1 48.5 / 112.8 / 201.  (Looks at 8, 32, ... as
-    // well: 240 rows, 5K 17.9 -> 18.0.)
+    // A wavefront that finds it is not raises an alarm, which all read behind a later barrier.  It looks
+    //   before the loops        if the scores of its first step span more than 2^14 in some lane (ten standard deviations of
+    //                           the scores of unit-variance inputs: a long tail, and a later score is likely to pass the head
+    //                           room above the first step's maximum); in the pipelined loop, also at those of the second
+    //   at stages 4, 16, 64...  of a frozen loop, behind the barrier, if a row sum has overflowed (three tiles a wavefront: at
+    //                           stage 1 too, whose plain loop has seen 32 keys by then)
+    // and what the last look misses the check behind the loops finds.  Looks lie two barriers apart or more, the plain loops
+    // have none at stage 0, and there is one word for before the loops and one for within: no wavefront writes a word that
+    // another may still have to read.  Before, every piece formed the scores of its first one to three stages twice to measure
+    // their spread, and every overflow was redone with the exact loop.  us, 8 heads: 24 rows, 2.5K tokens 10.8 -> 10.5, 64 rows,
+    // 20K 24.8 -> 21.6, 240 rows, 5K / 20K 18.0 -> 17.9 / 34.9 -> 34.1, four sequences of 900-9K 35.0 -> 33.2.  (Looks at 8, 32,
+    // ... as well: 240 rows, 5K 17.9 -> 18.0; 320 rows, 64K with one key in twenty eight times as long 107.8, without the look at
+    // stage 1 112.8.)
     auto alarm = [&](bool bad, int word) {
         if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_any[word] = 1;
     };
@@ -732,7 +736,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     };
 
     // ---- reference m of every row tile from one unmasked step (before the fast loop) ----
-    auto init_reference = [&](int buf, int ks, f32x4 (&keep)[TPW][2]) {
+    auto init_reference = [&](int buf, int ks, [[maybe_unused]] float head_room, f32x4 (&keep)[TPW][2]) {
         if constexpr (!kF32) {
             // (Formed here: as an address that the compiler kept from before the stages were requested, it came back from
             // scratch memory in the three-tile kernel, and the wait for it drained the whole ring before the first step.)
@@ -755,7 +759,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                 const float tm = highest(s0, s1);
                 // fp16 holds 2^(x - m) only up to 2^16: its reference sits a little above the
                 // first step's maximum, which trades low-end resolution for head room
-                m[t] = quad_column_max(tm) * c_log2 + (kGuard ? 4.0f : 0.0f);
+                m[t] = quad_column_max(tm) * c_log2 + (kGuard ? head_room : 0.0f);
                 if constexpr (kGuard) wide |= is_wide(s0, s1, tm);
             }
             if constexpr (kGuard) alarm(wide, 0);
@@ -915,7 +919,7 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // ring slot is free all the same) across the barrier.  After every barrier
     // the two waves of a SIMD are then half a step apart, and one's matrix work
     // overlaps the other's vector work.
-    auto run_fast_n = [&](int n_fast, auto ntag, auto gtag) -> int {
+    auto run_fast_n = [&](int n_fast, auto ntag, auto gtag, [[maybe_unused]] float room) -> int {
         if constexpr (!kF32) {
             constexpr bool kWatch = kGuard && !decltype(gtag)::value;
             const bool late = wave >= kWaves / 2;
@@ -943,16 +947,16 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
                         admit(s);
                         if (late) fast_pv(pf, vf, ntag);        // late waves carry it over
                     }
-                    fast_sx(kptr(s, 0), kptr(s, 0) + VREG, pf, vf, ntag, gtag);
+                    fast_sx(kptr(s, 0), kptr(s, 0) + VREG, pf, vf, ntag, gtag, room);
                     fast_pv(pf, vf, ntag);
-                    fast_sx(kptr(s, 1), kptr(s, 1) + VREG, pf, vf, ntag, gtag);
+                    fast_sx(kptr(s, 1), kptr(s, 1) + VREG, pf, vf, ntag, gtag, room);
                 } else {
                     if (s > 0) {
                         if (!late) fast_pv(pf, vf, ntag);
                         admit(s);
                         if (late) fast_pv(pf, vf, ntag);
                     }
-                    fast_sx(kptr(s, wk), kptr(s, wk) + VREG, pf, vf, ntag, gtag);
+                    fast_sx(kptr(s, wk), kptr(s, wk) + VREG, pf, vf, ntag, gtag, room);
                 }
             };
             if constexpr (kGuard && (TPW > 1 || !kWatch)) {
@@ -1033,22 +1037,22 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     };
     // the fast loop is compiled once per possible tile count of a wave, so that
     // its body has no per-tile branches
-    auto run_fast_tag = [&](int n_fast, bool guarded, f32x4 (&Sa)[TPW][2], auto ntag) -> int {
+    auto run_fast_tag = [&](int n_fast, bool guarded, float room, f32x4 (&Sa)[TPW][2], auto ntag) -> int {
         if constexpr (kGuard)
-            if (guarded) return run_fast_n(n_fast, ntag, std::true_type{});      // uniform over the workgroup
+            if (guarded) return run_fast_n(n_fast, ntag, std::true_type{}, room);      // uniform over the workgroup
         if constexpr (kPipe) {
             return run_pipe_n(n_fast, Sa, ntag);
         } else {
-            return run_fast_n(n_fast, ntag, std::false_type{});
+            return run_fast_n(n_fast, ntag, std::false_type{}, 0.f);
         }
     };
-    auto run_fast = [&](int n_fast, bool guarded, f32x4 (&Sa)[TPW][2]) -> int {
-        if (my_nt == TPW) return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, TPW>{});
+    auto run_fast = [&](int n_fast, bool guarded, float room, f32x4 (&Sa)[TPW][2]) -> int {
+        if (my_nt == TPW) return run_fast_tag(n_fast, guarded, room, Sa, std::integral_constant<int, TPW>{});
         if (TPW > 1 && my_nt == TPW - 1)
-            return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, (TPW > 1 ? TPW - 1 : 0)>{});
+            return run_fast_tag(n_fast, guarded, room, Sa, std::integral_constant<int, (TPW > 1 ? TPW - 1 : 0)>{});
         if (TPW > 2 && my_nt == TPW - 2)
-            return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, (TPW > 2 ? TPW - 2 : 0)>{});
-        return run_fast_tag(n_fast, guarded, Sa, std::integral_constant<int, 0>{});
+            return run_fast_tag(n_fast, guarded, room, Sa, std::integral_constant<int, (TPW > 2 ? TPW - 2 : 0)>{});
+        return run_fast_tag(n_fast, guarded, room, Sa, std::integral_constant<int, 0>{});
     };
     static_assert(TPW <= 3, "run_fast dispatches on at most three tile counts");
 
@@ -1061,7 +1065,16 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
     // number: the whole split is redone with the careful step.  bf16 shares fp32's
     // exponent range, so that happens only for scores ~100 above the reference.
     // An fp16 P overflows 16 above it: fp16 has a pass between the two, the fast loop
-    // with a guarded reference.  fp32 is the small correctness shape and has no fast loop.
+    // with a guarded reference.  It serves pieces whose first scores already show a long
+    // tail and redoes those that overflowed later on, these without room above the
+    // reference: no weight is above 1 then, as in the exact loop, and none less exact
+    // (with room a row's largest weight is rounded too, and the error of a redone piece
+    // was up to 1.2 times as large).  With one tile a wavefront and two key groups the
+    // exact loop is the faster redo.  us, exact loop and guarded without room, 8 heads, one
+    // key in 200 eight times as long: 240 rows, 5K in four row groups 27.1 and 28.1, 64
+    // rows, 20K 29.9 and 30.8; 104 rows, 16 sequences of 8K-20K 268 and 256, 320 rows,
+    // 64K 170 and 137.
+    // fp32 is the small correctness shape and has no fast loop.
     constexpr bool kHasFast = !kF32;
     constexpr int kPasses = kGuard ? 3 : 2;
     // With one tile a wavefront the piece is bound by its K/V, and all that the ring holds is requested at once.  With more it
@@ -1114,22 +1127,25 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
         if (n_fast > 0) {
             stamp(2);
             f32x4 Sa[TPW][2];
+            [[maybe_unused]] float room = kGuardRoom;
             if constexpr (kGuard) {
-                if (pass == 1 && !kept) {
+                if (pass == 1 && !kept) {             // an overflowed piece
+                    room = 0.f;
                     wait_stage(0);
                     __syncthreads();
                 }
             }
-            init_reference(0, wk, Sa);
+            init_reference(0, wk, room > 0.f ? 4.f : 0.f, Sa);
             if constexpr (kGuard) {
                 __syncthreads();
                 if (alarmed(0)) pass = 1;              // uniform over the workgroup
             }
-            [[maybe_unused]] const int end = run_fast(n_fast, pass == 1, Sa);
+            [[maybe_unused]] const int end = run_fast(n_fast, pass == 1, room, Sa);
             if constexpr (kGuard) {
                 kept = end == 0;
                 if (end < n_fast) {                   // a redo begins once no transfer is under way and no wavefront reads the ring
                     if (!kept) wait_vmcnt<0>();
+                    if (kExactRedo && !kept) pass = 1;
                     __syncthreads();
                     continue;
                 }
@@ -1145,11 +1161,14 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
 #pragma unroll
         for (int t = 0; t < TPW; ++t) bad |= !(O[t][NT][0] < 1.0e30f);
         if (!workgroup_any(bad, wave, lane, s_any + kWaves)) break;
+        if constexpr (kExactRedo) pass = 1;
+        if constexpr (!kGuard) {
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-            m[t] = kMInit;
+            for (int t = 0; t < TPW; ++t) {
+                m[t] = kMInit;
 #pragma unroll
-            for (int u = 0; u <= NT; ++u) O[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int u = 0; u <= NT; ++u) O[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
         }
     }
 

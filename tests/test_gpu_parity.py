@@ -575,6 +575,60 @@ def test_fp16_overflow_found_at_every_look(oracle_mod, N, G, D):
         assert_close(got, want, case.dtype, f"N={N} G={G} D={D} split={split} plan={step.plan.as_dict()}")
 
 
+def _copies(case, n, planned):
+    """One sequence n times over (same pages, queries and tree), announced with ``planned`` tokens."""
+    import dataclasses
+    table = np.full((1, (planned + case.N + 15) // 16), -1, dtype=np.int32)
+    table[:, :case.page_table.shape[1]] = case.page_table
+    rep = lambda a: np.ascontiguousarray(np.repeat(a, n, axis=0))
+    return dataclasses.replace(case, B=n, q=rep(case.q), page_table=rep(table), ctx_lens=rep(case.ctx_lens),
+                               tree_parent=rep(case.tree_parent), max_pages_per_seq=table.shape[1])
+
+
+_LAYOUTS = ("1x4x2", "1x8x1", "2x4x2", "2x8x1", "3x8x1")        # tiles a wavefront x row wavefronts x key groups
+
+
+def _layout(plan):
+    return _LAYOUTS[plan.kernel_variant % 5]
+
+
+@pytest.mark.parametrize("N,G,layout", [(6, 4, "1x4x2"), (26, 4, "1x8x1"), (16, 8, "2x4x2"), (60, 4, "2x8x1"), (40, 8, "3x8x1")])
+def test_fp16_redone_piece_keeps_its_small_weights(oracle_mod, N, G, layout):
+    """One key of 16384 lies about 17.5 (log2 units) above the frozen reference of every row: fp16's P overflows and the piece is
+    redone.  All other keys then weigh 2^-20 and less, near the end of what fp16 holds, so a reference above the offender
+    loses them: four above it, the output is off by a thousandth of the offender's V row."""
+    C, hot, target = 16384, 20 * 64 + 9, 24.5
+    case = W.make_case("f16_small", 1950 + N, dtype=W.DT_F16, Hq=8 * G, Hkv=8, D=128, ctx_lens=[C], trees=[W.random_tree(N, 6, _rng(N))])
+    # channel 0 belongs to the offender: 8 in every query, nothing in the other keys
+    c = case.scale * 1.4426950408889634
+    case.q[..., 0] = W.store(np.full((1,), 8.0, np.float32), W.DT_F16)[0]
+    case.k_pool[:, :, :, 0] = 0
+    row = np.zeros((8, 128), np.float32)
+    row[:, 0] = target / (8.0 * c)
+    case.k_pool[int(case.page_table[0, hot // 16]), :, hot % 16, :] = W.store(row, W.DT_F16)
+    many = _copies(case, 8, 33000)
+    got, step = _run(many, split_tokens=C, max_ctx_len=33000, flags=B.OWL_FLAG_FP32_PARTIALS)
+    assert step.plan.row_groups == 1 and _layout(step.plan) == layout, step.plan.as_dict()
+    assert all(np.array_equal(got[0], got[b]) for b in range(1, 8))
+    rows = sample_rows(case, 64, seed=N, always=[(0, 0, 0), (0, N - 1, case.Hq - 1)])
+    want = oracle_mod.verify_attn_case(case, rows=rows)
+    pos = np.arange(C)
+    pages, q = case.page_table[0, pos // 16], W.widen(case.q[0], W.DT_F16).astype(np.float64)
+    keys, vals = (W.widen(p[pages, :, pos % 16, :], W.DT_F16).astype(np.float64) for p in (case.k_pool, case.v_pool))       # [C, Hkv, D]
+    over = -np.inf
+    for (_, i, h), w64 in zip(rows, want):
+        x = c * keys[:, h // G] @ q[i, h]
+        over = max(over, x[hot] - x[:64].max() - 4.0)
+        # What fp16 makes of weights 2^(x - highest): a redone piece has no worse ones.  (A lower reference keeps more of
+        # them; 1e-4 covers a weight's own error, of its score in fp32 sums, and a rounding at another place.)
+        w = np.exp2(x - x[hot])
+        off = np.abs(w - w.astype(np.float16)) + 1e-4 * w
+        bound = (off[:, None] * np.abs(vals[:, h // G] - w64)).sum(axis=0) / w.sum() + 1e-5
+        err = np.abs(got[0, i, h] - w64)
+        assert (err <= bound).all(), (layout, i, h, float(err.max()), float(bound.max()))
+    assert over > 16.0, over
+
+
 @pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # 2 / 15 / 20 row tiles: all three fast loops
 def test_bf16_reference_overflow_redo(oracle_mod, N, G):
     """bf16 storage keeps the softmax reference of a split frozen at the maxima of its first keys.
