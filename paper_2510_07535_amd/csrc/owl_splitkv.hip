@@ -1109,6 +1109,13 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             __syncthreads();
         }
     }
+    // (fp16) An overflow leaves a row sum infinite.  One that is no number comes from the inputs, and no other reference mends it.
+    auto not_a_number = [&]() -> bool {
+        bool any = false;
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) any |= O[t][NT][0] != O[t][NT][0];
+        return workgroup_any(any, wave, lane, s_any + kWaves);
+    };
     [[maybe_unused]] bool kept = false;               // (fp16) the ring still holds the first stages
     for (int pass = 0; pass < kPasses; ++pass) {
         if constexpr (kGuard) {
@@ -1144,13 +1151,16 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
             if constexpr (kGuard) {
                 kept = end == 0;
                 if (end < n_fast) {                   // a redo begins once no transfer is under way and no wavefront reads the ring
-                    if (!kept) wait_vmcnt<0>();
-                    if (kExactRedo && !kept) pass = 1;
+                    if (!kept) {
+                        wait_vmcnt<0>();
+                        if (kExactRedo || not_a_number()) pass = 1;
+                    }
                     __syncthreads();
                     continue;
                 }
             }
         } else {
+            if constexpr (kGuard) pass = kPasses - 1;         // a redo would do the same once more
             stamp(2);
         }
         stamp(3);
@@ -1161,8 +1171,10 @@ __device__ __forceinline__ void run_piece(const KParams &launch_args, unsigned c
 #pragma unroll
         for (int t = 0; t < TPW; ++t) bad |= !(O[t][NT][0] < 1.0e30f);
         if (!workgroup_any(bad, wave, lane, s_any + kWaves)) break;
-        if constexpr (kExactRedo) pass = 1;
-        if constexpr (!kGuard) {
+        if constexpr (kGuard) {
+            __syncthreads();
+            if (kExactRedo || not_a_number()) pass = 1;
+        } else {
 #pragma unroll
             for (int t = 0; t < TPW; ++t) {
                 m[t] = kMInit;

@@ -629,6 +629,30 @@ def test_fp16_redone_piece_keeps_its_small_weights(oracle_mod, N, G, layout):
     assert over > 16.0, over
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("N,G,L", [(6, 4, 40), (60, 4, 63), (40, 8, 20), (26, 4, 700)])
+def test_fp16_non_finite_draft_stays_in_its_subtree(oracle_mod, N, G, L, bad):
+    """A draft whose K row holds a value that is no number (or infinite) spoils the rows that see it and no other, in pieces
+    without a whole prefix stage, which have nothing to redo, and in longer ones."""
+    tree = W.random_tree(N, 6, _rng(N))
+    case = W.make_case("f16_nan", 990 + N, dtype=W.DT_F16, Hq=2 * G, Hkv=2, D=128, ctx_lens=[L], trees=[tree])
+    want = oracle_mod.verify_attn_case(case)
+    node = N // 2
+    page, slot = int(case.page_table[0, (L + node) // 16]), (L + node) % 16
+    case.k_pool[page, :, slot, 7] = np.array([bad], np.float16).view(np.uint16)[0]
+    got, step = _run(case)
+    sees = np.zeros(N, bool)
+    for i in range(N):
+        j = i
+        while j >= 0 and j != node:
+            j = int(tree[j])
+        sees[i] = j == node
+    assert sees.any() and not sees.all()
+    assert_close(got[:, ~sees], want[:, ~sees], case.dtype, f"{bad} plan={step.plan.as_dict()}")
+    if np.isnan(bad):
+        assert np.isnan(got[:, sees]).all()
+
+
 @pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # 2 / 15 / 20 row tiles: all three fast loops
 def test_bf16_reference_overflow_redo(oracle_mod, N, G):
     """bf16 storage keeps the softmax reference of a split frozen at the maxima of its first keys.
