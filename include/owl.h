@@ -350,7 +350,8 @@ owl_status owl_commit_kv(const owl_verify_desc *desc, void *k_cache, void *v_cac
  *   z_out      [n_rows][d] float32
  *   workspace  >= owl_drafter_cell_workspace_size() bytes
  * Every pointer is 16-byte aligned.  Outputs must not overlap inputs.  d_in is a multiple of 32, d a multiple of 16
- * and at most 16384.  A token outside [0, vocab) contributes e = 0 and is flagged
+ * and at most 16384.  With the same n_states a row comes out the same, bit for bit,
+ * however many rows are in the call.  A token outside [0, vocab) contributes e = 0 and is flagged
  * (OWL_DEV_BAD_TOKEN); a parent_row outside [0, n_states) is read as 0 and flagged
  * (OWL_DEV_BAD_ROW).  `phases`: OWL_DRAFTER_PROJ forms W^m h into the workspace,
  * OWL_DRAFTER_GATES does the rest from the workspace; owl_drafter_cell runs both.

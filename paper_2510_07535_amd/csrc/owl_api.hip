@@ -701,7 +701,7 @@ owl_status owl_drafter_cell_phases(const owl_drafter_desc *desc, const void *h, 
         if (launch_drafter_gates(desc->dtype, proj, z, tokens, parent_row, emb, gamma_c, beta_c, gamma_z, beta_z,
                                  h_out, h_out_f32, z_out, proj + (size_t)desc->n_states * 4 * desc->d, desc->n_states,
                                  desc->n_rows, desc->d, desc->vocab,
-                                 desc->alpha, desc->eps, dev_status, s) != hipSuccess)
+                                 desc->alpha, desc->eps, dev_status, device_cus(), s) != hipSuccess)
             return OWL_ERR_HIP;
     return OWL_OK;
 }

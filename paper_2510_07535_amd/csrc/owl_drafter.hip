@@ -351,7 +351,7 @@ hipError_t launch_drafter_tile_weights(const void *w_rows, void *w_tiled, int d_
 // (of s^c, then of z'), and the transcendental work of one row (three sigmoids
 // and two GeLUs per channel) keeps a single compute unit busy for ~20 us, so a
 // row is spread over workgroups of 256 threads x C channels, in two launches:
-//   1. z' = z g^f + f(s^c) g^i, and per chunk of 256 C channels the mean and centred sum of squares of z'
+//   1. z' = z g^f + f(s^c) g^i, and per unit of 256 or 512 channels the mean and centred sum of squares of z'
 //   2. merge those; h' = f(z') g^o
 // The statistics of s^c need no transcendentals: every workgroup of launch 1 forms them from the whole row by itself, in
 // registers, while its own operands are on their way: 48 KB of s^c and 24 KB of embedding from L2 at d = 12288, against a launch
@@ -360,12 +360,16 @@ hipError_t launch_drafter_tile_weights(const void *w_rows, void *w_tiled, int d_
 // The partials of z' are (mean, M2) pairs merged with the pairwise update
 //     M2 = sum_c M2_c + n_c (mean_c - mean)^2 ,
 // which keeps the variance as accurate as a two-pass sum.
+// A row comes out the same, bit for bit, whatever C is, and with it however many rows are in the call: a unit depends on d
+// alone, its sums form one balanced tree over its channels (in a lane, then over the lanes, then over the wavefronts), and where
+// the compiler could contract a product into a sum or not, the code says which.
 // ---------------------------------------------------------------------------
 constexpr int kGateThreads = 256;
 constexpr int kRowChunk = kGateThreads * 4;                // channels that a workgroup reads at a time for a whole row
 constexpr int kRowMaxChunks = 16;                          // d <= 16384
-constexpr int kGateMaxChunks = 32;                         // chunks of a row: one lane of a wavefront each, and what the scratch holds
-constexpr int kGateWorkgroups = 256;                       // see launch_gates_dt
+constexpr int kGateMaxUnits = 32;                          // units of a row: one lane of a wavefront each, and what the scratch holds
+__host__ __device__ constexpr int gate_unit(int d) { return d <= 256 * kGateMaxUnits ? 256 : 512; }
+static_assert(kRowChunk * kRowMaxChunks <= gate_unit(kRowChunk * kRowMaxChunks) * kGateMaxUnits, "a row's units fit the scratch");
 
 // Sum over the workgroup, the same in every thread.  Each call of a kernel has words of its own in `scratch`, so that one
 // barrier is enough.  (Shuffles through LDS and two barriers a sum, and a loop over the chunks' partials in the hidden kernel:
@@ -439,7 +443,7 @@ template <bool kF16, int C> __device__ __forceinline__ Chan<C> add_emb(const flo
     else raw = __builtin_bit_cast(Bits16<C>, *reinterpret_cast<const V *>(e));
     Chan<C> v = ld<C>(s);
 #pragma unroll
-    for (int i = 0; i < C; ++i) v.x[i] += alpha * widen16<kF16>(raw.x[i]);
+    for (int i = 0; i < C; ++i) v.x[i] = __builtin_fmaf(alpha, widen16<kF16>(raw.x[i]), v.x[i]);
     return v;
 }
 
@@ -450,7 +454,7 @@ struct GateArgs {
     const float *gamma_c, *beta_c, *gamma_z, *beta_z;
     uint16_t *h_out;
     float *h_out_f32, *z_out;
-    float *part_z;                // [M][kGateMaxChunks][2]: mean and centred sum of squares per chunk
+    float *part_z;                // [M][kGateMaxUnits][2]: mean and centred sum of squares per unit
     int P, d, vocab;
     float alpha, eps;
     uint32_t *status;
@@ -481,27 +485,48 @@ __device__ __forceinline__ GateRow gate_row(const GateArgs &a, int r, bool flag)
     return GateRow{a.s + (int64_t)p * 4 * a.d, a.z + (int64_t)p * a.d, a.emb + (int64_t)tok * a.d, alpha};
 }
 
-// Mean and centred sum of squares of the live channels of this workgroup's chunk.
-template <int C> __device__ __forceinline__ void chunk_stats(Chan<C> v, bool live, int n_live, float *scratch, float *out2)
+// Sum of the C numbers of a lane over a unit of W wavefronts, the same in each of their threads.
+template <int C, int W> __device__ __forceinline__ float unit_sum(const Chan<C> &v, float *scratch)
 {
-    float sum = 0.f, sq = 0.f;
-#pragma unroll
-    for (int i = 0; i < C; ++i) sum += v.x[i];
-    const float mean = block_sum(live ? sum : 0.f, scratch) / (float)n_live;
-#pragma unroll
-    for (int i = 0; i < C; ++i) sq += (v.x[i] - mean) * (v.x[i] - mean);
-    const float m2 = block_sum(live ? sq : 0.f, scratch + kGateWaves);
-    if (threadIdx.x == 0) out2[0] = mean, out2[1] = m2;
+    float sum = v.x[0];
+    if constexpr (C == 2) sum += v.x[1];
+    if constexpr (C == 4) sum = (sum + v.x[1]) + (v.x[2] + v.x[3]);
+    sum = wave_sum(sum);
+    if constexpr (W == 1) {
+        return sum;
+    } else {
+        const int wave = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) scratch[wave] = sum;
+        __syncthreads();
+        const float *u = scratch + wave / W * W;
+        return W == 2 ? u[0] + u[1] : (u[0] + u[1]) + (u[2] + u[3]);
+    }
 }
 
-// Mean and 1 / sqrt(variance + eps) of a row from its chunks' partials, one chunk a lane: a loop over them waits for each.
-__device__ __forceinline__ void merge_stats(const float2 part, int chunk, int d, float eps, float *mean_out, float *rstd_out)
+// Mean and centred sum of squares of the live channels (from channel j on) of each unit of this workgroup.
+template <int C, int UNIT> __device__ __forceinline__ void unit_stats(Chan<C> v, int j, int d, float *scratch, float *part)
 {
-    const int c = threadIdx.x & 63;
-    const float n = (float)max(min(chunk, d - c * chunk), 0);                // channels of the lane's chunk
+#pragma clang fp contract(off)
+    constexpr int kWaves = UNIT / (64 * C);
+    static_assert(kWaves >= 1 && kWaves <= kGateWaves && (kWaves & (kWaves - 1)) == 0, "a workgroup holds whole units");
+    const int unit = j / UNIT, n_live = min(UNIT, d - unit * UNIT);      // (of a unit behind the row: not above zero, not stored)
+#pragma unroll
+    for (int i = 0; i < C; ++i) v.x[i] = j < d ? v.x[i] : 0.f;
+    const float mean = unit_sum<C, kWaves>(v, scratch) / (float)n_live;
+#pragma unroll
+    for (int i = 0; i < C; ++i) v.x[i] = j < d ? (v.x[i] - mean) * (v.x[i] - mean) : 0.f;
+    const float m2 = unit_sum<C, kWaves>(v, scratch + kGateWaves);
+    if (threadIdx.x % (64 * kWaves) == 0 && n_live > 0) part[2 * unit] = mean, part[2 * unit + 1] = m2;
+}
+
+// Mean and 1 / sqrt(variance + eps) of a row from its units' partials, one unit a lane: a loop over them waits for each.
+__device__ __forceinline__ void merge_stats(const float2 part, int d, float eps, float *mean_out, float *rstd_out)
+{
+    const int u = threadIdx.x & 63, unit = gate_unit(d);
+    const float n = (float)max(min(unit, d - u * unit), 0);                  // channels of the lane's unit
     const float mean = wave_sum(n > 0.f ? part.x * n : 0.f) / (float)d;
     const float dm = part.x - mean;
-    const float m2 = wave_sum(n > 0.f ? part.y + n * dm * dm : 0.f);
+    const float m2 = wave_sum(n > 0.f ? __builtin_fmaf(n * dm, dm, part.y) : 0.f);
     *mean_out = mean;
     *rstd_out = 1.0f / sqrtf(m2 / (float)d + eps);
 }
@@ -528,7 +553,7 @@ __device__ __forceinline__ void row_stats(const GateArgs &a, const GateRow &g, f
     for (int c = 0; c < MAXC; ++c)
         if (c * kRowChunk + j0 < a.d) {
             const float4 x = make_float4(v[c].x[0] - mean, v[c].x[1] - mean, v[c].x[2] - mean, v[c].x[3] - mean);
-            sq += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
+            sq += __builtin_fmaf(x.x, x.x, x.y * x.y) + __builtin_fmaf(x.z, x.z, x.w * x.w);
         }
     *mean_out = mean;
     *rstd_out = 1.0f / sqrtf(block_sum(sq, scratch + kGateWaves) / (float)a.d + a.eps);
@@ -555,9 +580,10 @@ __global__ void __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_
     Chan<C> zn;
 #pragma unroll
     for (int i = 0; i < C; ++i)
-        zn.x[i] = zo.x[i] * sigmoid_f(sf.x[i]) + gelu_f((sc.x[i] - mean) * rstd * ga.x[i] + be.x[i]) * sigmoid_f(si.x[i]);
+        zn.x[i] = __builtin_fmaf(zo.x[i], sigmoid_f(sf.x[i]),
+                                 gelu_f(__builtin_fmaf((sc.x[i] - mean) * rstd, ga.x[i], be.x[i])) * sigmoid_f(si.x[i]));
     if (live) st<C>(a.z_out + (int64_t)r * a.d + j, zn);
-    chunk_stats<C>(zn, live, min(kChunk, a.d - c * kChunk), scratch + 2 * kGateWaves, a.part_z + ((int64_t)r * kGateMaxChunks + c) * 2);
+    unit_stats<C, gate_unit(MAXC * kRowChunk)>(zn, j, a.d, scratch + 2 * kGateWaves, a.part_z + (int64_t)r * kGateMaxUnits * 2);
 }
 
 template <bool kF16, int C>
@@ -565,22 +591,22 @@ __global__ void __launch_bounds__(kGateThreads) drafter_hidden_kernel(GateArgs a
 {
     constexpr int kChunk = kGateThreads * C;
     const int c = blockIdx.x, r = blockIdx.y, j = c * kChunk + threadIdx.x * C;
-    // (everything is asked for before the statistics are merged; lanes past the last chunk read chunk 0 and do not count)
-    const int n_chunks = (a.d + kChunk - 1) / kChunk, chunk = (int)(threadIdx.x & 63) < n_chunks ? threadIdx.x & 63 : 0;
-    const float2 part = reinterpret_cast<const float2 *>(a.part_z)[(int64_t)r * kGateMaxChunks + chunk];
+    // (everything is asked for before the statistics are merged; lanes past the last unit read unit 0 and do not count)
+    const int u = threadIdx.x & 63;
+    const float2 part = reinterpret_cast<const float2 *>(a.part_z)[(int64_t)r * kGateMaxUnits + (u * gate_unit(a.d) < a.d ? u : 0)];
     const bool live = j < a.d;
     const int jl = live ? j : 0;
     const Chan<C> zn = ld<C>(a.z_out + (int64_t)r * a.d + jl), ga = ld_or<C>(a.gamma_z, jl, 1.f), be = ld_or<C>(a.beta_z, jl, 0.f);
     const GateRow g = gate_row(a, r, false);
     const Chan<C> so = add_emb<kF16, C>(g.sp + 2 * a.d + jl, g.ep + jl, g.alpha);
     float mean, rstd;
-    merge_stats(part, kChunk, a.d, a.eps, &mean, &rstd);
+    merge_stats(part, a.d, a.eps, &mean, &rstd);
     if (!live) return;
     Chan<C> hn;
     Bits16<C> out;
 #pragma unroll
     for (int i = 0; i < C; ++i) {
-        hn.x[i] = gelu_f((zn.x[i] - mean) * rstd * ga.x[i] + be.x[i]) * sigmoid_f(so.x[i]);
+        hn.x[i] = gelu_f(__builtin_fmaf((zn.x[i] - mean) * rstd, ga.x[i], be.x[i])) * sigmoid_f(so.x[i]);
         out.x[i] = narrow16<kF16>(hn.x[i]);
     }
     if (a.h_out) {
@@ -594,7 +620,7 @@ __global__ void __launch_bounds__(kGateThreads) drafter_hidden_kernel(GateArgs a
     if (a.h_out_f32) st<C>(a.h_out_f32 + (int64_t)r * a.d + j, hn);
 }
 
-size_t drafter_gate_scratch_floats(int M) { return (size_t)M * kGateMaxChunks * 2; }
+size_t drafter_gate_scratch_floats(int M) { return (size_t)M * kGateMaxUnits * 2; }
 
 template <bool kF16, int MAXC, int C> static void launch_gates_as(const GateArgs &a, int M, hipStream_t st)
 {
@@ -608,21 +634,23 @@ template <bool kF16, int C> static void launch_gates_c(const GateArgs &a, int M,
     const int rounds = (a.d + 4 * kRowChunk - 1) / (4 * kRowChunk);
     if (rounds == 1) launch_gates_as<kF16, 4, C>(a, M, st);
     else if (rounds == 2) launch_gates_as<kF16, 8, C>(a, M, st);
-    else if constexpr (C > 1) {                             // (with one channel a lane a row of this width has too many chunks)
+    else if constexpr (C > 1) {                             // (one channel a lane: no workgroup holds a unit of 512, see launch_gates_dt)
         if (rounds == 3) launch_gates_as<kF16, 12, C>(a, M, st);
         else launch_gates_as<kF16, kRowMaxChunks, C>(a, M, st);
     }
 }
 
-// Channels a lane: a lane's sigmoids and GeLUs follow each other, about 100 instructions a channel, so it takes as few as leave no more
-// than one workgroup a compute unit (each reads its whole row) and no more chunks than the scratch holds.  us per cell, four a lane -> as
+// Channels a lane: a lane's sigmoids and GeLUs follow each other, so it takes as few as leave no more than one workgroup a
+// compute unit (each reads its whole row) and whole units in each.  us per cell, four a lane -> as
 // few as that (up to 512 workgroups, up to 1024): bf16, 10 rows, 2048 from 2048 15.4 -> 13.9 (13.9, 14.4), 4096 from 4096 31.3 -> 30.0 (30.0, 30.0),
 // 12288 from 4096 72.7 -> 71.6 (71.6, 71.6); fp16, 16384 from 4096 92.6 -> 92.8 (93.4, 93.4); 40 rows, 12288 77.4 -> 77.5 (77.6, 78.9).
-template <bool kF16> static hipError_t launch_gates_dt(const GateArgs &a, int M, hipStream_t st)
+template <bool kF16> static hipError_t launch_gates_dt(const GateArgs &a, int M, int n_cus, hipStream_t st)
 {
+    static_assert(gate_unit(8 * kRowChunk) <= kGateThreads && gate_unit(8 * kRowChunk + 1) > kGateThreads,
+                  "one channel a lane serves rows of up to two rounds, see launch_gates_c");
     auto fits = [&](int channels) {
-        const int chunks = (a.d + kGateThreads * channels - 1) / (kGateThreads * channels);
-        return chunks <= kGateMaxChunks && chunks * M <= kGateWorkgroups;
+        const int chunk = kGateThreads * channels;
+        return gate_unit(a.d) <= chunk && (a.d + chunk - 1) / chunk * M <= n_cus;
     };
     if (fits(1)) launch_gates_c<kF16, 1>(a, M, st);
     else if (fits(2)) launch_gates_c<kF16, 2>(a, M, st);
@@ -634,7 +662,7 @@ hipError_t launch_drafter_gates(int dtype, const float *s, const float *z, const
                                 const int32_t *parent_row, const void *emb, const float *gamma_c,
                                 const float *beta_c, const float *gamma_z, const float *beta_z, void *h_out,
                                 float *h_out_f32, float *z_out, float *gate_scratch, int P, int M, int d, int vocab,
-                                float alpha, float eps, uint32_t *status, hipStream_t st)
+                                float alpha, float eps, uint32_t *status, int n_cus, hipStream_t st)
 {
     GateArgs a;
     a.s = s, a.z = z, a.tokens = tokens, a.parent_row = parent_row, a.emb = static_cast<const uint16_t *>(emb);
@@ -642,7 +670,7 @@ hipError_t launch_drafter_gates(int dtype, const float *s, const float *z, const
     a.h_out = static_cast<uint16_t *>(h_out), a.h_out_f32 = h_out_f32, a.z_out = z_out;
     a.part_z = gate_scratch;
     a.P = P, a.d = d, a.vocab = vocab, a.alpha = alpha, a.eps = eps, a.status = status;
-    return dtype == OWL_F16 ? launch_gates_dt<true>(a, M, st) : launch_gates_dt<false>(a, M, st);
+    return dtype == OWL_F16 ? launch_gates_dt<true>(a, M, n_cus, st) : launch_gates_dt<false>(a, M, n_cus, st);
 }
 
 }  // namespace owl

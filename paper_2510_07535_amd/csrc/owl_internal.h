@@ -92,7 +92,7 @@ hipError_t launch_drafter_gates(int dtype, const float *s, const float *z, const
                                 const int32_t *parent_row, const void *emb, const float *gamma_c,
                                 const float *beta_c, const float *gamma_z, const float *beta_z, void *h_out,
                                 float *h_out_f32, float *z_out, float *gate_scratch, int P, int M, int d, int vocab,
-                                float alpha, float eps, uint32_t *status, hipStream_t st);
+                                float alpha, float eps, uint32_t *status, int n_cus, hipStream_t st);
 size_t drafter_gate_scratch_floats(int M);
 hipError_t launch_tree_mask(const int32_t *parent, int B, int N, uint64_t *anc, int32_t *depth,
                             uint32_t *status, hipStream_t s);

@@ -9,6 +9,8 @@ divides by a standard deviation of order one and sigmoid / GeLU have slopes belo
 max-abs 2e-4 on z' and on the fp32 h'; the 16-bit h' must be the fp32 h' rounded
 to nearest even, bit for bit, hence within that bar plus half a unit in the last
 place (at most 2^-8 relative for bf16, 2^-11 for fp16) of the oracle's value."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -88,6 +90,21 @@ def test_gates_by_channels_a_lane(dtype, d, M):
     _check(case, 1.0)
 
 
+@pytest.mark.parametrize("dtype,d", [(W.DT_BF16, 16), (W.DT_F16, 272), (W.DT_F16, 1040), (W.DT_BF16, 4112), (W.DT_BF16, 8192), (W.DT_F16, 8208),
+                                     (W.DT_BF16, 12288), (W.DT_F16, 16384)])
+def test_a_row_does_not_depend_on_the_rows_beside_it(dtype, d):
+    """A row of a call of 64 is the row of a call of 1, 7 or 31 bit for bit: the gates take another number of channels a lane
+    there, but sum the same units of a row in the same order."""
+    case = W.make_drafter_case("t", 800 + d % 83, dtype=dtype, d_in=32, d=d, P=3, M=64, vocab=50)
+    all_rows = _check(case, 1.0).result()
+    for m in (1, 7, 31):
+        few = dataclasses.replace(case, M=m, tokens=case.tokens[:m].copy(), parent_row=case.parent_row[:m].copy())
+        step = DrafterStep(few, 1.0)
+        step.run()
+        for a, b in zip(step.result(), all_rows):
+            assert np.array_equal(a, b[:m]), (d, m)
+
+
 def _tiled_by_definition(w_bits, d_in, d):
     """The tiled layout built from its definition in the header, granule by granule."""
     rows = w_bits.reshape(4 * d, d_in)
@@ -141,7 +158,6 @@ def test_two_steps_recurrence():
     alpha = OD.drafter_alpha(8, 384)
     s1 = _check(case, alpha)
     _, h16, z1 = s1.result()
-    import dataclasses
     nxt = dataclasses.replace(case, h=h16.copy(), z=z1.copy(), tokens=(case.tokens + 3) % case.vocab)
     _check(nxt, alpha)
 
