@@ -174,8 +174,12 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
 
     const int64_t src = ((int64_t)from_page * stride_page + from % kPage * stride_token) * es;
     const int64_t dst = ((int64_t)to_page * stride_page + to % kPage * stride_token) * es;
-    // 16-byte piece `id` of the moved rows belongs to row id >> log_pieces; past the end: the last row once more, not stored
-    const int total = na << log_pieces, piece = (tid & ((1 << log_pieces) - 1)) * 16;
+    // The path climbs, so the rows that are in place already are its first ones.  16-byte piece `id` of the others belongs to row
+    // first + (id >> log_pieces); past the end: the last row once more, not stored
+    const uint64_t moved = __builtin_amdgcn_ballot_w64(lane < na && src != dst);
+    if (moved == 0) return;                                 // uniform over the workgroup, as are the others
+    const int first = __builtin_ctzll(moved), rows = na - first;
+    const int total = rows << log_pieces, piece = (tid & ((1 << log_pieces) - 1)) * 16;
     typedef uint32_t Piece __attribute__((ext_vector_type(4)));          // (an array of the struct uint4 goes to scratch memory)
     auto move = [&](auto pieces) {
         constexpr int n = decltype(pieces)::value;
@@ -183,9 +187,9 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
         int64_t at[n];
 #pragma unroll
         for (int r = 0; r < n; ++r) {
-            const int id = tid + r * kCommitThreads, i = min(id >> log_pieces, na - 1);
+            const int id = tid + r * kCommitThreads, i = first + min(id >> log_pieces, rows - 1);
             const int64_t s = shfl64(src, i), d = shfl64(dst, i);
-            at[r] = id < total && s != d ? d + piece : -1;  // (a row already in place is left alone)
+            at[r] = id < total && s != d ? d + piece : -1;  // (two table entries may name one page)
             held[r] = *reinterpret_cast<const Piece *>(cache + s + piece);
         }
         __syncthreads();                                    // all reads done before the first write
@@ -193,7 +197,6 @@ __global__ void __launch_bounds__(kCommitThreads) commit_kernel(
         for (int r = 0; r < n; ++r)
             if (at[r] >= 0) *reinterpret_cast<Piece *>(cache + at[r]) = held[r];
     };
-    if (total == 0) return;                                 // uniform over the workgroup, as are the others
     if (total <= kCommitThreads) move(std::integral_constant<int, 1>{});
     else move(std::integral_constant<int, kCommitMaxPieces>{});
 }

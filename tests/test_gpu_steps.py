@@ -198,6 +198,31 @@ def test_commit_around_one_piece_a_thread(dtype, D):
         assert np.array_equal(new_ctx.cpu().numpy(), want_ctx)
 
 
+@pytest.mark.parametrize("dtype,D", [(W.DT_BF16, 64), (W.DT_F16, 128), (W.DT_F32, 128)])
+def test_commit_of_a_path_whose_first_rows_are_in_place(dtype, D):
+    """Only what lies behind the rows in place is moved, so the line between one piece a thread and eight counts from there: all
+    rows in place, all but the last, and twenty in place with as many moved ones as one piece a thread holds, one less, one more."""
+    r = _rng(D + dtype)
+    line, N = 256 * 16 // (D * (4 if dtype == W.DT_F32 else 2)), 64
+    paths = [list(range(N)), list(range(N - 2)) + [N - 1]]
+    paths += [list(range(20)) + sorted(21 + r.choice(N - 21, size=line + k, replace=False)) for k in (-1, 0, 1)]
+    ctx = [1000, 33, 37, 0, 16]
+    case = W.make_case("commit-in-place", 43, dtype=dtype, Hq=4, Hkv=2, D=D, ctx_lens=ctx, trees=[W.random_tree(N, 6, r) for _ in ctx])
+    acc, na = np.full((case.B, N), -1, dtype=np.int32), np.array([len(p) for p in paths], dtype=np.int32)
+    for b, p in enumerate(paths):
+        acc[b, :len(p)] = p
+    step = VerifyStep(case)
+    new_ctx = torch.zeros(case.B, dtype=torch.int32, device=DEV)
+    B.owl_commit_kv(step.desc, step.k, step.v, step.page_table, step.ctx_lens, _i32(acc), _i32(na), new_ctx, step.status)
+    torch.cuda.synchronize()
+    assert step.dev_status() == 0
+    for name, pool, dev in (("k", case.k_pool, step.k), ("v", case.v_pool, step.v)):
+        want, want_ctx = S.commit_kv(pool, case.page_table, case.ctx_lens, acc, na, case.stride_page,
+                                     case.stride_head, case.stride_token, case.Hkv, case.D)
+        assert np.array_equal(dev.cpu().numpy().view(np.uint8).ravel(), want.view(np.uint8).ravel()), name
+        assert np.array_equal(new_ctx.cpu().numpy(), want_ctx)
+
+
 def test_commit_then_verify_sees_the_committed_rows():
     """After the commit, a verify step over the longer context reads the moved rows:
     compare with the oracle run on the oracle-committed cache."""
