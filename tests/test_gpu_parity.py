@@ -25,6 +25,42 @@ def _run(case, **kw):
     return out, step
 
 
+def _copies(case, n, planned):
+    """One sequence n times over (same pages, queries and tree), announced with ``planned`` tokens."""
+    import dataclasses
+    table = np.full((1, (planned + case.N + 15) // 16), -1, dtype=np.int32)
+    table[:, :case.page_table.shape[1]] = case.page_table
+    rep = lambda a: np.ascontiguousarray(np.repeat(a, n, axis=0))
+    return dataclasses.replace(case, B=n, q=rep(case.q), page_table=rep(table), ctx_lens=rep(case.ctx_lens),
+                               tree_parent=rep(case.tree_parent), max_pages_per_seq=table.shape[1])
+
+
+_LAYOUTS = ("1x4x2", "1x8x1", "2x4x2", "2x8x1", "3x8x1")        # tiles a wavefront x row wavefronts x key groups
+
+
+def _layout(plan):
+    return _LAYOUTS[plan.kernel_variant % 5]
+
+
+# Shapes that plan each loop with splits of C tokens out of `planned`: N, G, KV heads, sequences, planned, C, layout.
+# (Two KV heads and one sequence plan row groups of at most four tiles, whatever N is: the plain loop with two key groups.)
+_EVERY_LOOP = [
+    (6, 4, 8, 4, 10340, 1280, "1x4x2"),
+    (26, 4, 8, 4, 10340, 1280, "1x8x1"),
+    (16, 8, 8, 8, 20580, 2560, "2x4x2"),
+    (60, 4, 8, 4, 10340, 1280, "2x8x1"),
+    (40, 8, 8, 4, 10340, 1280, "3x8x1"),
+]
+
+
+def _run_in_layout(case, copies, planned, split, layout, **kw):
+    """``copies`` equal sequences in splits of ``split`` tokens, which the plan has to give to ``layout``; all come out the same."""
+    got, step = _run(_copies(case, copies, planned), split_tokens=split, max_ctx_len=planned, **kw)
+    assert step.plan.row_groups == 1 and _layout(step.plan) == layout, step.plan.as_dict()
+    assert all(np.array_equal(got[0], got[b]) for b in range(1, copies)), layout
+    return got[:1]
+
+
 # ---------------------------------------------------------------------------
 # small and ragged shapes, full element-by-element comparison
 # ---------------------------------------------------------------------------
@@ -538,11 +574,11 @@ def test_work_dealt_by_length(oracle_mod, name, Hq, Hkv, D, ctx, n, dealt):
 @pytest.mark.parametrize("frac,gain,tag", [(0.05, 8.0, "frequent outliers: guarded reference"),
                                            (0.0007, 40.0, "rare late outliers: frozen reference, overflow, redo"),
                                            (0.02, 3.0, "mild tail: frozen reference holds")])
-@pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # 2 / 15 / 20 row tiles: all three fast loops
+@pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # row groups of at most four tiles: two key groups
 def test_fp16_score_range_paths(oracle_mod, frac, gain, tag, N, G):
     """fp16 probabilities overflow 2^16 above their reference.  The kernel takes a loop with a guarded (moving) reference if the
     scores of a split's first keys already show a long tail; otherwise it freezes the reference and, should a later score
-    overflow it after all, redoes the split with the guarded loop.  All routes must give the oracle's result."""
+    overflow it after all, redoes the split.  All routes must give the oracle's result."""
     r = _rng(77 + N)
     case = W.make_case("f16range", 910 + N, dtype=W.DT_F16, Hq=2 * G, Hkv=2, D=128, ctx_lens=[9000, 700],
                        trees=[W.random_tree(N, 6, r) for _ in range(2)], outlier_frac=frac, outlier_gain=gain)
@@ -550,11 +586,11 @@ def test_fp16_score_range_paths(oracle_mod, frac, gain, tag, N, G):
     assert_close(got, oracle_mod.verify_attn_case(case), case.dtype, f"{tag}, N={N} G={G}")
 
 
-@pytest.mark.parametrize("N,G,D", [(6, 4, 128), (60, 4, 64), (26, 4, 128), (60, 4, 128), (40, 8, 128)])     # 2, 15, 7, 15, 20 row tiles
+@pytest.mark.parametrize("N,G,D", [(6, 4, 128), (60, 4, 64), (26, 4, 128), (60, 4, 128), (40, 8, 128)])     # likewise
 def test_fp16_overflow_found_at_every_look(oracle_mod, N, G, D):
-    """A frozen fp16 loop looks for overflowed row sums at stages 4, 16, 64, ... (with three tiles a wavefront at stage 1
-    too), and once more behind its last stage.  Each split here has one key that overflows the reference, in another place: the second step, the stages
-    around a look, the last fast stage.  The first split has none."""
+    """A frozen fp16 loop looks for overflowed row sums at stages 4, 16, 64, ... and once more behind its last stage.  Each split
+    here has one key that overflows the reference, in another place: the second step, the stages around a look, the last fast
+    stage.  The first split has none."""
     C, L = 1280, 8 * 1280 + 100
     hot = [s * C + 64 * stage + slot for s, (stage, slot) in enumerate([(0, 40), (1, 9), (3, 63), (4, 0), (15, 40), (16, 3), (19, 63)], 1)]
     case = W.make_case("f16_looks", 950 + N + D, dtype=W.DT_F16, Hq=2 * G, Hkv=2, D=D, ctx_lens=[L], trees=[W.random_tree(N, 6, _rng(N))])
@@ -575,23 +611,6 @@ def test_fp16_overflow_found_at_every_look(oracle_mod, N, G, D):
         assert_close(got, want, case.dtype, f"N={N} G={G} D={D} split={split} plan={step.plan.as_dict()}")
 
 
-def _copies(case, n, planned):
-    """One sequence n times over (same pages, queries and tree), announced with ``planned`` tokens."""
-    import dataclasses
-    table = np.full((1, (planned + case.N + 15) // 16), -1, dtype=np.int32)
-    table[:, :case.page_table.shape[1]] = case.page_table
-    rep = lambda a: np.ascontiguousarray(np.repeat(a, n, axis=0))
-    return dataclasses.replace(case, B=n, q=rep(case.q), page_table=rep(table), ctx_lens=rep(case.ctx_lens),
-                               tree_parent=rep(case.tree_parent), max_pages_per_seq=table.shape[1])
-
-
-_LAYOUTS = ("1x4x2", "1x8x1", "2x4x2", "2x8x1", "3x8x1")        # tiles a wavefront x row wavefronts x key groups
-
-
-def _layout(plan):
-    return _LAYOUTS[plan.kernel_variant % 5]
-
-
 @pytest.mark.parametrize("N,G,layout", [(6, 4, "1x4x2"), (26, 4, "1x8x1"), (16, 8, "2x4x2"), (60, 4, "2x8x1"), (40, 8, "3x8x1")])
 def test_fp16_redone_piece_keeps_its_small_weights(oracle_mod, N, G, layout):
     """One key of 16384 lies about 17.5 (log2 units) above the frozen reference of every row: fp16's P overflows and the piece is
@@ -606,10 +625,7 @@ def test_fp16_redone_piece_keeps_its_small_weights(oracle_mod, N, G, layout):
     row = np.zeros((8, 128), np.float32)
     row[:, 0] = target / (8.0 * c)
     case.k_pool[int(case.page_table[0, hot // 16]), :, hot % 16, :] = W.store(row, W.DT_F16)
-    many = _copies(case, 8, 33000)
-    got, step = _run(many, split_tokens=C, max_ctx_len=33000, flags=B.OWL_FLAG_FP32_PARTIALS)
-    assert step.plan.row_groups == 1 and _layout(step.plan) == layout, step.plan.as_dict()
-    assert all(np.array_equal(got[0], got[b]) for b in range(1, 8))
+    got = _run_in_layout(case, 8, 33000, C, layout, flags=B.OWL_FLAG_FP32_PARTIALS)
     rows = sample_rows(case, 64, seed=N, always=[(0, 0, 0), (0, N - 1, case.Hq - 1)])
     want = oracle_mod.verify_attn_case(case, rows=rows)
     pos = np.arange(C)
@@ -627,6 +643,65 @@ def test_fp16_redone_piece_keeps_its_small_weights(oracle_mod, N, G, layout):
         err = np.abs(got[0, i, h] - w64)
         assert (err <= bound).all(), (layout, i, h, float(err.max()), float(bound.max()))
     assert over > 16.0, over
+
+
+def _heat(case, hot, gain):
+    for pos in hot:
+        page = int(case.page_table[0, pos // 16])
+        row = W.widen(case.k_pool[page, :, pos % 16, :], case.dtype) * gain
+        case.k_pool[page, :, pos % 16, :] = W.store(row.astype(np.float32), case.dtype)
+
+
+def _most_above(case, pos, C):
+    """By how much (log2 units) the score of key pos exceeds those of the first 64 keys of its split, in the row where that is most."""
+    q, c = W.widen(case.q[0], case.dtype), case.scale * 1.4426950408889634
+    at = np.append(np.arange(pos // C * C, pos // C * C + 64), pos)
+    keys = W.widen(case.k_pool[case.page_table[0, at // 16], :, at % 16, :], case.dtype)                  # [65, Hkv, D]
+    x = np.stack([c * q[:, h] @ keys[:, h // case.G].T for h in range(case.Hq)])                          # [Hq, N, 65]
+    return float((x[..., -1] - x[..., :-1].max(axis=-1)).max())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,G,Hkv,n,planned,C,layout", _EVERY_LOOP)
+def test_fp16_overflow_found_in_every_loop(oracle_mod, N, G, Hkv, n, planned, C, layout, D):
+    """One overflowing key a split, as above, in every loop: the pipelined ones give way at stage 0 with the ring kept (second
+    step), at stages 4 and 16, and behind the loop; with three tiles a wavefront there is a look at stage 1.  The stages around
+    each look, and the last."""
+    last = C // 64 - 1
+    places = [(0, 40), (0, 63), (1, 9), (3, 63), (4, 0), (15, 40), (16, 3), (last, 63)]
+    hot = [s * C + 64 * stage + slot for s, (stage, slot) in enumerate(places)]
+    case = W.make_case("f16_looks", 1150 + N + D, dtype=W.DT_F16, Hq=Hkv * G, Hkv=Hkv, D=D, ctx_lens=[8 * C + 100],
+                       trees=[W.random_tree(N, 6, _rng(N))])
+    _heat(case, hot, 32.0)
+    for pos in hot[2:]:
+        assert _most_above(case, pos, C) > 21.0, pos
+    got = _run_in_layout(case, n, planned, C, layout)
+    _close_to_oracle(oracle_mod, case, got, f"{layout} D={D}")
+    dealt, step = _run(_copies(case, n, planned), max_ctx_len=planned)
+    _close_to_oracle(oracle_mod, case, dealt[-1:], f"dealt, plan={step.plan.as_dict()}")
+
+
+@pytest.mark.parametrize("frac,gain", [(0.05, 8.0), (0.0007, 40.0), (0.02, 3.0)])
+@pytest.mark.parametrize("N,G,Hkv,n,planned,C,layout", _EVERY_LOOP)
+def test_fp16_score_range_in_every_loop(oracle_mod, N, G, Hkv, n, planned, C, layout, frac, gain):
+    """Frequent, rare and mild outliers, as in test_fp16_score_range_paths, in every loop."""
+    case = W.make_case("f16range", 1250 + N, dtype=W.DT_F16, Hq=Hkv * G, Hkv=Hkv, D=128, ctx_lens=[9000],
+                       trees=[W.random_tree(N, 6, _rng(N))], outlier_frac=frac, outlier_gain=gain)
+    got = _run_in_layout(case, n, planned, C, layout)
+    _close_to_oracle(oracle_mod, case, got, f"{layout} {frac} {gain}")
+
+
+@pytest.mark.parametrize("N,G,Hkv,n,planned,C,layout", _EVERY_LOOP)
+def test_bf16_reference_overflow_redo_in_every_loop(oracle_mod, N, G, Hkv, n, planned, C, layout):
+    """As test_bf16_reference_overflow_redo, in every loop."""
+    case = W.make_case("bf16_redo", 1350 + N, dtype=W.DT_BF16, Hq=Hkv * G, Hkv=Hkv, D=128, ctx_lens=[6 * C + 77],
+                       trees=[W.random_tree(N, 6, _rng(N))])
+    hot = [C + 700, 2 * C + 1270, 3 * C + 100, 4 * C + 300]
+    _heat(case, hot, 64.0)
+    for pos in hot:
+        assert _most_above(case, pos, C) > 104.0, pos
+    got = _run_in_layout(case, n, planned, C, layout)
+    _close_to_oracle(oracle_mod, case, got, layout)
 
 
 @pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
@@ -653,7 +728,7 @@ def test_fp16_non_finite_draft_stays_in_its_subtree(oracle_mod, N, G, L, bad):
         assert np.isnan(got[:, sees]).all()
 
 
-@pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # 2 / 15 / 20 row tiles: all three fast loops
+@pytest.mark.parametrize("N,G", [(6, 4), (60, 4), (40, 8)])     # row groups of at most four tiles: two key groups
 def test_bf16_reference_overflow_redo(oracle_mod, N, G):
     """bf16 storage keeps the softmax reference of a split frozen at the maxima of its first keys.
     A later score more than ~100 (log2 units) above it overflows 2^(x - m); the row sum shows it
