@@ -52,13 +52,13 @@ __device__ __forceinline__ void scale(float4 &acc, float a)
     acc.x *= a; acc.y *= a; acc.z *= a; acc.w *= a;
 }
 
-// This kernel is a chain: arguments, partials, merge, store.  One wavefront takes about 3.6 ns from one instruction to the next, so beside the round
-// trips the number of instructions between them counts (it was 1000 for 32 partials and is 400): addresses advance by a
-// constant instead of a product for each partial, a row's three statistics come in one load, the greatest reference of the partials
-// in flight is found first (one rescale for all of them instead of one each), the halves enter the sums as they are (v_fma_mix), four
-// wavefronts share the end, and what a batch needs to find its partials (LATE) is a kernel of its own.  us per call, 8 heads, bf16: 24 rows,
-// 5K / 32K tokens 11.65 -> 11.2 / 27.7 -> 27.25, 240 rows, 5K 16.85 -> 16.5, 320 rows, 1 head, 128K 34.7 -> 34.0, four sequences
-// of 900-9K, 48 rows 19.85 -> 19.35.
+// This kernel is a chain: arguments, partials, merge, store.  Beside the round trips the number of instructions between them
+// counts (executed by a wavefront: 633 with 32 partials a row and 1024 with 128, now 403 and 666): addresses advance by a constant
+// instead of a product for each partial, a row's three statistics come in one load, the greatest reference of the partials
+// in flight is found first (one rescale for all of them instead of one each), the halves enter the sums as they are
+// (v_fma_mix), four wavefronts share the end, and what a batch needs to find its partials (LATE) is a kernel of its own.
+// us per call, 8 heads, bf16: 24 rows, 5K / 32K tokens 11.65 -> 11.2 / 27.7 -> 27.25, 240 rows, 5K 16.85 -> 16.5, 320 rows, 1 head,
+// 128K 34.7 -> 34.0, four sequences of 900-9K, 48 rows 19.85 -> 19.35.
 template <int D, bool HALF, int WAVES, bool BY_CHANNEL, bool LATE>
 __global__ void __launch_bounds__(64 * WAVES) combine_kernel(const KParams p)
 {
